@@ -38,6 +38,12 @@ hipError_t launch_bwd_mfma_hash(const GridDev& g, const MlpDev& m, const RaysDev
 hipError_t launch_bwd_mfma_hexplane(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
                                     int n_cu, hipStream_t stream);
 
+// the tile kernels (lp_mfma_bwd_tile.h): all inputs grid channels, voxel grids or triplanes
+hipError_t launch_bwd_tile_voxel(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
+                                 int n_cu, hipStream_t stream);
+hipError_t launch_bwd_tile_triplane(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
+                                    int n_cu, hipStream_t stream);
+
 // the shapes that run as a pair of waves per ray (lp_mfma_bwd_ws.hip)
 bool bwd_ws_supported(const GridDev& g, const MlpDev& m);
 hipError_t launch_bwd_mfma_ws(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,

@@ -1,0 +1,1092 @@
+// Matrix-core backward kernel of the Renderer (Eq. (2), Section 3.4 of the paper) over TILES of rays: a
+// wavefront marches four neighbouring rays together, eight samples of each per 32-sample step, from the
+// last samples to the first (rays that do not run side by side are marched one at a time, 32 samples per step).
+// A workgroup is eight wavefronts of 256 registers, two per SIMD, that share the MLP's weights in LDS
+// and nothing else: no wave waits for another between the staging of the weights and the final sums.
+//
+// Per step a wave
+//   1. recomputes the MLP forward from the sampled features (nothing was stored but one scalar per ray),
+//   2. rebuilds the transmittance from the cached optical depth and evaluates Eq. (2) with scans over
+//      the samples of each ray,
+//   3. back-propagates on the matrix cores: input gradients dX = W^T dZ chained in registers, weight
+//      gradients dW = dZ X^T contracted over the samples of the step,
+//   4. adds the feature gradient to the grid gradient: scatter_window below, or, where the step's samples
+//      are too far apart for it, the run-merging walk of lp_mfma_bwd_common.h.
+//
+// What bounds it and why it is laid out like this (256^3 x 16 voxels, 800^2 rays x 512 samples, and eight
+// 256^2 x 32 triplanes, 4 x 256^2 rays x 192 samples each):
+//   - The grid gradient is bound by the rate of atomic adds (2.1e10 64-byte lines/s on this chip, whatever
+//     the locality). One ray's samples touch 3.2 (voxel) and 9.9 (triplane) lines per sample after run
+//     merging; the union of the texels that four neighbouring rays touch with eight samples each is 0.7 and
+//     3.5 lines per sample.
+//   - A wave does not overlap its own vector and matrix instructions; two waves per SIMD do. The
+//     accumulators of the weight gradients (104 registers for 16-64-64-4: the two thin matrices on 16 x 16
+//     tiles) leave room for two waves only if a step's activations live in LDS instead of registers.
+//   - In LDS they are transposed by the reads (lp_tile_lds.h); on the matrix cores the transposition by 0/1
+//     products took 36 of the 168 products of a step and as many permutes. The transposed weights of the
+//     input-gradient chain are column reads of the same images, which halves the LDS that weights take.
+//   - Vector work alternates with products that do not wait for it (weave below).
+//   - Products with four rows (the output layer) carry the hi and the lo halves of the operand in rows
+//     that would be empty, or in empty parts of the K range: 8 + 2 + 8 instructions instead of 12 + 6 + 12.
+#pragma once
+#include "lp_kernels.h"
+#include "lp_mfma.h"
+#include "lp_mfma_mlp.h"
+#include "lp_mfma_bwd_common.h"
+#include "lp_tile_lds.h"
+
+namespace lp {
+
+namespace {
+
+constexpr int kTileWaves = 8;
+constexpr int kTileRays = 4;                     // rays of a tile
+constexpr int kTileSamples = 32 / kTileRays;     // samples of each per step
+
+// LDS in bytes: the waves' step tensors first (so that a wave's base has none of the address bits that the
+// images' exclusive-ors flip), then the weights, then the waves' small areas.
+template <int C, int H, int NH>
+struct TileLds {
+    using W1 = TileImage<C, false>;
+    using WH = TileImage<H, true>;
+    // one wave: two tensors of 32 samples, each a hi and a lo image
+    static constexpr int kAct = 8192;
+    static constexpr int A = 0, B = kAct;
+    static constexpr int W2_AT = kTileWaves * 2 * kAct;
+    static constexpr int W1_AT = W2_AT + (NH == 2 ? 2 * WH::bytes(H) : 0);
+    static constexpr int kWo = 2 * H + 16;                       // bytes of an output-layer row (padded)
+    static constexpr int WO_AT = W1_AT + 2 * W1::bytes(H);       // 4 rows hi, 4 rows lo
+    static constexpr int BIAS_AT = WO_AT + 8 * kWo;              // b1[H] b2[H] bo[4]
+    static constexpr int SMALL_AT = BIAS_AT + (2 * H + 4) * 4;
+    // one wave: output gradients; per ray its geometry (10 floats) and upstream gradients (5 floats)
+    static constexpr int kRayBytes = 64;
+    static constexpr int RAY = 512;
+    static constexpr int kSmall = RAY + kTileRays * kRayBytes;
+    static constexpr int kTotal = SMALL_AT + kTileWaves * kSmall;
+    static_assert(W2_AT % 4096 == 0 && W1_AT % 1024 == 0 && SMALL_AT % 16 == 0 && kSmall % 16 == 0, "alignment");
+    static_assert(kTotal <= 160 * 1024, "LDS budget of a gfx950 compute unit");
+};
+
+// Alternates N matrix products with U pieces of vector work that do not wait for them, in exactly this order
+// (the pieces start after SKIP products). A 32 x 32 x 16 product occupies the matrix cores for 32 cycles, in
+// which the same wave can issue eight vector instructions: measured on this chip, 24 products and 192
+// multiply-adds take 1770 cycles one after the other and 1190 alternating (1330 and 1090 per wave with two waves
+// on the SIMD).
+//
+// The compiler moves instructions without side effects across scheduling barriers, so each result is pinned in its
+// place by an empty asm statement.
+template <class T>
+__device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }
+
+template <int I, int END, class F>
+__device__ __forceinline__ void repeat(F& f)
+{
+    if constexpr (I < END) {
+        f(std::integral_constant<int, I>());
+        repeat<I + 1, END>(f);
+    }
+}
+template <int N, int U, int SKIP, int I = 0, class P, class V>
+__device__ __forceinline__ void weave(P& product, V& piece)
+{
+    if constexpr (I < N) {
+        product(std::integral_constant<int, I>());
+        constexpr int from = I <= SKIP ? 0 : U * (I - SKIP) / (N - SKIP), to = I < SKIP ? 0 : U * (I + 1 - SKIP) / (N - SKIP);
+        repeat<from, to>(piece);
+        __builtin_amdgcn_sched_barrier(0);
+        weave<N, U, SKIP, I + 1>(product, piece);
+    }
+}
+
+// 1 / x for x in [1, inf]: the hardware's estimate and one Newton step (within an ulp; inf gives 0)
+__device__ __forceinline__ float recip(float x)
+{
+    const float r = __builtin_amdgcn_rcpf(x);
+    const float e = fmaf(-x, r, 1.0f);
+    return x < 3.0e38f ? fmaf(e, r, r) : r;
+}
+
+// Inclusive prefix sum over the samples of a ray: segments of 8 lanes (`tile`) or of 32.  k = position in
+// the segment.
+__device__ __forceinline__ float ray_scan(float v, int k, bool tile)
+{
+    float t = dpp_or_zero<0x111, 0xf>(v);
+    v += k >= 1 ? t : 0.0f;
+    t = dpp_or_zero<0x112, 0xf>(v);
+    v += k >= 2 ? t : 0.0f;
+    t = dpp_or_zero<0x114, 0xf>(v);
+    v += k >= 4 ? t : 0.0f;
+    t = dpp_or_zero<0x118, 0xf>(v);
+    v += tile ? 0.0f : t;
+    t = dpp_or_zero<0x142, 0xa>(v);
+    v += tile ? 0.0f : t;
+    return v;
+}
+
+// Interpolated channels [ch0, ch0 + NCH) at cell c: the corners in groups of four (the two x faces of a voxel
+// cell, the planes of a triplane); a group's loads are issued together.  STAGED: one group after the
+// other (at most 4 NCH registers of raw texels), else the compiler may issue them all.
+template <int KIND, int C, int NCH, int GT, bool STAGED>
+__device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const Cell3& c, int ch0, float* feat)
+{
+    constexpr int kPerVec = GT == LP_F32 ? 4 : 8, kVecs = NCH / kPerVec;
+    constexpr unsigned kElem = GT == LP_F32 ? 4u : 2u;
+    constexpr int kGroups = KIND == LP_GRID_TRIPLANE ? 3 : 2;
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) feat[k] = 0.0f;
+#pragma unroll
+    for (int gr = 0; gr < kGroups; ++gr) {
+        uint4 raw[4][kVecs];
+        float w[4];
+        if constexpr (KIND == LP_GRID_TRIPLANE) {
+            const int a = gr, b = (gr + 1) % 3;
+            const char* P = reinterpret_cast<const char*>(g.data[gr]) + (size_t)scene * g.N[a] * g.N[b] * C * kElem;
+            const unsigned sa = (unsigned)g.N[b] * C;
+            const unsigned base = (unsigned)c.i[a] * sa + (unsigned)c.i[b] * C + ch0;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int da = d >> 1, db = d & 1;
+                const uint4* p = reinterpret_cast<const uint4*>(P + (size_t)((base + da * sa + db * C) * kElem));
+#pragma unroll
+                for (int i = 0; i < kVecs; ++i) raw[d][i] = p[i];
+                w[d] = (da ? c.f[a] : 1.0f - c.f[a]) * (db ? c.f[b] : 1.0f - c.f[b]);
+            }
+        } else {
+            const char* V = reinterpret_cast<const char*>(g.data[0]) +
+                            (size_t)scene * g.N[0] * g.N[1] * g.N[2] * C * kElem;
+            const unsigned sy = (unsigned)g.N[2] * C, sx = (unsigned)g.N[1] * sy;
+            const unsigned base = ((unsigned)c.i[0] + gr) * sx + (unsigned)c.i[1] * sy + (unsigned)c.i[2] * C + ch0;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int dy = d >> 1, dz = d & 1;
+                const uint4* p = reinterpret_cast<const uint4*>(V + (size_t)((base + dy * sy + dz * C) * kElem));
+#pragma unroll
+                for (int i = 0; i < kVecs; ++i) raw[d][i] = p[i];
+                w[d] = (gr ? c.f[0] : 1.0f - c.f[0]) * (dy ? c.f[1] : 1.0f - c.f[1]) * (dz ? c.f[2] : 1.0f - c.f[2]);
+            }
+        }
+        if constexpr (STAGED) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int i = 0; i < kVecs; ++i) {
+                float v[kPerVec];
+                unpack_values<GT>(raw[d][i], v);
+#pragma unroll
+                for (int e = 0; e < kPerVec; ++e) feat[kPerVec * i + e] += w[d] * v[e];
+            }
+        if constexpr (STAGED) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// ---- scatter of a step's feature gradient as a matrix product ----
+// The samples of a step lie in a small window of texels (of each plane).  The window's gradient is
+//     window[texel][channel] = sum over the 32 samples of weight[texel][sample] * dF[sample][channel],
+// a contraction over the samples that the matrix cores take in fp32 (no operand splitting: the weights
+// and the gradient are the same fp32 values a scalar scatter would multiply), and each texel that was
+// touched gets one atomic add per channel, instead of one per run of samples in a cell and corner.
+// The weight of a texel is the product of its coordinates' weights along the axes (1 - f at the sample's cell,
+// f at the next, 0 elsewhere); these stand in an LDS table [axis][coordinate in the window][sample],
+// from which lane = texel reads the samples of its lane group as 16-byte vectors.
+constexpr int kWinExtent = 12;                       // texels of a window along one axis at most
+constexpr int kWinTexels = 128;                      // texels of a window at most; larger ones take the walk
+constexpr int kWinRow = 144;                         // bytes of a table row: 32 samples (and 16 of padding: no bank conflicts)
+constexpr int kWinZeroRow = 3 * kWinExtent;          // a row of zeros, for lanes without a texel
+constexpr int kWinOffsets = (kWinZeroRow + 1) * kWinRow;
+static_assert(kWinOffsets + 32 * 4 <= 8192 && ((kWinZeroRow + 1) * kWinRow) % 16 == 0, "the table fits a wave's area");
+
+struct Window {
+    int lo[3], ext[3];   // uniform: first texel and number of texels along each axis
+};
+
+// v of another lane of the row of 16 (a permutation: every lane has a source)
+template <int CTRL>
+__device__ __forceinline__ int row_perm(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+
+// extremes over lanes 0 .. 31 (both lane groups hold the same cells)
+__device__ __forceinline__ Window find_window(const Cell3& c)
+{
+    int lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) lo[a] = hi[a] = c.i[a];
+    auto step = [&](auto perm) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = min(lo[a], perm(lo[a]));
+            hi[a] = max(hi[a], perm(hi[a]));
+        }
+    };
+    step([](int v) { return row_perm<0xb1>(v); });    // lane ^ 1
+    step([](int v) { return row_perm<0x4e>(v); });    // lane ^ 2
+    step([](int v) { return row_perm<0x141>(v); });   // mirrored halves of a row
+    step([](int v) { return row_perm<0x140>(v); });   // mirrored row
+    Window w;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        w.lo[a] = min(__builtin_amdgcn_readlane(lo[a], 0), __builtin_amdgcn_readlane(lo[a], 16));
+        w.ext[a] = max(__builtin_amdgcn_readlane(hi[a], 0), __builtin_amdgcn_readlane(hi[a], 16)) - w.lo[a] + 2;
+    }
+    return w;
+}
+
+template <int KIND>
+__device__ __forceinline__ bool window_fits(const Window& w)
+{
+    if (max(w.ext[0], max(w.ext[1], w.ext[2])) > kWinExtent) return false;
+    if constexpr (KIND == LP_GRID_TRIPLANE)
+        return max(w.ext[0] * w.ext[1], max(w.ext[1] * w.ext[2], w.ext[2] * w.ext[0])) <= kWinTexels;
+    else
+        return w.ext[0] * w.ext[1] * w.ext[2] <= kWinTexels;
+}
+
+// n / d for 0 <= n < 2^12 and the reciprocal inv of d <= 144 (the offset of one half keeps the rounding away)
+__device__ __forceinline__ int small_div(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
+
+// dFt: feature gradient, lane = channel (16 channels: lanes 16 .. 31 repeat lanes 0 .. 15), register r =
+// column d_row(r, grp) of the step.  `area`: the wave's LDS area for the table.
+template <int KIND, int C>
+__device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
+                                               const Window& win, const Cell3& cell, const f32x16& dFt, int lane)
+{
+    const int col = lane & 31, grp = lane >> 5;
+    // the table: zeros, then this sample's two entries per axis (lane group 0 the lower, 1 the upper)
+    wave_lds_fence();
+    for (int i = lane; i < (kWinZeroRow + 1) * kWinRow / 16; i += 64)
+        lds_put<u32x4>(area + 16 * i, u32x4{0u, 0u, 0u, 0u});
+    wave_lds_fence();
+    const int pos = slot_to_sample(col);   // 16 grp + r for column d_row(r, grp)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int row = a * kWinExtent + cell.i[a] - win.lo[a] + grp;
+        lds_put<float>(area + row * kWinRow + pos * 4, grp ? cell.f[a] : 1.0f - cell.f[a]);
+    }
+    wave_lds_fence();
+
+    constexpr int kLanes = C == 32 ? 32 : 16;         // texels per matrix product
+    constexpr int kVec = C == 32 ? 4 : 2;             // 16-byte vectors of samples per lane
+    const int slot = lane & (kLanes - 1);
+    const int first = C == 32 ? 64 * grp : 32 * (lane >> 4);   // byte offset of this lane's samples in a row
+    float b16[8];
+    if constexpr (C == 16) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            float a = dFt[k], b = dFt[k + 8];
+            asm("" : "+v"(a), "+v"(b));   // (or the compiler turns the choice into an indexed read of dFt)
+            b16[k] = (lane & 16) ? b : a;
+        }
+    }
+
+    constexpr int kPlanes = KIND == LP_GRID_TRIPLANE ? 3 : 1;
+#pragma unroll
+    for (int pl = 0; pl < kPlanes; ++pl) {
+        // axes of the window, slowest first
+        const int a0 = KIND == LP_GRID_TRIPLANE ? pl : 0, a1 = KIND == LP_GRID_TRIPLANE ? (pl + 1) % 3 : 1;
+        const int e1 = win.ext[a1], e2 = KIND == LP_GRID_TRIPLANE ? 1 : win.ext[2];
+        const int total = win.ext[a0] * e1 * e2;
+        const float inv12 = __builtin_amdgcn_rcpf((float)(e1 * e2)), inv2 = __builtin_amdgcn_rcpf((float)e2);
+        char* out;
+        if constexpr (KIND == LP_GRID_TRIPLANE) out = reinterpret_cast<char*>(d_grid[pl] + (size_t)scene * g.N[a0] * g.N[a1] * C);
+        else out = reinterpret_cast<char*>(d_grid[0] + (size_t)scene * g.N[0] * g.N[1] * g.N[2] * C);
+        for (int n0 = 0; n0 < total; n0 += kLanes) {
+            const bool live = n0 + slot < total;
+            const int n = live ? n0 + slot : 0;   // (lanes without a texel: all weights zero, the first texel's address)
+            const int t0 = small_div(n, inv12), rest = n - t0 * (e1 * e2);
+            const int t1 = KIND == LP_GRID_TRIPLANE ? rest : small_div(rest, inv2), t2 = rest - t1 * e2;
+            unsigned off;
+            if constexpr (KIND == LP_GRID_TRIPLANE)
+                off = ((unsigned)(win.lo[a0] + t0) * (unsigned)g.N[a1] + (unsigned)(win.lo[a1] + t1)) * C;
+            else
+                off = (((unsigned)(win.lo[0] + t0) * (unsigned)g.N[1] + (unsigned)(win.lo[1] + t1)) * (unsigned)g.N[2] +
+                       (unsigned)(win.lo[2] + t2)) * C;
+            const uint32_t r0 = area + (live ? a0 * kWinExtent + t0 : kWinZeroRow) * kWinRow + first;
+            const uint32_t r1 = area + (live ? a1 * kWinExtent + t1 : kWinZeroRow) * kWinRow + first;
+            const uint32_t r2 = area + (live ? 2 * kWinExtent + t2 : kWinZeroRow) * kWinRow + first;
+            float w[4 * kVec];
+#pragma unroll
+            for (int v = 0; v < kVec; ++v) {
+                const f32x4 x = lds_get<f32x4>(r0 + 16 * v), y = lds_get<f32x4>(r1 + 16 * v);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[4 * v + e] = x[e] * y[e];
+                if constexpr (KIND != LP_GRID_TRIPLANE) {
+                    const f32x4 z = lds_get<f32x4>(r2 + 16 * v);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[4 * v + e] *= z[e];
+                }
+            }
+            // offsets of all texels of this product, for the lanes that will hold their rows
+            wave_lds_fence();
+            if (lane < kLanes) lds_put<uint32_t>(area + kWinOffsets + 4 * slot, off);
+            wave_lds_fence();
+            auto add = [&](unsigned texel_off, float v) {
+                if (v != 0.0f) atomicAdd(reinterpret_cast<float*>(out + 4u * (texel_off + (unsigned)(lane & (C - 1)))), v);
+            };
+            if constexpr (C == 32) {
+                f32x16 acc = zero16();
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[r], dFt[r], acc, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (n0 + 8 * q >= total) break;
+                    const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 4 * (8 * q + 4 * grp));
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) add(o[p], acc[4 * q + p]);
+                }
+            } else {
+                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int k = 0; k < 8; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b16[k], acc, 0, 0, 0);
+                const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 16 * (lane >> 4));
+#pragma unroll
+                for (int p = 0; p < 4; ++p) add(o[p], acc[p]);
+            }
+        }
+    }
+}
+
+// The walk on a step of the tile kernel: records and feature gradient go through LDS in the order of the
+// walk (16 positions per lane group): samples of one ray in order, or ray after ray of a tile, every other
+// one backwards, so that the step from ray to ray is a short one.
+template <int KIND, int C>
+__device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_grid[3], int scene, char* area,
+                                             const Cell3& cell, const f32x16& dFt, int lane, bool tile)
+{
+    const int col = lane & 31, grp = lane >> 5;
+    auto flip = [tile](int c) { return (tile && (c & 8)) ? c ^ 7 : c; };   // column <-> position of the walk
+    float* info = reinterpret_cast<float*>(area);
+    float* grad = reinterpret_cast<float*>(area + 2048);
+    wave_lds_fence();
+    if (grp == 0) write_scatter_record<KIND, C>(info + flip(col) * 16, g, cell);
+    if (col < C) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) grad[flip(d_row(r, grp)) * C + col] = dFt[r];
+    }
+    wave_lds_fence();
+    f32x16 v;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = grad[(16 * grp + r) * C + (col & (C - 1))];
+    scatter_channels<KIND, C, true>(g, d_grid, scene, info, v, col, grp);
+    wave_lds_fence();
+}
+
+// One launch: `n_items` work items, consecutive tiles of kTileRays rays (`tiles`) or single rays, handed out
+// to the first `busy` waves of each workgroup in groups of `busy`, the groups in a scrambled order
+// (neighbouring rays add into the same lines; spread over time their adds do not queue up at one L2 channel).
+struct TileSchedule {
+    long long n_groups, group_mul, group_step;
+    int tiles, busy;
+};
+
+template <int KIND, int C, int H, int NH, bool CC, int GT>
+__global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, MlpDev m, RaysDev rays, BwdIo io,
+                                                                   TileSchedule sched)
+{
+    using L = TileLds<C, H, NH>;
+    using IW1 = typename L::W1;      // also the image of a step's input features
+    using IH = typename L::WH;       // also the image of a step's hidden tensors
+    constexpr int MB = H / 32, KS1 = C / 16, KSH = H / 16, G16 = H / 16;
+    constexpr int kLoH = IH::bytes(32), kLoF = IW1::bytes(32);   // hi image -> lo image of a step's tensors
+    extern __shared__ uint4 lds_raw[];
+    const uint32_t lds = (uint32_t)(uintptr_t)(LdsByte*)reinterpret_cast<char*>(lds_raw);
+
+    // ---- staging ----
+    if constexpr (NH == 2) stage_image<IH, H, true>(lds + L::W2_AT, m.W[1], H, H);
+    stage_image<IW1, C, false>(lds + L::W1_AT, m.W[0], H, C);
+    for (int idx = threadIdx.x; idx < 4 * (H / 8); idx += blockDim.x) {   // output layer, rows
+        const int row = idx / (H / 8), chunk = idx % (H / 8);
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = m.W[NH][row * H + 16 * (chunk >> 1) + 8 * (e / 4) + 4 * (chunk & 1) + (e % 4)];
+        Frag hi, lo;
+        split8(x, hi, lo);
+        lds_put_chunk(lds + L::WO_AT + row * L::kWo + chunk * 16, hi);
+        lds_put_chunk(lds + L::WO_AT + (4 + row) * L::kWo + chunk * 16, lo);
+    }
+    float* bias = reinterpret_cast<float*>(reinterpret_cast<char*>(lds_raw) + L::BIAS_AT);
+    for (int i = threadIdx.x; i < H; i += blockDim.x) {
+        bias[i] = m.b[0][i];
+        bias[H + i] = NH == 2 ? m.b[1][i] : 0.0f;
+    }
+    if (threadIdx.x < 4) bias[2 * H + threadIdx.x] = m.b[NH][threadIdx.x];
+    __syncthreads();
+
+    uint32_t lane_id = threadIdx.x & 63;   // (refreshed like the addresses)
+    const int lane = lane_id, col = lane & 31, grp = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t acts = lds + wave * 2 * L::kAct;               // this wave's step tensors
+    const uint32_t dz_at = lds + L::SMALL_AT + wave * L::kSmall;  // its output gradients
+    const uint32_t ray_at = dz_at + L::RAY;                       // its rays
+    const int S = rays.S;
+
+    // gradient accumulators, alive for the whole kernel
+    f32x16 dW2[MB][MB];                    // NH == 2
+    f32x16 dW1w[MB];                       // C == 32
+    f32x4 dW1t[G16];                       // C == 16
+    f32x4 dWo = {0.0f, 0.0f, 0.0f, 0.0f};  // lane = hidden feature (H = 32: twice, for half of the samples each), register = output
+    float db1[C == 32 ? MB : G16], db2[MB];
+    float dbo[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int a = 0; a < MB; ++a) {
+        db2[a] = 0.0f;
+        if constexpr (C == 32) { dW1w[a] = zero16(); db1[a] = 0.0f; }
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+            if constexpr (NH == 2) dW2[a][b] = zero16();
+    }
+#pragma unroll
+    for (int a = 0; a < G16; ++a) {
+        const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (C == 16) { dW1t[a] = z; db1[a] = 0.0f; }
+    }
+
+    // ---- work items ----
+    const bool tiles = sched.tiles != 0;
+    const int rays_per_item = tiles ? kTileRays : 1;
+    const int blocks_per_xcd = gridDim.x / 8;
+    const long long per_xcd = (sched.n_groups + 7) / 8;
+    long long seq = per_xcd * (blockIdx.x % 8) + blockIdx.x / 8;
+    const long long seq_end = min(per_xcd * (blockIdx.x % 8 + 1), sched.n_groups);
+    long long group = seq < seq_end ? (seq * sched.group_mul) % sched.n_groups : 0;
+    auto item_ray = [&]() { return (group * sched.busy + wave) * rays_per_item; };   // first ray of the item
+    auto next_group = [&]() {
+        do {
+            seq += blocks_per_xcd;
+            group += sched.group_step;
+            if (group >= sched.n_groups) group -= sched.n_groups;
+        } while (seq < seq_end && item_ray() >= rays.M);
+    };
+    bool live = wave < sched.busy && seq < seq_end;
+    if (live && item_ray() >= rays.M) { next_group(); live = seq < seq_end; }
+
+    // the rays being marched: `tile` (four rays, eight samples each per step) or one ray, number `sub` of the item
+    bool tile = false;
+    int sub = 0, j0 = 0, scene = 0;
+    int k = 0;                  // this lane's sample in the step
+    bool ray_ok = false;        // the lane's ray exists
+    float tau_end = 0.0f, carry = 0.0f;
+    Cell3 cell;
+    Frag fh[KS1], fl[KS1];
+
+    // the lane's ray, kept in LDS between the steps
+    auto geometry = [&]() {
+        const int col = lane_id & 31;
+        const uint32_t p = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
+        const f32x4 a = lds_get<f32x4>(p), b = lds_get<f32x4>(p + 16);
+        RayGeom q;
+        q.ox = a[0]; q.oy = a[1]; q.oz = a[2]; q.dx = a[3]; q.dy = b[0]; q.dz = b[1]; q.near = b[2]; q.delta = b[3];
+        q.delta64 = lds_get<double>(p + 32);
+        q.scene = scene;
+        q.time = 0.0f;
+        return q;
+    };
+    // loads the rays of the current item (`sub` = 0: and decides how they are marched)
+    auto load_rays = [&]() {
+        const int col = lane_id & 31, grp = lane_id >> 5;
+        const long long first = item_ray();
+        if (tiles && sub == 0) {
+            // side by side: in one scene, and within three cells of the first ray at both ends
+            const long long r = min(first + (col >> 3), rays.M - 1);
+            const RayGeom q = load_ray_geom(rays, r);
+            const Cell3 c0 = sample_cell_for<CC, GT>(g, q, 0), c1 = sample_cell_for<CC, GT>(g, q, S - 1);
+            bool apart = q.scene != __builtin_amdgcn_readfirstlane(q.scene);
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                apart = apart || abs(c0.i[a] - __builtin_amdgcn_readfirstlane(c0.i[a])) > 3 ||
+                        abs(c1.i[a] - __builtin_amdgcn_readfirstlane(c1.i[a])) > 3;
+            tile = __ballot(apart) == 0ull;
+        }
+        const long long r = first + (tile ? (col >> 3) : sub);
+        ray_ok = r < rays.M;
+        const long long ray = min(r, rays.M - 1);
+        const RayGeom q = load_ray_geom(rays, ray);
+        scene = __builtin_amdgcn_readfirstlane(q.scene);
+        k = tile ? (col & 7) : col;
+        const float p0 = io.d_rgb[3 * ray + 0], p1 = io.d_rgb[3 * ray + 1], p2 = io.d_rgb[3 * ray + 2];
+        const float p_alpha = io.d_alpha ? io.d_alpha[ray] : 0.0f;
+        const float p_depth = io.d_depth ? io.d_depth[ray] : 0.0f;
+        tau_end = io.cache[ray];   // optical depth up to the end of the current step
+        // d(loss)/dT_S through alpha = 1 - T_S and rgb += T_S bg, times T_S
+        const float kS = __expf(-tau_end) * (p_alpha - (p0 * io.bg[0] + p1 * io.bg[1] + p2 * io.bg[2]));
+        wave_lds_fence();
+        if (k == 0 && grp == 0) {
+            const uint32_t p = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
+            const f32x4 v[3] = {{q.ox, q.oy, q.oz, q.dx}, {q.dy, q.dz, q.near, q.delta}, {p0, p1, p2, p_depth}};
+            lds_put<f32x4>(p, v[0]);
+            lds_put<f32x4>(p + 16, v[1]);
+            lds_put<double>(p + 32, q.delta64);
+            lds_put<float>(p + 40, kS);
+            lds_put<f32x4>(p + 48, v[2]);
+        }
+        wave_lds_fence();
+        carry = 0.0f;              // sum of w_j a_j over all later steps
+        const int step = tile ? kTileSamples : 32;
+        j0 = ((S - 1) / step) * step;
+    };
+    // features of the lane's sample of the step at j0
+    auto sample = [&]() {
+        refresh(lane_id);
+        const int grp = lane_id >> 5;
+        const RayGeom q = geometry();
+        cell = sample_cell_for<CC, GT>(g, q, min(j0 + k, S - 1));
+        float feat[C / 2];
+        gather_stream<KIND, C, C / 2, GT, (C == 32 || KIND == LP_GRID_TRIPLANE)>(g, scene, cell, grp * (C / 2), feat);
+#pragma unroll
+        for (int s = 0; s < KS1; ++s) split8(feat + 8 * s, fh[s], fl[s]);
+        // complete before the scatter: memory operations return in order, and the scatter's adds are slow
+#pragma unroll
+        for (int s = 0; s < KS1; ++s)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) asm volatile("" : "+v"(fh[s].d[w]), "+v"(fl[s].d[w]));
+    };
+    if (live) {
+        load_rays();
+        sample();
+    }
+
+    // addresses: this lane's chunks and columns of the step tensors; those of the weights differ by uniform amounts
+    uint32_t own_h = acts + IH::own(lane), col_h = acts + IH::col32(lane), col16_h = acts + IH::col16(lane);
+    uint32_t col64_h = acts + IH::col64(lane), own_f = acts + IW1::own(lane);
+    uint32_t col_f = acts + (C == 32 ? IW1::col32(lane) : IW1::col16(lane)), col_f32 = acts + IW1::col32(lane);
+    const uint32_t to_w2 = lds + L::W2_AT - acts, to_w1 = lds + L::W1_AT - acts;
+
+    // Values 2 u, 2 u + 1 (u = 0 .. 7) of row block mb of a layer's output -> relu -> operand of the next layer, and
+    // with every fourth pair a chunk into the images at `where`.
+    auto activate_pair = [&](const f32x16& d, int mb, int u, uint32_t where, Frag (&h)[1][KSH], Frag (&l)[1][KSH]) {
+        const int s = 2 * mb + u / 4;
+        split2(relu_f(d[2 * u]), relu_f(d[2 * u + 1]), h[0][s].d[u % 4], l[0][s].d[u % 4]);
+        pin(h[0][s].d[u % 4]);
+        pin(l[0][s].d[u % 4]);
+        if (u % 4 == 3) {
+            lds_put_chunk((own_h ^ IH::own_step(s)) + where, h[0][s]);
+            lds_put_chunk((own_h ^ IH::own_step(s)) + where + kLoH, l[0][s]);
+        }
+    };
+    // The same for a gradient with the mask relu'(.) taken from the stored activation's hi half: 0 or 1 per half
+    // (written out, or the compiler takes the halves apart), applied by 16-bit products on the split halves (left to
+    // the compiler, which keeps the wait states between a vector write and a matrix read).
+    auto gradient_pair = [&](const f32x16& d, int mb, int u, const Frag (&act)[2], Frag (&h)[1][KSH], Frag (&l)[1][KSH]) {
+        typedef __attribute__((__vector_size__(4))) unsigned short u16x2;
+        constexpr uint32_t kOnes = 0x00010001u;
+        const int s = 2 * mb + u / 4;
+        uint32_t on, hi, lo;
+        split2(d[2 * u], d[2 * u + 1], hi, lo);
+        asm("v_pk_min_u16 %0, %1, %2" : "=v"(on) : "v"(act[u / 4].d[u % 4]), "s"(kOnes));
+        h[0][s].d[u % 4] = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, hi) * __builtin_bit_cast(u16x2, on)));
+        l[0][s].d[u % 4] = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, lo) * __builtin_bit_cast(u16x2, on)));
+        pin(h[0][s].d[u % 4]);
+        pin(l[0][s].d[u % 4]);
+    };
+    auto read_acts = [&](uint32_t where, int mb, Frag (&act)[2]) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) act[s] = lds_chunk((own_h ^ IH::own_step(2 * mb + s)) + where);
+    };
+    // D registers of a layer -> operand fragments -> the wave's images at A or B
+    auto store_hidden = [&](uint32_t where, const Frag (&h)[1][KSH], const Frag (&l)[1][KSH]) {
+#pragma unroll
+        for (int s = 0; s < KSH; ++s) {
+            lds_put_chunk((own_h ^ IH::own_step(s)) + where, h[0][s]);
+            lds_put_chunk((own_h ^ IH::own_step(s)) + where + kLoH, l[0][s]);
+        }
+    };
+    while (live) {
+        refresh(own_h); refresh(own_f); refresh(lane_id);
+        const uint32_t own_w = own_h + to_w2, own_w1 = own_f + to_w1;
+        const int lane = lane_id, col = lane & 31, grp = lane >> 5;
+        // ---- MLP forward ----
+        float z[4];
+        {
+            auto none = [](auto) {};
+            Frag hh[1][KSH], hl[1][KSH], wh[2], wl[2];   // weights of two products, the next one's read ahead
+            f32x16 acc[MB], acc2[MB];
+            auto start = [&](f32x16 (&a)[MB], const float* b) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 v = *reinterpret_cast<const f32x4*>(b + 32 * mb + 8 * q + 4 * grp);
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) a[mb][4 * q + p] = v[p];
+                    }
+            };
+            auto read_w = [&](int slot, uint32_t at, int lo) { wh[slot] = lds_chunk(at); wl[slot] = lds_chunk(at + lo); };
+            // product number i of the first layer: K-step i / 3 % KS1 of row block i / (3 KS1)
+            auto w1_at = [&](int t) { return (own_w1 ^ IW1::own_step(t % KS1)) + (t / KS1) * 32 * IW1::kRow; };
+            auto layer1 = [&](auto ic) {
+                constexpr int i = decltype(ic)::value, t = i / 3, s = t % KS1, mb = t / KS1;
+                if constexpr (i % 3 == 0 && t + 1 < MB * KS1) read_w((t + 1) & 1, w1_at(t + 1), IW1::bytes(H));
+                acc[mb] = mfma1(i % 3 == 0 ? wl[t & 1] : wh[t & 1], i % 3 == 1 ? fl[s] : fh[s], acc[mb]);
+                pin(acc[mb]);
+            };
+            start(acc, bias);
+            read_w(0, w1_at(0), IW1::bytes(H));
+            auto activate_1a = [&](auto u) { activate_pair(acc[0], 0, u, L::A, hh, hl); };
+            {
+                auto first = [&](auto i) { layer1(i); };
+                weave<3 * KS1, 0, 0>(first, none);
+            }
+            // second layer: the K-steps of the first block of activations for all rows, then those of the second block
+            constexpr int T2 = MB * KSH;   // (row block, K-step) pairs in this order
+            auto mb_of = [](int t) { return MB == 1 ? 0 : t < 4 ? t & 1 : (t - 4) >> 1; };
+            auto s_of = [](int t) { return MB == 1 ? t : t < 4 ? t >> 1 : 2 + (t & 1); };
+            auto w2_at = [&](int t) { return (own_w ^ IH::own_step(s_of(t))) + mb_of(t) * 32 * IH::kRow; };
+            auto layer2 = [&](auto ic) {
+                constexpr int i = decltype(ic)::value, t = i / 3;
+                const int s = s_of(t), mb = mb_of(t);
+                if constexpr (i % 3 == 0 && t + 1 < T2) read_w((t + 1) & 1, w2_at(t + 1), IH::bytes(H));
+                acc2[mb] = mfma1(i % 3 == 0 ? wl[t & 1] : wh[t & 1], i % 3 == 1 ? hl[0][s] : hh[0][s], acc2[mb]);
+                pin(acc2[mb]);
+            };
+            if constexpr (MB == 2) {
+                auto second = [&](auto i) { layer1(std::integral_constant<int, decltype(i)::value + 3 * KS1>()); };
+                weave<3 * KS1, 8, 1>(second, activate_1a);
+            } else {
+                repeat<0, 8>(activate_1a);
+            }
+            auto activate_1b = [&](auto u) { if constexpr (MB == 2) activate_pair(acc[MB - 1], MB - 1, u, L::A, hh, hl); };
+            if constexpr (NH == 2) {
+                start(acc2, bias + H);
+                read_w(0, w2_at(0), IH::bytes(H));
+                auto part1 = [&](auto i) { layer2(i); };
+                weave<(MB == 2 ? 12 : 6), (MB == 2 ? 8 : 0), 2>(part1, activate_1b);
+                if constexpr (MB == 2) {
+                    auto part2 = [&](auto i) { layer2(std::integral_constant<int, decltype(i)::value + 12>()); };
+                    weave<6, 0, 0>(part2, none);
+                }
+            } else {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc2[mb] = acc[mb];
+            }
+            // output layer: rows 0..3 and 4..7 of the operand are the hi halves of the four rows (one copy per
+            // lane group), rows 8..11 and 12..15 their lo halves
+            constexpr int kHere = NH == 2 ? L::B : L::A;
+            f32x16 o;
+            const f32x4 b = *reinterpret_cast<const f32x4*>(bias + 2 * H);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[r] = r < 4 ? b[r] : 0.0f;
+            const uint32_t wo_at = lds + L::WO_AT + ((col & 3) + ((col >> 1) & 4)) * L::kWo + grp * 16;
+            Frag wo[2];
+            wo[0] = lds_chunk(wo_at);
+            auto output = [&](auto ic) {
+                constexpr int i = decltype(ic)::value, s = i / 2;
+                if constexpr (i % 2 == 0 && s + 1 < KSH) wo[(s + 1) & 1] = lds_chunk(wo_at + 32 * (s + 1));
+                o = mfma1(wo[s & 1], i % 2 ? hh[0][s] : hl[0][s], o);
+                pin(o);
+            };
+            auto activate_2a = [&](auto u) { if constexpr (NH == 2) activate_pair(acc2[0], 0, u, kHere, hh, hl); };
+            auto activate_2b = [&](auto u) {
+                if constexpr (NH == 2 && MB == 2) activate_pair(acc2[MB - 1], MB - 1, u, kHere, hh, hl);
+                else activate_1b(u);
+            };
+            if constexpr (NH == 2 && MB == 2) {
+                auto part3 = [&](auto i) { layer2(std::integral_constant<int, decltype(i)::value + 18>()); };
+                weave<6, 8, 1>(part3, activate_2a);
+            } else if constexpr (NH == 2) {
+                repeat<0, 8>(activate_2a);
+            }
+            weave<4, (MB == 2 ? 8 : 0), 0>(output, activate_2b);
+            if constexpr (MB == 2) {
+                auto rest = [&](auto i) { output(std::integral_constant<int, decltype(i)::value + 4>()); };
+                weave<4, 0, 0>(rest, none);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] = o[i] + o[4 + i];
+        }
+
+        // ---- Eq. (2); column col stands for sample j0 + k of the lane's ray (both lane groups alike) ----
+        uint32_t zh0, zl0, zh1, zl1;
+        {
+            const uint32_t geo = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
+            const float near = lds_get<float>(geo + 24), delta = lds_get<float>(geo + 28), kS = lds_get<float>(geo + 40);
+            const f32x4 p = lds_get<f32x4>(geo + 48);
+            const float p0 = p[0], p1 = p[1], p2 = p[2], p_depth = p[3];
+            const int j = j0 + k;
+            const bool valid = ray_ok && j < S;
+            const int last = lane | (tile ? kTileSamples - 1 : 31);
+            const float t = near + ((float)j + 0.5f) * delta;
+            // softplus and its derivative from one exponential
+            const float ez = __expf(-fabsf(z[0])), rz = recip(1.0f + ez);
+            const float sd = valid ? (fmaxf(z[0], 0.0f) + __logf(1.0f + ez)) * delta : 0.0f;
+            const float incl = ray_scan(sd, k, tile);
+            const float tau_start = tau_end - __shfl(incl, last, 64);
+            const float Tprev = __expf(-(tau_start + (incl - sd)));
+            const float w = Tprev * one_minus_exp_neg(sd);
+            const float Tq = Tprev - w;
+            const float c1 = recip(1.0f + __expf(-z[1])), c2 = recip(1.0f + __expf(-z[2])), c3 = recip(1.0f + __expf(-z[3]));
+            const float aa = p0 * c1 + p1 * c2 + p2 * c3 + p_depth * t;
+            const float wa = w * aa;
+            const float pre = ray_scan(wa, k, tile);
+            const float wa_total = __shfl(pre, last, 64);
+            const float suf = wa_total - pre + wa;
+            const float dsigma = delta * (Tq * aa - (suf - wa + carry) + kS);
+            carry += wa_total;
+            tau_end = tau_start;
+            float dz[4];
+            dz[0] = valid ? dsigma * (z[0] >= 0.0f ? rz : ez * rz) : 0.0f;
+            dz[1] = valid ? w * p0 * c1 * (1.0f - c1) : 0.0f;
+            dz[2] = valid ? w * p1 * c2 * (1.0f - c2) : 0.0f;
+            dz[3] = valid ? w * p2 * c3 * (1.0f - c3) : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dbo[i] += dz[i];
+            split2(dz[0], dz[1], zh0, zl0);
+            split2(dz[2], dz[3], zh1, zl1);
+            lds_put<u32x4>(dz_at + col * 16, u32x4{zh0, zh1, zl0, zl1});   // (both lane groups the same)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+
+        constexpr int kLast = NH == 2 ? L::B : L::A;   // the last hidden layer's activations
+        refresh(own_h); refresh(col_h); refresh(col64_h);
+        auto none = [](auto) {};
+        // ---- last hidden layer: dZ = relu'(.) * (Wout^T dZo); the K range holds hi*hi, hi*lo, lo*hi ----
+        f32x16 acc[MB];
+        Frag gz_h[1][KSH], gz_l[1][KSH], act[MB][2];
+        {
+            Frag b;
+            b.d[0] = zh0; b.d[1] = zh1; b.d[2] = grp ? 0u : zl0; b.d[3] = grp ? 0u : zl1;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                read_acts(kLast, mb, act[mb]);
+                // columns 32 mb + (lane & 31) of the output layer's rows: hi halves for lane group 0, lo halves for 1
+                const int t16 = lane & 15, c4 = t16 & 3, G = 2 * mb + ((lane >> 4) & 1);
+                Frag a;
+                lds_read_tr(lds + L::WO_AT + (4 * grp + (t16 >> 2)) * L::kWo + (2 * G + (c4 & 1)) * 16 + (c4 >> 1) * 8, a.d[0], a.d[1]);
+                a.d[2] = grp ? 0u : a.d[0]; a.d[3] = grp ? 0u : a.d[1];
+                acc[mb] = mfma1(a, b, zero16());
+            }
+        }
+        // ---- dWo += dZo Hlast^T, beside the masking and splitting: sixteen 4 x 4 blocks (four outputs, four
+        //      features), four samples per product ----
+        {
+            const int t16 = lane & 15;
+            const uint32_t zp = dz_at + ((H == 32 ? 16 * (lane >> 5) : 0) + (t16 >> 2)) * 16;
+            s16x4 ah[2], al[2], bh[2], bl[2];
+            auto read = [&](int n) {
+                const uint32_t hp = col64_h ^ IH::rows4(n & 3);
+                ah[n & 1] = lds_tr(zp + n * 64); al[n & 1] = lds_tr(zp + n * 64 + 8);
+                bh[n & 1] = lds_tr(hp + (n >> 2) * 16 * IH::kRow + kLast);
+                bl[n & 1] = lds_tr(hp + (n >> 2) * 16 * IH::kRow + kLast + kLoH);
+            };
+            auto product = [&](auto ic) {
+                constexpr int i = decltype(ic)::value, n = i / 3;
+                if constexpr (i % 3 == 0 && n + 1 < H / 8) read(n + 1);
+                dWo = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(i % 3 == 0 ? al[n & 1] : ah[n & 1], i % 3 == 1 ? bl[n & 1] : bh[n & 1], dWo, 0, 0, 0);
+                pin(dWo);
+            };
+            auto piece = [&](auto ic) {
+                constexpr int u = decltype(ic)::value;
+                gradient_pair(acc[u / 8], u / 8, u % 8, act[u / 8], gz_h, gz_l);
+            };
+            read(0);
+            weave<3 * H / 8, 8 * MB, 3>(product, piece);
+        }
+
+        if constexpr (NH == 2) {
+            store_hidden(L::B, gz_h, gz_l);
+            refresh(own_h); refresh(col_h);
+            const uint32_t col_w = col_h + to_w2;
+            // ---- W2^T dZ2, row block after row block; beside it the transposed dZ2, db2 and the first block of dZ1 ----
+            f32x16 up[MB];   // W2^T dZ2
+            Frag g1_h[1][KSH], g1_l[1][KSH];
+            {
+                Frag wh[2], wl[2];
+                auto read_w = [&](int t) {
+                    wh[t & 1] = IH::read(col_w ^ (64 * (t / KSH)), (t % KSH) * 16 * IH::kRow);
+                    wl[t & 1] = IH::read(col_w ^ (64 * (t / KSH)), (t % KSH) * 16 * IH::kRow + IH::bytes(H));
+                };
+                auto product = [&](auto ic) {
+                    constexpr int i = decltype(ic)::value, t = i / 3, mb = t / KSH, s = t % KSH;
+                    if constexpr (i % 3 == 0 && t + 1 < MB * KSH) read_w(t + 1);
+                    up[mb] = mfma1(i % 3 == 0 ? wl[t & 1] : wh[t & 1], i % 3 == 1 ? gz_l[0][s] : gz_h[0][s],
+                                   i == 3 * KSH * mb ? zero16() : up[mb]);
+                    pin(up[mb]);
+                };
+                read_w(0);
+                weave<3 * KSH, 0, 0>(product, none);
+                if constexpr (MB == 2) {
+                    read_acts(L::A, 0, act[0]);
+                    auto second = [&](auto i) { product(std::integral_constant<int, decltype(i)::value + 3 * KSH>()); };
+                    auto piece = [&](auto u) { gradient_pair(up[0], 0, u, act[0], g1_h, g1_l); };
+                    weave<3 * KSH, 8, 2>(second, piece);
+                }
+            }
+            // ---- dW2 += dZ2 H1^T ; db2 += sum dZ2; beside it the last block of dZ1 ----
+            {
+                Frag ah[2], al[2], bh[2], bl[2];
+                auto read_a = [&](int q) {   // (mb, ks) = q / 2, q % 2
+                    ah[q & 1] = IH::read(col_h ^ (64 * (q / 2)), (q % 2) * 16 * IH::kRow + L::B);
+                    al[q & 1] = IH::read(col_h ^ (64 * (q / 2)), (q % 2) * 16 * IH::kRow + L::B + kLoH);
+                };
+                auto read_b = [&](int t) {   // t = (mb, ks, nb)
+                    const int nb = t % MB, ks = (t / MB) % 2;
+                    bh[t & 1] = IH::read(col_h ^ (64 * nb), ks * 16 * IH::kRow + L::A);
+                    bl[t & 1] = IH::read(col_h ^ (64 * nb), ks * 16 * IH::kRow + L::A + kLoH);
+                };
+                auto product = [&](auto ic) {
+                    constexpr int i = decltype(ic)::value, t = i / 3, nb = t % MB, q = t / MB, mb = q / 2;
+                    if constexpr (i % 3 == 0 && t + 1 < 2 * MB * MB) read_b(t + 1);
+                    if constexpr (i % 3 == 0 && nb == 0 && q + 1 < 2 * MB) read_a(q + 1);
+                    dW2[mb][nb] = mfma1(i % 3 == 0 ? al[q & 1] : ah[q & 1], i % 3 == 1 ? bl[t & 1] : bh[t & 1], dW2[mb][nb]);
+                    pin(dW2[mb][nb]);
+                    if constexpr (i % (3 * MB) == 1) {
+                        db2[mb] = frag_sum(al[q & 1], frag_sum(ah[q & 1], db2[mb]));
+                        pin(db2[mb]);
+                    }
+                };
+                auto piece = [&](auto u) { gradient_pair(up[MB - 1], MB - 1, u, act[MB - 1], g1_h, g1_l); };
+                read_acts(L::A, MB - 1, act[MB - 1]);
+                read_a(0);
+                read_b(0);
+                weave<6 * MB * MB, 8, 1>(product, piece);
+            }
+#pragma unroll
+            for (int s = 0; s < KSH; ++s) { gz_h[0][s] = g1_h[0][s]; gz_l[0][s] = g1_l[0][s]; }
+        }
+        // dZ1 and the features as images: NH == 2 in A and B, NH == 1 in B and A
+        constexpr int kZ = NH == 2 ? L::A : L::B, kF = NH == 2 ? L::B : L::A;
+        refresh(own_h); refresh(own_f); refresh(C == 32 ? col_f : col_f32);
+        const uint32_t col_w1 = (C == 32 ? col_f : col_f32) + to_w1;
+        store_hidden(kZ, gz_h, gz_l);
+#pragma unroll
+        for (int s = 0; s < KS1; ++s) {
+            lds_put_chunk((own_f ^ IW1::own_step(s)) + kF, fh[s]);
+            lds_put_chunk((own_f ^ IW1::own_step(s)) + kF + kLoF, fl[s]);
+        }
+        // ---- feature gradient, transposed: dF^T[sample][channel] = dZ1^T W1 (lane = channel) ----
+        f32x16 dFt;
+        {
+            Frag wh[2], wl[2];
+            auto read_w = [&](int s) {
+                wh[s & 1] = IW1::read(col_w1, s * 16 * IW1::kRow);
+                wl[s & 1] = IW1::read(col_w1, s * 16 * IW1::kRow + IW1::bytes(H));
+            };
+            auto product = [&](auto ic) {
+                constexpr int i = decltype(ic)::value, s = i / 3;
+                if constexpr (i % 3 == 0 && s + 1 < KSH) read_w(s + 1);
+                dFt = mfma1(i % 3 == 0 ? gz_l[0][s] : gz_h[0][s], i % 3 == 1 ? wl[s & 1] : wh[s & 1], i == 0 ? zero16() : dFt);
+                pin(dFt);
+            };
+            read_w(0);
+            weave<3 * KSH, 0, 0>(product, none);
+        }
+        refresh(col_h); refresh(col16_h); refresh(col_f);
+        // ---- dW1 += dZ1 F^T ; db1 += sum dZ1 ----
+        if constexpr (C == 32) {
+            Frag bh[2], bl[2], ah[2], al[2];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                bh[ks] = IW1::read(col_f, ks * 16 * IW1::kRow + kF);
+                bl[ks] = IW1::read(col_f, ks * 16 * IW1::kRow + kF + kLoF);
+            }
+            auto read_a = [&](int q) {
+                ah[q & 1] = IH::read(col_h ^ (64 * (q / 2)), (q % 2) * 16 * IH::kRow + kZ);
+                al[q & 1] = IH::read(col_h ^ (64 * (q / 2)), (q % 2) * 16 * IH::kRow + kZ + kLoH);
+            };
+            auto product = [&](auto ic) {
+                constexpr int i = decltype(ic)::value, q = i / 3, mb = q / 2, ks = q % 2;
+                if constexpr (i % 3 == 0 && q + 1 < 2 * MB) read_a(q + 1);
+                dW1w[mb] = mfma1(i % 3 == 0 ? al[q & 1] : ah[q & 1], i % 3 == 1 ? bl[ks] : bh[ks], dW1w[mb]);
+                pin(dW1w[mb]);
+                if constexpr (i % 3 == 1) {
+                    db1[mb] = frag_sum(al[q & 1], frag_sum(ah[q & 1], db1[mb]));
+                    pin(db1[mb]);
+                }
+            };
+            read_a(0);
+            weave<6 * MB, 0, 0>(product, none);
+        } else {
+            const Frag bh = IW1::read(col_f, kF), bl = IW1::read(col_f, kF + kLoF);
+            Frag ah[2], al[2];
+            auto read_a = [&](int G) {
+                ah[G & 1] = IH::read(col16_h ^ (32 * G), kZ);
+                al[G & 1] = IH::read(col16_h ^ (32 * G), kZ + kLoH);
+            };
+            auto product = [&](auto ic) {
+                constexpr int i = decltype(ic)::value, G = i / 3;
+                if constexpr (i % 3 == 0 && G + 1 < G16) read_a(G + 1);
+                dW1t[G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(i % 3 == 0 ? al[G & 1] : ah[G & 1]), as_bf16x8(i % 3 == 1 ? bl : bh), dW1t[G], 0, 0, 0);
+                pin(dW1t[G]);
+                if constexpr (i % 3 == 1) {
+                    db1[G] = frag_sum(al[G & 1], frag_sum(ah[G & 1], db1[G]));
+                    pin(db1[G]);
+                }
+            };
+            read_a(0);
+            weave<3 * G16, 0, 0>(product, none);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+
+        // ---- features of the next step, then the scatter of this one ----
+        const Cell3 here = cell;
+        const int here_scene = scene;
+        const bool here_tile = tile;
+        j0 -= tile ? kTileSamples : 32;
+        if (j0 < 0) {
+            if (tiles && !tile && sub + 1 < kTileRays && item_ray() + sub + 1 < rays.M) {
+                ++sub;
+            } else {
+                sub = 0;
+                next_group();
+                live = seq < seq_end;
+            }
+            if (live) load_rays();
+        }
+        if (live) sample();
+        __builtin_amdgcn_sched_barrier(0);
+        refresh(lane_id);
+        const Window win = find_window(here);
+        if (window_fits<KIND>(win)) scatter_window<KIND, C>(g, io.d_grid, here_scene, acts + L::A, win, here, dFt, lane_id);
+        else scatter_walk<KIND, C>(g, io.d_grid, here_scene, reinterpret_cast<char*>(lds_raw) + wave * 2 * L::kAct, here, dFt, lane_id, here_tile);
+        wave_lds_fence();
+    }
+
+    // ---- sums over the workgroup's waves (halving), then one record ----
+    constexpr int kRegs = (NH == 2 ? 16 * MB * MB : 0) + (C == 32 ? 16 * MB : 4 * G16) + 4 + (C == 32 ? MB : G16) + MB + 4;
+    static_assert(kTileWaves / 2 * kRegs * 256 <= L::kTotal, "half the waves' accumulators fit the LDS");
+    auto each = [&](auto f) {
+        int n = 0;
+        if constexpr (NH == 2) {
+#pragma unroll
+            for (int a = 0; a < MB; ++a)
+#pragma unroll
+                for (int b = 0; b < MB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { float v = dW2[a][b][r]; f(n++, v); dW2[a][b][r] = v; }
+        }
+        if constexpr (C == 32) {
+#pragma unroll
+            for (int a = 0; a < MB; ++a) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) { float v = dW1w[a][r]; f(n++, v); dW1w[a][r] = v; }
+                f(n++, db1[a]);
+            }
+        } else {
+#pragma unroll
+            for (int a = 0; a < G16; ++a) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { float v = dW1t[a][r]; f(n++, v); dW1t[a][r] = v; }
+                f(n++, db1[a]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { float v = dWo[r]; f(n++, v); dWo[r] = v; }
+#pragma unroll
+        for (int a = 0; a < MB; ++a) f(n++, db2[a]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f(n++, dbo[i]);
+    };
+    float* sums = reinterpret_cast<float*>(lds_raw);
+#pragma unroll 1
+    for (int half = kTileWaves / 2; half >= 1; half >>= 1) {
+        __syncthreads();
+        if (wave >= half && wave < 2 * half) {
+            float* mine = sums + (size_t)(wave - half) * kRegs * 64 + lane;
+            each([&](int n, float& v) { mine[n * 64] = v; });
+        }
+        __syncthreads();
+        if (wave < half) {
+            const float* theirs = sums + (size_t)wave * kRegs * 64 + lane;
+            each([&](int n, float& v) { v += theirs[n * 64]; });
+        }
+    }
+    if (wave != 0) return;
+    float* rec = io.ws + (size_t)blockIdx.x * io.ws_stride;
+    if constexpr (NH == 2) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int nb = 0; nb < MB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) rec[m.w_off[1] + (32 * mb + d_row(r, grp)) * H + 32 * nb + col] = dW2[mb][nb][r];
+            const float s2 = db2[mb] + __shfl_xor(db2[mb], 32, 64);
+            if (grp == 0) rec[m.b_off[1] + 32 * mb + col] = s2;
+        }
+    }
+    const int i16 = lane & 15, q16 = lane >> 4;
+    if constexpr (C == 32) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) rec[m.w_off[0] + (32 * mb + d_row(r, grp)) * C + col] = dW1w[mb][r];
+            const float s1 = db1[mb] + __shfl_xor(db1[mb], 32, 64);
+            if (grp == 0) rec[m.b_off[0] + 32 * mb + col] = s1;
+        }
+    } else {
+#pragma unroll
+        for (int G = 0; G < G16; ++G) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) rec[m.w_off[0] + (16 * G + 4 * q16 + r) * C + i16] = dW1t[G][r];
+            float s1 = db1[G] + __shfl_xor(db1[G], 16, 64);
+            s1 += __shfl_xor(s1, 32, 64);
+            if (lane < 16) rec[m.b_off[0] + 16 * G + i16] = s1;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float s = H == 32 ? dWo[r] + __shfl_xor(dWo[r], 32, 64) : dWo[r];
+        if (lane < H) rec[m.w_off[NH] + r * H + lane] = s;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float s = wave_sum(grp == 0 ? dbo[i] : 0.0f);
+        if (lane == 0) rec[m.b_off[NH] + i] = s;
+    }
+}
+
+template <int KIND, int C, int H, int NH, bool CC, int GT = LP_F32>
+hipError_t launch_bwd_tile(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io, int n_cu,
+                           hipStream_t stream)
+{
+    using L = TileLds<C, H, NH>;
+    auto kernel = bwd_tile_kernel<KIND, C, H, NH, CC, GT>;
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, L::kTotal);
+    if (e != hipSuccess) return e;
+    const int blocks = (n_cu + 7) / 8 * 8;
+    const long long waves = (long long)blocks * kTileWaves;
+    // Tiles or single rays: the longest wave's number of steps decides.  A tile's step is cheaper to scatter
+    // (measured about 1.4 times), but a launch of few rays spreads over more waves ray by ray.
+    auto rounds = [&](long long items) { return (items + waves - 1) / waves; };
+    const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays;
+    const long long tile_steps = rounds(n_tiles) * ((rays.S + kTileSamples - 1) / kTileSamples);
+    const long long ray_steps = rounds(rays.M) * ((rays.S + 31) / 32);
+    TileSchedule sc;
+    sc.tiles = 20 * tile_steps <= 21 * ray_steps;
+    const long long items = sc.tiles ? n_tiles : rays.M;
+    sc.busy = (int)((items + blocks - 1) / blocks < kTileWaves ? (items + blocks - 1) / blocks : kTileWaves);
+    sc.n_groups = (items + sc.busy - 1) / sc.busy;
+    // multiplier of the scramble: a prime that does not divide the number of groups, so that
+    // group -> group * mul mod n_groups is a bijection
+    sc.group_mul = 1;
+    for (long long p : {7919LL, 7907LL, 7901LL, 7883LL})
+        if (sc.n_groups > p && sc.n_groups % p != 0) { sc.group_mul = p; break; }
+    sc.group_step = ((long long)(blocks / 8) * sc.group_mul) % sc.n_groups;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTileWaves * 64), L::kTotal, stream, g, m, rays, io, sc);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(reduce_params_kernel, dim3((m.param_total + 63) / 64), dim3(kReduceThreads), 0, stream, m, io, blocks);
+    return hipGetLastError();
+}
+
+template <int KIND>
+hipError_t dispatch_bwd_tile(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io, int n_cu,
+                             hipStream_t stream)
+{
+    const int C = m.dims[0], H = m.dims[1], NH = m.n_layers - 1;
+    if (g.C != C) return hipErrorInvalidValue;
+    // grids stored in bf16 / fp16 take the contraction as a run-time branch (no second set of instantiations)
+#define LP_CASE(c, h, nh)                                                                                       \
+    if (C == c && H == h && NH == nh) {                                                                         \
+        if (g.dtype == LP_BF16) return launch_bwd_tile<KIND, c, h, nh, false, LP_BF16>(g, m, rays, io, n_cu, stream); \
+        if (g.dtype == LP_F16) return launch_bwd_tile<KIND, c, h, nh, false, LP_F16>(g, m, rays, io, n_cu, stream);   \
+        return g.contract > 0.0 ? launch_bwd_tile<KIND, c, h, nh, true>(g, m, rays, io, n_cu, stream)           \
+                                : launch_bwd_tile<KIND, c, h, nh, false>(g, m, rays, io, n_cu, stream);         \
+    }
+    LP_CASE(16, 32, 1) LP_CASE(16, 64, 1) LP_CASE(32, 32, 1) LP_CASE(32, 64, 1)
+    LP_CASE(16, 32, 2) LP_CASE(16, 64, 2) LP_CASE(32, 32, 2) LP_CASE(32, 64, 2)
+#undef LP_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+}  // namespace lp

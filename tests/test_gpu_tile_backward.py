@@ -1,0 +1,69 @@
+"""The tile kernels of the Renderer's backward (four neighbouring rays per wavefront, eight samples of each per
+step) where their layout has edges: sample counts around the step widths, a ray count that leaves a partial
+tile, scenes that change inside a tile, neighbouring rays that take the windowed scatter and rays apart
+from each other that are marched one at a time and take the walk.  Every case is checked against the CPU
+oracle at the bounds of `parity.check_case`."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import lp_inputs
+from lp_inputs import TRIPLANE, VOXEL
+
+from parity import check_case, summary
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    import oracle as o
+    return o
+
+
+def _with_camera_rays(inp, n_rays, image, rows):
+    """`inp` with the rays of a `rows` x image strip of a pinhole view (neighbouring rays in order)."""
+    rot, pos = lp_inputs.camera_pose(33.0, 17.0, 2.5)
+    o, d = lp_inputs.pinhole_rays(image, rot, pos)
+    first = (image // 2) * image
+    idx = (first + np.arange(n_rays)) % (image * image)
+    assert n_rays <= rows * image
+    full = lambda v: np.full(n_rays, v, dtype=np.float32)
+    scene = None if inp.n_scenes == 1 else (np.arange(n_rays) // 7 % inp.n_scenes).astype(np.int32)
+    target = np.random.default_rng(3).random((n_rays, 3), dtype=np.float32)
+    return dataclasses.replace(inp, origins=np.ascontiguousarray(o[idx]), dirs=np.ascontiguousarray(d[idx]), near=full(1.0),
+                               far=full(4.0), scene=scene, target=target)
+
+
+SHAPES = [(VOXEL, 16, (16, 64, 64, 4)), (VOXEL, 32, (32, 64, 4)), (TRIPLANE, 32, (32, 64, 64, 4)), (TRIPLANE, 16, (16, 32, 4)),
+          (VOXEL, 16, (16, 32, 32, 4)), (TRIPLANE, 32, (32, 32, 4))]
+
+
+@pytest.mark.parametrize("kind,channels,dims", SHAPES)
+@pytest.mark.parametrize("samples", [1, 7, 8])
+def test_single_step_tiles(lp, oracle, kind, channels, dims, samples):
+    """At most eight samples per ray: tiles of four rays in one step; 203 rays leave a partial tile, the scene
+    changes inside tiles (those rays are marched one at a time)."""
+    inp = lp_inputs.make_small(kind, channels=channels, res=(21, 17, 19), mlp_dims=dims, n_rays=8, samples=samples, seed=211,
+                               n_scenes=2, grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3)
+    inp = _with_camera_rays(inp, 203, 64, 4)
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"single step {kind} {dims} S={samples}")), flush=True)
+
+
+@pytest.mark.parametrize("kind,channels,dims", SHAPES)
+@pytest.mark.parametrize("samples", [33, 63])
+def test_tiles_of_several_steps(lp, oracle, kind, channels, dims, samples):
+    """More rays than wavefronts, neighbours in order: several tiles per wavefront, ragged last step."""
+    inp = lp_inputs.make_small(kind, channels=channels, res=(40, 33, 37), mlp_dims=dims, n_rays=8, samples=samples, seed=223,
+                               grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3)
+    inp = _with_camera_rays(inp, 8190, 128, 64)
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"tiles {kind} {dims} S={samples}")), flush=True)
+
+
+@pytest.mark.parametrize("kind,channels,dims", SHAPES[:4])
+def test_rays_apart_in_tile_order(lp, oracle, kind, channels, dims):
+    """Enough rays for tiles, but in random order: every item is marched ray by ray and scattered by the walk."""
+    inp = lp_inputs.make_small(kind, channels=channels, res=(40, 33, 37), mlp_dims=dims, n_rays=8190, samples=40, seed=227,
+                               grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3)
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"apart {kind} {dims}")), flush=True)
