@@ -53,7 +53,7 @@ __device__ __forceinline__ void stage_chain(uint4* lds, const float* W1, int ld1
     auto out_row = [=](int p) { return (p >= first_row && p < first_row + n_out) ? p - first_row : -1; };
     stage_operand(lds + L::A1, W1, MB, KS1, ld1, block_row, [](int s, int gg, int e) { return k_input<C>(s, gg, e); });
     stage_operand(lds + L::A2, W2, MB, KSH, kH, block_row, hidden_col);
-    stage_operand(lds + L::A3, Wo, 1, KSH, kH, [=](int, int i) { return i < 8 ? out_row(i & 3) : -1; }, hidden_col);
+    stage_output_rows(lds + L::A3, Wo, KSH, kH, out_row);
     if constexpr (BWD) {
         stage_operand_t(lds + L::T3, Wo, MB, 1, kH, block_row, [=](int, int, int e) { return e < 4 ? out_row(e) : -1; });
         stage_operand_t(lds + L::T2, W2, MB, KSH, kH, block_row, hidden_col);

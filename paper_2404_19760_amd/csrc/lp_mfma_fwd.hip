@@ -1,11 +1,12 @@
 // Matrix-core forward kernel of the Renderer (Eq. (1), Section 3.3; fused as in Section 3.4).
 //
 // A workgroup is 4 wavefronts sharing the MLP weights in LDS (bf16 hi/lo MFMA A operands).
-// A wavefront marches ONE ray at a time, 64 consecutive samples per step: lanes (i, g) sample
-// and interpolate the g-th half of the channels of samples i and 32 + i, the MLP runs on the
-// matrix cores for the 64 samples (two N blocks of 32), then lane l owns sample l of the step
+// A wavefront marches ONE ray at a time, 64 consecutive samples per step, sampled by whole texels (lp_gather.h) or
+// with lanes (i, g) interpolating the g-th half of the channels of samples i and 32 + i; the MLP runs on the
+// matrix cores for the 64 samples (two N blocks of 32, a stage apart), then lane l owns sample l of the step
 // for the density / colour heads and the emission-absorption update, where the transmittance
 // prefix is a wave-level scan of sigma * Delta.  Nothing per sample is written to memory.
+#include "lp_gather.h"
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
@@ -16,21 +17,39 @@ namespace {
 
 constexpr int kWaves = 4;
 
-// NB = N blocks of 32 samples per step.  NB = 2: lane l owns sample l of the 64-sample step.
-// NB = 1 (half the registers, two waves per SIMD for the wide MLPs): both lane groups hold the
-// decoder outputs of sample (lane & 31); group 0 alone accumulates.
-template <int KIND, int C, int H, int NH, int NB, bool CC, int CG, int GT>
-__global__ __launch_bounds__(kWaves * 64) void fwd_mfma_kernel(GridDev g, MlpDev m, RaysDev rays, FwdOut out)
+// Whether the wave samples by whole texels (lp_gather.h): 32 grid channels, any structure but a HexPlane (measured: eight
+// 256^2 triplanes 46.3 -> 28.6 ms, 64^3 voxels 3.0 -> 2.4, 160^3 with contract coordinates 1.98 -> 1.52). With 16
+// channels the texels take a quarter or a third of those loads and the kernel is bound by the MLP: a lane per
+// sample is then the cheaper one (256^3 voxels 14.05 against 14.2 ms, stored in bf16 9.45 against 9.57).
+template <int KIND, int C, int CG>
+constexpr bool kWaveGather = C == 32 && CG == C && KIND != LP_GRID_HEXPLANE;
+
+// LDS: the MLP, then (16-byte units from kGatherAt) the waves' gather areas.
+template <int KIND, int C, int H, int NH, int CG>
+struct FwdLds {
+    static constexpr int kGatherAt = (MlpLds<C, H, NH, false, 2>::END + 15) / 16 * 16;
+    static constexpr int kWave = kWaveGather<KIND, C, CG> ? WaveGatherLds<KIND == LP_GRID_HEXPLANE ? LP_GRID_VOXEL : KIND, CG>::kBytes : 0;
+    static constexpr int kBytes = kGatherAt * 16 + kWaves * kWave;
+};
+
+// Lane l owns sample l of a 64-sample step.
+// (three waves per SIMD where the registers allow it without spilling)
+template <int KIND, int C, int H, int NH, bool CC, int CG, int GT>
+__global__ __launch_bounds__(kWaves * 64, (CG == C && KIND != LP_GRID_HEXPLANE) ? 3 : 1) void fwd_mfma_kernel(GridDev g, MlpDev m, RaysDev rays, FwdOut out)
 {
-    constexpr int kStep = 32 * NB;
+    constexpr int kStep = 64;
+    using L = MlpLds<C, H, NH, false, 2>;
+    using F = FwdLds<KIND, C, H, NH, CG>;
     extern __shared__ uint4 lds[];
-    stage_mlp<C, H, NH, false, NB, CG>(lds, m);
+    stage_mlp<C, H, NH, false, 2, CG>(lds, m);
     __syncthreads();
 
     const int lane = threadIdx.x & 63;
     const RaySchedule sched = ray_schedule(rays.M, kWaves);
     const int S = rays.S;
     const bool identity = m.feat_act != 0;   // rendered features without the sigmoid (two-MLP decoder only)
+    const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)reinterpret_cast<char*>(lds) + F::kGatherAt * 16 +
+                          __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * F::kWave;
 
     for (long long ray = sched.first; ray < sched.end; ray += sched.stride) {
         RayGeom q = load_ray_geom(rays, ray);
@@ -40,13 +59,17 @@ __global__ __launch_bounds__(kWaves * 64) void fwd_mfma_kernel(GridDev g, MlpDev
 
         for (int j0 = 0; j0 < S; j0 += kStep) {
             struct { float z[4]; } a;
-            if constexpr (NB == 2) {
-                forward_outputs<KIND, C, H, NH, CC, CG, GT>(g, lds, q, j0, S, lane, a.z);
-            } else {
-                StepActs<C, H, NH, NB> full;
-                forward_step<KIND, C, H, NH, false, NB, false, CC, CG, GT>(g, lds, q, j0, S, lane, full);
+            if constexpr (kWaveGather<KIND, C, CG>) {
+                using G = WaveGatherLds<KIND, C>;
+                Frag fh[2][C / 16], fl[2][C / 16];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) a.z[k] = full.z[k];
+                for (int nb = 0; nb < 2; ++nb) {
+                    const Cell3 c = sample_cell_for<CC, GT>(g, q, min(j0 + 32 * nb + (lane & 31), S - 1));
+                    wave_features<KIND, C, GT>(g, q.scene, c, area, area + G::IMG, lane, fh[nb], fl[nb]);
+                }
+                mlp_outputs<C, H, NH>(lds, reinterpret_cast<const float*>(lds + L::BIAS), lane, fh, fl, a.z);
+            } else {
+                forward_outputs<KIND, C, H, NH, CC, CG, GT>(g, lds, q, j0, S, lane, a.z);
             }
 
             // heads and emission-absorption update; the lane owns sample j0 + pos
@@ -56,7 +79,7 @@ __global__ __launch_bounds__(kWaves * 64) void fwd_mfma_kernel(GridDev g, MlpDev
             const float sd = j < S ? fast_softplus(a.z[0]) * q.delta : 0.0f;
             const float incl = group_scan_incl<kStep>(sd, pos);
             const float Tprev = __expf(-(tau + (incl - sd)));
-            const float w = (NB == 2 || lane < 32) ? Tprev * one_minus_exp_neg(sd) : 0.0f;
+            const float w = Tprev * one_minus_exp_neg(sd);
             acc_r += w * feature_head(a.z[1], identity);
             acc_g += w * feature_head(a.z[2], identity);
             acc_b += w * feature_head(a.z[3], identity);
@@ -80,12 +103,12 @@ __global__ __launch_bounds__(kWaves * 64) void fwd_mfma_kernel(GridDev g, MlpDev
     }
 }
 
-template <int KIND, int C, int H, int NH, int NB, bool CC, int CG, int GT = LP_F32>
+template <int KIND, int C, int H, int NH, bool CC, int CG, int GT = LP_F32>
 hipError_t launch_fwd(const GridDev& g, const MlpDev& m, const RaysDev& rays, const FwdOut& out, int n_cu,
                       hipStream_t stream)
 {
-    constexpr int kLdsBytes = MlpLds<C, H, NH, false, NB>::bytes(kWaves);
-    auto kernel = fwd_mfma_kernel<KIND, C, H, NH, NB, CC, CG, GT>;
+    constexpr int kLdsBytes = FwdLds<KIND, C, H, NH, CG>::kBytes;
+    auto kernel = fwd_mfma_kernel<KIND, C, H, NH, CC, CG, GT>;
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
     // persistent grid: as many workgroups as fit a compute unit's registers, a multiple of the 8 XCDs, no more than the rays need
@@ -105,24 +128,24 @@ hipError_t dispatch_fwd(const GridDev& g, const MlpDev& m, const RaysDev& rays, 
     // grids stored in bf16 / fp16: plain inputs; the contraction is a run-time branch of these kernels
 #define LP_CASE(c, h, nh)                                                                                     \
     if (C == c && CG == c && H == h && NH == nh && g.dtype != LP_F32)                  \
-        return g.dtype == LP_BF16 ? launch_fwd<KIND, c, h, nh, 2, false, c, LP_BF16>(g, m, rays, out, n_cu, stream) \
-                                  : launch_fwd<KIND, c, h, nh, 2, false, c, LP_F16>(g, m, rays, out, n_cu, stream);
+        return g.dtype == LP_BF16 ? launch_fwd<KIND, c, h, nh, false, c, LP_BF16>(g, m, rays, out, n_cu, stream) \
+                                  : launch_fwd<KIND, c, h, nh, false, c, LP_F16>(g, m, rays, out, n_cu, stream);
     LP_CASE(16, 32, 1) LP_CASE(16, 64, 1) LP_CASE(32, 32, 1) LP_CASE(32, 64, 1)
     LP_CASE(16, 32, 2) LP_CASE(16, 64, 2) LP_CASE(32, 32, 2) LP_CASE(32, 64, 2)
 #undef LP_CASE
     if (g.dtype != LP_F32 && CG == C) return hipErrorInvalidValue;   // (the decoder kernels read any storage type)
 #define LP_CASE(c, cg, h, nh)                                                                          \
     if (C == c && CG == cg && H == h && NH == nh)                                                      \
-        return g.contract > 0.0 ? launch_fwd<KIND, c, h, nh, 2, true, cg>(g, m, rays, out, n_cu, stream) \
-                                : launch_fwd<KIND, c, h, nh, 2, false, cg>(g, m, rays, out, n_cu, stream);
+        return g.contract > 0.0 ? launch_fwd<KIND, c, h, nh, true, cg>(g, m, rays, out, n_cu, stream) \
+                                : launch_fwd<KIND, c, h, nh, false, cg>(g, m, rays, out, n_cu, stream);
     LP_CASE(16, 16, 32, 1) LP_CASE(16, 16, 64, 1) LP_CASE(32, 32, 32, 1) LP_CASE(32, 32, 64, 1)
     LP_CASE(16, 16, 32, 2) LP_CASE(16, 16, 64, 2) LP_CASE(32, 32, 32, 2) LP_CASE(32, 32, 64, 2)
 #undef LP_CASE
     // 16 grid channels + direction inputs (the two-MLP decoder merged into one MLP of 32 inputs)
 #define LP_CASE(h, nh)                                                                                  \
     if (C == 32 && CG == 16 && H == h && NH == nh)                                                      \
-        return g.contract > 0.0 ? launch_fwd<KIND, 32, h, nh, 2, true, 16, kAnyDtype>(g, m, rays, out, n_cu, stream) \
-                                : launch_fwd<KIND, 32, h, nh, 2, false, 16, kAnyDtype>(g, m, rays, out, n_cu, stream);
+        return g.contract > 0.0 ? launch_fwd<KIND, 32, h, nh, true, 16, kAnyDtype>(g, m, rays, out, n_cu, stream) \
+                                : launch_fwd<KIND, 32, h, nh, false, 16, kAnyDtype>(g, m, rays, out, n_cu, stream);
     LP_CASE(32, 1) LP_CASE(64, 1) LP_CASE(32, 2) LP_CASE(64, 2)
 #undef LP_CASE
     return hipErrorInvalidValue;
@@ -135,14 +158,14 @@ hipError_t dispatch_fwd_hash(const GridDev& g, const MlpDev& m, const RaysDev& r
     const int C = m.dims[0], H = m.dims[1], NH = m.n_layers - 1;
 #define LP_CASE(c, h, nh)                         \
     if (C == c && g.C == c && H == h && NH == nh) \
-        return launch_fwd<LP_GRID_HASH, c, h, nh, 2, false, c, kAnyDtype>(g, m, rays, out, n_cu, stream);
+        return launch_fwd<LP_GRID_HASH, c, h, nh, false, c, kAnyDtype>(g, m, rays, out, n_cu, stream);
     LP_CASE(16, 32, 1) LP_CASE(16, 64, 1) LP_CASE(32, 32, 1) LP_CASE(32, 64, 1)
     LP_CASE(16, 32, 2) LP_CASE(16, 64, 2) LP_CASE(32, 32, 2) LP_CASE(32, 64, 2)
 #undef LP_CASE
     // 16 table channels + direction inputs (the two-MLP decoder merged into one MLP of 32 inputs)
 #define LP_CASE(h, nh)                             \
     if (C == 32 && g.C == 16 && H == h && NH == nh) \
-        return launch_fwd<LP_GRID_HASH, 32, h, nh, 2, false, 16, kAnyDtype>(g, m, rays, out, n_cu, stream);
+        return launch_fwd<LP_GRID_HASH, 32, h, nh, false, 16, kAnyDtype>(g, m, rays, out, n_cu, stream);
     LP_CASE(32, 1) LP_CASE(64, 1) LP_CASE(32, 2) LP_CASE(64, 2)
 #undef LP_CASE
     return hipErrorInvalidValue;
@@ -155,14 +178,14 @@ hipError_t dispatch_fwd_hexplane(const GridDev& g, const MlpDev& m, const RaysDe
     const int C = m.dims[0], H = m.dims[1], NH = m.n_layers - 1;
 #define LP_CASE(c, h, nh)                         \
     if (C == c && g.C == c && H == h && NH == nh) \
-        return launch_fwd<LP_GRID_HEXPLANE, c, h, nh, 2, false, c, kAnyDtype>(g, m, rays, out, n_cu, stream);
+        return launch_fwd<LP_GRID_HEXPLANE, c, h, nh, false, c, kAnyDtype>(g, m, rays, out, n_cu, stream);
     LP_CASE(16, 32, 1) LP_CASE(16, 64, 1) LP_CASE(32, 32, 1) LP_CASE(32, 64, 1)
     LP_CASE(16, 32, 2) LP_CASE(16, 64, 2) LP_CASE(32, 32, 2) LP_CASE(32, 64, 2)
 #undef LP_CASE
     // 16 plane channels + direction inputs (the two-MLP decoder merged into one MLP of 32 inputs)
 #define LP_CASE(h, nh)                             \
     if (C == 32 && g.C == 16 && H == h && NH == nh) \
-        return launch_fwd<LP_GRID_HEXPLANE, 32, h, nh, 2, false, 16, kAnyDtype>(g, m, rays, out, n_cu, stream);
+        return launch_fwd<LP_GRID_HEXPLANE, 32, h, nh, false, 16, kAnyDtype>(g, m, rays, out, n_cu, stream);
     LP_CASE(32, 1) LP_CASE(64, 1) LP_CASE(32, 2) LP_CASE(64, 2)
 #undef LP_CASE
     return hipErrorInvalidValue;

@@ -4,6 +4,7 @@
 // every sample instead of reading stored activations).
 #pragma once
 #include "lp_mfma.h"
+#include "lp_weave.h"
 
 namespace lp {
 
@@ -17,8 +18,8 @@ struct MlpLds {
     // offsets in uint4 (16 B) units; one (block, K-step) = 64 hi + 64 lo entries = 128 units
     static constexpr int A1 = 0;                                   // W1   [MB][KS1]
     static constexpr int A2 = A1 + MB * KS1 * 128;                 // W2   [MB][KSH]   (NH == 2)
-    static constexpr int A3 = A2 + (NH == 2 ? MB * KSH * 128 : 0); // Wout [1][KSH], rows 0..3 = rows 4..7
-    static constexpr int FWD_END = A3 + KSH * 128;
+    static constexpr int A3 = A2 + (NH == 2 ? MB * KSH * 128 : 0); // Wout [KSH], four rows
+    static constexpr int FWD_END = A3 + KSH * 16;
     // transposed weights for the input-gradient chain (backward only)
     static constexpr int T3 = FWD_END;                             // Wout^T [MB][1]
     static constexpr int T2 = T3 + (BWD ? MB * 128 : 0);           // W2^T   [MB][KSH]  (NH == 2)
@@ -32,6 +33,32 @@ struct MlpLds {
     static constexpr int bytes(int waves) { return (END + (BWD ? waves * INFO_UNITS : 0)) * 16; }
 };
 
+// The output layer as MFMA A operand: its four rows stand for all 32 (row i reads row i % 4), so that both lane
+// groups of a sample column hold the outputs (D rows 4g + p) and the operand takes 256 bytes of LDS per K-step.
+// row_of(r): source row of output r (negative: zeros).
+template <class RowFn>
+__device__ __forceinline__ void stage_output_rows(uint4* dst, const float* __restrict__ W, int n_ks, int ld, RowFn row_of)
+{
+    __bf16* out = reinterpret_cast<__bf16*>(dst);
+#pragma unroll 1
+    for (int idx = threadIdx.x; idx < n_ks * 64; idx += blockDim.x) {
+        const int e = idx & 7, row = (idx >> 3) & 3, gg = (idx >> 5) & 1, s = idx >> 6;
+        const int r = row_of(row);
+        const float v = r >= 0 ? W[(size_t)r * ld + k_hidden(s, gg, e)] : 0.0f;
+        const __bf16 h = (__bf16)v;
+        out[s * 128 + (gg * 4 + row) * 8 + e] = h;
+        out[s * 128 + 64 + (gg * 4 + row) * 8 + e] = (__bf16)(v - (float)h);
+    }
+}
+
+__device__ __forceinline__ void load_output_rows(const uint4* blk, int lane, Frag& hi, Frag& lo)
+{
+    const int at = (lane >> 5) * 4 + (lane & 3);
+    const uint4 h = blk[at], l = blk[8 + at];
+    hi.d[0] = h.x; hi.d[1] = h.y; hi.d[2] = h.z; hi.d[3] = h.w;
+    lo.d[0] = l.x; lo.d[1] = l.y; lo.d[2] = l.z; lo.d[3] = l.w;
+}
+
 // CG = channels of the grid (the gradient of the first CG inputs is scattered); CG < C: the
 // other inputs are per-ray direction inputs.
 template <int C, int H, int NH, bool BWD, int NB, int CG = C>
@@ -44,9 +71,7 @@ __device__ __forceinline__ void stage_mlp(uint4* lds, const MlpDev& m)
     stage_operand(lds + L::A1, m.W[0], MB, KS1, C, block_row,
                   [](int s, int gg, int e) { return k_input<C>(s, gg, e); });
     if constexpr (NH == 2) stage_operand(lds + L::A2, m.W[1], MB, KSH, H, block_row, hidden_col);
-    // output layer: rows 0..3 and 4..7 both carry the 4 outputs, so that both lane groups of a
-    // sample column hold them (D rows 4g + p)
-    stage_operand(lds + L::A3, m.W[NH], 1, KSH, H, [](int, int i) { return i < 8 ? (i & 3) : -1; }, hidden_col);
+    stage_output_rows(lds + L::A3, m.W[NH], KSH, H, [](int r) { return r; });
     if constexpr (BWD) {
         // A[m][k] = W^T[m][k] = W[k][m]: read W with (row, col) swapped.  stage_operand reads
         // W[row_of * ld + col_of], so pass the transposed roles: "row" = k index, "col" = m index.
@@ -282,8 +307,7 @@ __device__ __forceinline__ void mlp_forward(const uint4* lds, int lane, StepActs
     const Frag (&lh)[NB][KSH] = NH == 2 ? a.h2h : a.h1h;
     const Frag (&ll)[NB][KSH] = NH == 2 ? a.h2l : a.h1l;
 
-    // output layer: its 4 rows are replicated in rows 0..3 and 4..7, so both lane groups of a
-    // sample column hold them.  NB = 2: lanes 0..31 take N block 0, lanes 32..63 N block 1, so
+    // output layer: both lane groups of a sample column hold its 4 rows.  NB = 2: lanes 0..31 take N block 0, lanes 32..63 N block 1, so
     // that lane l owns sample j0 + l.  NB = 1: both lane groups own sample j0 + col.
     f32x16 o[NB];
     const f32x4 b = *reinterpret_cast<const f32x4*>(sbias + 2 * H);
@@ -294,7 +318,7 @@ __device__ __forceinline__ void mlp_forward(const uint4* lds, int lane, StepActs
 #pragma unroll
     for (int s = 0; s < KSH; ++s) {
         Frag ah, al;
-        load_operand(lds + L::A3 + s * 128, lane, ah, al);
+        load_output_rows(lds + L::A3 + s * 16, lane, ah, al);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) o[nb] = mfma3(ah, al, lh[nb][s], ll[nb][s], o[nb]);
     }
@@ -319,10 +343,9 @@ __device__ __forceinline__ void forward_step(const GridDev& g, const uint4* lds,
     mlp_forward<C, H, NH, BWD, NB>(lds, lane, a);
 }
 
-// MLP of one 64-sample step from the input fragments of its two N blocks, keeping nothing but
-// the decoder outputs: the first layer runs on both N blocks at once (sharing the weight
-// operands), the remaining layers one N block after the other, so that at most one block's
-// accumulators and activations are alive at a time (registers for a second wave per SIMD).
+// MLP of one 64-sample step from the input fragments of its two N blocks, keeping nothing but the decoder
+// outputs.  The blocks are one stage apart: while one block's layer runs on the matrix cores, the vector ALU
+// turns the other block's layer output into operands (relu, split), one piece between two products.
 // `lds` points at the MLP's weights (layout MlpLds), `bias1` at the first layer's bias (the
 // layout's own, or one that holds a ray's constant inputs already contracted).  z = outputs of
 // sample j0 + lane.
@@ -334,45 +357,102 @@ __device__ __forceinline__ void mlp_outputs(const uint4* lds, const float* bias1
     constexpr int MB = L::MB, KS1 = L::KS1, KSH = L::KSH;
     const int grp = lane >> 5;
     const float* sbias = reinterpret_cast<const float*>(lds + L::BIAS);
-    Frag h1h[2][KSH], h1l[2][KSH];
+    auto none = [](auto) {};
+    auto product = [](const Frag& a, const Frag& b, f32x16& acc) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), acc, 0, 0, 0);
+        pin(acc);
+    };
+    auto start = [&](f32x16 (&acc)[MB], const float* b) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(b + 32 * mb + 8 * q + 4 * grp);
+#pragma unroll
+                for (int p = 0; p < 4; ++p) acc[mb][4 * q + p] = v[p];
+            }
+    };
+    // pair u of a block's layer output -> operand
+    auto activate = [](const f32x16 (&acc)[MB], int u, Frag (&h)[KSH], Frag (&l)[KSH]) {
+        const int mb = u / 8, r = 2 * (u % 8), s = u / 4;
+        split2(relu_f(acc[mb][r]), relu_f(acc[mb][r + 1]), h[s].d[u % 4], l[s].d[u % 4]);
+        pin(h[s].d[u % 4]);
+        pin(l[s].d[u % 4]);
+    };
+    Frag wh[2], wl[2];   // weights of two products, the next one's read ahead
+    auto read_w = [&](const uint4* base, int t) { load_operand(base + t * 128, lane, wh[t & 1], wl[t & 1]); };
+    // product number i of a layer: small terms first; KS K-steps per row block
+    auto layer = [&](auto ic, auto ks_of, const uint4* base, f32x16 (&acc)[MB], const auto& bh, const auto& bl) {
+        constexpr int i = decltype(ic)::value, KS = decltype(ks_of)::value, t = i / 3, s = t % KS, mb = t / KS;
+        if constexpr (i % 3 == 0 && t + 1 < MB * KS) read_w(base, t + 1);
+        product(i % 3 == 0 ? wl[t & 1] : wh[t & 1], i % 3 == 1 ? bl[s] : bh[s], acc[mb]);
+    };
+    using K1 = std::integral_constant<int, KS1>;
+    using KH = std::integral_constant<int, KSH>;
+    constexpr int N1 = 3 * MB * KS1, N2 = 3 * MB * KSH, NO = 2 * KSH, U = 8 * MB;
+
+    f32x16 a0[MB], a1[MB], c0[MB], c1[MB];   // layer outputs of the two blocks
+    Frag h0h[KSH], h0l[KSH], h1h[KSH], h1l[KSH];
+    start(a0, bias1);
+    read_w(lds + L::A1, 0);
     {
-        f32x16 acc[MB][2];
-        init_bias<MB, 2>(acc, bias1, grp);
-        layer_mfma<MB, KS1, 2>(acc, lds + L::A1, lane, fh, fl);
-        to_operands<MB, true, 2>(acc, h1h, h1l);
+        auto p = [&](auto i) { layer(i, K1(), lds + L::A1, a0, fh[0], fl[0]); };
+        weave<N1, 0, 0>(p, none);
     }
+    start(a1, bias1);
+    read_w(lds + L::A1, 0);
+    {
+        auto p = [&](auto i) { layer(i, K1(), lds + L::A1, a1, fh[1], fl[1]); };
+        auto v = [&](auto u) { activate(a0, decltype(u)::value, h0h, h0l); };
+        weave<N1, U, 1>(p, v);
+    }
+    if constexpr (NH == 2) {
+        start(c0, sbias + H);
+        read_w(lds + L::A2, 0);
+        {
+            auto p = [&](auto i) { layer(i, KH(), lds + L::A2, c0, h0h, h0l); };
+            auto v = [&](auto u) { activate(a1, decltype(u)::value, h1h, h1l); };
+            weave<N2, U, 1>(p, v);
+        }
+        start(c1, sbias + H);
+        read_w(lds + L::A2, 0);
+        {
+            auto p = [&](auto i) { layer(i, KH(), lds + L::A2, c1, h1h, h1l); };
+            auto v = [&](auto u) { activate(c0, decltype(u)::value, h0h, h0l); };
+            weave<N2, U, 1>(p, v);
+        }
+    }
+    // output layer: rows i of the operand with i & 8 hold the lo halves of the weights, so that two products per
+    // K-step give all four (the outputs are the sums of D rows p and 8 + p)
     const f32x4 bo = *reinterpret_cast<const f32x4*>(sbias + 2 * H);
-    __builtin_amdgcn_sched_barrier(0);
+    f32x16 o0, o1;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        Frag lh[1][KSH], ll[1][KSH];
-        if constexpr (NH == 2) {
-            Frag inh[1][KSH], inl[1][KSH];
-#pragma unroll
-            for (int s = 0; s < KSH; ++s) { inh[0][s] = h1h[nb][s]; inl[0][s] = h1l[nb][s]; }
-            f32x16 acc[MB][1];
-            init_bias<MB, 1>(acc, sbias + H, grp);
-            layer_mfma<MB, KSH, 1>(acc, lds + L::A2, lane, inh, inl);
-            to_operands<MB, true, 1>(acc, lh, ll);
-        } else {
-#pragma unroll
-            for (int s = 0; s < KSH; ++s) { lh[0][s] = h1h[nb][s]; ll[0][s] = h1l[nb][s]; }
-        }
-        f32x16 o;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[r] = r < 4 ? bo[r] : 0.0f;
-#pragma unroll
-        for (int s = 0; s < KSH; ++s) {
-            Frag ah, al;
-            load_operand(lds + L::A3 + s * 128, lane, ah, al);
-            o = mfma3(ah, al, lh[0][s], ll[0][s], o);
-        }
-        // lanes 0..31 own the samples of N block 0, lanes 32..63 those of N block 1
-#pragma unroll
-        for (int k = 0; k < 4; ++k) z[k] = (nb == 0 || grp) ? o[k] : z[k];
-        // keep the two N blocks apart: interleaving them would double the live registers
-        __builtin_amdgcn_sched_barrier(0);
+    for (int r = 0; r < 16; ++r) o0[r] = o1[r] = r < 4 ? bo[r] : 0.0f;
+    const uint4* out_rows = lds + L::A3 + grp * 4 + (lane & 3) + ((lane >> 3) & 1) * 8;
+    Frag wo[2];
+    auto read_o = [&](int s) { wo[s & 1] = __builtin_bit_cast(Frag, out_rows[16 * s]); };
+    auto output = [&](auto ic, f32x16& o, const Frag (&h)[KSH], const Frag (&l)[KSH]) {
+        constexpr int i = decltype(ic)::value, s = i / 2;
+        if constexpr (i % 2 == 0 && s + 1 < KSH) read_o(s + 1);
+        product(wo[s & 1], i % 2 ? h[s] : l[s], o);
+    };
+    read_o(0);
+    {
+        auto p = [&](auto i) { output(i, o0, h0h, h0l); };
+        auto v = [&](auto u) {
+            if constexpr (NH == 2) activate(c1, decltype(u)::value, h1h, h1l);
+            else activate(a1, decltype(u)::value, h1h, h1l);
+        };
+        weave<NO, U, 0>(p, v);
     }
+    read_o(0);
+    {
+        auto p = [&](auto i) { output(i, o1, h1h, h1l); };
+        weave<NO, 0, 0>(p, none);
+    }
+    // lanes 0..31 own the samples of N block 0, lanes 32..63 those of N block 1
+#pragma unroll
+    for (int k = 0; k < 4; ++k) z[k] = grp ? o1[k] + o1[4 + k] : o0[k] + o0[4 + k];
 }
 
 // Sampling + MLP of one 64-sample step for the forward kernel.  z = outputs of sample j0 + lane.
