@@ -20,7 +20,7 @@ LIB = os.environ.get("LP_LIB_OUT", os.path.join(HERE, "liblightplane.so"))
 
 SOURCES = ["lp_api.hip", "lp_diag.hip", "lp_decoder.hip", "lp_generic.hip", "lp_mfma_fwd.hip", "lp_mfma_bwd.hip", "lp_mfma_bwd_b.hip", "lp_mfma_bwd_ws.hip",
            "lp_mfma_bwd_hash.hip", "lp_mfma_bwd_tile_voxel.hip", "lp_mfma_bwd_tile_triplane.hip", "lp_mfma_bwd_hexplane.hip",
-           "lp_mfma_dec2_fwd.hip", "lp_mfma_dec2_bwd.hip", "lp_splat_fast.hip",
+           "lp_mfma_dec2_fwd.hip", "lp_mfma_dec2_bwd.hip", "lp_splat_fast.hip", "lp_splat_naive_bwd.hip",
            "lp_splat_mfma.hip", "lp_splat_mfma_bwd.hip", "lp_splat_mfma_bwd_t32.hip"]
 
 HIPCC_FLAGS = [

@@ -898,6 +898,11 @@ lp_status lp_splat_bwd(const lp_grid* target, const lp_rays* rays, const lp_spla
         if (e != hipSuccess) return hip_fail("Splatter backward kernel launch", e);
         return LP_OK;
     }
+    if (m.n_layers == 0 && lp::splat_naive_bwd_supported(g, sd)) {
+        hipError_t e = lp::launch_splat_naive_bwd(g, r, sd, n_cu, s);
+        if (e != hipSuccess) return hip_fail("Splatter backward kernel launch", e);
+        return LP_OK;
+    }
     GenericShape shape;
     if (!generic_shape(m, (size_t)m.act_total + 2 * (size_t)m.max_width + sd.n_in, true, &shape))
         return fail(LP_ERR_UNSUPPORTED, "MLP too large for the Splatter backward kernel's LDS budget");

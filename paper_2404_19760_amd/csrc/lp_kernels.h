@@ -53,6 +53,10 @@ hipError_t launch_bwd_mfma_ws(const GridDev& g, const MlpDev& m, const RaysDev& 
 bool splat_naive_supported(const GridDev& tgt);
 hipError_t launch_splat_naive(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu,
                               hipStream_t stream);
+// its backward (lp_splat_naive_bwd.hip): the same targets, d_theta and d_feats on 16-byte boundaries
+bool splat_naive_bwd_supported(const GridDev& tgt, const SplatDev& sp);
+hipError_t launch_splat_naive_bwd(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu,
+                                  hipStream_t stream);
 
 // ---- Splatter forward with an MLP on the matrix cores (lp_splat_mfma.hip) ----------------
 // Shapes covered: prior and target with the same 16 or 32 fp32 channels, no contraction; one or
