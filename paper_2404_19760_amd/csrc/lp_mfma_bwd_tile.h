@@ -10,8 +10,8 @@
 //      the samples of each ray,
 //   3. back-propagates on the matrix cores: input gradients dX = W^T dZ chained in registers, weight
 //      gradients dW = dZ X^T contracted over the samples of the step,
-//   4. adds the feature gradient to the grid gradient: scatter_window below, or, where the step's samples
-//      are too far apart for it, the run-merging walk of lp_mfma_bwd_common.h.
+//   4. adds the feature gradient to the grid gradient: scatter_step below, as matrix products over small windows of
+//      texels or, where the step's samples are too far apart for it, with the run-merging walk of lp_mfma_bwd_common.h.
 //
 // What bounds it and why it is laid out like this (256^3 x 16 voxels, 800^2 rays x 512 samples, and eight
 // 256^2 x 32 triplanes, 4 x 256^2 rays x 192 samples each):
@@ -176,12 +176,15 @@ __device__ __forceinline__ int row_perm(int v)
     return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
 }
 
-// extremes over lanes 0 .. 31 (both lane groups hold the same cells)
-__device__ __forceinline__ Window find_window(const Cell3& c)
+// extremes over the members among lanes 0 .. 31 (both lane groups hold the same cells; one member at least)
+__device__ __forceinline__ Window find_window(const Cell3& c, bool member)
 {
     int lo[3], hi[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) lo[a] = hi[a] = c.i[a];
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = member ? c.i[a] : 0x7fffffff;
+        hi[a] = member ? c.i[a] : 0;
+    }
     auto step = [&](auto perm) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -216,10 +219,11 @@ __device__ __forceinline__ bool window_fits(const Window& w)
 __device__ __forceinline__ int small_div(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
 
 // dFt: feature gradient, lane = channel (16 channels: lanes 16 .. 31 repeat lanes 0 .. 15), register r =
-// column d_row(r, grp) of the step.  `area`: the wave's LDS area for the table.
+// column d_row(r, grp) of the step.  `member`: the lane's sample belongs to the window (others have weight
+// zero).  `area`: the wave's LDS area for the table.
 template <int KIND, int C>
 __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
-                                               const Window& win, const Cell3& cell, const f32x16& dFt, int lane)
+                                               const Window& win, const Cell3& cell, bool member, const f32x16& dFt, int lane)
 {
     const int col = lane & 31, grp = lane >> 5;
     // the table: zeros, then this sample's two entries per axis (lane group 0 the lower, 1 the upper)
@@ -228,10 +232,12 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
         lds_put<u32x4>(area + 16 * i, u32x4{0u, 0u, 0u, 0u});
     wave_lds_fence();
     const int pos = slot_to_sample(col);   // 16 grp + r for column d_row(r, grp)
+    if (member) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int row = a * kWinExtent + cell.i[a] - win.lo[a] + grp;
-        lds_put<float>(area + row * kWinRow + pos * 4, grp ? cell.f[a] : 1.0f - cell.f[a]);
+        for (int a = 0; a < 3; ++a) {
+            const int row = a * kWinExtent + cell.i[a] - win.lo[a] + grp;
+            lds_put<float>(area + row * kWinRow + pos * 4, grp ? cell.f[a] : 1.0f - cell.f[a]);
+        }
     }
     wave_lds_fence();
 
@@ -339,6 +345,43 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
     for (int r = 0; r < 16; ++r) v[r] = grad[(16 * grp + r) * C + (col & (C - 1))];
     scatter_channels<KIND, C, true>(g, d_grid, scene, info, v, col, grp);
     wave_lds_fence();
+}
+
+// A step's scatter.  Where the samples of the whole step spread too far for one window, they are taken as two or four
+// runs of consecutive samples (of every ray of the tile) with a window each: on 160^3 x 32 voxels with contract
+// coordinates, 256^2 rays x 384 samples, 27 % of the steps do not fit and nearly all of their halves do, and a step
+// in the walk adds 512 lines against some 160 of two windows.  The products would spread an infinite or
+// undefined gradient over its window, so a step that holds one takes the walk, which keeps it to the sample's own corners.
+template <int KIND, int C>
+__device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
+                                             char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, bool tile)
+{
+    const int col = lane & 31, k = tile ? (col & (kTileSamples - 1)) : col, full = tile ? kTileSamples : 32;
+    float probe = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) probe = fmaf(dFt[r], 0.0f, probe);
+    const bool finite = __ballot(probe != 0.0f) == 0ull;
+    int len = full;
+    Window win = find_window(cell, true);
+    bool fits = finite && window_fits<KIND>(win);
+    while (!fits && finite && len > full / 4) {
+        len >>= 1;
+        fits = true;
+        for (int p = full - len; p >= 0 && fits; p -= len) {
+            win = find_window(cell, (unsigned)(k - p) < (unsigned)len);
+            fits = window_fits<KIND>(win);
+        }
+    }
+    if (!fits) {
+        scatter_walk<KIND, C>(g, d_grid, scene, area_ptr, cell, dFt, lane, tile);
+        return;
+    }
+    for (int p = 0;;) {   // `win` is the first run's
+        scatter_window<KIND, C>(g, d_grid, scene, area, win, cell, (unsigned)(k - p) < (unsigned)len, dFt, lane);
+        p += len;
+        if (p >= full) break;
+        win = find_window(cell, (unsigned)(k - p) < (unsigned)len);
+    }
 }
 
 // One launch: `n_items` work items, consecutive tiles of kTileRays rays (`tiles`) or single rays, handed out
@@ -904,9 +947,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         if (live) sample();
         __builtin_amdgcn_sched_barrier(0);
         refresh(lane_id);
-        const Window win = find_window(here);
-        if (window_fits<KIND>(win)) scatter_window<KIND, C>(g, io.d_grid, here_scene, acts + L::A, win, here, dFt, lane_id);
-        else scatter_walk<KIND, C>(g, io.d_grid, here_scene, reinterpret_cast<char*>(lds_raw) + wave * 2 * L::kAct, here, dFt, lane_id, here_tile);
+        scatter_step<KIND, C>(g, io.d_grid, here_scene, acts + L::A, reinterpret_cast<char*>(lds_raw) + wave * 2 * L::kAct,
+                              here, dFt, lane_id, here_tile);
         wave_lds_fence();
     }
 

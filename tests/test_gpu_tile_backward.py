@@ -67,3 +67,33 @@ def test_rays_apart_in_tile_order(lp, oracle, kind, channels, dims):
     inp = lp_inputs.make_small(kind, channels=channels, res=(40, 33, 37), mlp_dims=dims, n_rays=8190, samples=40, seed=227,
                                grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3)
     print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"apart {kind} {dims}")), flush=True)
+
+
+@pytest.mark.parametrize("kind,channels,dims", SHAPES[:4])
+@pytest.mark.parametrize("res", [64, 150, 400])
+def test_split_windows(lp, oracle, kind, channels, dims, res):
+    """Steps that take one, two or four windows, and some that take the walk: the coordinate steps of a ray grow with
+    the resolution.  (The short axes keep the oracle's arrays small, but no shorter: on a plane of 29 x 31 texels each
+    element sums so many samples that the units at their kink reach 3.5 % of the elements, as in the parameters' gradients.)"""
+    shape = (res, 64, 90) if res > 64 else (64, 64, 64)
+    inp = lp_inputs.make_small(kind, channels=channels, res=shape, mlp_dims=dims, n_rays=8, samples=40, seed=229,
+                               grid_std=0.3, aabb_min=(-1.5,) * 3, aabb_max=(1.5,) * 3)
+    inp = _with_camera_rays(inp, 2048 * 4, 128, 64)
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"windows {kind} {dims} res={res}")), flush=True)
+
+
+@pytest.mark.parametrize("kind,channels,dims", SHAPES[:4])
+def test_undefined_gradient_stays_on_its_ray(lp, kind, channels, dims):
+    """A pixel whose loss is not a number spoils the cells of its own ray and no others: as in the scalar kernels."""
+    import torch
+
+    inp = lp_inputs.make_small(kind, channels=channels, res=(40, 33, 37), mlp_dims=dims, n_rays=8, samples=40, seed=233,
+                               grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3)
+    inp = _with_camera_rays(inp, 2048 * 4, 128, 64)
+    grid, mlp, rays, bg = lp.to_device(inp, "cuda:0")
+    _, _, _, cache = lp.render_fwd(grid, mlp, rays, bg, lp.LP_MATH_BF16X3)
+    d_rgb = torch.ones((inp.n_rays, 3), device="cuda")
+    d_rgb[4001] = float("nan")
+    bad = [torch.isnan(lp.render_bwd(grid, mlp, rays, bg, d_rgb, cache, None, None, mode)[0][0])
+           for mode in (lp.LP_MATH_BF16X3, lp.LP_MATH_GENERIC)]
+    assert bad[1].any() and torch.equal(bad[0], bad[1])
