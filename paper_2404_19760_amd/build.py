@@ -19,7 +19,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.environ.get("LP_LIB_OUT", os.path.join(HERE, "liblightplane.so"))
 
 SOURCES = ["lp_api.hip", "lp_diag.hip", "lp_decoder.hip", "lp_generic.hip", "lp_mfma_fwd.hip", "lp_mfma_bwd.hip", "lp_mfma_bwd_b.hip", "lp_mfma_bwd_ws.hip",
-           "lp_mfma_bwd_hash.hip", "lp_mfma_bwd_tile_voxel.hip", "lp_mfma_bwd_tile_triplane.hip", "lp_mfma_bwd_hexplane.hip",
+           "lp_mfma_bwd_hash.hip", "lp_mfma_bwd_tile_voxel.hip", "lp_mfma_bwd_tile_triplane.hip", "lp_mfma_bwd_tile_hash.hip",
+           "lp_mfma_bwd_hexplane.hip",
            "lp_mfma_dec2_fwd.hip", "lp_mfma_dec2_bwd.hip", "lp_splat_fast.hip", "lp_splat_naive_bwd.hip",
            "lp_splat_mfma.hip", "lp_splat_mfma_bwd.hip", "lp_splat_mfma_bwd_t32.hip"]
 
@@ -48,6 +49,7 @@ PER_SOURCE_FLAGS = {"lp_mfma_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                     "lp_mfma_bwd_ws.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                     "lp_mfma_bwd_tile_voxel.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                     "lp_mfma_bwd_tile_triplane.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+                    "lp_mfma_bwd_tile_hash.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                     "lp_mfma_bwd_hash.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                     "lp_mfma_bwd_hexplane.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                     "lp_diag.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],

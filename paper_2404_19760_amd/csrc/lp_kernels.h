@@ -30,7 +30,7 @@ hipError_t launch_bwd_mfma(const GridDev& g, const MlpDev& m, const RaysDev& ray
 // coordinates or with two 64-wide hidden layers on a triplane)
 hipError_t launch_bwd_mfma_b(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
                              int n_cu, hipStream_t stream);
-// its instantiations for hash tables (lp_mfma_bwd_hash.hip)
+// its instantiations for hash tables with direction inputs (lp_mfma_bwd_hash.hip)
 hipError_t launch_bwd_mfma_hash(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
                                 int n_cu, hipStream_t stream);
 
@@ -38,11 +38,13 @@ hipError_t launch_bwd_mfma_hash(const GridDev& g, const MlpDev& m, const RaysDev
 hipError_t launch_bwd_mfma_hexplane(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
                                     int n_cu, hipStream_t stream);
 
-// the tile kernels (lp_mfma_bwd_tile.h): all inputs grid channels, voxel grids or triplanes
+// the tile kernels (lp_mfma_bwd_tile.h): all inputs grid channels, voxel grids, triplanes or hash tables
 hipError_t launch_bwd_tile_voxel(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
                                  int n_cu, hipStream_t stream);
 hipError_t launch_bwd_tile_triplane(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
                                     int n_cu, hipStream_t stream);
+hipError_t launch_bwd_tile_hash(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
+                                int n_cu, hipStream_t stream);
 
 // the shapes that run as a pair of waves per ray (lp_mfma_bwd_ws.hip)
 bool bwd_ws_supported(const GridDev& g, const MlpDev& m);

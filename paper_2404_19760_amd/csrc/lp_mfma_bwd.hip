@@ -47,6 +47,7 @@ hipError_t launch_bwd_mfma(const GridDev& g, const MlpDev& m, const RaysDev& ray
     if (m.dims[0] == g.C) {
         if (g.kind == LP_GRID_VOXEL) return launch_bwd_tile_voxel(g, m, rays, io, n_cu, stream);
         if (g.kind == LP_GRID_TRIPLANE) return launch_bwd_tile_triplane(g, m, rays, io, n_cu, stream);
+        if (g.kind == LP_GRID_HASH) return launch_bwd_tile_hash(g, m, rays, io, n_cu, stream);
     }
     if (g.kind == LP_GRID_HASH) return launch_bwd_mfma_hash(g, m, rays, io, n_cu, stream);
     if (g.kind == LP_GRID_HEXPLANE) return launch_bwd_mfma_hexplane(g, m, rays, io, n_cu, stream);

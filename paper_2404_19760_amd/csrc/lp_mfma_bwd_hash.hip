@@ -9,12 +9,6 @@ hipError_t launch_bwd_mfma_hash(const GridDev& g, const MlpDev& m, const RaysDev
                                 hipStream_t stream)
 {
     const int C = m.dims[0], H = m.dims[1], NH = m.n_layers - 1;
-#define LP_CASE(c, h, nh)                         \
-    if (C == c && g.C == c && H == h && NH == nh) \
-        return launch_bwd<LP_GRID_HASH, c, h, nh, false, c, kAnyDtype>(g, m, rays, io, n_cu, stream);
-    LP_CASE(16, 32, 1) LP_CASE(16, 64, 1) LP_CASE(32, 32, 1) LP_CASE(32, 64, 1)
-    LP_CASE(16, 32, 2) LP_CASE(16, 64, 2) LP_CASE(32, 32, 2) LP_CASE(32, 64, 2)
-#undef LP_CASE
     // 16 grid channels + direction inputs (the two-MLP decoder merged into one MLP of 32 inputs)
 #define LP_CASE(h, nh)                             \
     if (C == 32 && g.C == 16 && H == h && NH == nh) \

@@ -34,6 +34,7 @@
 #include "lp_mfma_mlp.h"
 #include "lp_mfma_bwd_common.h"
 #include "lp_tile_lds.h"
+#include "lp_tile_scatter.h"
 #include "lp_weave.h"
 
 namespace lp {
@@ -41,8 +42,6 @@ namespace lp {
 namespace {
 
 constexpr int kTileWaves = 8;
-constexpr int kTileRays = 4;                     // rays of a tile
-constexpr int kTileSamples = 32 / kTileRays;     // samples of each per step
 
 // LDS in bytes: the waves' step tensors first (so that a wave's base has none of the address bits that the
 // images' exclusive-ors flip), then the weights, then the waves' small areas.
@@ -121,6 +120,18 @@ __device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const
                 for (int i = 0; i < kVecs; ++i) raw[d][i] = p[i];
                 w[d] = (da ? c.f[a] : 1.0f - c.f[a]) * (db ? c.f[b] : 1.0f - c.f[b]);
             }
+        } else if constexpr (KIND == LP_GRID_HASH) {
+            const char* V = reinterpret_cast<const char*>(g.data[0]) + (size_t)scene * g.hash_size * C * kElem;
+            unsigned slot[8];
+            hash_corner_slots(c, g.hash_size, slot);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int dy = d >> 1, dz = d & 1;
+                const uint4* p = reinterpret_cast<const uint4*>(V + (size_t)((slot[4 * gr + d] * C + ch0) * kElem));
+#pragma unroll
+                for (int i = 0; i < kVecs; ++i) raw[d][i] = p[i];
+                w[d] = (gr ? c.f[0] : 1.0f - c.f[0]) * (dy ? c.f[1] : 1.0f - c.f[1]) * (dz ? c.f[2] : 1.0f - c.f[2]);
+            }
         } else {
             const char* V = reinterpret_cast<const char*>(g.data[0]) +
                             (size_t)scene * g.N[0] * g.N[1] * g.N[2] * C * kElem;
@@ -146,241 +157,6 @@ __device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const
                 for (int e = 0; e < kPerVec; ++e) feat[kPerVec * i + e] += w[d] * v[e];
             }
         if constexpr (STAGED) __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// ---- scatter of a step's feature gradient as a matrix product ----
-// The samples of a step lie in a small window of texels (of each plane).  The window's gradient is
-//     window[texel][channel] = sum over the 32 samples of weight[texel][sample] * dF[sample][channel],
-// a contraction over the samples that the matrix cores take in fp32 (no operand splitting: the weights
-// and the gradient are the same fp32 values a scalar scatter would multiply), and each texel that was
-// touched gets one atomic add per channel, instead of one per run of samples in a cell and corner.
-// The weight of a texel is the product of its coordinates' weights along the axes (1 - f at the sample's cell,
-// f at the next, 0 elsewhere); these stand in an LDS table [axis][coordinate in the window][sample],
-// from which lane = texel reads the samples of its lane group as 16-byte vectors.
-constexpr int kWinExtent = 12;                       // texels of a window along one axis at most
-constexpr int kWinTexels = 128;                      // texels of a window at most; larger ones take the walk
-constexpr int kWinRow = 144;                         // bytes of a table row: 32 samples (and 16 of padding: no bank conflicts)
-constexpr int kWinZeroRow = 3 * kWinExtent;          // a row of zeros, for lanes without a texel
-constexpr int kWinOffsets = (kWinZeroRow + 1) * kWinRow;
-static_assert(kWinOffsets + 32 * 4 <= 8192 && ((kWinZeroRow + 1) * kWinRow) % 16 == 0, "the table fits a wave's area");
-
-struct Window {
-    int lo[3], ext[3];   // uniform: first texel and number of texels along each axis
-};
-
-// v of another lane of the row of 16 (a permutation: every lane has a source)
-template <int CTRL>
-__device__ __forceinline__ int row_perm(int v)
-{
-    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
-}
-
-// extremes over the members among lanes 0 .. 31 (both lane groups hold the same cells; one member at least)
-__device__ __forceinline__ Window find_window(const Cell3& c, bool member)
-{
-    int lo[3], hi[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        lo[a] = member ? c.i[a] : 0x7fffffff;
-        hi[a] = member ? c.i[a] : 0;
-    }
-    auto step = [&](auto perm) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = min(lo[a], perm(lo[a]));
-            hi[a] = max(hi[a], perm(hi[a]));
-        }
-    };
-    step([](int v) { return row_perm<0xb1>(v); });    // lane ^ 1
-    step([](int v) { return row_perm<0x4e>(v); });    // lane ^ 2
-    step([](int v) { return row_perm<0x141>(v); });   // mirrored halves of a row
-    step([](int v) { return row_perm<0x140>(v); });   // mirrored row
-    Window w;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        w.lo[a] = min(__builtin_amdgcn_readlane(lo[a], 0), __builtin_amdgcn_readlane(lo[a], 16));
-        w.ext[a] = max(__builtin_amdgcn_readlane(hi[a], 0), __builtin_amdgcn_readlane(hi[a], 16)) - w.lo[a] + 2;
-    }
-    return w;
-}
-
-template <int KIND>
-__device__ __forceinline__ bool window_fits(const Window& w)
-{
-    if (max(w.ext[0], max(w.ext[1], w.ext[2])) > kWinExtent) return false;
-    if constexpr (KIND == LP_GRID_TRIPLANE)
-        return max(w.ext[0] * w.ext[1], max(w.ext[1] * w.ext[2], w.ext[2] * w.ext[0])) <= kWinTexels;
-    else
-        return w.ext[0] * w.ext[1] * w.ext[2] <= kWinTexels;
-}
-
-// n / d for 0 <= n < 2^12 and the reciprocal inv of d <= 144 (the offset of one half keeps the rounding away)
-__device__ __forceinline__ int small_div(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
-
-// dFt: feature gradient, lane = channel (16 channels: lanes 16 .. 31 repeat lanes 0 .. 15), register r =
-// column d_row(r, grp) of the step.  `member`: the lane's sample belongs to the window (others have weight
-// zero).  `area`: the wave's LDS area for the table.
-template <int KIND, int C>
-__device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
-                                               const Window& win, const Cell3& cell, bool member, const f32x16& dFt, int lane)
-{
-    const int col = lane & 31, grp = lane >> 5;
-    // the table: zeros, then this sample's two entries per axis (lane group 0 the lower, 1 the upper)
-    wave_lds_fence();
-    for (int i = lane; i < (kWinZeroRow + 1) * kWinRow / 16; i += 64)
-        lds_put<u32x4>(area + 16 * i, u32x4{0u, 0u, 0u, 0u});
-    wave_lds_fence();
-    const int pos = slot_to_sample(col);   // 16 grp + r for column d_row(r, grp)
-    if (member) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int row = a * kWinExtent + cell.i[a] - win.lo[a] + grp;
-            lds_put<float>(area + row * kWinRow + pos * 4, grp ? cell.f[a] : 1.0f - cell.f[a]);
-        }
-    }
-    wave_lds_fence();
-
-    constexpr int kLanes = C == 32 ? 32 : 16;         // texels per matrix product
-    constexpr int kVec = C == 32 ? 4 : 2;             // 16-byte vectors of samples per lane
-    const int slot = lane & (kLanes - 1);
-    const int first = C == 32 ? 64 * grp : 32 * (lane >> 4);   // byte offset of this lane's samples in a row
-    float b16[8];
-    if constexpr (C == 16) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            float a = dFt[k], b = dFt[k + 8];
-            asm("" : "+v"(a), "+v"(b));   // (or the compiler turns the choice into an indexed read of dFt)
-            b16[k] = (lane & 16) ? b : a;
-        }
-    }
-
-    constexpr int kPlanes = KIND == LP_GRID_TRIPLANE ? 3 : 1;
-#pragma unroll
-    for (int pl = 0; pl < kPlanes; ++pl) {
-        // axes of the window, slowest first
-        const int a0 = KIND == LP_GRID_TRIPLANE ? pl : 0, a1 = KIND == LP_GRID_TRIPLANE ? (pl + 1) % 3 : 1;
-        const int e1 = win.ext[a1], e2 = KIND == LP_GRID_TRIPLANE ? 1 : win.ext[2];
-        const int total = win.ext[a0] * e1 * e2;
-        const float inv12 = __builtin_amdgcn_rcpf((float)(e1 * e2)), inv2 = __builtin_amdgcn_rcpf((float)e2);
-        char* out;
-        if constexpr (KIND == LP_GRID_TRIPLANE) out = reinterpret_cast<char*>(d_grid[pl] + (size_t)scene * g.N[a0] * g.N[a1] * C);
-        else out = reinterpret_cast<char*>(d_grid[0] + (size_t)scene * g.N[0] * g.N[1] * g.N[2] * C);
-        for (int n0 = 0; n0 < total; n0 += kLanes) {
-            const bool live = n0 + slot < total;
-            const int n = live ? n0 + slot : 0;   // (lanes without a texel: all weights zero, the first texel's address)
-            const int t0 = small_div(n, inv12), rest = n - t0 * (e1 * e2);
-            const int t1 = KIND == LP_GRID_TRIPLANE ? rest : small_div(rest, inv2), t2 = rest - t1 * e2;
-            unsigned off;
-            if constexpr (KIND == LP_GRID_TRIPLANE)
-                off = ((unsigned)(win.lo[a0] + t0) * (unsigned)g.N[a1] + (unsigned)(win.lo[a1] + t1)) * C;
-            else
-                off = (((unsigned)(win.lo[0] + t0) * (unsigned)g.N[1] + (unsigned)(win.lo[1] + t1)) * (unsigned)g.N[2] +
-                       (unsigned)(win.lo[2] + t2)) * C;
-            const uint32_t r0 = area + (live ? a0 * kWinExtent + t0 : kWinZeroRow) * kWinRow + first;
-            const uint32_t r1 = area + (live ? a1 * kWinExtent + t1 : kWinZeroRow) * kWinRow + first;
-            const uint32_t r2 = area + (live ? 2 * kWinExtent + t2 : kWinZeroRow) * kWinRow + first;
-            float w[4 * kVec];
-#pragma unroll
-            for (int v = 0; v < kVec; ++v) {
-                const f32x4 x = lds_get<f32x4>(r0 + 16 * v), y = lds_get<f32x4>(r1 + 16 * v);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[4 * v + e] = x[e] * y[e];
-                if constexpr (KIND != LP_GRID_TRIPLANE) {
-                    const f32x4 z = lds_get<f32x4>(r2 + 16 * v);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[4 * v + e] *= z[e];
-                }
-            }
-            // offsets of all texels of this product, for the lanes that will hold their rows
-            wave_lds_fence();
-            if (lane < kLanes) lds_put<uint32_t>(area + kWinOffsets + 4 * slot, off);
-            wave_lds_fence();
-            auto add = [&](unsigned texel_off, float v) {
-                if (v != 0.0f) atomicAdd(reinterpret_cast<float*>(out + 4u * (texel_off + (unsigned)(lane & (C - 1)))), v);
-            };
-            if constexpr (C == 32) {
-                f32x16 acc = zero16();
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[r], dFt[r], acc, 0, 0, 0);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (n0 + 8 * q >= total) break;
-                    const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 4 * (8 * q + 4 * grp));
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) add(o[p], acc[4 * q + p]);
-                }
-            } else {
-                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int k = 0; k < 8; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b16[k], acc, 0, 0, 0);
-                const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 16 * (lane >> 4));
-#pragma unroll
-                for (int p = 0; p < 4; ++p) add(o[p], acc[p]);
-            }
-        }
-    }
-}
-
-// The walk on a step of the tile kernel: records and feature gradient go through LDS in the order of the
-// walk (16 positions per lane group): samples of one ray in order, or ray after ray of a tile, every other
-// one backwards, so that the step from ray to ray is a short one.
-template <int KIND, int C>
-__device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_grid[3], int scene, char* area,
-                                             const Cell3& cell, const f32x16& dFt, int lane, bool tile)
-{
-    const int col = lane & 31, grp = lane >> 5;
-    auto flip = [tile](int c) { return (tile && (c & 8)) ? c ^ 7 : c; };   // column <-> position of the walk
-    float* info = reinterpret_cast<float*>(area);
-    float* grad = reinterpret_cast<float*>(area + 2048);
-    wave_lds_fence();
-    if (grp == 0) write_scatter_record<KIND, C>(info + flip(col) * 16, g, cell);
-    if (col < C) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) grad[flip(d_row(r, grp)) * C + col] = dFt[r];
-    }
-    wave_lds_fence();
-    f32x16 v;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = grad[(16 * grp + r) * C + (col & (C - 1))];
-    scatter_channels<KIND, C, true>(g, d_grid, scene, info, v, col, grp);
-    wave_lds_fence();
-}
-
-// A step's scatter.  Where the samples of the whole step spread too far for one window, they are taken as two or four
-// runs of consecutive samples (of every ray of the tile) with a window each: on 160^3 x 32 voxels with contract
-// coordinates, 256^2 rays x 384 samples, 27 % of the steps do not fit and nearly all of their halves do, and a step
-// in the walk adds 512 lines against some 160 of two windows.  The products would spread an infinite or
-// undefined gradient over its window, so a step that holds one takes the walk, which keeps it to the sample's own corners.
-template <int KIND, int C>
-__device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
-                                             char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, bool tile)
-{
-    const int col = lane & 31, k = tile ? (col & (kTileSamples - 1)) : col, full = tile ? kTileSamples : 32;
-    float probe = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) probe = fmaf(dFt[r], 0.0f, probe);
-    const bool finite = __ballot(probe != 0.0f) == 0ull;
-    int len = full;
-    Window win = find_window(cell, true);
-    bool fits = finite && window_fits<KIND>(win);
-    while (!fits && finite && len > full / 4) {
-        len >>= 1;
-        fits = true;
-        for (int p = full - len; p >= 0 && fits; p -= len) {
-            win = find_window(cell, (unsigned)(k - p) < (unsigned)len);
-            fits = window_fits<KIND>(win);
-        }
-    }
-    if (!fits) {
-        scatter_walk<KIND, C>(g, d_grid, scene, area_ptr, cell, dFt, lane, tile);
-        return;
-    }
-    for (int p = 0;;) {   // `win` is the first run's
-        scatter_window<KIND, C>(g, d_grid, scene, area, win, cell, (unsigned)(k - p) < (unsigned)len, dFt, lane);
-        p += len;
-        if (p >= full) break;
-        win = find_window(cell, (unsigned)(k - p) < (unsigned)len);
     }
 }
 
@@ -499,16 +275,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         const int col = lane_id & 31, grp = lane_id >> 5;
         const long long first = item_ray();
         if (tiles && sub == 0) {
-            // side by side: in one scene, and within three cells of the first ray at both ends
-            const long long r = min(first + (col >> 3), rays.M - 1);
-            const RayGeom q = load_ray_geom(rays, r);
-            const Cell3 c0 = sample_cell_for<CC, GT>(g, q, 0), c1 = sample_cell_for<CC, GT>(g, q, S - 1);
-            bool apart = q.scene != __builtin_amdgcn_readfirstlane(q.scene);
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                apart = apart || abs(c0.i[a] - __builtin_amdgcn_readfirstlane(c0.i[a])) > 3 ||
-                        abs(c1.i[a] - __builtin_amdgcn_readfirstlane(c1.i[a])) > 3;
-            tile = __ballot(apart) == 0ull;
+            tile = side_by_side(rays, first, col, [&](const RayGeom& q, int j) { return sample_cell_for<CC, GT>(g, q, j); });
         }
         const long long r = first + (tile ? (col >> 3) : sub);
         ray_ok = r < rays.M;

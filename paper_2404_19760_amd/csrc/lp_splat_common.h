@@ -8,8 +8,8 @@ namespace lp {
 // Weight sums: lane `corner` (< 8 voxel and hash table, < 12 triplane) of each lane group walks the
 // group's 16 points and adds the summed weight of every run into theta_w (hash table: a run = the
 // points whose corner `corner` falls into the same entry).
-template <int KIND, int C>
-__device__ __forceinline__ void scatter_weights(const GridDev& g, float* const theta_w[3], int scene,
+template <int KIND, int C, bool IN_ORDER = false>   // (record order: as scatter_channels)
+__device__ __forceinline__ void scatter_weights(const GridDev& g, float* const* theta_w, int scene,
                                                 const float* info, int corner, int grp)
 {
     constexpr int NC = KIND == LP_GRID_TRIPLANE ? 12 : 8;
@@ -40,7 +40,7 @@ __device__ __forceinline__ void scatter_weights(const GridDev& g, float* const t
     unsigned prev = 0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const float* rec = info + d_row(r, grp) * 16;
+        const float* rec = info + (IN_ORDER ? 16 * grp + r : d_row(r, grp)) * 16;
         const float w = rec[widx];
         const unsigned base = reinterpret_cast<const unsigned*>(rec)[bidx];
         if (r > 0 && base != prev) {
