@@ -1,63 +1,67 @@
 // Naive Splatter forward (Section 3.3 "Splatter": every point of a pixel's ray pushes the pixel's
-// feature vector into the cell that contains it), wavefront per ray.
+// feature vector into the cell that contains it).
 //
-// The push is the Renderer's backward scatter with a feature gradient that is constant along
-// the ray, so it runs on the same machinery: a step is 32 points; lane (col, grp) of the step
-// places point slot col and publishes its corner weights and cell offset in LDS; then the lanes
-// turn into channels, walk 16 consecutive points each, sum the weights of runs that stay in one
-// cell and issue one atomic add per corner on whole 64-byte lines (value = pixel feature times
-// summed weight).  The weight sums go to the one-channel structure the same way, one lane per
-// corner.  Ray groups are visited in scrambled order like the Renderer's backward (atomic adds
-// of neighbouring rays queue up at the same L2 channel).
+// What bounds it: the rate of atomic adds (2.1e10 64-byte lines/s on this chip). Pushed ray by ray, a point adds
+// about 10 lines after runs in a cell are merged; a step is therefore a tile of four neighbouring rays, eight points
+// of each, whose window of texels is summed as a matrix product of interpolation weights and pixel features
+// (lp_tile_scatter.h) and added once per texel: 3.9 lines per point. The weight sums go to the one-channel structure
+// by the lanes that hold the texels' weights. Rays that do not run side by side are pushed one after the other, 32
+// points per step, by the run-merging walk.
+// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.41 ms ray by ray -> 2.34 ms (1.95 ms of it are the adds).
+// Tiles are visited in scrambled order like the Renderer's backward
+// (atomic adds of neighbouring rays queue up at the same L2 channel).
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
 #include "lp_mfma_bwd_common.h"
 #include "lp_splat_common.h"
+#include "lp_tile_scatter.h"
 
 namespace lp {
 
 namespace {
 
 constexpr int kWaves = 4;
+constexpr int kArea = 6144;   // LDS of a wave: the window's table, or the records of a walk
 
 template <int KIND, int C, bool CC>
-__global__ __launch_bounds__(kWaves * 64) void splat_naive_kernel(GridDev tgt, RaysDev rays, SplatDev sp,
-                                                                  long long group_mul)
+__global__ __launch_bounds__(kWaves * 64) void splat_naive_kernel(GridDev tgt, RaysDev rays, SplatDev sp, PushOrder order)
 {
-    __shared__ float info_all[kWaves][32 * 16];
+    __shared__ __align__(16) char areas[kWaves][kArea];
     const int lane = threadIdx.x & 63;
-    const int col = lane & 31, grp = lane >> 5;
+    const int col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float* info = info_all[wave];
+    const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)areas[wave];
 
-    const long long n_groups = (rays.M + kWaves - 1) / kWaves;
-    const RaySchedule sched = ray_schedule(n_groups * kWaves, kWaves);
+    const int rays_per_item = order.tiles ? kTileRays : 1;
+    const RaySchedule sched = ray_schedule(order.n_groups * kWaves, kWaves);
     const int S = rays.S;
     for (long long seq = sched.first; seq < sched.end; seq += sched.stride) {
-        const long long ray = ((seq / kWaves) * group_mul % n_groups) * kWaves + seq % kWaves;
-        if (ray >= rays.M) continue;
-        const RayGeom q = load_ray_geom(rays, ray);
-        // the pixel's feature of this lane's channel (16 channels: both halves of a lane group)
-        const float v = sp.feats[(size_t)ray * C + (col & (C - 1))];
-        f32x16 val;
+        const long long first = (((seq / kWaves) * order.group_mul % order.n_groups) * kWaves + seq % kWaves) * rays_per_item;
+        if (first >= rays.M) continue;
+        const bool tile = order.tiles && side_by_side(rays, first, col, [&](const RayGeom& r, int j) { return sample_cell<CC>(tgt, r, j); });
+        const int n_sub = tile ? 1 : (int)min((long long)rays_per_item, rays.M - first);
+        for (int sub = 0; sub < n_sub; ++sub) {
+            const long long r = first + (tile ? col / kTileSamples : sub);
+            const bool ray_ok = r < rays.M;
+            const RayGeom q = load_ray_geom(rays, min(r, rays.M - 1));
+            const int scene = __builtin_amdgcn_readfirstlane(q.scene);
+            // the pixels' features of this lane's channel (16 channels: both halves of a lane group)
+            f32x16 val;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) val[r] = v;
-        for (int j0 = 0; j0 < S; j0 += kBwdStep) {
-            const int j = j0 + slot_to_sample(col);
-            const Cell3 c = sample_cell<CC>(tgt, q, min(j, S - 1));
-            wave_lds_fence();
-            if (grp == 0) {
-                float* rec = info + col * 16;
-                write_scatter_record<KIND, C, true>(rec, tgt, c);
-                if (j >= S) {  // a point past the end of the ray pushes nothing
+            for (int i = 0; i < kTileRays; ++i) {
+                const long long at = min(first + (tile ? i : sub), rays.M - 1);
+                const float v = sp.feats[(size_t)at * C + (col & (C - 1))];
 #pragma unroll
-                    for (int k = 0; k < (KIND == LP_GRID_TRIPLANE ? 12 : 8); ++k) rec[k] = 0.0f;
-                }
+                for (int e = 0; e < 4; ++e) val[4 * i + e] = v;
             }
-            wave_lds_fence();
-            scatter_channels<KIND, C>(tgt, sp.theta, q.scene, info, val, col, grp);
-            scatter_weights<KIND, C>(tgt, sp.theta_w, q.scene, info, col, grp);
+            const int step = tile ? kTileSamples : 32, k = tile ? col % kTileSamples : col;
+            for (int j0 = 0; j0 < S; j0 += step) {
+                const int j = j0 + k;
+                const Cell3 c = sample_cell<CC>(tgt, q, min(j, S - 1));
+                scatter_step<KIND, C, Scatter::kPushRay>(tgt, sp.theta, scene, area, areas[wave], c, val, lane, tile,
+                                                         sp.theta_w, ray_ok && j < S);
+            }
         }
     }
 }
@@ -65,14 +69,12 @@ __global__ __launch_bounds__(kWaves * 64) void splat_naive_kernel(GridDev tgt, R
 template <int KIND, int C, bool CC>
 hipError_t launch(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu, hipStream_t stream)
 {
-    long long blocks = 4LL * n_cu;   // small kernel: four workgroups per compute unit
-    const long long need = (rays.M + kWaves - 1) / kWaves;
-    if (blocks > need) blocks = need;
+    long long blocks = 4LL * n_cu;   // four workgroups per compute unit
     blocks = (blocks + 7) / 8 * 8;
-    const long long n_groups = need;
-    const long long group_mul = splat_group_multiplier(n_groups);
+    const PushOrder order = push_order(rays, blocks * kWaves, kWaves);
+    if (blocks > order.n_groups) blocks = (order.n_groups + 7) / 8 * 8;
     hipLaunchKernelGGL((splat_naive_kernel<KIND, C, CC>), dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt,
-                       rays, sp, group_mul);
+                       rays, sp, order);
     return hipGetLastError();
 }
 
