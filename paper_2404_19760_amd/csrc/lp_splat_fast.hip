@@ -7,7 +7,7 @@
 // (lp_tile_scatter.h) and added once per texel: 3.9 lines per point. The weight sums go to the one-channel structure
 // by the lanes that hold the texels' weights. Rays that do not run side by side are pushed one after the other, 32
 // points per step, by the run-merging walk.
-// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.41 ms ray by ray -> 2.34 ms (1.95 ms of it are the adds).
+// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.41 ms ray by ray -> 2.18 ms (1.95 ms of it are the adds).
 // Tiles are visited in scrambled order like the Renderer's backward
 // (atomic adds of neighbouring rays queue up at the same L2 channel).
 #include "lp_kernels.h"
@@ -22,7 +22,8 @@ namespace lp {
 namespace {
 
 constexpr int kWaves = 4;
-constexpr int kArea = 6144;   // LDS of a wave: the window's table, or the records of a walk
+constexpr int kArea = kWinBytes;   // LDS of a wave: the window's table, or the records of a walk
+static_assert(kArea >= 32 * 16 * 4, "the walk's records");
 
 template <int KIND, int C, bool CC>
 __global__ __launch_bounds__(kWaves * 64) void splat_naive_kernel(GridDev tgt, RaysDev rays, SplatDev sp, PushOrder order)
