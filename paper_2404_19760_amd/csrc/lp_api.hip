@@ -815,8 +815,15 @@ lp_status lp_splat_fwd(const lp_grid* target, const lp_rays* rays, const lp_spla
     }
     for (int p = 0; p < n_planes; ++p) {
         const long long cells = plane_cells(target, p);
-        hipLaunchKernelGGL(lp::splat_normalise_kernel, dim3((unsigned)((cells * target->C + threads - 1) / threads)),
-                           dim3(threads), 0, s, theta[p], theta_w[p], cells, target->C);
+        const int C = target->C;
+        if (C % 4 == 0 && C <= 4 * threads && ((uintptr_t)theta[p] & 15u) == 0) {   // 16-byte loads and stores
+            const int rows = threads / (C / 4);   // cells of a block
+            hipLaunchKernelGGL(lp::splat_normalise4_kernel, dim3((unsigned)((cells + rows - 1) / rows)), dim3(C / 4, rows),
+                               0, s, theta[p], theta_w[p], cells, C);
+        } else {
+            hipLaunchKernelGGL(lp::splat_normalise_kernel, dim3((unsigned)((cells * C + threads - 1) / threads)),
+                               dim3(threads), 0, s, theta[p], theta_w[p], cells, C);
+        }
     }
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail("Splatter normalisation kernel launch", e);

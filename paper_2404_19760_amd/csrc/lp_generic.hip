@@ -636,6 +636,23 @@ __global__ void splat_normalise_kernel(float* theta, const float* theta_w, long 
     theta[i] = w > 0.0f ? theta[i] / w : 0.0f;
 }
 
+// The same, four channels (16-byte aligned) per thread: threadIdx.y walks the cells, so that no index is divided.
+// What bounds it: memory. Cells where nothing landed are written without being read.
+// 160^3 x 32 after 65536 rays: 0.281 -> 0.134 ms.
+__global__ void splat_normalise4_kernel(float* theta, const float* theta_w, long long cells, int C)
+{
+    const long long cell = (long long)blockIdx.x * blockDim.y + threadIdx.y;
+    if (cell >= cells) return;
+    const float w = theta_w[cell];
+    float4* p = reinterpret_cast<float4*>(theta + cell * C) + threadIdx.x;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (w > 0.0f) {
+        v = *p;
+        v = make_float4(v.x / w, v.y / w, v.z / w, v.w / w);
+    }
+    *p = v;
+}
+
 __global__ void fill_zero_kernel(float* p, long long n)
 {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;

@@ -12,6 +12,7 @@ constexpr int kReduceThreads = 1024;  // block size of reduce_params_kernel; one
 __global__ void reduce_params_kernel(MlpDev m, BwdIo io, int n_records);
 __global__ void splat_fwd_generic_kernel(GridDev tgt, MlpDev m, RaysDev rays, SplatDev sp);
 __global__ void splat_normalise_kernel(float* theta, const float* theta_w, long long cells, int C);
+__global__ void splat_normalise4_kernel(float* theta, const float* theta_w, long long cells, int C);
 __global__ void fill_zero_kernel(float* p, long long n);
 __global__ void splat_bwd_generic_kernel(GridDev tgt, MlpDev m, RaysDev rays, SplatDev sp, BwdIo io,
                                          int tiles_per_block);
