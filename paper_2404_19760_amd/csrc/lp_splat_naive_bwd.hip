@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tg
                     G = reinterpret_cast<const char*>(sp.d_theta[0] + (size_t)q.scene * tgt.hash_size * C);
                 else
                     G = reinterpret_cast<const char*>(sp.d_theta[0] + (size_t)q.scene * tgt.N[0] * tgt.N[1] * tgt.N[2] * C);
-                const int end = points * Rec::kPoint;
+                const int end = points * Rec::kPoint, live = (S - j0) * Rec::kPoint;
                 for (int at = 0; at < end; at += kUnroll * kTexels * 8) {
                     u32x2 rec[kUnroll];
                     f32x4 x[kUnroll];
@@ -127,6 +127,11 @@ __global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tg
                     for (int u = 0; u < kUnroll; ++u) rec[u] = lds_get<u32x2>(mine + p * Rec::kPlane + at + u * kTexels * 8);
 #pragma unroll
                     for (int u = 0; u < kUnroll; ++u) x[u] = *reinterpret_cast<const f32x4*>(G + (rec[u][1] + piece));
+                    if (at + kUnroll * kTexels * 8 > live) {   // past the ray's end: nothing, also where the texel is infinite
+#pragma unroll
+                        for (int u = 0; u < kUnroll; ++u)
+                            if (at + (u * kTexels + lane / kLanes) * 8 >= live) x[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    }
 #pragma unroll
                     for (int u = 0; u < kUnroll; ++u)
 #pragma unroll

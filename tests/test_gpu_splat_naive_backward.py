@@ -39,3 +39,26 @@ def test_equals_the_generic_kernel(lp, kind, channels, n_rays, samples):
     # products and quotient)
     n = samples * (12 if kind == TRIPLANE else 8)
     assert ((got - want).abs() <= 2 * (n + 3) * 2.0 ** -24 * total).all()
+
+
+@pytest.mark.parametrize("kind", [VOXEL, TRIPLANE, HASH])
+@pytest.mark.parametrize("samples", [1, 33, 90])
+def test_infinite_gradients_stay_infinite(lp, kind, samples):
+    """An infinite gradient makes the same pixels infinite or undefined as on the generic kernel: a ray is read in units
+    of 32 points, and what is read past its end must not meet the infinity."""
+    kw = dict(hash_size=256) if kind == HASH else {}
+    sp = lp_inputs.make_splat_small(kind, channels=32, res=(9, 8, 10), n_rays=130, samples=samples, seed=11, n_scenes=2,
+                                    far=(2.2, 6.0), **kw)
+    target, rays, splat = lp.splat_to_device(sp)
+    theta, theta_w = lp.splat_fwd(target, rays, splat)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    d_theta = [torch.randn(t.shape, generator=gen, device="cuda") for t in theta]
+    for t in d_theta:
+        t[torch.rand(t.shape, generator=gen, device="cuda") < 0.02] = float("inf")
+    ws = torch.empty(lp.lp_splat_bwd_workspace_bytes(target, rays, splat), dtype=torch.uint8, device="cuda")
+    got, want = torch.full_like(splat.feats, 7.0), torch.full_like(splat.feats, -7.0)
+    lp.lp_splat_bwd(target, rays, splat, theta_w, d_theta, got, [], [], [], ws)
+    lp.lp_splat_bwd(target, rays, splat, theta_w, [_on_odd_address(t) for t in d_theta], want, [], [], [], ws)
+    assert torch.isposinf(want).any()
+    assert torch.equal(torch.isposinf(got), torch.isposinf(want))
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
