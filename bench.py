@@ -36,15 +36,13 @@ import numpy as np
 HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 
-# HBM bytes per launch of the backward kernel from two rocprofv3 --pmc runs (FETCH_SIZE scaled
-# by 2.0, WRITE_SIZE by 1.0 against a 1 GiB copy kernel in the same run); the summary with the
-# commands is profiles/large_voxel256_fwd_bwd_kernels.md.  None = not measured for that workload.
-MEASURED_BWD_HBM_BYTES = {"large": 19.51e9 + 65.42e9}
+# HBM bytes per launch of the backward kernel, from counters (FETCH_SIZE and WRITE_SIZE against a 1 GiB copy in the
+# same run).  Not measured for the tile kernels yet: a workload that is not listed gets no such figure.
+MEASURED_BWD_HBM_BYTES = {}
 # 64-byte lines of atomic adds per launch of the backward kernel: TCC_ATOMIC (each request is one line,
-# written through as 64 bytes: WRITE_SIZE / 64 gives the same number); profiles/atomic_line_rate.md.
-MEASURED_BWD_ATOMIC_LINES = {"large": 65.42e9 / 64, "batched": 257.0e9 / 64, "voxel": 171758784.0,
-                             "contract": 140152160.0, "single_scene": 15266496.0, "decoder": 52144736.0,
-                             "hash": 10885988.0}
+# written through as 64 bytes: WRITE_SIZE / 64 gives the same number); profiles/atomic_line_rate.md.  Workloads of the
+# one-wave kernels; the tile kernels add fewer lines.
+MEASURED_BWD_ATOMIC_LINES = {"decoder": 52144736.0}
 
 
 def parse():
@@ -75,7 +73,7 @@ def parse():
     ap.add_argument("--ws-phases", action="store_true",
                     help="with a measurement build of the library (LP_EXTRA_HIPCC_FLAGS=-DLP_WS_PHASES python "
                          "paper_2404_19760_amd/build.py): after the run, print where the two roles of the two-wave "
-                         "backward spend their cycles (a second JSON line)")
+                         "backward (LP_BWD_TWO_WAVE=1) spend their cycles (a second JSON line)")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a plain 1 GiB device-to-device copy kernel (reference for HBM counters)")
     return ap.parse_args()
