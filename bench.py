@@ -40,9 +40,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # same run).  Not measured for the tile kernels yet: a workload that is not listed gets no such figure.
 MEASURED_BWD_HBM_BYTES = {}
 # 64-byte lines of atomic adds per launch of the backward kernel: TCC_ATOMIC (each request is one line,
-# written through as 64 bytes: WRITE_SIZE / 64 gives the same number); profiles/atomic_line_rate.md.  Workloads of the
-# one-wave kernels; the tile kernels add fewer lines.
-MEASURED_BWD_ATOMIC_LINES = {"decoder": 52144736.0}
+# written through as 64 bytes: WRITE_SIZE / 64 gives the same number); profiles/large_voxel256_tile_backward.md and
+# profiles/atomic_line_rate.md (decoder, a one-wave kernel).  Not counted yet for the other workloads on tile kernels.
+MEASURED_BWD_ATOMIC_LINES = {"large": 18368049.0 * 1024 / 64, "decoder": 52144736.0}
 
 
 def parse():
