@@ -280,10 +280,13 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
     }
     wave_lds_fence();
     f32x16 v;
+    [[maybe_unused]] const unsigned there = (unsigned)__ballot(valid);   // a bit per column
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         if constexpr (WHAT == Scatter::kPushRay) v[r] = grp ? dFt[8 + 4 * (r / 8)] : dFt[4 * (r / 8)];   // position 16 grp + r: ray 2 grp + r / 8
         else v[r] = grad[(16 * grp + r) * C + (col & (C - 1))];
+        // what does not exist pushes nothing: weight zero alone would turn an infinite feature into an undefined one
+        if constexpr (kPushes) v[r] = ((there >> flip(16 * grp + r)) & 1u) ? v[r] : 0.0f;
     }
     scatter_channels<KIND, C, true>(g, d_grid, scene, info, v, col, grp);
     if constexpr (kPushes) scatter_weights<KIND, C, true>(g, sums, scene, info, col, grp);

@@ -71,6 +71,23 @@ def test_undefined_pixel_stays_on_its_ray(lp, kind, channels):
         assert torch.isnan(b).any() and torch.equal(torch.isnan(a), torch.isnan(b))
 
 
+@pytest.mark.parametrize("kind,channels", SPLATS)
+@pytest.mark.parametrize("n_rays,samples", [(8190, 24), (8192, 29), (37, 29)])
+def test_infinite_pixel_stays_infinite(lp, kind, channels, n_rays, samples):
+    """The last pixel's feature is infinite: the cells of its ray are infinite and none is undefined, whether its tile
+    (n_rays % 4 = 2) or its last step has places left over, whose points must not meet the infinity with weight zero."""
+    import torch
+    sp = _splat(kind, channels, n_rays, samples, (40, 33, 37))
+    sp.feats[-1] = np.inf
+    target, rays, splat = lp.splat_to_device(sp)
+    got = lp.splat_fwd(target, rays, splat)[0]
+    alone = dataclasses.replace(sp, **{n: getattr(sp, n)[-1:] for n in ("origins", "dirs", "near", "far", "feats")})
+    reached = lp.splat_fwd(*lp.splat_to_device(alone))[1]
+    for a, w in zip(got, reached):
+        assert (w > 0).any() and not torch.isnan(a).any()
+        assert torch.equal(torch.isposinf(a), (w > 0)[..., None].expand_as(a))
+
+
 HASHES = [(16, (16, 64, 64, 4), 1 << 15), (16, (16, 32, 4), 64), (32, (32, 64, 4), 4096), (32, (32, 32, 32, 4), 1)]
 
 
