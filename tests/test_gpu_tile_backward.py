@@ -97,3 +97,28 @@ def test_undefined_gradient_stays_on_its_ray(lp, kind, channels, dims):
     bad = [torch.isnan(lp.render_bwd(grid, mlp, rays, bg, d_rgb, cache, None, None, mode)[0][0])
            for mode in (lp.LP_MATH_BF16X3, lp.LP_MATH_GENERIC)]
     assert bad[1].any() and torch.equal(bad[0], bad[1])
+
+
+def test_optical_depth_of_opaque_rays(lp):
+    """The backward walks a ray's optical depth back from its end, step by step.  Constant density (sigma Delta = 2 per
+    sample, 1027 in all) makes every rounding of that walk fall to the same side: held in fp32 it ends 9.8e-4 off at
+    the front after 64 steps of eight samples, where all the weight is.  What remains is the depth the forward kept: at most half
+    an ulp (6.1e-5) for each of its eight steps and for the value kept."""
+    import torch
+
+    samples, n_rays, delta = 512, 8192, 0.10033512115478516
+    inp = lp_inputs.make_small(VOXEL, channels=16, res=(5, 4, 6), mlp_dims=(16, 64, 64, 4), n_rays=1, samples=samples, seed=239)
+    rows = lambda a: np.repeat(a, n_rays, axis=0)
+    full = lambda v: np.full(n_rays, v, dtype=np.float32)
+    biases = [np.zeros_like(b) for b in inp.biases]
+    biases[-1][:] = (20.0, 0.3, -0.2, 0.1)   # density 20, a constant colour: the weights are zero
+    inp = dataclasses.replace(inp, origins=rows(inp.origins), dirs=rows(inp.dirs), near=full(0.0), far=full(samples * delta),
+                              target=rows(inp.target), weights=[np.zeros_like(w) for w in inp.weights], biases=biases)
+    grid, mlp, rays, bg = lp.to_device(inp, "cuda:0")
+    _, _, _, cache = lp.render_fwd(grid, mlp, rays, bg, lp.LP_MATH_BF16X3)
+    d_rgb = torch.ones((n_rays, 3), device="cuda")
+    db = lp.render_bwd(grid, mlp, rays, bg, d_rgb, cache, None, None, lp.LP_MATH_BF16X3)[2][-1].double().cpu().numpy()
+    for k in (1, 2, 3):   # d(colour) = sum of the weights (1) x slope of the sigmoid, over the rays
+        c = 1.0 / (1.0 + np.exp(-float(inp.biases[-1][k])))
+        want = n_rays * c * (1.0 - c)
+        assert abs(db[k] - want) <= (9 * 6.1e-5 + 1e-5) * want, (k, db[k] / want - 1.0)
