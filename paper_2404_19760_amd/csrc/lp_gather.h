@@ -185,7 +185,9 @@ __device__ __forceinline__ void wave_features(const GridDev& g, int scene, const
 {
     using Image = TileImage<C, false>;
     publish_gather<KIND, C>(rec, lane, g, c);
+    wave_lds_fence();   // (also: the last step's reads of the image are done)
     wave_gather<KIND, C, GT, AHEAD>(g, scene, rec, img, lane);
+    wave_lds_fence();   // (also: the reads of the records are done)
     const uint32_t own = img + Image::own(lane);
 #pragma unroll
     for (int s = 0; s < C / 16; ++s) {

@@ -29,6 +29,16 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
+// Between LDS stores of some lanes of a wave and loads of the same bytes by others (either order).  LDS operations of one
+// wave execute in order; this only pins the compiler's order, which no address of a single lane asks for.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 struct Frag {  // one MFMA A or B operand: 8 bf16 = 4 dwords
     uint32_t d[4];
 };

@@ -1,4 +1,4 @@
-// Pieces shared by the matrix-core backward kernels: wave-level LDS fence, ReLU-derivative
+// Pieces shared by the matrix-core backward kernels: ReLU-derivative
 // masking, bias-gradient sums, and the scatter of the feature gradient into the grid gradient.
 #pragma once
 #include "lp_mfma.h"
@@ -9,16 +9,6 @@ namespace lp {
 constexpr int kBwdNB = 1;               // N blocks (of 32 samples) per backward step
 constexpr int kBwdStep = 32 * kBwdNB;   // samples per step
 constexpr int kBwdKS = 2 * kBwdNB;      // K-steps of a contraction over the samples of a step
-
-__device__ __forceinline__ void wave_lds_fence()
-{
-    // LDS operations of one wave execute in order; this only pins the compiler's ordering of
-    // the tile stores of some lanes against the tile loads of others
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    __builtin_amdgcn_sched_barrier(0);
-}
 
 // sum of the 8 bf16 values of a fragment, added to acc
 __device__ __forceinline__ float frag_sum(const Frag& f, float acc)
