@@ -494,7 +494,6 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             // (in fp64: a step of eight samples takes four times the subtractions of one of 32, and in fp32 each of them
             // rounds to the spacing of the whole depth, which at the front of an opaque ray is all of its weight)
             const double tau64 = lds_get<double>(geo + 40) - (double)__shfl(incl, last, 64);
-            if (k == 0 && grp == 0) lds_put<double>(geo + 40, tau64);
             const float tau_start = (float)tau64;
             const float Tprev = __expf(-(tau_start + (incl - sd)));
             const float w = Tprev * one_minus_exp_neg(sd);
@@ -517,6 +516,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             split2(dz[0], dz[1], zh0, zl0);
             split2(dz[2], dz[3], zh1, zl1);
             lds_put<u32x4>(dz_at + col * 16, u32x4{zh0, zh1, zl0, zl1});   // (both lane groups the same)
+            wave_lds_fence();   // the activations, the output gradients; every lane has read its ray
+            if (k == 0 && grp == 0) lds_put<double>(geo + 40, tau64);
         }
         __builtin_amdgcn_sched_barrier(0);
 
@@ -567,6 +568,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         }
 
         if constexpr (NH == 2) {
+            wave_lds_fence();   // the last layer's activations have been read
             store_hidden(L::B, gz_h, gz_l);
             refresh(own_h); refresh(col_h);
             const uint32_t col_w = col_h + to_w2;
@@ -595,6 +597,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
                     weave<3 * KSH, 8, 2>(second, piece);
                 }
             }
+            wave_lds_fence();   // dZ2
             // ---- dW2 += dZ2 H1^T ; db2 += sum dZ2; beside it the last block of dZ1 ----
             {
                 Frag ah[2], al[2], bh[2], bl[2];
@@ -631,6 +634,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         constexpr int kZ = NH == 2 ? L::A : L::B, kF = NH == 2 ? L::B : L::A;
         refresh(own_h); refresh(own_f); refresh(C == 32 ? col_f : col_f32);
         const uint32_t col_w1 = (C == 32 ? col_f : col_f32) + to_w1;
+        wave_lds_fence();   // what they replace has been read
         store_hidden(kZ, gz_h, gz_l);
 #pragma unroll
         for (int s = 0; s < KS1; ++s) {
@@ -655,6 +659,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             weave<3 * KSH, 0, 0>(product, none);
         }
         refresh(col_h); refresh(col16_h); refresh(col_f);
+        wave_lds_fence();   // dZ1 and the features
         // ---- dW1 += dZ1 F^T ; db1 += sum dZ1 ----
         if constexpr (C == 32) {
             Frag bh[2], bl[2], ah[2], al[2];

@@ -6,6 +6,8 @@ they are written down (a lambda's stand where it is defined, right before its us
 import os
 import re
 
+import pytest
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2404_19760_amd", "csrc")
 FENCE = (r"wave_lds_fence\(\)", [("fence", None)])
 
@@ -48,3 +50,40 @@ def test_sampling_by_whole_texels():
                           (r"\bwave_gather<", [("read", "records"), ("store", "image")]), (r"= lds_chunk\(", [("read", "image")])])
     assert {b for w, b in step if w == "read"} == {"records", "image"}
     _check(step)
+
+
+@pytest.mark.parametrize("hidden_layers", [1, 2])
+def test_step_of_the_tile_backward(hidden_layers):
+    body = _between(_source("lp_mfma_bwd_tile.h"), r"^    while \(live\) \{", r"^    // ---- sums|^    constexpr int kRegs")
+    if hidden_layers == 1:   # without the part between the output layer and the first one
+        a = next(i for i, l in enumerate(body) if l.rstrip() == "        if constexpr (NH == 2) {")
+        b = next(i for i in range(a, len(body)) if body[i].rstrip() == "        }")
+        body = body[:a] + body[b:]
+    two = hidden_layers == 2
+    names = {"kHere": "B" if two else "A", "kLast": "B" if two else "A", "kZ": "A" if two else "B", "kF": "B" if two else "A",
+             "L::A": "A", "L::B": "B"}
+    area = r"(L::A|L::B|kHere|kLast|kZ|kF)\b"
+    step = _events(body, [
+        FENCE,
+        (r"activate_pair\([^()]*, " + area, [("store", "$1")]),
+        (r"store_hidden\(" + area, [("store", "$1")]),
+        (r"lds_put_chunk\(.*\+ " + area, [("store", "$1")]),
+        (r"lds_put<u32x4>\(dz_at", [("store", "output gradients")]),
+        (r"lds_tr\(zp ", [("read", "output gradients")]),
+        (r"lds_tr\(hp [^;]*?\+ " + area, [("read", "$1")]),
+        (r"I(?:H|W1)::read\((?:col_h|col16_h|col_f)\b[^;]*?" + area, [("read", "$1")]),
+        (r"lds_get<double>\(geo \+ 40\)", [("read", "optical depth")]),
+        (r"lds_put<double>\(geo \+ 40,", [("store", "optical depth")]),
+        (r"\bload_rays\(\)", [("fence", None), ("store", "optical depth"), ("fence", None)]),
+        (r"\bscatter_step<", [("fence", None), ("store", "A"), ("fence", None), ("read", "A")]),
+    ], names)
+    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "optical depth"} == {b for w, b in step if w == "store"}
+    _check(step)
+
+
+@pytest.mark.parametrize("function", ["scatter_window", "scatter_walk"])
+def test_scatter_begins_with_a_fence(function):
+    """(As the check of the whole step assumes.)"""
+    body = _between(_source("lp_tile_scatter.h"), r"void %s\(" % function, r"^}")
+    lds = next(i for i, l in enumerate(body) if re.search(r"lds_put|lds_get|wave_lds_fence|write_scatter_record", l))
+    assert "wave_lds_fence()" in body[lds]
