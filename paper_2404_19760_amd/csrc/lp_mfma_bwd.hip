@@ -41,8 +41,10 @@ hipError_t launch_bwd_mfma(const GridDev& g, const MlpDev& m, const RaysDev& ray
     static const bool one_wave = chosen("LP_BWD_ONE_WAVE"), two_wave = chosen("LP_BWD_TWO_WAVE");
     if ((one_wave || two_wave) && bwd_ws_supported(g, m)) {
         if (two_wave) return launch_bwd_mfma_ws(g, m, rays, io, n_cu, stream);
-        if (g.dtype == LP_F32 && !(g.contract > 0.0))
-            return launch_bwd<LP_GRID_VOXEL, 16, 64, 2, false, 16>(g, m, rays, io, n_cu, stream);
+        if (g.dtype == LP_BF16) return launch_bwd<LP_GRID_VOXEL, 16, 64, 2, false, 16, LP_BF16>(g, m, rays, io, n_cu, stream);
+        if (g.dtype == LP_F16) return launch_bwd<LP_GRID_VOXEL, 16, 64, 2, false, 16, LP_F16>(g, m, rays, io, n_cu, stream);
+        return g.contract > 0.0 ? launch_bwd<LP_GRID_VOXEL, 16, 64, 2, true, 16>(g, m, rays, io, n_cu, stream)
+                                : launch_bwd<LP_GRID_VOXEL, 16, 64, 2, false, 16>(g, m, rays, io, n_cu, stream);
     }
     if (m.dims[0] == g.C) {
         if (g.kind == LP_GRID_VOXEL) return launch_bwd_tile_voxel(g, m, rays, io, n_cu, stream);
