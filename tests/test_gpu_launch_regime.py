@@ -1,9 +1,11 @@
 """GPU parity in the launch regime the benchmark runs: more rays than resident wavefronts.
 
-With at most 1024 rays every wavefront of the matrix-core backward marches one ray and the ray
-groups are visited in order.  Beyond that a wavefront marches several rays in a row (carrying
-the next ray's first samples over the ray boundary, prefetching its features), and beyond
-31 676 rays the ray groups are visited in a scrambled order.  These cases put every backward
+With at most 2048 rays (1024 in the one-wave kernels of the decoder and of HexPlanes) every wavefront of the
+matrix-core backward marches one ray and the ray groups are visited in order.  Beyond that a wavefront marches
+several rays in a row (sampling the next ray's first step before the last one's scatter) or, where the longest
+wave has about as few steps that way, tiles of four neighbouring rays; beyond some 8000 groups (31 676 rays of a
+one-wave kernel, 253 000 in tiles: the full-size cases of test_gpu_parity.py) these are visited in a scrambled
+order.  These cases put every backward
 kernel family into that regime and compare forward outputs and every gradient tensor with the
 CPU oracle, element by element (Section 3.4, Eq. (2)): once with a strided subset of the rays
 and once with a contiguous block of pixels, whose neighbouring rays add into the same
@@ -32,9 +34,8 @@ def _pixel_block(image: int, lo: int, hi: int) -> np.ndarray:
 
 @pytest.mark.parametrize("pick", ["every_16th_ray", "block_of_200x200_pixels"])
 def test_large_config_with_40000_rays(lp, oracle, pick):
-    """Largest configuration (voxel 256^3 x 16, MLP 16-64-64-4, 512 samples per ray), 40 000 rays:
-    10 000 ray groups, about 10 rays per wavefront, scrambled group order, the next step's and the
-    next ray's texel loads issued early."""
+    """Largest configuration (voxel 256^3 x 16, MLP 16-64-64-4, 512 samples per ray), 40 000 rays: every 16th ray,
+    in tiles that are marched ray by ray, or neighbouring rays, about five tiles per wavefront."""
     inp = lp_inputs.make_inputs("large")
     idx = np.arange(0, inp.n_rays, 16) if pick == "every_16th_ray" else _pixel_block(800, 300, 500)
     assert idx.size == 40000
@@ -46,7 +47,7 @@ def test_large_config_with_40000_rays(lp, oracle, pick):
 @pytest.mark.parametrize("pick", ["strided", "block"])
 def test_voxel_config_with_many_rays(lp, oracle, pick):
     """Voxel 64^3 x 32 configuration: 36 864 rays strided over the four views, or a 192 x 192 pixel
-    block of the first view (32 channels: corner carry-over across cells, no cross-step prefetch)."""
+    block of the first view (32 channels: corner carry-over across cells in the walk)."""
     inp = lp_inputs.make_inputs("voxel")
     idx = lp_inputs.strided_ray_subset(inp.n_rays, 36864, offset=3) if pick == "strided" else _pixel_block(256, 32, 224)
     worst = check_case(lp, oracle, inp.subset(idx), lp.LP_MATH_BF16X3, label=f"voxel {pick}")
@@ -65,8 +66,8 @@ def test_batched_config_block_of_each_scene(lp, oracle):
 
 @pytest.mark.parametrize("dims", [(16, 64, 64, 4), (16, 32, 4)])
 def test_triplane_16_channels_with_many_rays(lp, oracle, dims):
-    """16-channel triplane (the tiny configuration's grid kind) with more rays than wavefronts: the
-    features of the next step are sampled before the current step's scatter, without early loads."""
+    """16-channel triplane (the tiny configuration's grid kind) with more rays than wavefronts, in tiles: 6400
+    neighbouring rays are 1600 tiles, one per wavefront."""
     w = lp_inputs.WORKLOADS["single_scene"]
     rays = lp_inputs.make_inputs("single_scene", with_grid=False)
     small = lp_inputs.make_small(TRIPLANE, channels=16, res=(48, 40, 44), mlp_dims=dims, n_rays=8, samples=96,
@@ -82,10 +83,9 @@ def test_triplane_16_channels_with_many_rays(lp, oracle, dims):
 
 
 @pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
-def test_two_wave_backward_with_contract_coordinates_and_many_rays(lp, oracle, dtype):
-    """The two-wave backward's other instantiations (contract coordinates compiled in for fp32 grids, a
-    run-time branch for grids stored in bf16) with several rays per pair of waves: a 16-channel voxel
-    grid, MLP 16-64-64-4, a block of 6 400 neighbouring rays that start inside the unit cube."""
+def test_tiles_with_contract_coordinates_and_many_rays(lp, oracle, dtype):
+    """The tile kernel under contract coordinates (compiled in for fp32 grids, a run-time branch for grids stored in
+    bf16): a 16-channel voxel grid, MLP 16-64-64-4, a block of 6 400 neighbouring rays that start inside the unit cube."""
     import dataclasses
     import torch
     w = lp_inputs.WORKLOADS["single_scene"]
@@ -101,7 +101,7 @@ def test_two_wave_backward_with_contract_coordinates_and_many_rays(lp, oracle, d
     if dtype != "float32":
         stored = [torch.from_numpy(g).to(tdt) for g in inp.grid]
         inp = dataclasses.replace(inp, grid=[t.to(torch.float32).numpy() for t in stored])
-    worst = check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"two-wave contract {dtype}",
+    worst = check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"tiles contract {dtype}",
                        grid_dtype=None if dtype == "float32" else tdt)
     print(summary(worst), flush=True)
 

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CASES = {"fp32": ("float32", 0.0), "fp32 contract": ("float32", 1.3), "bf16 contract": ("bfloat16", 1.3),
          "bf16": ("bfloat16", 0.0), "fp16": ("float16", 0.0)}
-SWITCHES = ["LP_BWD_ONE_WAVE"]
+SWITCHES = ["LP_BWD_ONE_WAVE", "LP_BWD_TWO_WAVE"]
 
 
 def _case(dtype, contract):

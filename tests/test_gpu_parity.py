@@ -87,9 +87,9 @@ def test_config_shapes_ragged(lp, oracle, kind, channels, dims, samples):
 
 
 def test_one_wave_backward_of_the_two_wave_shape():
-    """The shape whose backward runs as a pair of waves per ray (voxel grid, 16 channels, MLP
-    16-64-64-4) also has the one-wave kernel; LP_BWD_ONE_WAVE=1 selects it when the library is loaded,
-    hence the child process.  Same parity bar."""
+    """The shape that also has the older kernels, one and two waves per ray (voxel grid, 16 channels, MLP 16-64-64-4):
+    LP_BWD_ONE_WAVE=1 selects the former when the library is loaded, hence the child process.  Same parity bar,
+    203 rays of two scenes."""
     import os, subprocess, sys
     env = dict(os.environ, LP_BWD_ONE_WAVE="1")
     test = os.path.abspath(__file__) + "::test_config_shapes_ragged[150-0-16-dims0]"

@@ -1,17 +1,18 @@
 """The tile kernels of the Renderer's backward (four neighbouring rays per wavefront, eight samples of each per
 step) where their layout has edges: sample counts around the step widths, a ray count that leaves a partial
 tile, scenes that change inside a tile, neighbouring rays that take the windowed scatter and rays apart
-from each other that are marched one at a time and take the walk.  Every case is checked against the CPU
-oracle at the bounds of `parity.check_case`."""
+from each other that are marched one at a time and take windows or the walk; grids in every storage type.  Every case is
+checked against the CPU oracle at the bounds of `parity.check_case`."""
 import dataclasses
 
 import numpy as np
 import pytest
 
 import lp_inputs
-from lp_inputs import TRIPLANE, VOXEL
+from lp_inputs import HASH, TRIPLANE, VOXEL
 
 from parity import check_case, summary
+from tile_rules import step_routes
 
 pytestmark = pytest.mark.gpu
 
@@ -61,12 +62,39 @@ def test_tiles_of_several_steps(lp, oracle, kind, channels, dims, samples):
     print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"tiles {kind} {dims} S={samples}")), flush=True)
 
 
+STORED = [(VOXEL, 16, (16, 64, 64, 4)), (VOXEL, 32, (32, 32, 32, 4)), (TRIPLANE, 16, (16, 64, 4)), (TRIPLANE, 32, (32, 64, 64, 4)),
+          (HASH, 16, (16, 64, 64, 4)), (HASH, 32, (32, 64, 4))]
+
+
+@pytest.mark.parametrize("kind,channels,dims", STORED)
+@pytest.mark.parametrize("dtype", ["bfloat16", "float16"])
+@pytest.mark.parametrize("contract", [0.0, 1.3])
+def test_tiles_of_grids_in_16_bits(lp, oracle, kind, channels, dims, dtype, contract):
+    """The storage types' own instantiations (the contraction is a branch of theirs) with side-by-side tiles."""
+    import torch
+    inp = lp_inputs.make_small(kind, channels=channels, res=(40, 33, 37), mlp_dims=dims, n_rays=8, samples=33, seed=251,
+                               grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3, hash_size=4096 if kind == HASH else None)
+    inp = _with_camera_rays(inp, 8190, 128, 64)
+    tdt = getattr(torch, dtype)
+    inp = dataclasses.replace(inp, grid=[torch.from_numpy(g).to(tdt).float().numpy() for g in inp.grid], contract_a=contract)
+    if contract:   # (the box holds all of space)
+        inp = dataclasses.replace(inp, aabb_min=(-1.0,) * 3, aabb_max=(1.0,) * 3)
+    routes = step_routes(inp)
+    assert sum(n for (how, _), n in routes.items() if how == "tile") >= 0.9 * sum(routes.values()), routes
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"stored {kind} {dims} {dtype} a={contract}", grid_dtype=tdt)), flush=True)
+
+
 @pytest.mark.parametrize("kind,channels,dims", SHAPES[:4])
-def test_rays_apart_in_tile_order(lp, oracle, kind, channels, dims):
-    """Enough rays for tiles, but in random order: every item is marched ray by ray and scattered by the walk."""
-    inp = lp_inputs.make_small(kind, channels=channels, res=(40, 33, 37), mlp_dims=dims, n_rays=8190, samples=40, seed=227,
-                               grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3)
-    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"apart {kind} {dims}")), flush=True)
+@pytest.mark.parametrize("samples,res,box,scatter", [(40, (40, 33, 37), 2.75, "windows"), (32, (72, 64, 68), 1.0, "walk")])
+def test_rays_apart_in_tile_order(lp, oracle, kind, channels, dims, samples, res, box, scatter):
+    """Enough rays for tiles, but in random order: every item is marched ray by ray.  In cells, their steps are short (whole
+    and halved windows) or long (the walk; samples outside the box keep a few of them in windows)."""
+    inp = lp_inputs.make_small(kind, channels=channels, res=res, mlp_dims=dims, n_rays=8190, samples=samples, seed=227,
+                               grid_std=0.3, aabb_min=(-box,) * 3, aabb_max=(box,) * 3)
+    routes = step_routes(inp)
+    walks = routes["ray", "walk"] / sum(routes.values())
+    assert not any(how == "tile" for how, _ in routes) and (walks == 0.0 if scatter == "windows" else walks > 0.9), routes
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"apart {kind} {dims} {scatter}")), flush=True)
 
 
 @pytest.mark.parametrize("kind,channels,dims", SHAPES[:4])
