@@ -160,8 +160,8 @@ __device__ __forceinline__ void to_operands(const f32x16 (&acc)[MB][NB], Frag (&
         }
 }
 
-// Everything the forward of one 64-sample step produces.  The forward kernel uses z only; the
-// backward keeps the operand fragments (they are the activations, already split).
+// Everything the forward of one step produces for the backward of the one-wave kernels: the operand fragments are the
+// activations, already split.
 template <int C, int H, int NH, int NB>
 struct StepActs {
     static constexpr int KS1 = C / 16, KSH = H / 16;
@@ -324,23 +324,6 @@ __device__ __forceinline__ void mlp_forward(const uint4* lds, int lane, StepActs
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) a.z[k] = (NB == 2 && grp) ? o[NB - 1][k] : o[0][k];
-}
-
-// Sampling + MLP forward of one step: lane (col, grp) samples its half of the channels of
-// sample col of every N block (PERM: of the permuted step, see slot_to_sample).
-template <int KIND, int C, int H, int NH, bool BWD, int NB, bool PERM = false, bool CC = false, int CG = C, int GT = LP_F32>
-__device__ __forceinline__ void forward_step(const GridDev& g, const uint4* lds, const RayGeom& q, int j0, int S,
-                                             int lane, StepActs<C, H, NH, NB>& a)
-{
-    const int col = lane & 31, grp = lane >> 5;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int j = min(j0 + 32 * nb + (PERM ? slot_to_sample(col) : col), S - 1);
-        const Cell3 c = sample_cell_for<CC, GT>(g, q, j);
-        a.cell[nb] = c;
-        sample_features<KIND, C, CG, GT>(g, q, c, grp, a.fh[nb], a.fl[nb]);
-    }
-    mlp_forward<C, H, NH, BWD, NB>(lds, lane, a);
 }
 
 // MLP of one 64-sample step from the input fragments of its two N blocks, keeping nothing but the decoder

@@ -17,11 +17,10 @@ constexpr int kTileSamples = 32 / kTileRays;     // samples of each per step
 
 // What is scattered.
 //   kGradient  a feature gradient per sample
-//   kPush      the Splatter: a vector per sample and the weights themselves, into a structure of one channel; weights
-//              with complements from the fp64 index, as the result is divided by their sums; samples that do not
-//              exist (past a ray's end) push nothing
-//   kPushRay   the same where all samples of a ray push the ray's vector
-enum class Scatter { kGradient, kPush, kPushRay };
+//   kPushRay   the Splatter: one vector for all samples of a ray, and the weights themselves into a structure of one
+//              channel; weights with complements from the fp64 index, as the result is divided by their sums; samples
+//              that do not exist (past a ray's end) push nothing
+enum class Scatter { kGradient, kPushRay };
 
 // ---- a step as a matrix product ----
 // The samples of a step lie in a small window of texels (of each plane).  The window's gradient is
@@ -105,7 +104,7 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
                                                uint32_t area, const Window& win, const Cell3& cell, bool member,
                                                const f32x16& dFt, int lane)
 {
-    constexpr bool kPushes = WHAT != Scatter::kGradient, kFold = WHAT == Scatter::kPushRay;
+    constexpr bool kPushes = WHAT == Scatter::kPushRay;
     const int col = lane & 31, grp = lane >> 5;
     // the table: zeros, then this sample's two entries per axis (lane group 0 the lower, 1 the upper)
     wave_lds_fence();
@@ -217,7 +216,7 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
                 sum += __shfl_xor(sum, 32, 64);
                 if (lane < kLanes && live && sum != 0.0f) atomicAdd(sums[pl] + scene_at + off / C, sum);
             }
-            if constexpr (kFold) {
+            if constexpr (kPushes) {
 #pragma unroll
                 for (int v = 0; v < kVec; ++v) w[v] = (w[4 * v] + w[4 * v + 1]) + (w[4 * v + 2] + w[4 * v + 3]);
             }
@@ -231,8 +230,8 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
             if constexpr (C == 32) {
                 f32x16 acc = zero16();
 #pragma unroll
-                for (int r = 0; r < (kFold ? 4 : 16); ++r)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[r], dFt[kFold ? 4 * r : r], acc, 0, 0, 0);
+                for (int r = 0; r < (kPushes ? 4 : 16); ++r)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[r], dFt[kPushes ? 4 * r : r], acc, 0, 0, 0);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     if (n0 + 8 * q >= n_texels) break;
@@ -243,8 +242,8 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
             } else {
                 f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int k = 0; k < (kFold ? 2 : 8); ++k)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b16[kFold ? 4 * k : k], acc, 0, 0, 0);
+                for (int k = 0; k < (kPushes ? 2 : 8); ++k)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b16[kPushes ? 4 * k : k], acc, 0, 0, 0);
                 const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 16 * (lane >> 4));
 #pragma unroll
                 for (int p = 0; p < 4; ++p) add(o[p], acc[p]);
@@ -260,7 +259,7 @@ template <int KIND, int C, Scatter WHAT>
 __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_grid[3], float* const* sums, int scene, char* area,
                                              const Cell3& cell, bool valid, const f32x16& dFt, int lane, bool tile)
 {
-    constexpr bool kPushes = WHAT != Scatter::kGradient;
+    constexpr bool kPushes = WHAT == Scatter::kPushRay;
     const int col = lane & 31, grp = lane >> 5;
     auto flip = [tile](int c) { return (tile && (c & 8)) ? c ^ 7 : c; };   // column <-> position of the walk
     float* info = reinterpret_cast<float*>(area);
@@ -274,7 +273,7 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
             for (int i = 0; i < (KIND == LP_GRID_TRIPLANE ? 12 : 8); ++i) rec[i] = 0.0f;
         }
     }
-    if (WHAT != Scatter::kPushRay && col < C) {
+    if (!kPushes && col < C) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) grad[flip(d_row(r, grp)) * C + col] = dFt[r];
     }
@@ -283,7 +282,7 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
     [[maybe_unused]] const unsigned there = (unsigned)__ballot(valid);   // a bit per column
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        if constexpr (WHAT == Scatter::kPushRay) v[r] = grp ? dFt[8 + 4 * (r / 8)] : dFt[4 * (r / 8)];   // position 16 grp + r: ray 2 grp + r / 8
+        if constexpr (kPushes) v[r] = grp ? dFt[8 + 4 * (r / 8)] : dFt[4 * (r / 8)];   // position 16 grp + r: ray 2 grp + r / 8
         else v[r] = grad[(16 * grp + r) * C + (col & (C - 1))];
         // what does not exist pushes nothing: weight zero alone would turn an infinite feature into an undefined one
         if constexpr (kPushes) v[r] = ((there >> flip(16 * grp + r)) & 1u) ? v[r] : 0.0f;
@@ -303,12 +302,12 @@ __device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_gr
                                              char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, bool tile,
                                              float* const* sums = nullptr, bool valid = true)
 {
-    constexpr bool kPushes = WHAT != Scatter::kGradient;
+    constexpr bool kPushes = WHAT == Scatter::kPushRay;
     const int col = lane & 31, k = tile ? (col & (kTileSamples - 1)) : col, full = tile ? kTileSamples : 32;
     float probe = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-        if (WHAT != Scatter::kPushRay || r % 4 == 0) probe = fmaf(dFt[r], 0.0f, probe);
+        if (!kPushes || r % 4 == 0) probe = fmaf(dFt[r], 0.0f, probe);
     if constexpr (kPushes) {   // (an undefined ray: its weights)
 #pragma unroll
         for (int a = 0; a < 3; ++a) probe = fmaf(cell.f[a], 0.0f, probe);
