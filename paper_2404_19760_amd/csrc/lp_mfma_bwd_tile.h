@@ -58,8 +58,7 @@ struct TileLds {
     static constexpr int WO_AT = W1_AT + 2 * W1::bytes(H);       // 4 rows hi, 4 rows lo
     static constexpr int BIAS_AT = WO_AT + 8 * kWo;              // b1[H] b2[H] bo[4]
     static constexpr int SMALL_AT = BIAS_AT + (2 * H + 4) * 4;
-    // one wave: output gradients; per ray its origin, direction, near (7 floats), d(loss)/d(T_S) T_S, spacing and optical
-    // depth up to the end of the current step (fp64), and upstream gradients (4 floats)
+    // one wave: output gradients; per ray its geometry (10 floats) and upstream gradients (5 floats)
     static constexpr int kRayBytes = 64;
     static constexpr int RAY = 512;
     static constexpr int kSmall = RAY + kTileRays * kRayBytes;
@@ -255,6 +254,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     int sub = 0, j0 = 0, scene = 0;
     int k = 0;                  // this lane's sample in the step
     bool ray_ok = false;        // the lane's ray exists
+    double tau_end = 0.0;       // optical depth up to the end of the current step (fp64: see Eq. (2) below)
     float carry = 0.0f;         // sum of w_j a_j over all later steps
     Cell3 cell;
     Frag fh[KS1], fl[KS1];
@@ -265,9 +265,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         const uint32_t p = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
         const f32x4 a = lds_get<f32x4>(p), b = lds_get<f32x4>(p + 16);
         RayGeom q;
-        q.ox = a[0]; q.oy = a[1]; q.oz = a[2]; q.dx = a[3]; q.dy = b[0]; q.dz = b[1]; q.near = b[2];
+        q.ox = a[0]; q.oy = a[1]; q.oz = a[2]; q.dx = a[3]; q.dy = b[0]; q.dz = b[1]; q.near = b[2]; q.delta = b[3];
         q.delta64 = lds_get<double>(p + 32);
-        q.delta = (float)q.delta64;
         q.scene = scene;
         q.time = 0.0f;
         return q;
@@ -294,14 +293,15 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         wave_lds_fence();
         if (k == 0 && grp == 0) {
             const uint32_t p = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
-            const f32x4 v[3] = {{q.ox, q.oy, q.oz, q.dx}, {q.dy, q.dz, q.near, kS}, {p0, p1, p2, p_depth}};
+            const f32x4 v[3] = {{q.ox, q.oy, q.oz, q.dx}, {q.dy, q.dz, q.near, q.delta}, {p0, p1, p2, p_depth}};
             lds_put<f32x4>(p, v[0]);
             lds_put<f32x4>(p + 16, v[1]);
             lds_put<double>(p + 32, q.delta64);
-            lds_put<double>(p + 40, (double)tau_S);
+            lds_put<float>(p + 40, kS);
             lds_put<f32x4>(p + 48, v[2]);
         }
         wave_lds_fence();
+        tau_end = (double)tau_S;
         carry = 0.0f;
         const int step = tile ? kTileSamples : 32;
         j0 = ((S - 1) / step) * step;
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         uint32_t zh0, zl0, zh1, zl1;
         {
             const uint32_t geo = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
-            const float near = lds_get<float>(geo + 24), kS = lds_get<float>(geo + 28), delta = (float)lds_get<double>(geo + 32);
+            const float near = lds_get<float>(geo + 24), delta = lds_get<float>(geo + 28), kS = lds_get<float>(geo + 40);
             const f32x4 p = lds_get<f32x4>(geo + 48);
             const float p0 = p[0], p1 = p[1], p2 = p[2], p_depth = p[3];
             const int j = j0 + k;
@@ -493,8 +493,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             const float incl = ray_scan(sd, k, tile);
             // (in fp64: a step of eight samples takes four times the subtractions of one of 32, and in fp32 each of them
             // rounds to the spacing of the whole depth, which at the front of an opaque ray is all of its weight)
-            const double tau64 = lds_get<double>(geo + 40) - (double)__shfl(incl, last, 64);
-            const float tau_start = (float)tau64;
+            tau_end -= (double)__shfl(incl, last, 64);
+            const float tau_start = (float)tau_end;
             const float Tprev = __expf(-(tau_start + (incl - sd)));
             const float w = Tprev * one_minus_exp_neg(sd);
             const float Tq = Tprev - w;
@@ -516,10 +516,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             split2(dz[0], dz[1], zh0, zl0);
             split2(dz[2], dz[3], zh1, zl1);
             lds_put<u32x4>(dz_at + col * 16, u32x4{zh0, zh1, zl0, zl1});   // (both lane groups the same)
-            wave_lds_fence();   // the activations, the output gradients; every lane has read its ray
-            if (k == 0 && grp == 0) lds_put<double>(geo + 40, tau64);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        wave_lds_fence();   // the activations, the output gradients
 
         constexpr int kLast = NH == 2 ? L::B : L::A;   // the last hidden layer's activations
         refresh(own_h); refresh(col_h); refresh(col64_h);

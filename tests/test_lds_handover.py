@@ -72,12 +72,12 @@ def test_step_of_the_tile_backward(hidden_layers):
         (r"lds_tr\(zp ", [("read", "output gradients")]),
         (r"lds_tr\(hp [^;]*?\+ " + area, [("read", "$1")]),
         (r"I(?:H|W1)::read\((?:col_h|col16_h|col_f)\b[^;]*?" + area, [("read", "$1")]),
-        (r"lds_get<double>\(geo \+ 40\)", [("read", "optical depth")]),
-        (r"lds_put<double>\(geo \+ 40,", [("store", "optical depth")]),
-        (r"\bload_rays\(\)", [("fence", None), ("store", "optical depth"), ("fence", None)]),
+        (r"lds_get<\w+>\(geo ", [("read", "rays")]),
+        (r"lds_put<\w+>\(geo ", [("store", "rays")]),
+        (r"\bload_rays\(\)", [("fence", None), ("store", "rays"), ("fence", None)]),
         (r"\bscatter_step<", [("fence", None), ("store", "A"), ("fence", None), ("read", "A")]),
     ], names)
-    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "optical depth"} == {b for w, b in step if w == "store"}
+    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "rays"} == {b for w, b in step if w == "store"}
     _check(step)
 
 
