@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     // the rays being marched: `tile` (four rays, eight samples each per step) or one ray, number `sub` of the item
     bool tile = false;
     int sub = 0, j0 = 0, scene = 0;
-    int k = 0;                  // this lane's sample in the step
+    auto step_sample = [&]() { return (int)lane_id & (tile ? kTileSamples - 1 : 31); };   // this lane's sample in the step
     bool ray_ok = false;        // the lane's ray exists
     double tau_end = 0.0;       // optical depth up to the end of the current step (fp64: see Eq. (2) below)
     float carry = 0.0f;         // sum of w_j a_j over all later steps
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         const long long ray = min(r, rays.M - 1);
         const RayGeom q = load_ray_geom(rays, ray);
         scene = __builtin_amdgcn_readfirstlane(q.scene);
-        k = tile ? (col & 7) : col;
+        const int k = step_sample();
         const float p0 = io.d_rgb[3 * ray + 0], p1 = io.d_rgb[3 * ray + 1], p2 = io.d_rgb[3 * ray + 2];
         const float p_alpha = io.d_alpha ? io.d_alpha[ray] : 0.0f;
         const float p_depth = io.d_depth ? io.d_depth[ray] : 0.0f;
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         refresh(lane_id);
         const int grp = lane_id >> 5;
         const RayGeom q = geometry();
-        cell = sample_cell_for<CC, GT>(g, q, min(j0 + k, S - 1));
+        cell = sample_cell_for<CC, GT>(g, q, min(j0 + step_sample(), S - 1));
         float feat[C / 2];
         gather_stream<KIND, C, C / 2, GT, (C == 32 || KIND == LP_GRID_TRIPLANE)>(g, scene, cell, grp * (C / 2), feat);
 #pragma unroll
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             const float near = lds_get<float>(geo + 24), delta = lds_get<float>(geo + 28), kS = lds_get<float>(geo + 40);
             const f32x4 p = lds_get<f32x4>(geo + 48);
             const float p0 = p[0], p1 = p[1], p2 = p[2], p_depth = p[3];
-            const int j = j0 + k;
+            const int k = step_sample(), j = j0 + k;
             const bool valid = ray_ok && j < S;
             const int last = lane | (tile ? kTileSamples - 1 : 31);
             const float t = near + ((float)j + 0.5f) * delta;
