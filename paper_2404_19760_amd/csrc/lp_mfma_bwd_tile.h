@@ -16,18 +16,21 @@
 // What bounds it and why it is laid out like this (256^3 x 16 voxels, 800^2 rays x 512 samples, and eight
 // 256^2 x 32 triplanes, 4 x 256^2 rays x 192 samples each):
 //   - The grid gradient is bound by the rate of atomic adds (2.1e10 64-byte lines/s on this chip, whatever
-//     the locality). One ray's samples touch 3.2 (voxel) and 9.9 (triplane) lines per sample after run
-//     merging; the union of the texels that four neighbouring rays touch with eight samples each is 0.7 and
-//     3.5 lines per sample.
+//     the locality). One ray's samples touch 3.1 (voxel) and 9.9 (triplane) lines per sample after run
+//     merging; the union of the texels that four neighbouring rays touch with eight samples each is 0.70 and
+//     3.63 lines per sample (counted: 2.31e8 lines in 48.4 ms, 23 % of that rate, and 1.46e9 in 96.3 ms, 73 %).
 //   - A wave does not overlap its own vector and matrix instructions; two waves per SIMD do. The
-//     accumulators of the weight gradients (104 registers for 16-64-64-4: the two thin matrices on 16 x 16
-//     tiles) leave room for two waves only if a step's activations live in LDS instead of registers.
+//     accumulators of the weight gradients (94 registers for 16-64-64-4: the two thin matrices on 16 x 16
+//     and 4 x 4 tiles) leave room for two waves only if a step's activations live in LDS instead of registers.
+//     Per SIMD the voxel kernel issues vector instructions in 50 % of the cycles and keeps the matrix cores busy in
+//     37 %, the triplane kernel 38 % and 45 % (1357 and 1662 vector instructions a step).
 //   - In LDS they are transposed by the reads (lp_tile_lds.h); on the matrix cores the transposition by 0/1
 //     products took 36 of the 168 products of a step and as many permutes. The transposed weights of the
 //     input-gradient chain are column reads of the same images, which halves the LDS that weights take.
 //   - Vector work alternates with products that do not wait for it (weave below).
 //   - Products with four rows (the output layer) carry the hi and the lo halves of the operand in rows
-//     that would be empty, or in empty parts of the K range: 8 + 2 + 8 instructions instead of 12 + 6 + 12.
+//     that would be empty, or in empty parts of the K range: 8 instead of 12 in the forward, 2 instead of 6 in the
+//     input-gradient chain.  The weight gradient takes 24 products of sixteen 4 x 4 blocks instead of 12 of 32 x 32.
 #pragma once
 #include "lp_kernels.h"
 #include "lp_mfma.h"
@@ -67,7 +70,8 @@ struct TileLds {
     static_assert(kTotal <= 160 * 1024, "LDS budget of a gfx950 compute unit");
 };
 
-// 1 / x for x in [1, inf]: the hardware's estimate and one Newton step (within an ulp; inf gives 0)
+// 1 / x for x in [1, inf]: the hardware's estimate and one Newton step; inf gives 0.  Correctly rounded, as the division
+// is, wherever the result is a normal number (measured: every mantissa of four binades); the estimate alone is 0.88 ulp off.
 __device__ __forceinline__ float recip(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x);
@@ -830,8 +834,12 @@ hipError_t launch_bwd_tile(const GridDev& g, const MlpDev& m, const RaysDev& ray
     if (e != hipSuccess) return e;
     const int blocks = (n_cu + 7) / 8 * 8;
     const long long waves = (long long)blocks * kTileWaves;
-    // Tiles or single rays: the longest wave's number of steps decides.  A tile's step is cheaper to scatter
-    // (measured about 1.4 times), but a launch of few rays spreads over more waves ray by ray.
+    // Tiles or single rays: the longest wave's number of steps decides.  A tile's step is cheaper to scatter, but a
+    // launch of few rays spreads over more waves ray by ray.  Neighbouring rays, backward time in single rays over that
+    // in tiles, for 16- and 32-channel voxel grids and triplanes and a hash table at 64 and 256 samples:
+    // 1.03 .. 2.6 where a wave's steps are as many, 0.81 .. 1.65 at 1.33 times as many in tiles (16-channel voxels and the
+    // hash table at 256 samples lose, 32 channels at 64 samples gain most), 0.68 .. 1.4 at 1.6 times.  The line stands
+    // where no structure loses.
     auto rounds = [&](long long items) { return (items + waves - 1) / waves; };
     const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays;
     const long long tile_steps = rounds(n_tiles) * ((rays.S + kTileSamples - 1) / kTileSamples);
