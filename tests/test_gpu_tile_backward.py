@@ -12,7 +12,7 @@ import lp_inputs
 from lp_inputs import HASH, TRIPLANE, VOXEL
 
 from parity import check_case, summary
-from tile_rules import step_routes
+from tile_rules import backward_in_tiles, step_routes
 
 pytestmark = pytest.mark.gpu
 
@@ -108,6 +108,17 @@ def test_split_windows(lp, oracle, kind, channels, dims, res):
                                grid_std=0.3, aabb_min=(-1.5,) * 3, aabb_max=(1.5,) * 3)
     inp = _with_camera_rays(inp, 2048 * 4, 128, 64)
     print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"windows {kind} {dims} res={res}")), flush=True)
+
+
+@pytest.mark.parametrize("n_rays,samples,tiles", [(2049, 64, False), (2600, 64, False), (4103, 64, False), (8197, 8, True), (9300, 8, True)])
+def test_last_partial_round(lp, oracle, n_rays, samples, tiles):
+    """Items beyond whole rounds of the 2048 wavefronts, which are spread over all workgroups: one, two or three to a
+    workgroup, single rays and tiles, the last tile a partial one."""
+    assert backward_in_tiles(n_rays, samples) == tiles
+    inp = lp_inputs.make_small(VOXEL, channels=16, res=(21, 17, 19), mlp_dims=(16, 32, 4), n_rays=8, samples=samples, seed=257,
+                               grid_std=0.3, aabb_min=(-2.75,) * 3, aabb_max=(2.75,) * 3)
+    inp = _with_camera_rays(inp, n_rays, 128, 128)
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"last round M={n_rays} S={samples}")), flush=True)
 
 
 @pytest.mark.parametrize("kind,channels,dims", SHAPES[:4])
