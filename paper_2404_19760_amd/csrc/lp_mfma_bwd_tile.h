@@ -64,7 +64,8 @@ struct TileLds {
     // one wave: output gradients; per ray its geometry (10 floats) and upstream gradients (5 floats)
     static constexpr int kRayBytes = 64;
     static constexpr int RAY = 512;
-    static constexpr int kSmall = RAY + kTileRays * kRayBytes;
+    static constexpr int DEPTH = RAY + kTileRays * kRayBytes;    // per ray, fp64: optical depth up to the end of the current step
+    static constexpr int kSmall = DEPTH + kTileRays * 8;
     static constexpr int kTotal = SMALL_AT + kTileWaves * kSmall;
     static_assert(W2_AT % 4096 == 0 && W1_AT % 1024 == 0 && SMALL_AT % 16 == 0 && kSmall % 16 == 0, "alignment");
     static_assert(kTotal <= 160 * 1024, "LDS budget of a gfx950 compute unit");
@@ -167,7 +168,7 @@ __device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const
 // One launch's work items: consecutive tiles of kTileRays rays (`tiles`) or single rays.  As many rounds as leave no wave of
 // any workgroup without an item hand them out in groups of kTileWaves, the groups in a scrambled order (neighbouring rays
 // add into the same lines; spread over time their adds do not queue up at one L2 channel).  What is left goes to the first
-// `busy` waves of every workgroup: up to four of them have a SIMD each, where a ray takes 0.55 to 0.7 of the time beside
+// `busy` waves of a workgroup, to as many workgroups as that takes: up to four of them have a SIMD each, where a ray takes 0.55 to 0.7 of the time beside
 // another.  (2600 rays in random order x 480 samples, 96^3 x 16 voxels, 16-64-64-4: the last 552 rays on 69 full workgroups 303 us,
 // spread over all 243; 32-64-64-4 on triplanes 128^2 469 -> 400.)
 struct TileSchedule {
@@ -265,7 +266,12 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     int sub = 0, j0 = 0, scene = 0;
     auto step_sample = [&]() { return (int)lane_id & (tile ? kTileSamples - 1 : 31); };   // this lane's sample in the step
     bool ray_ok = false;        // the lane's ray exists
-    double tau_end = 0.0;       // optical depth up to the end of the current step (fp64: see Eq. (2) below)
+    // Optical depth up to the end of the current step (fp64: see Eq. (2) below).  The widest kernels have no registers left
+    // for it: in scratch memory it would be read behind the last step's atomic adds (triplane 128^2 x 32, 16 384 rays x 77
+    // samples: 350 us of backward with the depth in LDS, 366 in registers; 64^3 x 32 voxels under 32-64-4: 9.86 ms a step
+    // in LDS, 9.66 in registers).
+    constexpr bool kDepthInLds = C == 32 && H == 64 && NH == 2;
+    double tau_end = 0.0;
     float carry = 0.0f;         // sum of w_j a_j over all later steps
     Cell3 cell;
     Frag fh[KS1], fl[KS1];
@@ -310,6 +316,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             lds_put<double>(p + 32, q.delta64);
             lds_put<float>(p + 40, kS);
             lds_put<f32x4>(p + 48, v[2]);
+            if constexpr (kDepthInLds) lds_put<double>(dz_at + L::DEPTH + (tile ? (col >> 3) : 0) * 8, (double)tau_S);
         }
         wave_lds_fence();
         tau_end = (double)tau_S;
@@ -504,6 +511,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             const float incl = ray_scan(sd, k, tile);
             // (in fp64: a step of eight samples takes four times the subtractions of one of 32, and in fp32 each of them
             // rounds to the spacing of the whole depth, which at the front of an opaque ray is all of its weight)
+            const uint32_t depth_at = dz_at + L::DEPTH + (tile ? (col >> 3) : 0) * 8;
+            if constexpr (kDepthInLds) tau_end = lds_get<double>(depth_at);
             tau_end -= (double)__shfl(incl, last, 64);
             const float tau_start = (float)tau_end;
             const float Tprev = __expf(-(tau_start + (incl - sd)));
@@ -527,8 +536,10 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             split2(dz[0], dz[1], zh0, zl0);
             split2(dz[2], dz[3], zh1, zl1);
             lds_put<u32x4>(dz_at + col * 16, u32x4{zh0, zh1, zl0, zl1});   // (both lane groups the same)
+            wave_lds_fence();   // the activations, the output gradients; every lane has read its ray's depth
+            if (kDepthInLds && k == 0 && grp == 0) lds_put<double>(depth_at, tau_end);
         }
-        wave_lds_fence();   // the activations, the output gradients
+        __builtin_amdgcn_sched_barrier(0);
 
         constexpr int kLast = NH == 2 ? L::B : L::A;   // the last hidden layer's activations
         refresh(own_h); refresh(col_h); refresh(col64_h);
@@ -856,6 +867,7 @@ hipError_t launch_bwd_tile(const GridDev& g, const MlpDev& m, const RaysDev& ray
     sc.rounds = items / waves;
     const long long tail = items - sc.rounds * waves;
     sc.busy = (int)((tail + blocks - 1) / blocks);
+    if (sc.rounds && sc.busy > kTileWaves / 2) sc.busy = kTileWaves;   // (they share SIMDs anyhow: 5128 tiles, 679 -> 669 us)
     sc.tail_per_xcd = sc.busy ? (int)(((tail + sc.busy - 1) / sc.busy + 7) / 8) : 0;
     // multiplier of the scramble: a prime that does not divide the number of groups, so that
     // group -> group * mul mod n_groups is a bijection

@@ -74,10 +74,12 @@ def test_step_of_the_tile_backward(hidden_layers):
         (r"I(?:H|W1)::read\((?:col_h|col16_h|col_f)\b[^;]*?" + area, [("read", "$1")]),
         (r"lds_get<\w+>\(geo ", [("read", "rays")]),
         (r"lds_put<\w+>\(geo ", [("store", "rays")]),
-        (r"\bload_rays\(\)", [("fence", None), ("store", "rays"), ("fence", None)]),
+        (r"lds_get<double>\(depth_at", [("read", "depths")]),
+        (r"lds_put<double>\(depth_at", [("store", "depths")]),
+        (r"\bload_rays\(\)", [("fence", None), ("store", "rays"), ("store", "depths"), ("fence", None)]),
         (r"\bscatter_step<", [("fence", None), ("store", "A"), ("fence", None), ("read", "A")]),
     ], names)
-    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "rays"} == {b for w, b in step if w == "store"}
+    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "rays", "depths"} == {b for w, b in step if w == "store"}
     _check(step)
 
 
