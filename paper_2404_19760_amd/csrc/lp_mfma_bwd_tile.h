@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         const int col = lane_id & 31, grp = lane_id >> 5;
         const long long first = item_ray();
         if (tiles && sub == 0) {
-            tile = side_by_side(rays, first, col, [&](const RayGeom& q, int j) { return sample_cell_for<CC, GT>(g, q, j); });
+            tile = side_by_side(rays, first, rays.M, col, [&](const RayGeom& q, int j) { return sample_cell_for<CC, GT>(g, q, j); });
         }
         const long long r = first + (tile ? (col >> 3) : sub);
         ray_ok = r < rays.M;

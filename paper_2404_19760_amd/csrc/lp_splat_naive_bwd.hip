@@ -6,11 +6,15 @@
 // per point, so the lanes of a wave are the 16-byte pieces of texels: 64 points publish a normalised weight and a byte
 // offset per corner in LDS, then each load instruction reads 8 (16 channels: 16) whole texels, every lane keeps the
 // sum of what it read over the whole ray, and the corners meet once per ray.
-// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.86 ms with a lane per ray (lp_generic.hip) -> 0.52 ms.
+// Large images are taken in patches of 4 x 4 pixels (lp_splat_patch.h): a texel is read once for the step's 128 points, 0.75
+// reads per point instead of eight, and a matrix product hands it to the rays; then instructions bound it (two waves a SIMD).
+// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.86 ms with a lane per ray (lp_generic.hip), 0.52 ms by texel pieces, 0.35 ms
+// in patches (in patches of 8 x 4 pixels, whose weights leave room for one wave a SIMD, 0.66).
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
 #include "lp_splat_common.h"
+#include "lp_splat_patch.h"
 #include "lp_tile_lds.h"
 
 namespace lp {
@@ -19,7 +23,11 @@ namespace {
 
 constexpr int kWaves = 4;
 constexpr int kPoints = 64;      // points whose records stand in LDS at a time
+constexpr int kPatchRays = 16;   // of a patch: see lp_splat_patch.h
+using Patch = PatchLds<kPatchRays>;
 constexpr int kPointUnit = 32;   // they are read in multiples of this many (the rest: weight zero)
+
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 
 template <int KIND>
 struct PushRecords {
@@ -29,6 +37,10 @@ struct PushRecords {
     static constexpr int kPlane = kPoints * kPoint;
     static constexpr int kBytes = kPlanes * kPlane;
 };
+
+// LDS of a patch's wave: two arrays of a float per slot take the map's place and a little more
+constexpr int kPatchBytes = Patch::MAP + Patch::kSlots * 8;
+static_assert(kPatchBytes >= Patch::kBytes, "the map");
 
 // Weights over the weight sums of the forward (0 where nothing landed, and past the ray's end) and texel
 // offsets of the lane's point.
@@ -83,85 +95,239 @@ __device__ __forceinline__ void publish_normalised(uint32_t at, const GridDev& t
     }
 }
 
+// One ray; `area`: PushRecords<KIND>::kBytes of LDS of the wave.
 template <int KIND, int C, bool CC>
-__global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tgt, RaysDev rays, SplatDev sp)
+__device__ __forceinline__ void ray_gradient(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, long long ray, uint32_t area,
+                                             int lane)
 {
     using Rec = PushRecords<KIND>;
     constexpr int kLanes = C / 4;            // lanes of a texel
     constexpr int kTexels = 64 / kLanes;     // texels of a load
     constexpr int kUnroll = 8;
     static_assert(kPointUnit * Rec::kCorners % (kTexels * kUnroll) == 0, "whole unrolled rounds");
-    __shared__ __align__(16) char records[kWaves][Rec::kBytes];
+    const uint32_t mine = area + (lane / kLanes) * 8;
+    const uint32_t piece = (lane % kLanes) * 16;
+    const int S = rays.S;
+    const RayGeom q = load_ray_geom(rays, ray);
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int j0 = 0; j0 < S; j0 += kPoints) {
+        const int j = j0 + lane;
+        const Cell3 c = sample_cell<CC>(tgt, q, min(j, S - 1));
+        wave_lds_fence();
+        publish_normalised<KIND, C>(area + lane * Rec::kPoint, tgt, sp, q.scene, c, j < S);
+        wave_lds_fence();
+        const int points = min((S - j0 + kPointUnit - 1) / kPointUnit * kPointUnit, kPoints);
+#pragma unroll
+        for (int p = 0; p < Rec::kPlanes; ++p) {
+            const char* G = reinterpret_cast<const char*>(sp.d_theta[p] + scene_texel<KIND>(tgt, p, q.scene) * C);
+            const int end = points * Rec::kPoint, live = (S - j0) * Rec::kPoint;
+            for (int at = 0; at < end; at += kUnroll * kTexels * 8) {
+                u32x2 rec[kUnroll];
+                f32x4 x[kUnroll];
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) rec[u] = lds_get<u32x2>(mine + p * Rec::kPlane + at + u * kTexels * 8);
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) x[u] = *reinterpret_cast<const f32x4*>(G + (rec[u][1] + piece));
+                if (at + kUnroll * kTexels * 8 > live) {   // past the ray's end: nothing, also where the texel is infinite
+#pragma unroll
+                    for (int u = 0; u < kUnroll; ++u)
+                        if (at + (u * kTexels + lane / kLanes) * 8 >= live) x[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] += __uint_as_float(rec[u][0]) * x[u][e];
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int d = kLanes; d < 64; d <<= 1) sum[e] += __shfl_xor(sum[e], d, 64);
+    if (lane < kLanes) {
+        const f32x4 v = {sum[0], sum[1], sum[2], sum[3]};
+        *reinterpret_cast<f32x4*>(sp.d_feats + (size_t)ray * C + 4 * lane) = v;
+    }
+}
+
+// Patches are taken from this many rays on, where points share texels. Time ray by ray over that in patches, 24^3 .. 160^3
+// voxels: 1.3 .. 2.5 at 65 536 rays, 0.7 .. 1.3 at 16 384 (fewer patches than wavefronts), 0.9 .. 1.25 where the points of a
+// ray are 3.6 texels apart.  Looking for an image takes 7 us, 8 % of 1.6e6 points ray by ray.  Triplanes stay ray by ray
+// (0.3 .. 1.4).
+constexpr long long kMinRays = 65536, kMinPoints = 4000000;
+__device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& rays) { return find_row(g, rays, 0.9, 2.0); }
+
+// Rays in their order.  `patches`: the patch kernel has been launched before and takes what it finds to be an image.
+template <int KIND, int C, bool CC>
+__global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tgt, RaysDev rays, SplatDev sp, bool patches)
+{
+    __shared__ __align__(16) char records[kWaves][PushRecords<KIND>::kBytes];
+    if (patches && image_row(tgt, rays) != 0) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)records[wave];
-    const uint32_t mine = area + (lane / kLanes) * 8;
-    const uint32_t piece = (lane % kLanes) * 16;
-
     const RaySchedule sched = ray_schedule(rays.M, kWaves);
-    const int S = rays.S;
-    for (long long ray = sched.first; ray < sched.end; ray += sched.stride) {
-        const RayGeom q = load_ray_geom(rays, ray);
-        float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int j0 = 0; j0 < S; j0 += kPoints) {
-            const int j = j0 + lane;
-            const Cell3 c = sample_cell<CC>(tgt, q, min(j, S - 1));
-            wave_lds_fence();
-            publish_normalised<KIND, C>(area + lane * Rec::kPoint, tgt, sp, q.scene, c, j < S);
-            wave_lds_fence();
-            const int points = min((S - j0 + kPointUnit - 1) / kPointUnit * kPointUnit, kPoints);
+    for (long long ray = sched.first; ray < sched.end; ray += sched.stride) ray_gradient<KIND, C, CC>(tgt, rays, sp, ray, area, lane);
+}
+
+// The gradient of a patch's pixels, d_feat[ray][channel] += weights[texel][ray] / theta_w[texel] x d_theta[texel][channel] in
+// fp32, for points [from, from + len) of a step, plane `pl` (`only`: of one ray).  false: they reach too many texels.
+// A product takes four texels; lane quarter q of a round of 32 texels reads texels 8 q .. 8 q + 7, two neighbouring channels of
+// each (16 channels: one).  `probe` becomes undefined where a gradient that was read is not finite.
+template <int KIND, int C>
+__device__ __forceinline__ bool pull_points(const GridDev& g, const SplatDev& sp, int scene, uint32_t area, const PatchCells& cells,
+                                            int from, int len, int only, int pl, f32x4 (&acc)[C / 16], float& probe, int lane)
+{
+    constexpr int kRounds = Patch::kSlots / 32, kVec = C / 16;
+    const int n_slots = patch_weights<KIND, C, kPatchRays>(area, g, cells, from, len, only, pl, lane);
+    if (n_slots <= 0) return n_slots == 0;
+    const size_t scene_at = scene_texel<KIND>(g, pl, scene);
+    const float* W = sp.theta_w_in[pl] + scene_at;
+    const int i16 = lane & 15, q = lane >> 4;
+    const char* G = reinterpret_cast<const char*>(sp.d_theta[pl] + scene_at * C) + 4 * kVec * i16;
+    // up to a whole round: the last texel again, with weight zero
+    if (lane < 32 && n_slots + lane < Patch::kSlots)
+        lds_put<uint32_t>(area + Patch::OFFSETS + 4 * (n_slots + lane), lds_get<uint32_t>(area + Patch::OFFSETS + 4 * (n_slots - 1)));
+    wave_lds_fence();
+    // all of the step's reads are under way before the first is waited for; the weight sums first
+    float sums[(Patch::kSlots + 63) / 64];
 #pragma unroll
-            for (int p = 0; p < Rec::kPlanes; ++p) {
-                const char* G;
-                if constexpr (KIND == LP_GRID_TRIPLANE)
-                    G = reinterpret_cast<const char*>(sp.d_theta[p] + (size_t)q.scene * tgt.N[p] * tgt.N[(p + 1) % 3] * C);
-                else if constexpr (KIND == LP_GRID_HASH)
-                    G = reinterpret_cast<const char*>(sp.d_theta[0] + (size_t)q.scene * tgt.hash_size * C);
-                else
-                    G = reinterpret_cast<const char*>(sp.d_theta[0] + (size_t)q.scene * tgt.N[0] * tgt.N[1] * tgt.N[2] * C);
-                const int end = points * Rec::kPoint, live = (S - j0) * Rec::kPoint;
-                for (int at = 0; at < end; at += kUnroll * kTexels * 8) {
-                    u32x2 rec[kUnroll];
-                    f32x4 x[kUnroll];
+    for (int n = 0; n < (Patch::kSlots + 63) / 64; ++n) {
+        if (64 * n >= n_slots) break;
+        sums[n] = W[lds_get<uint32_t>(area + Patch::OFFSETS + 4 * min(64 * n + lane, n_slots - 1)) / C];
+    }
+    float x[kRounds][8][kVec];
 #pragma unroll
-                    for (int u = 0; u < kUnroll; ++u) rec[u] = lds_get<u32x2>(mine + p * Rec::kPlane + at + u * kTexels * 8);
+    for (int n = 0; n < kRounds; ++n) {
+        if (32 * n >= n_slots) break;
 #pragma unroll
-                    for (int u = 0; u < kUnroll; ++u) x[u] = *reinterpret_cast<const f32x4*>(G + (rec[u][1] + piece));
-                    if (at + kUnroll * kTexels * 8 > live) {   // past the ray's end: nothing, also where the texel is infinite
+        for (int v = 0; v < 2; ++v) {
+            const u32x4 off = lds_get<u32x4>(area + Patch::OFFSETS + 4 * (32 * n + 8 * q + 4 * v));
 #pragma unroll
-                        for (int u = 0; u < kUnroll; ++u)
-                            if (at + (u * kTexels + lane / kLanes) * 8 >= live) x[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                    }
-#pragma unroll
-                    for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) sum[e] += __uint_as_float(rec[u][0]) * x[u][e];
+            for (int e = 0; e < 4; ++e) {
+                const float* at = reinterpret_cast<const float*>(G + 4u * off[e]);
+                if constexpr (kVec == 2) {
+                    const f32x2 y = *reinterpret_cast<const f32x2*>(at);
+                    x[n][4 * v + e][0] = y[0];
+                    x[n][4 * v + e][kVec - 1] = y[1];
+                } else {
+                    x[n][4 * v + e][0] = *at;
                 }
             }
         }
+    }
+    // 1 / theta_w (0 where nothing landed) behind a power of two that keeps the reciprocal of a tiny sum finite
+    constexpr int SCALE = Patch::MAP, INVERSE = Patch::MAP + Patch::kSlots * 4;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int d = kLanes; d < 64; d <<= 1) sum[e] += __shfl_xor(sum[e], d, 64);
-        if (lane < kLanes) {
-            const f32x4 v = {sum[0], sum[1], sum[2], sum[3]};
-            *reinterpret_cast<f32x4*>(sp.d_feats + (size_t)ray * C + 4 * lane) = v;
+    for (int n = 0; n < (Patch::kSlots + 63) / 64; ++n) {
+        if (64 * n >= n_slots) break;
+        if (64 * n + lane < Patch::kSlots) {
+            const float w = sums[n], scale = w < 0x1p-100f ? 0x1p80f : 1.0f;
+            const bool there = 64 * n + lane < n_slots && w > 0.0f;
+            lds_put<float>(area + SCALE + 4 * (64 * n + lane), there ? scale : 0.0f);
+            lds_put<float>(area + INVERSE + 4 * (64 * n + lane), there ? 1.0f / (w * scale) : 0.0f);
         }
     }
+    wave_lds_fence();
+#pragma unroll
+    for (int n = 0; n < kRounds; ++n) {
+        if (32 * n >= n_slots) break;
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int mine = 32 * n + 8 * q + 4 * v;
+            const f32x4 scale = lds_get<f32x4>(area + SCALE + 4 * mine), inverse = lds_get<f32x4>(area + INVERSE + 4 * mine);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float w = (lds_get<float>(area + min(mine + e, n_slots - 1) * Patch::kRow + 4 * i16) * scale[e]) * inverse[e];
+#pragma unroll
+                for (int h = 0; h < kVec; ++h) {
+                    probe = fmaf(x[n][4 * v + e][h], 0.0f, probe);
+                    acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x[n][4 * v + e][h], acc[h], 0, 0, 0);
+                }
+            }
+        }
+    }
+    return true;
+}
+
+// Images, patch after patch (lp_splat_patch.h).  A patch whose rays are not neighbours or not finite, or that reads a gradient
+// that is not (a product would spread it over all of its rays), is taken ray by ray.
+template <int KIND, int C, bool CC>
+__global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev tgt, RaysDev rays, SplatDev sp)
+{
+    extern __shared__ uint4 lds_raw[];
+    const long long row = image_row(tgt, rays);
+    if (row == 0) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)(reinterpret_cast<char*>(lds_raw) + wave * kPatchBytes);
+    static_assert(PushRecords<KIND>::kBytes <= kPatchBytes, "the records of a ray");
+    constexpr int kPlanes = PushRecords<KIND>::kPlanes;
+    const PatchGrid<kPatchRays> grid(rays.M, row);
+    const int S = rays.S;
+    const RaySchedule sched = ray_schedule(grid.count, kWaves);
+    for (long long patch = sched.first; patch < sched.end; patch += sched.stride) {
+        bool ok;
+        const RayGeom q = load_ray_geom(rays, grid.ray(patch, lane & (kPatchRays - 1), ok));
+        bool whole = patch_holds<KIND, CC>(tgt, q, ok, S);
+        f32x4 acc[C / 16];
+#pragma unroll
+        for (int h = 0; h < C / 16; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (whole) {
+            const int scene = __builtin_amdgcn_readfirstlane(__shfl(q.scene, __builtin_ctzll(__ballot(ok)), 64));
+            float probe = 0.0f;
+            for (int j0 = 0; j0 < S; j0 += kPatchPoints) {
+                const PatchCells cells = patch_cells<CC>(tgt, q, ok, j0, S, S);
+#pragma unroll 1
+                for (int pl = 0; pl < kPlanes; ++pl)
+                    patch_steps<kPatchRays>([&](int from, int len, int only) {
+                        return pull_points<KIND, C>(tgt, sp, scene, area, cells, from, len, only, pl, acc, probe, lane);
+                    });
+            }
+            whole = __ballot(probe != 0.0f) == 0ull;
+        }
+        for (int i = 0; i < kPatchRays; ++i) {
+            if (whole) break;
+            bool there;
+            const long long at = grid.ray(patch, i, there);
+            if (there) ray_gradient<KIND, C, CC>(tgt, rays, sp, at, area, lane);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {   // register r: ray 4 (lane / 16) + r, the lane's channels
+            bool there;
+            const long long at = grid.ray(patch, 4 * (lane >> 4) + r, there);
+            if (!whole || !there) continue;
+            float* out = sp.d_feats + (size_t)at * C + C / 16 * (lane & 15);
+            if constexpr (C == 32) *reinterpret_cast<f32x2*>(out) = f32x2{acc[0][r], acc[C / 16 - 1][r]};
+            else *out = acc[0][r];
+        }
+        wave_lds_fence();
+    }
+}
+
+template <int KIND, int C, bool CC>
+hipError_t launch_t(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu, hipStream_t stream)
+{
+    const bool patches = KIND != LP_GRID_TRIPLANE && rays.M >= kMinRays && rays.M * rays.S >= kMinPoints;
+    if constexpr (KIND != LP_GRID_TRIPLANE) if (patches) {
+        auto kernel = splat_patch_bwd_kernel<KIND, C, CC>;
+        const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWaves * kPatchBytes);
+        if (e != hipSuccess) return e;
+        const long long blocks = (2LL * n_cu + 7) / 8 * 8;   // the LDS of two workgroups fits a compute unit
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kWaves * kPatchBytes, stream, tgt, rays, sp);
+    }
+    long long blocks = 6LL * n_cu;   // the LDS of six workgroups fits a compute unit for every structure
+    const long long need = (rays.M + kWaves - 1) / kWaves;
+    if (blocks > need) blocks = need;
+    blocks = (blocks + 7) / 8 * 8;
+    hipLaunchKernelGGL((splat_naive_bwd_kernel<KIND, C, CC>), dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt, rays, sp, patches);
+    return hipGetLastError();
 }
 
 template <int KIND, int C>
 hipError_t launch(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu, hipStream_t stream)
 {
-    long long blocks = 6LL * n_cu;   // the LDS of six workgroups fits a compute unit for every structure
-    const long long need = (rays.M + kWaves - 1) / kWaves;
-    if (blocks > need) blocks = need;
-    blocks = (blocks + 7) / 8 * 8;
-    if (tgt.contract > 0.0)
-        hipLaunchKernelGGL((splat_naive_bwd_kernel<KIND, C, true>), dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt, rays, sp);
-    else
-        hipLaunchKernelGGL((splat_naive_bwd_kernel<KIND, C, false>), dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt, rays, sp);
-    return hipGetLastError();
+    return tgt.contract > 0.0 ? launch_t<KIND, C, true>(tgt, rays, sp, n_cu, stream) : launch_t<KIND, C, false>(tgt, rays, sp, n_cu, stream);
 }
 
 template <int KIND>

@@ -363,11 +363,12 @@ inline PushOrder push_order(const RaysDev& rays, long long waves, int waves_per_
     return o;
 }
 
-// Whether the four rays from `first` on run side by side: in one scene, and within three cells of the first at both ends.
+// Whether the four rays from `first` on (those below `end`) run side by side: in one scene, and within three cells of the
+// first at both ends.
 template <class CellOf>
-__device__ __forceinline__ bool side_by_side(const RaysDev& rays, long long first, int col, CellOf cell_of)
+__device__ __forceinline__ bool side_by_side(const RaysDev& rays, long long first, long long end, int col, CellOf cell_of)
 {
-    const RayGeom q = load_ray_geom(rays, min(first + col / kTileSamples, rays.M - 1));
+    const RayGeom q = load_ray_geom(rays, min(first + col / kTileSamples, end - 1));
     const Cell3 c0 = cell_of(q, 0), c1 = cell_of(q, rays.S - 1);
     bool apart = q.scene != __builtin_amdgcn_readfirstlane(q.scene);
 #pragma unroll

@@ -18,6 +18,40 @@ def backward_in_tiles(n_rays, samples, n_cu=256):
     return 20 * tile_steps <= 21 * (rounds(n_rays) * -(-samples // 32))
 
 
+def image_row(inp, pixel, step):
+    """Length of an image's row that the Splatter's patch kernels find in a list of rays (lp_splat_patch.h find_row), 0: none."""
+    end = (inp.origins + inp.far[:, None] * inp.dirs).astype(np.float32)
+    d2 = lambda a, b: ((a - b) ** 2).sum(-1)
+    along, ahead = d2(end[0], end[1]), end[1] - end[0]
+    if not d2(end[1] + ahead, end[2]) < 0.25 * along:
+        return 0
+    k = np.arange(8, min(4096, (inp.n_rays - 1) // 2) + 1)
+    back = d2(end[k], end[0])
+    k = k[(back < 16 * along) & (back < 0.25 * d2(end[k - 1], end[0])) & (d2(end[k + 1], end[k] + ahead) < 0.25 * along) &
+          (d2(end[2 * k], end[k] + (end[k] - end[0])) < 0.25 * back)]
+    if not len(k):
+        return 0
+    row = int(k[0])
+    down = end[row] - end[0]
+    if not d2(end[row + row // 2], end[row // 2] + down) < 0.25 * d2(down, 0):
+        return 0
+    at = min(inp.n_rays // row - 1, row // 2) * row + row // 2
+
+    def texel(r, t):
+        x = inp.origins[r].astype(np.float64) + t * inp.dirs[r]
+        if inp.contract_a:
+            a, m = inp.contract_a, np.maximum(np.abs(x), 1.0)
+            x = np.where(np.abs(x) <= 1.0, 0.5 * a * x, 0.5 * np.sign(x) * ((2.0 - a) * (1.0 - 1.0 / m) + a))
+        lo, hi, n = (np.asarray(v, dtype=np.float64) for v in (inp.aabb_min, inp.aabb_max, inp.res))
+        return np.clip((x - lo) * (n - 1) / (hi - lo), 0, n - 1)
+
+    near, far = float(inp.near[at]), float(inp.far[at])
+    t = 0.5 * (near + far)
+    apart = lambda a, b: np.sqrt(((a - b) ** 2).sum())
+    close = apart(texel(at, t), texel(at + 1, t)) <= pixel and apart(texel(at, t), texel(at, t + (far - near) / inp.samples)) <= step
+    return row if close else 0
+
+
 def cells(inp):
     """[rays][samples][3] cell indices."""
     delta = (inp.far.astype(np.float64) - inp.near) / inp.samples
