@@ -10,14 +10,20 @@ constexpr int kBwdNB = 1;               // N blocks (of 32 samples) per backward
 constexpr int kBwdStep = 32 * kBwdNB;   // samples per step
 constexpr int kBwdKS = 2 * kBwdNB;      // K-steps of a contraction over the samples of a step
 
-// sum of the 8 bf16 values of a fragment, added to acc
-__device__ __forceinline__ float frag_sum(const Frag& f, float acc)
+// sum of the 2 bf16 values of a dword, added to acc
+__device__ __forceinline__ float pair_sum(uint32_t pair, float acc)
 {
     bf16x2 one;
     one[0] = (__bf16)1.0f;
     one[1] = (__bf16)1.0f;
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), one, acc, false);
+}
+
+// sum of the 8 bf16 values of a fragment, added to acc
+__device__ __forceinline__ float frag_sum(const Frag& f, float acc)
+{
 #pragma unroll
-    for (int d = 0; d < 4; ++d) acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, f.d[d]), one, acc, false);
+    for (int d = 0; d < 4; ++d) acc = pair_sum(f.d[d], acc);
     return acc;
 }
 

@@ -1,21 +1,23 @@
 // Splatter forward with an MLP on the matrix cores (Section 3.3 "Splatter": each point of a
 // pixel's ray pushes g_s(pixel feature, prior structure sampled at the point, encoded
-// direction) into the target structure), wavefront per ray.
+// direction) into the target structure).
 //
-// A step is 32 points.  The MLP runs transposed like the Renderer's (hidden layers D = W X with
-// the points along N).  The pixel feature and the direction encoding are the same for every
-// point of a ray, so their part of the first layer, W1[:, per-ray inputs] x, is evaluated once per
-// ray and joins the bias; a step's first layer then contracts the prior's channels (gathered
-// per point) only.  The last layer is taken
+// A step is 32 points: a tile of four neighbouring rays, eight points of each, or 32 points of one ray.  The MLP runs
+// transposed like the Renderer's (hidden layers D = W X with the points along N).  The pixel feature and the direction encoding
+// are the same for every point of a ray, so their part of the first layer, W1[:, per-ray inputs] x, is evaluated once per
+// item, for the four rays side by side, and is the accumulator that a step's first layer starts from; it then contracts the
+// prior's channels (gathered per point) only.  The last layer is taken
 // with the roles swapped, V = H^T Wout^T (points along M, channels along N), which leaves lane =
-// channel and registers = 16 consecutive points: the layout the run-merging scatter of the
-// Renderer's backward works on, so the push shares that code.  Contract coordinates are a
+// channel and registers = points: the layout that the scatter of a tile works on (lp_tile_scatter.h).  Contract coordinates are a
 // run-time branch in the point placement (uniform over the launch).
+// What bounds it: the atomic adds.  160^3 x 32 voxels, prior alike, MLP 67-64-64-32, 4 x 64^2 rays x 160 points: ray by ray
+// 9.6 lines per point, 1.41 ms at 86 % of the rate of the adds; in tiles 5.25 lines, 0.76 ms at 86 %.
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
 #include "lp_mfma_bwd_common.h"
 #include "lp_splat_common.h"
+#include "lp_tile_scatter.h"
 
 namespace lp {
 
@@ -36,10 +38,10 @@ struct SplatLds {
     static constexpr int A3 = A2 + (NH == 2 ? MB * KSH * 128 : 0);  // Wout as B operand [1][KSH]
     static constexpr int BIAS = A3 + KSH * 128;                     // floats b1[64] b2[64] bout[32]
     static constexpr int WAVE = BIAS + (2 * kHidden + 32) / 4;      // per-wave areas
-    // a wave's area: 32 scatter records of 16 dwords, the ray's first-layer bias, its 48 inputs
-    static constexpr int W_INFO = 0, W_BIAS = 128, W_X = W_BIAS + kHidden / 4, W_UNITS = W_X + 48 / 4;
+    // a wave's area: the scatter's, and its four rays' 48 inputs
+    static constexpr int W_X = kWinBytes / 16, W_UNITS = W_X + kTileRays * 48 / 4;
     static constexpr int UNITS = WAVE + kWaves * W_UNITS;
-    static_assert(UNITS * 16 <= 64 * 1024, "static LDS of a workgroup");
+    static_assert(2 * UNITS * 16 <= 160 * 1024, "two workgroups fit the LDS of a compute unit");
 };
 
 template <int KSP, int KSE, int NH, int CO>
@@ -70,13 +72,12 @@ __device__ __forceinline__ void stage_splat_mlp(uint4* lds, const MlpDev& m, int
 }
 
 template <int KIND, int KSP, int KSE, int NH>
-__global__ __launch_bounds__(kWaves * 64) void splat_mfma_kernel(GridDev tgt, MlpDev m, RaysDev rays, SplatDev sp,
-                                                                 long long group_mul)
+__global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt, MlpDev m, RaysDev rays, SplatDev sp, PushOrder order)
 {
     constexpr int CO = 16 * KSP;  // the target has the prior's channel count
     using L = SplatLds<KSP, KSE, NH>;
     constexpr int MB = L::MB, KSH = L::KSH;
-    __shared__ uint4 lds[L::UNITS];
+    extern __shared__ uint4 lds[];
     stage_splat_mlp<KSP, KSE, NH, CO>(lds, m, sp.n_in);
     __syncthreads();
 
@@ -84,96 +85,97 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_kernel(GridDev tgt, Ml
     const int col = lane & 31, grp = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint4* wave_area = lds + L::WAVE + wave * L::W_UNITS;
-    float* info = reinterpret_cast<float*>(wave_area + L::W_INFO);
-    float* ray_bias = reinterpret_cast<float*>(wave_area + L::W_BIAS);
-    float* ray_x = reinterpret_cast<float*>(wave_area + L::W_X);
+    char* const area_ptr = reinterpret_cast<char*>(wave_area);
+    const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)area_ptr;
+    float* ray_x = reinterpret_cast<float*>(wave_area + L::W_X);   // [4][48]
     const float* sbias = reinterpret_cast<const float*>(lds + L::BIAS);
     const float bias_out = sbias[2 * kHidden + col];
     const int n_in = sp.n_in, n_extra = sp.n_in + m.n_enc;
 
-    const long long n_groups = (rays.M + kWaves - 1) / kWaves;
-    const RaySchedule sched = ray_schedule(n_groups * kWaves, kWaves);
+    const int rays_per_item = order.tiles ? kTileRays : 1;
+    const RaySchedule sched = ray_schedule(order.n_groups * kWaves, kWaves);
     const int S = rays.S;
     for (long long seq = sched.first; seq < sched.end; seq += sched.stride) {
-        const long long ray = ((seq / kWaves) * group_mul % n_groups) * kWaves + seq % kWaves;
-        if (ray >= rays.M) continue;
-        const RayGeom q = load_ray_geom(rays, ray);
-        // ---- the ray's inputs x (pixel feature, direction encoding, zeros), one per lane, and its
-        //      first-layer bias b1 + W1[:, per-ray inputs] x ----
-        {
-            const float d[3] = {q.dx, q.dy, q.dz};
-            const float x_lane = lane < n_in ? sp.feats[(size_t)ray * n_in + lane]
-                                             : lane < n_extra ? dir_encoding(d, lane - n_in) : 0.0f;
-            wave_lds_fence();
-            if (lane < 48) ray_x[lane] = x_lane;
-            wave_lds_fence();
-            f32x16 acc[MB][1];
-            init_bias<MB, 1>(acc, sbias, grp);
-            Frag eh[1][KSE], el[1][KSE];
-#pragma unroll
-            for (int s = 0; s < KSE; ++s) {
-                float x[8];
-                *reinterpret_cast<f32x4*>(x) = *reinterpret_cast<const f32x4*>(ray_x + 16 * s + 8 * grp);
-                *reinterpret_cast<f32x4*>(x + 4) = *reinterpret_cast<const f32x4*>(ray_x + 16 * s + 8 * grp + 4);
-                split8(x, eh[0][s], el[0][s]);
-            }
-            layer_mfma<MB, KSE, 1>(acc, lds + L::A1E, lane, eh, el);
-            if (col == 0) {  // every column holds the same values
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) ray_bias[32 * mb + d_row(r, grp)] = acc[mb][0][r];
-            }
-            wave_lds_fence();
-        }
-        for (int j0 = 0; j0 < S; j0 += kBwdStep) {
-            const int j = j0 + slot_to_sample(col);
-            const int jj = min(j, S - 1);
-            Frag fh[1][KSP], fl[1][KSP];
+        const long long first = (((seq / kWaves) * order.group_mul % order.n_groups) * kWaves + seq % kWaves) * rays_per_item;
+        if (first >= rays.M) continue;
+        const long long end = min(first + rays_per_item, rays.M);
+        const bool tile = order.tiles && side_by_side<kPushApart>(rays, first, end, col, [&](const RayGeom& r, int j) { return sample_cell_any(tgt, r, j); });
+        const int n_sub = tile ? 1 : (int)(end - first);
+        for (int sub = 0; sub < n_sub; ++sub) {
+            const long long ray = first + (tile ? col / kTileSamples : sub);
+            const bool ray_ok = ray < end;
+            const RayGeom q = load_ray_geom(rays, min(ray, end - 1));
+            const int scene = __builtin_amdgcn_readfirstlane(q.scene);
+            // ---- the rays' inputs x (pixel feature, direction encoding, zeros), one per lane, and the first layer's
+            //      accumulators b1 + W1[:, per-ray inputs] x of the rays' columns ----
+            f32x16 start[MB][1];
             {
-                const Cell3 cp = sample_cell_any(sp.prior, q, jj);
+                wave_lds_fence();
 #pragma unroll
-                for (int s = 0; s < KSP; ++s) {
-                    float feat[8];
-                    gather_half<KIND, CO, 8, LP_F32>(sp.prior, q.scene, cp, 16 * s + 8 * grp, feat);
-                    split8(feat, fh[0][s], fl[0][s]);
+                for (int i = 0; i < kTileRays; ++i) {
+                    if (i > 0 && !tile) break;
+                    const long long at = min(first + (tile ? i : sub), end - 1);
+                    const float d[3] = {rays.dirs[3 * at], rays.dirs[3 * at + 1], rays.dirs[3 * at + 2]};
+                    const float x_lane = lane < n_in ? sp.feats[(size_t)at * n_in + lane]
+                                                     : lane < n_extra ? dir_encoding(d, lane - n_in) : 0.0f;
+                    if (lane < 48) ray_x[48 * i + lane] = x_lane;
                 }
-            }
-            const Cell3 ct = sample_cell_any(tgt, q, jj);
-            wave_lds_fence();
-            if (grp == 0) {
-                float* rec = info + col * 16;
-                write_scatter_record<KIND, CO, true>(rec, tgt, ct);
-                if (j >= S) {  // a point past the end of the ray pushes nothing
+                wave_lds_fence();
+                init_bias<MB, 1>(start, sbias, grp);
+                const float* mine = ray_x + (tile ? 48 * (col / kTileSamples) : 0);
+                Frag eh[1][KSE], el[1][KSE];
 #pragma unroll
-                    for (int k = 0; k < (KIND == LP_GRID_VOXEL ? 8 : 12); ++k) rec[k] = 0.0f;
+                for (int s = 0; s < KSE; ++s) {
+                    float x[8];
+                    *reinterpret_cast<f32x4*>(x) = *reinterpret_cast<const f32x4*>(mine + 16 * s + 8 * grp);
+                    *reinterpret_cast<f32x4*>(x + 4) = *reinterpret_cast<const f32x4*>(mine + 16 * s + 8 * grp + 4);
+                    split8(x, eh[0][s], el[0][s]);
                 }
+                layer_mfma<MB, KSE, 1>(start, lds + L::A1E, lane, eh, el);
             }
-            Frag lh[1][KSH], ll[1][KSH];
-            {
-                f32x16 acc[MB][1];
-                init_bias<MB, 1>(acc, ray_bias, grp);
-                layer_mfma<MB, KSP, 1>(acc, lds + L::A1P, lane, fh, fl);
-                to_operands<MB, true, 1>(acc, lh, ll);
-                if constexpr (NH == 2) {
-                    init_bias<MB, 1>(acc, sbias + kHidden, grp);
-                    layer_mfma<MB, KSH, 1>(acc, lds + L::A2, lane, lh, ll);
+            const int step = tile ? kTileSamples : 32, k = tile ? col % kTileSamples : col;
+            for (int j0 = 0; j0 < S; j0 += step) {
+                const int j = j0 + k, jj = min(j, S - 1);
+                Frag fh[1][KSP], fl[1][KSP];
+                {
+                    const Cell3 cp = sample_cell_any(sp.prior, q, jj);
+#pragma unroll
+                    for (int s = 0; s < KSP; ++s) {
+                        float feat[8];
+                        gather_half<KIND, CO, 8, LP_F32>(sp.prior, scene, cp, 16 * s + 8 * grp, feat);
+                        split8(feat, fh[0][s], fl[0][s]);
+                        __builtin_amdgcn_sched_barrier(0);   // one K-step's loads at a time
+                    }
+                }
+                Frag lh[1][KSH], ll[1][KSH];
+                {
+                    f32x16 acc[MB][1];
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) acc[mb][0] = start[mb][0];
+                    layer_mfma<MB, KSP, 1>(acc, lds + L::A1P, lane, fh, fl);
                     to_operands<MB, true, 1>(acc, lh, ll);
+                    if constexpr (NH == 2) {
+                        init_bias<MB, 1>(acc, sbias + kHidden, grp);
+                        layer_mfma<MB, KSH, 1>(acc, lds + L::A2, lane, lh, ll);
+                        to_operands<MB, true, 1>(acc, lh, ll);
+                    }
                 }
-            }
-            // V[point][channel]: the hidden activations are the A operand as they stand
-            f32x16 v;
+                __builtin_amdgcn_sched_barrier(0);
+                // V[point][channel]: the hidden activations are the A operand as they stand
+                f32x16 v;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) v[r] = bias_out;
+                for (int r = 0; r < 16; ++r) v[r] = bias_out;
 #pragma unroll
-            for (int s = 0; s < KSH; ++s) {
-                Frag wh, wl;
-                load_operand(lds + L::A3 + s * 128, lane, wh, wl);
-                v = mfma3(lh[0][s], ll[0][s], wh, wl, v);
+                for (int s = 0; s < KSH; ++s) {
+                    Frag wh, wl;
+                    load_operand(lds + L::A3 + s * 128, lane, wh, wl);
+                    v = mfma3(lh[0][s], ll[0][s], wh, wl, v);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
+                refresh(lane_here);
+                scatter_step<KIND, CO, Scatter::kPushPoints, RayWindows::kWhole>(tgt, sp.theta, scene, area, area_ptr, sample_cell_any(tgt, q, jj), v, lane_here, tile, sp.theta_w, ray_ok && j < S);
             }
-            wave_lds_fence();
-            scatter_channels<KIND, CO>(tgt, sp.theta, q.scene, info, v, col, grp);
-            scatter_weights<KIND, CO>(tgt, sp.theta_w, q.scene, info, col, grp);
         }
     }
 }
@@ -182,12 +184,14 @@ template <int KIND, int KSP, int KSE, int NH>
 hipError_t launch(const GridDev& tgt, const MlpDev& m, const RaysDev& rays, const SplatDev& sp, int n_cu,
                   hipStream_t stream)
 {
-    long long blocks = 2LL * n_cu;
-    const long long need = (rays.M + kWaves - 1) / kWaves;
-    if (blocks > need) blocks = need;
-    blocks = (blocks + 7) / 8 * 8;
-    hipLaunchKernelGGL((splat_mfma_kernel<KIND, KSP, KSE, NH>), dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream,
-                       tgt, m, rays, sp, splat_group_multiplier(need));
+    constexpr int kLdsBytes = SplatLds<KSP, KSE, NH>::UNITS * 16;
+    auto kernel = splat_mfma_kernel<KIND, KSP, KSE, NH>;
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (e != hipSuccess) return e;
+    long long blocks = (2LL * n_cu + 7) / 8 * 8;
+    const PushOrder order = push_order(rays, blocks * kWaves, kWaves);
+    if (blocks > order.n_groups) blocks = (order.n_groups + 7) / 8 * 8;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, order);
     return hipGetLastError();
 }
 

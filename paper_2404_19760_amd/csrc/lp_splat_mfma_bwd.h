@@ -1,5 +1,6 @@
 // Splatter backward with an MLP on the matrix cores (Section 3.3 "Splatter" and Section 3.4:
-// nothing of the forward is stored, every point's MLP forward is recomputed), wavefront per ray.
+// nothing of the forward is stored, every point's MLP forward is recomputed).  A step is 32 points: a tile of four neighbouring
+// rays, eight points of each, or 32 points of one ray.
 //
 // The gradient that reaches a point's pushed vector is the normalised output gradient read at
 // the point: sum over the cell's corners of weight * d_theta / theta_w.  From there the step is
@@ -8,12 +9,18 @@
 // cores with 0/1 selection matrices), accumulators parked in the accumulation registers for the
 // whole kernel and written as one record of partial sums per wave.  The gradient of the MLP's
 // inputs is taken with the operands swapped (lane = input, register = point): the prior's
-// channels go through the run-merging scatter into the prior's gradient.
+// channels go through the scatter of a tile into the prior's gradient (lp_tile_scatter.h).
 //
 // The pixel feature and the direction encoding are the same for every point of a ray, so their
 // part of the first layer is taken once per ray: W1[:, per-ray inputs] x joins the bias before
-// the ray's steps, and after them the sum s of dZ1 over the ray's points gives both the weight
-// gradient s x^T (one rank-one matrix-core update per block) and the input gradient W1^T s.
+// the steps, and after them the sum s of dZ1 over the ray's points gives both the weight
+// gradient s x^T (one matrix-core update per block, the rays of a tile along K) and the input gradient W1^T s.
+//
+// What bounds it: one wave per SIMD (the accumulators fill its registers) that waits for its own loads and LDS reads half of
+// the time; the matrix cores are busy 21 %.  160^3 x 32 voxels, prior alike, MLP 67-64-64-32, 4 x 64^2 rays x 160 points: ray by
+// ray 6.8 lines of atomic adds per point, 1.48 ms; in tiles 4.6 lines, 1.38; with all texel loads of a gather under way at once
+// 1.36.  160^2 triplanes forward and backward 4.57 -> 2.29.  Tiles only where a wave has no more steps that way: at twice as
+// many (1600 rays x 160 points) 0.53 to 0.97 times as fast as ray by ray.
 //
 // This header holds the kernel and its launcher templates; two translation units instantiate
 // them (the instantiations for 32-channel triplanes are built without the build flag that keeps
@@ -24,6 +31,7 @@
 #include "lp_mfma_mlp.h"
 #include "lp_mfma_bwd_common.h"
 #include "lp_splat_common.h"
+#include "lp_tile_scatter.h"
 
 namespace lp {
 
@@ -53,10 +61,10 @@ struct SplatBwdLds {
     static constexpr int T1E = lds_place(T1P + KSH * 128, NBE * KSH * 128);  // W1^T, per-ray rows [NBE][KSH]
     static constexpr int SEL = lds_place(T1E + NBE * KSH * 128, 4 * 64);     // 4 selection operands, 64 lanes each
     static constexpr int BIAS = lds_place(SEL + 4 * 64, 2 * kHidden / 4);    // floats b1[64] b2[64]
-    // a wave's area: 32 scatter records of 16 dwords, the ray's first-layer bias, the ray's sum of dZ1
-    // and its 48 per-ray inputs
-    static constexpr int W_INFO = 0, W_BIAS = 128, W_SUM = W_BIAS + kHidden / 4, W_X = W_SUM + kHidden / 4,
-                         W_UNITS = W_X + 48 / 4;
+    // a wave's area: the scatter's, then per ray of a tile the first-layer bias, the sum of dZ1, the 48 per-ray inputs and its
+    // geometry
+    static constexpr int W_BIAS = kWinBytes / 16, W_SUM = W_BIAS + kTileRays * kHidden / 4, W_X = W_SUM + kTileRays * kHidden / 4,
+                         W_GEO = W_X + kTileRays * 48 / 4, W_UNITS = W_GEO + kTileRays * 3;
     static constexpr int WAVE = lds_place(BIAS + 2 * kHidden / 4, kWaves * W_UNITS);  // per-wave areas
     static constexpr int UNITS = WAVE + kWaves * W_UNITS;
     static_assert(T2 + HH <= 4096, "the regions up to W2^T lie below the 64 KiB line");
@@ -156,28 +164,29 @@ __device__ __forceinline__ void gather_normalised(const GridDev& tgt, const Spla
     GridDev dth = tgt;
 #pragma unroll
     for (int p = 0; p < 3; ++p) dth.data[p] = sp.d_theta[p];
+    GatherRaw<KIND, 8, LP_F32> raw[C / 16];   // all loads are under way before the first is waited for
+#pragma unroll
+    for (int s = 0; s < C / 16; ++s) gather_issue<KIND, C, 8, LP_F32>(dth, scene, c, 16 * s + 8 * grp, raw[s]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < C / 16; ++s) {
-        GatherRaw<KIND, 8, LP_F32> raw;
-        gather_issue<KIND, C, 8, LP_F32>(dth, scene, c, 16 * s + 8 * grp, raw);
         float v[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int d = 0; d < NC; ++d)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 float x[4];
-                unpack_values<LP_F32>(raw.v[d][i], x);
+                unpack_values<LP_F32>(raw[s].v[d][i], x);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[4 * i + e] += wn[d] * x[e];
             }
         split8(v, gh[0][s], gl[0][s]);
-        __builtin_amdgcn_sched_barrier(0);  // one K-step's loads at a time
     }
 }
 
 template <int KIND, int KSP, int KSE, int NH>
 __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt, MlpDev m, RaysDev rays,
-                                                                     SplatDev sp, BwdIo io, long long group_mul)
+                                                                     SplatDev sp, BwdIo io, PushOrder order)
 {
     using L = SplatBwdLds<KSP, KSE, NH>;
     constexpr int MB = L::MB, KSH = L::KSH, NBE = L::NBE;
@@ -197,10 +206,12 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
     const uint4* lds_upper = lds + upper_units;
     auto block = [&](int unit) { return unit < 4096 ? lds + unit : lds_upper + (unit - 4096); };
     uint4* wave_area = const_cast<uint4*>(block(L::WAVE)) + wave * L::W_UNITS;
-    float* info = reinterpret_cast<float*>(wave_area + L::W_INFO);
-    float* ray_bias = reinterpret_cast<float*>(wave_area + L::W_BIAS);
-    float* ray_sum = reinterpret_cast<float*>(wave_area + L::W_SUM);
-    float* ray_x = reinterpret_cast<float*>(wave_area + L::W_X);
+    char* const area_ptr = reinterpret_cast<char*>(wave_area);
+    const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)area_ptr;
+    float* ray_bias = reinterpret_cast<float*>(wave_area + L::W_BIAS);   // [4][64]
+    float* ray_sum = reinterpret_cast<float*>(wave_area + L::W_SUM);     // [4][64]
+    float* ray_x = reinterpret_cast<float*>(wave_area + L::W_X);         // [4][48]
+    const uint32_t geo_at = area + 16 * L::W_GEO;
     const float* sbias = reinterpret_cast<const float*>(block(L::BIAS));
     const int n_in = sp.n_in, n_extra = sp.n_in + m.n_enc;
 
@@ -253,71 +264,112 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) db1[mb] = db2[mb] = 0.0f;
 
-    const long long n_groups = (rays.M + kWaves - 1) / kWaves;
-    const RaySchedule sched = ray_schedule(n_groups * kWaves, kWaves);
+    const int rays_per_item = order.tiles ? kTileRays : 1;
+    const RaySchedule sched = ray_schedule(order.n_groups * kWaves, kWaves);
     const int S = rays.S;
     for (long long seq = sched.first; seq < sched.end; seq += sched.stride) {
-        const long long ray = ((seq / kWaves) * group_mul % n_groups) * kWaves + seq % kWaves;
-        if (ray >= rays.M) continue;
-        const RayGeom q = load_ray_geom(rays, ray);
-        // ---- the ray's inputs x (pixel feature, direction encoding, zeros), one per lane, and its
-        //      first-layer bias b1 + W1[:, per-ray inputs] x ----
-        {
-            const float d[3] = {q.dx, q.dy, q.dz};
-            const float x_lane = lane < n_in ? sp.feats[(size_t)ray * n_in + lane]
-                                             : lane < n_extra ? dir_encoding(d, lane - n_in) : 0.0f;
+        const long long first = (((seq / kWaves) * order.group_mul % order.n_groups) * kWaves + seq % kWaves) * rays_per_item;
+        if (first >= rays.M) continue;
+        const long long end = min(first + rays_per_item, rays.M);
+        const bool tile = order.tiles && side_by_side<kPushApart>(rays, first, end, col, [&](const RayGeom& r, int j) { return sample_cell_any(sp.prior, r, j); });
+        const int n_sub = tile ? 1 : (int)(end - first);
+        for (int sub = 0; sub < n_sub; ++sub) {
+        const long long ray = first + (tile ? col / kTileSamples : sub);
+        const bool ray_ok = ray < end;
+        const int my_ray = tile ? col / kTileSamples : 0;   // of the item, that the lane's column belongs to
+        int scene;
+        {   // the rays' geometry is kept in LDS between its uses
+            const RayGeom q = load_ray_geom(rays, min(ray, end - 1));
+            scene = __builtin_amdgcn_readfirstlane(q.scene);
             wave_lds_fence();
-            if (lane < 48) ray_x[lane] = x_lane;
+            if (grp == 0 && (tile ? col % kTileSamples : col) == 0) {
+                lds_put<f32x4>(geo_at + 48 * my_ray, f32x4{q.ox, q.oy, q.oz, q.dx});
+                lds_put<f32x4>(geo_at + 48 * my_ray + 16, f32x4{q.dy, q.dz, q.near, q.delta});
+                lds_put<double>(geo_at + 48 * my_ray + 32, q.delta64);
+            }
+            wave_lds_fence();
+        }
+        auto geometry = [&]() {
+            uint32_t at = geo_at + 48 * my_ray;
+            refresh(at);   // (or what is derived from it is kept through the step)
+            const f32x4 a = lds_get<f32x4>(at), b = lds_get<f32x4>(at + 16);
+            RayGeom q;
+            q.ox = a[0]; q.oy = a[1]; q.oz = a[2]; q.dx = a[3]; q.dy = b[0]; q.dz = b[1]; q.near = b[2]; q.delta = b[3];
+            q.delta64 = lds_get<double>(at + 32);
+            q.scene = scene;
+            q.time = 0.0f;
+            return q;
+        };
+        // ---- the rays' inputs x (pixel feature, direction encoding, zeros), one per lane, and their
+        //      first-layer biases b1 + W1[:, per-ray inputs] x ----
+        {
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < kTileRays; ++i) {
+                const long long at = min(first + (tile ? i : sub), end - 1);
+                const float d[3] = {rays.dirs[3 * at], rays.dirs[3 * at + 1], rays.dirs[3 * at + 2]};
+                const float x_lane = lane < n_in ? sp.feats[(size_t)at * n_in + lane]
+                                                 : lane < n_extra ? dir_encoding(d, lane - n_in) : 0.0f;
+                if (lane < 48) ray_x[48 * i + lane] = x_lane;
+                if (!tile) break;
+            }
             wave_lds_fence();
             f32x16 acc[MB][1];
             init_bias<MB, 1>(acc, sbias, grp);
             Frag eh[1][KSE], el[1][KSE];
+            const float* mine = ray_x + 48 * my_ray;
 #pragma unroll
             for (int s = 0; s < KSE; ++s) {
                 float x[8];
-                *reinterpret_cast<f32x4*>(x) = *reinterpret_cast<const f32x4*>(ray_x + 16 * s + 8 * grp);
-                *reinterpret_cast<f32x4*>(x + 4) = *reinterpret_cast<const f32x4*>(ray_x + 16 * s + 8 * grp + 4);
+                *reinterpret_cast<f32x4*>(x) = *reinterpret_cast<const f32x4*>(mine + 16 * s + 8 * grp);
+                *reinterpret_cast<f32x4*>(x + 4) = *reinterpret_cast<const f32x4*>(mine + 16 * s + 8 * grp + 4);
                 split8(x, eh[0][s], el[0][s]);
             }
             layer_mfma<MB, KSE, 1>(acc, block(L::A1E), lane, eh, el);
             wave_lds_fence();
-            if (col == 0) {  // every column holds the same values
+            if (col % kTileSamples == 0) {  // the columns of a ray hold the same values
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) ray_bias[32 * mb + d_row(r, grp)] = acc[mb][0][r];
+                    for (int r = 0; r < 16; ++r) ray_bias[kHidden * (col / kTileSamples) + 32 * mb + d_row(r, grp)] = acc[mb][0][r];
             }
             wave_lds_fence();
         }
-        float dbr[MB];   // dZ1 summed over this lane group's points of the ray, hidden unit 32 mb + col
+        // dZ1 summed over this lane group's points of the columns 8 i .. 8 i + 7 (ray i of a tile), hidden unit 32 mb + col
+        float dbr[MB][kTileRays];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) dbr[mb] = 0.0f;
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < kTileRays; ++i) dbr[mb][i] = 0.0f;
         __builtin_amdgcn_sched_barrier(0);
 
-        for (int j0 = 0; j0 < S; j0 += kBwdStep) {
-            const int j = j0 + slot_to_sample(col);
-            const bool valid = j < S;
+        const int step = tile ? kTileSamples : kBwdStep, k = tile ? col % kTileSamples : col;
+        for (int j0 = 0; j0 < S; j0 += step) {
+            const int j = j0 + k;
+            const bool valid = ray_ok && j < S;
             const int jj = min(j, S - 1);
             Frag fh[1][KSP], fl[1][KSP];
-            const Cell3 cp = sample_cell_any(sp.prior, q, jj);
+            {
+                const Cell3 cp = sample_cell_any(sp.prior, geometry(), jj);
+                GatherRaw<KIND, 8, LP_F32> raw[KSP];
 #pragma unroll
-            for (int s = 0; s < KSP; ++s) {
-                float feat[8];
-                gather_half<KIND, CP, 8, LP_F32>(sp.prior, q.scene, cp, 16 * s + 8 * grp, feat);
-                split8(feat, fh[0][s], fl[0][s]);
-                // one K-step's loads at a time: issued together they would need a register each
+                for (int s = 0; s < KSP; ++s) gather_issue<KIND, CP, 8, LP_F32>(sp.prior, scene, cp, 16 * s + 8 * grp, raw[s]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < KSP; ++s) {
+                    float feat[8];
+                    gather_finish<KIND, 8, LP_F32>(cp, raw[s], feat);
+                    split8(feat, fh[0][s], fl[0][s]);
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
             Frag gv_h[1][KSP], gv_l[1][KSP];
-            gather_normalised<KIND, CP>(tgt, sp, q.scene, sample_cell_any(tgt, q, jj), grp, valid, gv_h, gv_l);
-            // scatter record of this lane's point in the prior, read at the end of the step
-            wave_lds_fence();
-            if (grp == 0) write_scatter_record<KIND, CP>(info + col * 16, sp.prior, cp);
+            gather_normalised<KIND, CP>(tgt, sp, scene, sample_cell_any(tgt, geometry(), jj), grp, valid, gv_h, gv_l);
 
             // ---- forward of the hidden layers ----
             Frag h1h[1][KSH], h1l[1][KSH], h2h[1][KSH], h2l[1][KSH];
             f32x16 acc[MB][1];
-            init_bias<MB, 1>(acc, ray_bias, grp);
+            init_bias<MB, 1>(acc, ray_bias + kHidden * my_ray, grp);
             layer_mfma<MB, KSP, 1>(acc, block(L::A1P), lane, fh, fl);
             to_operands<MB, true, 1>(acc, h1h, h1l);
             if constexpr (NH == 2) {
@@ -383,7 +435,13 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
                     Frag ah[kBwdKS], al[kBwdKS];
                     transpose_hidden(gz_h, gz_l, mb, ah, al);
 #pragma unroll
-                    for (int ks = 0; ks < kBwdKS; ++ks) dbr[mb] = frag_sum(al[ks], frag_sum(ah[ks], dbr[mb]));
+                    for (int ks = 0; ks < kBwdKS; ++ks)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {   // half a fragment: four points of column group 2 ks + h
+                            float& sum = dbr[mb][2 * ks + h];
+                            sum = pair_sum(al[ks].d[2 * h], pair_sum(al[ks].d[2 * h + 1], sum));
+                            sum = pair_sum(ah[ks].d[2 * h], pair_sum(ah[ks].d[2 * h + 1], sum));
+                        }
                     mfma6_parked(dW1p[mb], ah, al, bh, bl);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -398,40 +456,55 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
             }
             __builtin_amdgcn_sched_barrier(0);
             wave_lds_fence();
-            scatter_channels<KIND, CP>(sp.prior, io.d_grid, q.scene, info, dXp, col, grp);
+            uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
+            refresh(lane_here);
+            scatter_step<KIND, CP, Scatter::kGradient, RayWindows::kWhole>(sp.prior, io.d_grid, scene, area, area_ptr, sample_cell_any(sp.prior, geometry(), jj), dXp, lane_here, tile);
         }
 
-        // ---- per-ray inputs: with s = sum of dZ1 over the ray, dW1 += s x^T and dx = W1^T s ----
-        float sz[MB];
+        // ---- per-ray inputs: with s = sum of dZ1 over a ray, dW1 += s x^T and dx = W1^T s ----
+        float sz[MB][kTileRays];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            db1[mb] += dbr[mb];
-            sz[mb] = dbr[mb] + __shfl_xor(dbr[mb], 32, 64);
+            const float all = (dbr[mb][0] + dbr[mb][1]) + (dbr[mb][2] + dbr[mb][3]);
+            db1[mb] += all;
+#pragma unroll
+            for (int i = 0; i < kTileRays; ++i) {   // a single ray: all columns are its
+                const float mine = tile ? dbr[mb][i] : i == 0 ? all : 0.0f;
+                sz[mb][i] = mine + __shfl_xor(mine, 32, 64);
+            }
         }
         wave_lds_fence();
         if (grp == 0) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) ray_sum[32 * mb + col] = sz[mb];
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < kTileRays; ++i) ray_sum[kHidden * i + 32 * mb + col] = sz[mb][i];
         }
-        // rank-one updates: the only non-zero K index is 0 (element 0 of lane group 0)
+        // a product over the rays: K indices 0 .. 3 (elements 0 .. 3 of lane group 0)
 #pragma unroll
         for (int be = 0; be < NBE; ++be) {
             Frag bh, bl;
             {
-                uint32_t h, l;
-                split2(32 * be + col < 48 ? ray_x[32 * be + col] : 0.0f, 0.0f, h, l);
-                bh.d[0] = grp == 0 ? h : 0u; bl.d[0] = grp == 0 ? l : 0u;
 #pragma unroll
-                for (int w = 1; w < 4; ++w) bh.d[w] = bl.d[w] = 0u;
+                for (int w = 0; w < 2; ++w) {
+                    const bool there = 32 * be + col < 48, both = there && tile;   // (a single ray: only x of ray 0 stands there)
+                    uint32_t h, l;
+                    split2((w == 0 ? there : both) ? ray_x[48 * 2 * w + 32 * be + col] : 0.0f,
+                           both ? ray_x[48 * (2 * w + 1) + 32 * be + col] : 0.0f, h, l);
+                    bh.d[w] = grp == 0 ? h : 0u; bl.d[w] = grp == 0 ? l : 0u;
+                    bh.d[2 + w] = bl.d[2 + w] = 0u;
+                }
             }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 Frag ah, al;
-                uint32_t h, l;
-                split2(sz[mb], 0.0f, h, l);
-                ah.d[0] = grp == 0 ? h : 0u; al.d[0] = grp == 0 ? l : 0u;
 #pragma unroll
-                for (int w = 1; w < 4; ++w) ah.d[w] = al.d[w] = 0u;
+                for (int w = 0; w < 2; ++w) {
+                    uint32_t h, l;
+                    split2(sz[mb][2 * w], sz[mb][2 * w + 1], h, l);
+                    ah.d[w] = grp == 0 ? h : 0u; al.d[w] = grp == 0 ? l : 0u;
+                    ah.d[2 + w] = al.d[2 + w] = 0u;
+                }
                 dW1e[mb][be] = mfma3(ah, al, bh, bl, dW1e[mb][be]);
                 park(dW1e[mb][be]);
                 __builtin_amdgcn_sched_barrier(0);
@@ -439,13 +512,13 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
         }
         wave_lds_fence();
         {
-            // s as an operand over the hidden units, the same in every row
+            // s as an operand over the hidden units, row i = ray i / 8
             Frag zh[KSH], zl[KSH];
 #pragma unroll
             for (int s = 0; s < KSH; ++s) {
                 float v[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = ray_sum[k_hidden(s, grp, e)];
+                for (int e = 0; e < 8; ++e) v[e] = ray_sum[kHidden * (col / kTileSamples) + k_hidden(s, grp, e)];
                 split8(v, zh[s], zl[s]);
             }
 #pragma unroll
@@ -458,10 +531,17 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
                     dx = s == 0 ? mfma3_first(zh[s], zl[s], th, tl) : mfma3(zh[s], zl[s], th, tl, dx);
                 }
                 const int k = 32 * be + col;
-                if (grp == 0 && k < n_in) sp.d_feats[(size_t)ray * n_in + k] = dx[0];
+                if (grp == 0 && k < n_in) {   // register 4 i of lane group 0: row 8 i
+#pragma unroll
+                    for (int i = 0; i < kTileRays; ++i) {
+                        const long long at = first + (tile ? i : sub);
+                        if ((tile || i == 0) && at < end) sp.d_feats[(size_t)at * n_in + k] = dx[4 * i];
+                    }
+                }
             }
         }
         __builtin_amdgcn_sched_barrier(0);
+        }
     }
 
     // ---- this wave's record of partial sums ----
@@ -515,9 +595,8 @@ hipError_t launch(const GridDev& tgt, const MlpDev& m, const RaysDev& rays, cons
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
     const int blocks = mfma_bwd_records(n_cu) / kWaves;  // every wave writes a record, busy or not
-    const long long n_groups = (rays.M + kWaves - 1) / kWaves;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, io,
-                       splat_group_multiplier(n_groups));
+                       push_order(rays, (long long)blocks * kWaves, kWaves, 1.05));
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_params_kernel, dim3((m.param_total + 63) / 64), dim3(kReduceThreads), 0, stream,

@@ -20,7 +20,8 @@ constexpr int kTileSamples = 32 / kTileRays;     // samples of each per step
 //   kPushRay   the Splatter: one vector for all samples of a ray, and the weights themselves into a structure of one
 //              channel; weights with complements from the fp64 index, as the result is divided by their sums; samples
 //              that do not exist (past a ray's end) push nothing
-enum class Scatter { kGradient, kPushRay };
+//   kPushPoints  the Splatter with an MLP: the same with a vector per sample
+enum class Scatter { kGradient, kPushRay, kPushPoints };
 
 // ---- a step as a matrix product ----
 // The samples of a step lie in a small window of texels (of each plane).  The window's gradient is
@@ -46,6 +47,12 @@ static_assert(kWinBytes <= 8192 && kWinBytes % 16 == 0 && kWinOffsets % 16 == 0,
 struct Window {
     int lo[3], ext[3];   // uniform: first texel and number of texels along each axis
 };
+
+// Windows for the steps of a single ray: the naive Splatter's take the walk (without neighbours there is little to merge); those of
+// the Splatter with an MLP a window if the whole step fits one (384 and 1600 rays over structures of 24 texels an axis, push: 1.1
+// to 2 times as fast as the walk; split windows over 160 an axis 0.9 to 1.05 times, their prior's gradient 0.89 to 0.99); the
+// Renderer's also several.
+enum class RayWindows { kNone, kWhole, kSplit };
 
 // v of another lane of the row of 16 (a permutation: every lane has a source)
 template <int CTRL>
@@ -104,7 +111,7 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
                                                uint32_t area, const Window& win, const Cell3& cell, bool member,
                                                const f32x16& dFt, int lane)
 {
-    constexpr bool kPushes = WHAT == Scatter::kPushRay;
+    constexpr bool kPushes = WHAT != Scatter::kGradient, kOfRay = WHAT == Scatter::kPushRay;
     const int col = lane & 31, grp = lane >> 5;
     // the table: zeros, then this sample's two entries per axis (lane group 0 the lower, 1 the upper)
     wave_lds_fence();
@@ -216,7 +223,7 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
                 sum += __shfl_xor(sum, 32, 64);
                 if (lane < kLanes && live && sum != 0.0f) atomicAdd(sums[pl] + scene_at + off / C, sum);
             }
-            if constexpr (kPushes) {
+            if constexpr (kOfRay) {
 #pragma unroll
                 for (int v = 0; v < kVec; ++v) w[v] = (w[4 * v] + w[4 * v + 1]) + (w[4 * v + 2] + w[4 * v + 3]);
             }
@@ -230,8 +237,8 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
             if constexpr (C == 32) {
                 f32x16 acc = zero16();
 #pragma unroll
-                for (int r = 0; r < (kPushes ? 4 : 16); ++r)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[r], dFt[kPushes ? 4 * r : r], acc, 0, 0, 0);
+                for (int r = 0; r < (kOfRay ? 4 : 16); ++r)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[r], dFt[kOfRay ? 4 * r : r], acc, 0, 0, 0);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     if (n0 + 8 * q >= n_texels) break;
@@ -242,8 +249,8 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
             } else {
                 f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int k = 0; k < (kPushes ? 2 : 8); ++k)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b16[kPushes ? 4 * k : k], acc, 0, 0, 0);
+                for (int k = 0; k < (kOfRay ? 2 : 8); ++k)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b16[kOfRay ? 4 * k : k], acc, 0, 0, 0);
                 const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 16 * (lane >> 4));
 #pragma unroll
                 for (int p = 0; p < 4; ++p) add(o[p], acc[p]);
@@ -259,7 +266,7 @@ template <int KIND, int C, Scatter WHAT>
 __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_grid[3], float* const* sums, int scene, char* area,
                                              const Cell3& cell, bool valid, const f32x16& dFt, int lane, bool tile)
 {
-    constexpr bool kPushes = WHAT == Scatter::kPushRay;
+    constexpr bool kPushes = WHAT != Scatter::kGradient, kOfRay = WHAT == Scatter::kPushRay;
     const int col = lane & 31, grp = lane >> 5;
     auto flip = [tile](int c) { return (tile && (c & 8)) ? c ^ 7 : c; };   // column <-> position of the walk
     float* info = reinterpret_cast<float*>(area);
@@ -273,7 +280,7 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
             for (int i = 0; i < (KIND == LP_GRID_TRIPLANE ? 12 : 8); ++i) rec[i] = 0.0f;
         }
     }
-    if (!kPushes && col < C) {
+    if (!kOfRay && col < C) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) grad[flip(d_row(r, grp)) * C + col] = dFt[r];
     }
@@ -282,7 +289,7 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
     [[maybe_unused]] const unsigned there = (unsigned)__ballot(valid);   // a bit per column
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        if constexpr (kPushes) v[r] = grp ? dFt[8 + 4 * (r / 8)] : dFt[4 * (r / 8)];   // position 16 grp + r: ray 2 grp + r / 8
+        if constexpr (kOfRay) v[r] = grp ? dFt[8 + 4 * (r / 8)] : dFt[4 * (r / 8)];   // position 16 grp + r: ray 2 grp + r / 8
         else v[r] = grad[(16 * grp + r) * C + (col & (C - 1))];
         // what does not exist pushes nothing: weight zero alone would turn an infinite feature into an undefined one
         if constexpr (kPushes) v[r] = ((there >> flip(16 * grp + r)) & 1u) ? v[r] : 0.0f;
@@ -296,27 +303,27 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
 // runs of consecutive samples (of every ray of the tile) with a window each: rays that leave the unit cube of contract
 // coordinates between two samples, mostly.  The products would spread an infinite or
 // undefined gradient over its window, so a step that holds one takes the walk, which keeps it to the sample's own corners.
-// The Splatter's steps of a single ray take the walk: without neighbours there is little to merge across rays.
-template <int KIND, int C, Scatter WHAT = Scatter::kGradient>
+// Steps of a single ray: see RayWindows.
+template <int KIND, int C, Scatter WHAT = Scatter::kGradient, RayWindows RAYS = WHAT == Scatter::kGradient ? RayWindows::kSplit : RayWindows::kNone>
 __device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
                                              char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, bool tile,
                                              float* const* sums = nullptr, bool valid = true)
 {
-    constexpr bool kPushes = WHAT == Scatter::kPushRay;
+    constexpr bool kPushes = WHAT != Scatter::kGradient, kOfRay = WHAT == Scatter::kPushRay;
     const int col = lane & 31, k = tile ? (col & (kTileSamples - 1)) : col, full = tile ? kTileSamples : 32;
     float probe = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-        if (!kPushes || r % 4 == 0) probe = fmaf(dFt[r], 0.0f, probe);
+        if (!kOfRay || r % 4 == 0) probe = fmaf(dFt[r], 0.0f, probe);
     if constexpr (kPushes) {   // (an undefined ray: its weights)
 #pragma unroll
         for (int a = 0; a < 3; ++a) probe = fmaf(cell.f[a], 0.0f, probe);
     }
-    const bool finite = __ballot(probe != 0.0f) == 0ull && (!kPushes || tile);
+    const bool finite = __ballot(probe != 0.0f) == 0ull && (RAYS != RayWindows::kNone || tile);
     int len = full;
     Window win = find_window(cell, true);
     bool fits = finite && window_fits<KIND>(win);
-    while (!fits && finite && len > full / 4) {
+    while (!fits && finite && len > full / 4 && (RAYS == RayWindows::kSplit || tile)) {
         len >>= 1;
         fits = true;
         for (int p = full - len; p >= 0 && fits; p -= len) {
@@ -349,23 +356,27 @@ struct PushOrder {
 // 32-channel voxel grids, a triplane and a hash table at 64 and 160 samples: 2.0 .. 4.7 where the steps are as many,
 // 1.7 .. 4.4 at 1.33 times as many, 1.08 .. 3.5 at twice, 0.95 .. 2.8 at four times (160^3 x 32 voxels, whose adds bind
 // either way, at 1.0).
-inline PushOrder push_order(const RaysDev& rays, long long waves, int waves_per_group)
+inline PushOrder push_order(const RaysDev& rays, long long waves, int waves_per_group, double tiles_up_to = 2.0)
 {
     auto rounds = [&](long long items) { return (items + waves - 1) / waves; };
     const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays;
     const long long tile_steps = rounds(n_tiles) * ((rays.S + kTileSamples - 1) / kTileSamples);
     const long long ray_steps = rounds(rays.M) * ((rays.S + 31) / 32);
     PushOrder o;
-    o.tiles = tile_steps <= 2 * ray_steps;
+    o.tiles = (double)tile_steps <= tiles_up_to * (double)ray_steps;
     const long long items = o.tiles ? n_tiles : rays.M;
     o.n_groups = (items + waves_per_group - 1) / waves_per_group;
     o.group_mul = splat_group_multiplier(o.n_groups);
     return o;
 }
 
-// Whether the four rays from `first` on (those below `end`) run side by side: in one scene, and within three cells of the
+// Splatter with an MLP: cells between the rays of a tile.  (64^2 pixels over 160^3 voxels, 1.3 voxels from pixel to pixel: push
+// 1.09 ms with 3, where most rays go one by one, 0.79 with 6, 0.76 with 9.)
+constexpr int kPushApart = 9;
+
+// Whether the four rays from `first` on (those below `end`) run side by side: in one scene, and within APART cells of the
 // first at both ends.
-template <class CellOf>
+template <int APART = 3, class CellOf>
 __device__ __forceinline__ bool side_by_side(const RaysDev& rays, long long first, long long end, int col, CellOf cell_of)
 {
     const RayGeom q = load_ray_geom(rays, min(first + col / kTileSamples, end - 1));
@@ -373,8 +384,8 @@ __device__ __forceinline__ bool side_by_side(const RaysDev& rays, long long firs
     bool apart = q.scene != __builtin_amdgcn_readfirstlane(q.scene);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
-        apart = apart || abs(c0.i[a] - __builtin_amdgcn_readfirstlane(c0.i[a])) > 3 ||
-                abs(c1.i[a] - __builtin_amdgcn_readfirstlane(c1.i[a])) > 3;
+        apart = apart || abs(c0.i[a] - __builtin_amdgcn_readfirstlane(c0.i[a])) > APART ||
+                abs(c1.i[a] - __builtin_amdgcn_readfirstlane(c1.i[a])) > APART;
     return __ballot(apart) == 0ull;
 }
 

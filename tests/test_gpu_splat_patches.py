@@ -21,7 +21,7 @@ def oracle():
     return o
 
 
-def _image(kind, channels, width, height, samples, res, views=1, cut=0, per_scene=None, contract=0.0, far=4.0):
+def _image(kind, channels, width, height, samples, res, views=1, cut=0, per_scene=None, contract=0.0, far=4.0, **mlp):
     """`views` images of width x height pixels, the last `cut` rays left out; `per_scene`: rays of a scene in turn."""
     f = (max(width, height) / 2.0) / np.tan(np.radians(30.0))
     u, v = (np.arange(width) + 0.5 - width / 2.0) / f, (np.arange(height) + 0.5 - height / 2.0) / f
@@ -40,7 +40,7 @@ def _image(kind, channels, width, height, samples, res, views=1, cut=0, per_scen
     kw = dict(hash_size=4096) if kind == HASH else {}
     box = 1.0 if contract else 2.75
     sp = lp_inputs.make_splat_small(kind, channels=channels, res=res, n_rays=n, samples=samples, seed=401 + samples + width,
-                                    n_scenes=2 if per_scene else 1, aabb_min=(-box,) * 3, aabb_max=(box,) * 3, **kw)
+                                    n_scenes=2 if per_scene else 1, aabb_min=(-box,) * 3, aabb_max=(box,) * 3, **kw, **mlp)
     scene = (np.arange(n) // per_scene % 2).astype(np.int32) if per_scene else None
     return dataclasses.replace(sp, origins=o, dirs=d, near=full(1.0), far=full(far), scene=scene, contract_a=contract)
 
