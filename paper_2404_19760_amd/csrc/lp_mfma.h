@@ -218,9 +218,18 @@ __device__ __forceinline__ float fast_softplus(float z)
     return fmaxf(z, 0.0f) + __logf(1.0f + __expf(-fabsf(z)));
 }
 
+// 1 / x for x in [1, inf]: the hardware's estimate and one Newton step; inf gives 0.  Correctly rounded, as the division
+// is, wherever the result is a normal number (measured: every mantissa of four binades); the estimate alone is 0.88 ulp off.
+__device__ __forceinline__ float recip(float x)
+{
+    const float r = __builtin_amdgcn_rcpf(x);
+    const float e = fmaf(-x, r, 1.0f);
+    return x < 3.0e38f ? fmaf(e, r, r) : r;
+}
+
 __device__ __forceinline__ float fast_logistic(float z)
 {
-    return __frcp_rn(1.0f + __expf(-z));
+    return recip(1.0f + __expf(-z));
 }
 
 // Rendered feature from its decoder output: logistic sigmoid, or the output itself (`identity`, a
@@ -280,16 +289,16 @@ __device__ __forceinline__ void gather_issue(const GridDev& g, int scene, const 
 {
     constexpr int kVecs = GatherRaw<KIND, NCH, GT>::kVecs;
     constexpr unsigned kElem = GT == LP_F32 ? 4u : 2u;  // bytes per stored value
+    // a uniform pointer per corner and one byte offset per lane (below 4 GiB): no address arithmetic per load
     if constexpr (KIND == LP_GRID_VOXEL) {
         const char* V = reinterpret_cast<const char*>(g.data[0]) + (size_t)scene * g.N[0] * g.N[1] * g.N[2] * C * kElem;
-        const unsigned sz = C, sy = (unsigned)g.N[2] * C, sx = (unsigned)g.N[1] * sy;
-        const unsigned base = (unsigned)c.i[0] * sx + (unsigned)c.i[1] * sy + (unsigned)c.i[2] * sz + ch0;
+        const size_t sz = C * kElem, sy = g.N[2] * sz, sx = g.N[1] * sy;
+        const unsigned off = ((((unsigned)c.i[0] * (unsigned)g.N[1] + (unsigned)c.i[1]) * (unsigned)g.N[2] + (unsigned)c.i[2]) * C + ch0) * kElem;
 #pragma unroll
         for (int d = 0; d < 8; ++d) {
-            const int dx = d >> 2, dy = (d >> 1) & 1, dz = d & 1;
-            const uint4* p = reinterpret_cast<const uint4*>(V + (size_t)(base + dx * sx + dy * sy + dz * sz) * kElem);
+            const char* p = V + (d >> 2) * sx + ((d >> 1) & 1) * sy + (d & 1) * sz;
 #pragma unroll
-            for (int i = 0; i < kVecs; ++i) raw.v[d][i] = p[i];
+            for (int i = 0; i < kVecs; ++i) raw.v[d][i] = *reinterpret_cast<const uint4*>(p + off + 16 * i);
         }
     } else if constexpr (KIND == LP_GRID_HASH) {
         const char* V = reinterpret_cast<const char*>(g.data[0]) + (size_t)scene * g.hash_size * C * kElem;
@@ -297,23 +306,21 @@ __device__ __forceinline__ void gather_issue(const GridDev& g, int scene, const 
         hash_corner_slots(c, g.hash_size, slot);
 #pragma unroll
         for (int d = 0; d < 8; ++d) {
-            const uint4* p = reinterpret_cast<const uint4*>(V + ((size_t)slot[d] * C + ch0) * kElem);
+            const unsigned off = (slot[d] * C + ch0) * kElem;
 #pragma unroll
-            for (int i = 0; i < kVecs; ++i) raw.v[d][i] = p[i];
+            for (int i = 0; i < kVecs; ++i) raw.v[d][i] = *reinterpret_cast<const uint4*>(V + off + 16 * i);
         }
     } else {
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) {
             const int a = pl, b = (pl + 1) % 3;
             const char* P = reinterpret_cast<const char*>(g.data[pl]) + (size_t)scene * g.N[a] * g.N[b] * C * kElem;
-            const unsigned sb = C, sa = (unsigned)g.N[b] * C;
-            const unsigned base = (unsigned)c.i[a] * sa + (unsigned)c.i[b] * sb + ch0;
+            const unsigned off = (((unsigned)c.i[a] * (unsigned)g.N[b] + (unsigned)c.i[b]) * C + ch0) * kElem;
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                const int da = d >> 1, db = d & 1;
-                const uint4* p = reinterpret_cast<const uint4*>(P + (size_t)(base + da * sa + db * sb) * kElem);
+                const char* p = P + ((size_t)(d >> 1) * g.N[b] + (d & 1)) * C * kElem;
 #pragma unroll
-                for (int i = 0; i < kVecs; ++i) raw.v[4 * pl + d][i] = p[i];
+                for (int i = 0; i < kVecs; ++i) raw.v[4 * pl + d][i] = *reinterpret_cast<const uint4*>(p + off + 16 * i);
             }
         }
     }

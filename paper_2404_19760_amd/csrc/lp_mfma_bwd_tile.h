@@ -71,15 +71,6 @@ struct TileLds {
     static_assert(kTotal <= 160 * 1024, "LDS budget of a gfx950 compute unit");
 };
 
-// 1 / x for x in [1, inf]: the hardware's estimate and one Newton step; inf gives 0.  Correctly rounded, as the division
-// is, wherever the result is a normal number (measured: every mantissa of four binades); the estimate alone is 0.88 ulp off.
-__device__ __forceinline__ float recip(float x)
-{
-    const float r = __builtin_amdgcn_rcpf(x);
-    const float e = fmaf(-x, r, 1.0f);
-    return x < 3.0e38f ? fmaf(e, r, r) : r;
-}
-
 // Inclusive prefix sum over the samples of a ray: segments of 8 lanes (`tile`) or of 32.  k = position in
 // the segment.
 __device__ __forceinline__ float ray_scan(float v, int k, bool tile)
@@ -112,17 +103,17 @@ __device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const
     for (int gr = 0; gr < kGroups; ++gr) {
         uint4 raw[4][kVecs];
         float w[4];
+        // (a uniform pointer per corner and one byte offset per lane, below 4 GiB: no address arithmetic per load)
         if constexpr (KIND == LP_GRID_TRIPLANE) {
             const int a = gr, b = (gr + 1) % 3;
             const char* P = reinterpret_cast<const char*>(g.data[gr]) + (size_t)scene * g.N[a] * g.N[b] * C * kElem;
-            const unsigned sa = (unsigned)g.N[b] * C;
-            const unsigned base = (unsigned)c.i[a] * sa + (unsigned)c.i[b] * C + ch0;
+            const unsigned off = (((unsigned)c.i[a] * (unsigned)g.N[b] + (unsigned)c.i[b]) * C + ch0) * kElem;
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const int da = d >> 1, db = d & 1;
-                const uint4* p = reinterpret_cast<const uint4*>(P + (size_t)((base + da * sa + db * C) * kElem));
+                const char* p = P + ((size_t)da * g.N[b] + db) * C * kElem;
 #pragma unroll
-                for (int i = 0; i < kVecs; ++i) raw[d][i] = p[i];
+                for (int i = 0; i < kVecs; ++i) raw[d][i] = *reinterpret_cast<const uint4*>(p + off + 16 * i);
                 w[d] = (da ? c.f[a] : 1.0f - c.f[a]) * (db ? c.f[b] : 1.0f - c.f[b]);
             }
         } else if constexpr (KIND == LP_GRID_HASH) {
@@ -132,22 +123,22 @@ __device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const int dy = d >> 1, dz = d & 1;
-                const uint4* p = reinterpret_cast<const uint4*>(V + (size_t)((slot[4 * gr + d] * C + ch0) * kElem));
+                const unsigned off = (slot[4 * gr + d] * C + ch0) * kElem;
 #pragma unroll
-                for (int i = 0; i < kVecs; ++i) raw[d][i] = p[i];
+                for (int i = 0; i < kVecs; ++i) raw[d][i] = *reinterpret_cast<const uint4*>(V + off + 16 * i);
                 w[d] = (gr ? c.f[0] : 1.0f - c.f[0]) * (dy ? c.f[1] : 1.0f - c.f[1]) * (dz ? c.f[2] : 1.0f - c.f[2]);
             }
         } else {
             const char* V = reinterpret_cast<const char*>(g.data[0]) +
                             (size_t)scene * g.N[0] * g.N[1] * g.N[2] * C * kElem;
-            const unsigned sy = (unsigned)g.N[2] * C, sx = (unsigned)g.N[1] * sy;
-            const unsigned base = ((unsigned)c.i[0] + gr) * sx + (unsigned)c.i[1] * sy + (unsigned)c.i[2] * C + ch0;
+            const size_t sz = C * kElem, sy = g.N[2] * sz, sx = g.N[1] * sy;
+            const unsigned off = ((((unsigned)c.i[0] * (unsigned)g.N[1] + (unsigned)c.i[1]) * (unsigned)g.N[2] + (unsigned)c.i[2]) * C + ch0) * kElem;
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const int dy = d >> 1, dz = d & 1;
-                const uint4* p = reinterpret_cast<const uint4*>(V + (size_t)((base + dy * sy + dz * C) * kElem));
+                const char* p = V + gr * sx + dy * sy + dz * sz;
 #pragma unroll
-                for (int i = 0; i < kVecs; ++i) raw[d][i] = p[i];
+                for (int i = 0; i < kVecs; ++i) raw[d][i] = *reinterpret_cast<const uint4*>(p + off + 16 * i);
                 w[d] = (gr ? c.f[0] : 1.0f - c.f[0]) * (dy ? c.f[1] : 1.0f - c.f[1]) * (dz ? c.f[2] : 1.0f - c.f[2]);
             }
         }

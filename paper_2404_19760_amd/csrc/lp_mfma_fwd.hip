@@ -1,11 +1,16 @@
 // Matrix-core forward kernel of the Renderer (Eq. (1), Section 3.3; fused as in Section 3.4).
 //
 // A workgroup is 4 wavefronts sharing the MLP weights in LDS (bf16 hi/lo MFMA A operands).
-// A wavefront marches ONE ray at a time, 64 consecutive samples per step, sampled by whole texels (lp_gather.h) or
-// with lanes (i, g) interpolating the g-th half of the channels of samples i and 32 + i; the MLP runs on the
+// A wavefront marches two neighbouring rays, 32 consecutive samples of each per step, or one ray, 64 samples per step; sampled by
+// whole texels (lp_gather.h) or with lanes (i, g) interpolating the g-th half of the channels of samples i of both halves of the
+// step; the MLP runs on the
 // matrix cores for the 64 samples (two N blocks of 32, a stage apart), then lane l owns sample l of the step
 // for the density / colour heads and the emission-absorption update, where the transmittance
-// prefix is a wave-level scan of sigma * Delta.  Nothing per sample is written to memory.
+// prefix is a scan of sigma * Delta over the lanes of a ray.  Nothing per sample is written to memory.
+// What bounds it: instruction issue (256^3 x 16 voxels in bf16, 563 563 rays x 330 samples: 970 wave instructions on the vector ALU
+// a step, the products among them, issue in 68 % of a SIMD's cycles and the matrix cores are busy in 42 %).  So rays come in pairs,
+// which leaves fewer places empty at their ends (330 samples: 6 % instead of 14 %), each lane forms the cell of one sample and the
+// halves of the wave exchange them, and a load's address is a uniform pointer and the lane's offset: 9.57 -> 8.46 ms.
 #include "lp_gather.h"
 #include "lp_kernels.h"
 #include "lp_mfma.h"
@@ -24,81 +29,119 @@ constexpr int kWaves = 4;
 template <int KIND, int C, int CG>
 constexpr bool kWaveGather = C == 32 && CG == C && KIND != LP_GRID_HEXPLANE;
 
-// LDS: the MLP, then (16-byte units from kGatherAt) the waves' gather areas.
+// LDS: the MLP, then (16-byte units from kGatherAt) the waves' gather areas, then their rays.
 template <int KIND, int C, int H, int NH, int CG>
 struct FwdLds {
     static constexpr int kGatherAt = (MlpLds<C, H, NH, false, 2>::END + 15) / 16 * 16;
     static constexpr int kWave = kWaveGather<KIND, C, CG> ? WaveGatherLds<KIND == LP_GRID_HEXPLANE ? LP_GRID_VOXEL : KIND, CG>::kBytes : 0;
-    static constexpr int kBytes = kGatherAt * 16 + kWaves * kWave;
+    static constexpr int kRays = 2 * 48;   // of a wave: the geometry of its two rays
+    static constexpr int RAYS_AT = kGatherAt * 16 + kWaves * kWave;
+    static constexpr int kBytes = RAYS_AT + kWaves * kRays;
+    static_assert(RAYS_AT % 16 == 0, "alignment");
 };
 
-// Lane l owns sample l of a 64-sample step.
+// Whether the kernel can take rays in pairs (the direction inputs of two rays and a HexPlane's reads leave no registers).
+template <int KIND, int C, int CG>
+constexpr bool kPairs = CG == C && KIND != LP_GRID_HEXPLANE;
+
+// Lane l owns sample l of a step: of 64 samples of a ray, or (`pairs`) of 32 of ray l / 32 of two.
 // (three waves per SIMD where the registers allow it without spilling)
 template <int KIND, int C, int H, int NH, bool CC, int CG, int GT>
-__global__ __launch_bounds__(kWaves * 64, (CG == C && KIND != LP_GRID_HEXPLANE) ? 3 : 1) void fwd_mfma_kernel(GridDev g, MlpDev m, RaysDev rays, FwdOut out)
+__global__ __launch_bounds__(kWaves * 64, (kPairs<KIND, C, CG> ? 3 : 1)) void fwd_mfma_kernel(GridDev g, MlpDev m, RaysDev rays, FwdOut out, bool pairs)
 {
-    constexpr int kStep = 64;
     using L = MlpLds<C, H, NH, false, 2>;
     using F = FwdLds<KIND, C, H, NH, CG>;
     extern __shared__ uint4 lds[];
     stage_mlp<C, H, NH, false, 2, CG>(lds, m);
     __syncthreads();
 
-    const int lane = threadIdx.x & 63;
-    const RaySchedule sched = ray_schedule(rays.M, kWaves);
-    const int S = rays.S;
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const bool two = kPairs<KIND, C, CG> && pairs;
+    const RaySchedule sched = ray_schedule(two ? (rays.M + 1) / 2 : rays.M, kWaves);
+    const int S = rays.S, step = two ? 32 : 64;
     const bool identity = m.feat_act != 0;   // rendered features without the sigmoid (two-MLP decoder only)
     const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)reinterpret_cast<char*>(lds) + F::kGatherAt * 16 +
                           __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * F::kWave;
+    const uint32_t ray_at = (uint32_t)(uintptr_t)(LdsByte*)reinterpret_cast<char*>(lds) + F::RAYS_AT + (threadIdx.x >> 5) * (F::kRays / 2);
 
-    for (long long ray = sched.first; ray < sched.end; ray += sched.stride) {
-        RayGeom q = load_ray_geom(rays, ray);
-        if constexpr (CG != C) set_direction_inputs(m, q);
+    for (long long item = sched.first; item < sched.end; item += sched.stride) {
+        const long long ray = two ? 2 * item : item;   // the first one
+        RayGeom q0 = load_ray_geom(rays, ray);
+        if constexpr (CG != C) set_direction_inputs(m, q0);
+        const RayGeom q1 = kPairs<KIND, C, CG> ? load_ray_geom(rays, two ? min(ray + 1, rays.M - 1) : ray) : q0;
+        wave_lds_fence();
+        if ((lane & 31) == 0) {   // each half's ray
+            const RayGeom& q = half ? q1 : q0;
+            lds_put<f32x4>(ray_at, f32x4{q.ox, q.oy, q.oz, q.dx});
+            lds_put<f32x4>(ray_at + 16, f32x4{q.dy, q.dz, q.near, q.delta});
+            lds_put<double>(ray_at + 32, q.delta64);
+        }
+        wave_lds_fence();
         float tau = 0.0f;                                              // optical depth of earlier steps
         float acc_r = 0.0f, acc_g = 0.0f, acc_b = 0.0f, acc_d = 0.0f;  // per-lane partial sums
 
-        for (int j0 = 0; j0 < S; j0 += kStep) {
+        for (int j0 = 0; j0 < S; j0 += step) {
+            const int j = j0 + (two ? lane & 31 : lane);
             struct { float z[4]; } a;
+            RayGeom q;   // the lane's ray (from LDS: kept in registers it would cost ten, or twenty converted to fp64 ahead of the loop)
+            {
+                uint32_t at = ray_at;
+                refresh(at);
+                const f32x4 u = lds_get<f32x4>(at), v = lds_get<f32x4>(at + 16);
+                q.ox = u[0]; q.oy = u[1]; q.oz = u[2]; q.dx = u[3]; q.dy = v[0]; q.dz = v[1]; q.near = v[2]; q.delta = v[3];
+                q.delta64 = lds_get<double>(at + 32);
+            }
+            const Cell3 mine = sample_cell_for<CC, GT>(g, q, min(j, S - 1));
             if constexpr (kWaveGather<KIND, C, CG>) {
                 using G = WaveGatherLds<KIND, C>;
                 Frag fh[2][C / 16], fl[2][C / 16];
+                Cell3 c[2];
+                block_cells(mine, c);
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const Cell3 c = sample_cell_for<CC, GT>(g, q, min(j0 + 32 * nb + (lane & 31), S - 1));
-                    wave_features<KIND, C, GT>(g, q.scene, c, area, area + G::IMG, lane, fh[nb], fl[nb]);
-                }
+                for (int nb = 0; nb < 2; ++nb)
+                    wave_features<KIND, C, GT>(g, nb ? q1.scene : q0.scene, c[nb], area, area + G::IMG, lane, fh[nb], fl[nb]);
                 mlp_outputs<C, H, NH>(lds, reinterpret_cast<const float*>(lds + L::BIAS), lane, fh, fl, a.z);
             } else {
-                forward_outputs<KIND, C, H, NH, CC, CG, GT>(g, lds, q, j0, S, lane, a.z);
+                forward_outputs<KIND, C, H, NH, CG, GT>(g, lds, q0, q1, mine, lane, a.z);
             }
 
-            // heads and emission-absorption update; the lane owns sample j0 + pos
-            const int pos = lane & (kStep - 1);
-            const int j = j0 + pos;
-            const float t = q.near + ((float)j + 0.5f) * q.delta;
-            const float sd = j < S ? fast_softplus(a.z[0]) * q.delta : 0.0f;
-            const float incl = group_scan_incl<kStep>(sd, pos);
+            // heads and emission-absorption update
+            uint32_t at = ray_at;
+            refresh(at);
+            const float near = lds_get<float>(at + 24), delta = lds_get<float>(at + 28);
+            const float t = near + ((float)j + 0.5f) * delta;
+            const float sd = j < S ? fast_softplus(a.z[0]) * delta : 0.0f;
+            float incl = group_scan_incl<32>(sd, lane);
+            incl += two ? 0.0f : dpp_or_zero<0x143, 0xc>(incl);   // (one ray: the lower half's sum into the upper half)
             const float Tprev = __expf(-(tau + (incl - sd)));
             const float w = Tprev * one_minus_exp_neg(sd);
             acc_r += w * feature_head(a.z[1], identity);
             acc_g += w * feature_head(a.z[2], identity);
             acc_b += w * feature_head(a.z[3], identity);
             acc_d += w * t;
-            tau += __shfl(incl, kStep - 1, kStep);
+            const float sum31 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(incl), 31));
+            const float sum63 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(incl), 63));
+            tau += two && half == 0 ? sum31 : sum63;
         }
 
-        acc_r = wave_sum(acc_r);
-        acc_g = wave_sum(acc_g);
-        acc_b = wave_sum(acc_b);
-        acc_d = wave_sum(acc_d);
-        if (lane == 0) {
+        auto ray_sum = [&](float v) {
+#pragma unroll
+            for (int k = 16; k > 0; k >>= 1) v += __shfl_xor(v, k, 64);
+            return two ? v : v + __shfl_xor(v, 32, 64);
+        };
+        acc_r = ray_sum(acc_r);
+        acc_g = ray_sum(acc_g);
+        acc_b = ray_sum(acc_b);
+        acc_d = ray_sum(acc_d);
+        if (lane == 0 || (two && lane == 32 && ray + 1 < rays.M)) {
+            const long long r = ray + half;
             const float T = __expf(-tau);
-            out.rgb[3 * ray + 0] = acc_r + T * out.bg[0];
-            out.rgb[3 * ray + 1] = acc_g + T * out.bg[1];
-            out.rgb[3 * ray + 2] = acc_b + T * out.bg[2];
-            if (out.alpha) out.alpha[ray] = one_minus_exp_neg(tau);
-            if (out.depth) out.depth[ray] = acc_d;
-            if (out.cache) out.cache[ray] = tau;
+            out.rgb[3 * r + 0] = acc_r + T * out.bg[0];
+            out.rgb[3 * r + 1] = acc_g + T * out.bg[1];
+            out.rgb[3 * r + 2] = acc_b + T * out.bg[2];
+            if (out.alpha) out.alpha[r] = one_minus_exp_neg(tau);
+            if (out.depth) out.depth[r] = acc_d;
+            if (out.cache) out.cache[r] = tau;
         }
     }
 }
@@ -112,11 +155,15 @@ hipError_t launch_fwd(const GridDev& g, const MlpDev& m, const RaysDev& rays, co
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
     // persistent grid: as many workgroups as fit a compute unit's registers, a multiple of the 8 XCDs, no more than the rays need
-    long long blocks = 3LL * n_cu;
-    const long long need = (rays.M + kWaves - 1) / kWaves;
-    if (blocks > need) blocks = need;
-    blocks = (blocks + 7) / 8 * 8;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, g, m, rays, out);
+    long long blocks = (3LL * n_cu + 7) / 8 * 8;
+    // pairs where the wave with the most items has no more steps that way
+    const long long waves = blocks * kWaves;
+    auto rounds = [&](long long items) { return (items + waves - 1) / waves; };
+    const long long pair_items = (rays.M + 1) / 2;
+    const bool pairs = kPairs<KIND, C, CG> && rounds(pair_items) * ((rays.S + 31) / 32) <= rounds(rays.M) * ((rays.S + 63) / 64);
+    const long long need = ((pairs ? pair_items : rays.M) + kWaves - 1) / kWaves;
+    if (blocks > need) blocks = (need + 7) / 8 * 8;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, g, m, rays, out, pairs);
     return hipGetLastError();
 }
 

@@ -438,21 +438,42 @@ __device__ __forceinline__ void mlp_outputs(const uint4* lds, const float* bias1
     for (int k = 0; k < 4; ++k) z[k] = grp ? o1[k] + o1[4 + k] : o0[k] + o0[4 + k];
 }
 
-// Sampling + MLP of one 64-sample step for the forward kernel.  z = outputs of sample j0 + lane.
-template <int KIND, int C, int H, int NH, bool CC, int CG = C, int GT = LP_F32>
-__device__ __forceinline__ void forward_outputs(const GridDev& g, const uint4* lds, const RayGeom& q, int j0,
-                                                int S, int lane, float (&z)[4])
+// The cells of both N blocks' samples (column lane % 32 of block nb), from each lane's own sample: lane l owns column l % 32 of N
+// block l / 32.
+__device__ __forceinline__ void block_cells(const Cell3& mine, Cell3 (&c)[2])
+{
+    auto both = [](uint32_t x, uint32_t& lower, uint32_t& upper) {   // what the wave's halves hold, in both of them
+        typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
+        const u32x2 r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        lower = r[0];
+        upper = r[1];
+    };
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        uint32_t lo, up;
+        both((uint32_t)mine.i[a], lo, up);
+        c[0].i[a] = (int)lo;
+        c[1].i[a] = (int)up;
+        both(__float_as_uint(mine.f[a]), lo, up);
+        c[0].f[a] = __uint_as_float(lo);
+        c[1].f[a] = __uint_as_float(up);
+        c[0].g[a] = c[1].g[a] = 0.0f;   // (not read here)
+    }
+}
+
+// Sampling + MLP of one step of the forward kernel, 32 samples of ray q0 and 32 of ray q1 (or of the same ray); `mine`: the
+// lane's own cell.  z = outputs of the lane's sample: N block lane / 32, column lane % 32.
+template <int KIND, int C, int H, int NH, int CG = C, int GT = LP_F32>
+__device__ __forceinline__ void forward_outputs(const GridDev& g, const uint4* lds, const RayGeom& q0, const RayGeom& q1, const Cell3& mine,
+                                                int lane, float (&z)[4])
 {
     using L = MlpLds<C, H, NH, false, 2>;
     constexpr int KS1 = L::KS1;
-    const int col = lane & 31, grp = lane >> 5;
     Frag fh[2][KS1], fl[2][KS1];
+    Cell3 c[2];
+    block_cells(mine, c);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const int j = min(j0 + 32 * nb + col, S - 1);
-        const Cell3 c = sample_cell_for<CC, GT>(g, q, j);
-        sample_features<KIND, C, CG, GT>(g, q, c, grp, fh[nb], fl[nb]);
-    }
+    for (int nb = 0; nb < 2; ++nb) sample_features<KIND, C, CG, GT>(g, nb ? q1 : q0, c[nb], lane >> 5, fh[nb], fl[nb]);
     mlp_outputs<C, H, NH>(lds, reinterpret_cast<const float*>(lds + L::BIAS), lane, fh, fl, z);
 }
 

@@ -1,0 +1,38 @@
+"""The matrix-core forward with rays in pairs, 32 samples of each per step, against the generic kernels: a last ray without a
+partner, sample counts around 32 and 64, the two rays of a pair in different scenes; and launches of single rays beside it."""
+import pytest
+import torch
+
+import lp_inputs
+from lp_inputs import HASH, TRIPLANE, VOXEL
+
+from parity import FWD_RTOL, close
+
+pytestmark = pytest.mark.gpu
+
+
+def _pairs(n_rays, samples, n_cu=256):
+    """The launch rule of lp_mfma_fwd.hip."""
+    waves = (3 * n_cu + 7) // 8 * 8 * 4
+    rounds = lambda items: -(-items // waves)
+    return rounds((n_rays + 1) // 2) * -(-samples // 32) <= rounds(n_rays) * -(-samples // 64)
+
+
+@pytest.mark.parametrize("kind,channels,dims,dtype", [(VOXEL, 16, (16, 64, 64, 4), torch.float32), (VOXEL, 32, (32, 32, 4), torch.bfloat16),
+                                                      (TRIPLANE, 32, (32, 64, 64, 4), torch.float32), (TRIPLANE, 16, (16, 32, 32, 4), torch.float16),
+                                                      (HASH, 16, (16, 64, 4), torch.float32)])
+@pytest.mark.parametrize("n_rays,samples,pairs", [(1, 1, True), (6143, 31, True), (6143, 33, True), (6143, 95, True), (77, 65, False), (9001, 161, False)])
+def test_equals_the_generic_kernels(lp, kind, channels, dims, dtype, n_rays, samples, pairs):
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    if n_cu == 256:
+        assert _pairs(n_rays, samples) == pairs
+    kw = dict(hash_size=4096) if kind == HASH else {}
+    inp = lp_inputs.make_small(kind, channels=channels, res=(24, 21, 26), mlp_dims=dims, n_rays=n_rays, samples=samples, seed=71 + samples,
+                               n_scenes=3, grid_std=0.3, **kw)
+    grid, mlp, rays, bg = lp.to_device(inp, "cuda:0")
+    rays.scene = torch.randint(0, 3, (n_rays,), dtype=torch.int32, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(5))
+    grid.data = [t.to(dtype) for t in grid.data]
+    got = lp.render_fwd(grid, mlp, rays, bg, lp.LP_MATH_BF16X3)
+    want = lp.render_fwd(grid, mlp, rays, bg, lp.LP_MATH_GENERIC)
+    for name, a, b in zip(("rgb", "alpha", "depth", "cache"), got, want):
+        close(a.cpu().numpy(), b.double().cpu().numpy(), FWD_RTOL, f"{name} M={n_rays} S={samples}")

@@ -26,7 +26,7 @@ def _in_tiles(n_rays, samples, waves, up_to):
 @pytest.mark.parametrize("channels,n_in,hidden,n_freq", [(16, 5, (64,), -1), (32, 32, (64, 64), 1)])
 @pytest.mark.parametrize("image", [dict(width=64, height=72, samples=9, res=(20, 23, 17), cut=1),
                                    dict(width=66, height=70, samples=8, res=(40, 33, 37), per_scene=7),
-                                   dict(width=64, height=72, samples=10, res=(90, 64, 70)),
+                                   dict(width=64, height=72, samples=10, res=(48, 40, 44)),
                                    dict(width=64, height=72, samples=9, res=(24, 22, 26), contract=1.0, far=9.0)])
 def test_splatter_with_mlp_in_tiles(lp, oracle, kind, channels, n_in, hidden, n_freq, image):
     sp = _image(kind, channels, **image, n_in=n_in, hidden=hidden, n_freq=n_freq, prior_channels=channels, prior_res=(19, 16, 15), bias_std=0.1)
