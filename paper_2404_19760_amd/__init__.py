@@ -135,14 +135,18 @@ def _check(status: int):
         raise LightplaneError(status, _lib.lp_last_error().decode())
 
 
-def _dev_f32(t: Optional[torch.Tensor], name: str, shape=None) -> Optional[int]:
+def _dev_f32(t: Optional[torch.Tensor], name: str, shape=None, index=None) -> Optional[int]:
     if t is None:
         return None
+    # (one test in the common case, and the name put together only for an error: a call marshals some twenty tensors, and
+    # small launches wait for that)
+    if t.is_cuda and t.dtype is torch.float32 and t.is_contiguous() and (shape is None or t.shape == shape):
+        return t.data_ptr()
+    if index is not None:
+        name = f"{name}[{index}]"
     if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
         raise ValueError(f"{name} must be a contiguous float32 tensor on the GPU")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return t.data_ptr()
+    raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
 _GRID_DTYPES = {torch.float32: LP_F32, torch.bfloat16: LP_BF16, torch.float16: LP_F16}
@@ -172,12 +176,13 @@ class Grid:
         return int(self.data[0].shape[-1])
 
     def shapes(self):
-        b, c = self.n_scenes, self.channels
+        first = self.data[0].shape
+        b, c = first[0], first[-1]
         nx, ny, nz = self.res
         if self.kind == LP_GRID_VOXEL:
             return [(b, nx, ny, nz, c)]
         if self.kind == LP_GRID_HASH:
-            return [(b, int(self.data[0].shape[1]), c)]
+            return [(b, first[1], c)]
         planes = [(b, nx, ny, c), (b, ny, nz, c), (b, nz, nx, c)]
         if self.kind == LP_GRID_HEXPLANE:
             if len(self.data) != 6:
@@ -186,34 +191,30 @@ class Grid:
             planes += [(b, nz, nt, c), (b, nx, nt, c), (b, ny, nt, c)]
         return planes
 
-    def c_struct(self) -> _Grid:
-        g = _Grid()
-        g.kind, g.B, g.C = self.kind, self.n_scenes, self.channels
-        g.NX, g.NY, g.NZ = [int(v) for v in self.res]
-        g.hash_size = int(self.data[0].shape[1]) if self.kind == LP_GRID_HASH else 0
-        shapes = self.shapes()
-        if len(self.data) != len(shapes):
+    def c_struct(self, shapes=None) -> _Grid:
+        """`shapes`: self.shapes(), if the caller has it."""
+        data = self.data
+        if shapes is None:
+            shapes = self.shapes()
+        nx, ny, nz = self.res
+        if len(data) != len(shapes):
             raise ValueError("wrong number of grid tensors for this kind")
-        dt = self.data[0].dtype
+        dt = data[0].dtype
         if dt not in _GRID_DTYPES:
             raise ValueError("grid tensors must be float32, bfloat16 or float16")
-        g.dtype = _GRID_DTYPES[dt]
-        for p, (t, s) in enumerate(zip(self.data, shapes)):
-            if not (t.is_cuda and t.dtype == dt and t.is_contiguous() and tuple(t.shape) == tuple(s)):
+        ptr = [None] * 6
+        for p, (t, s) in enumerate(zip(data, shapes)):
+            if not (t.is_cuda and t.dtype is dt and t.is_contiguous() and t.shape == s):
                 raise ValueError(f"grid.data[{p}] must be a contiguous GPU tensor of shape {tuple(s)} and the "
                                  "dtype of grid.data[0]")
-            if p < 3:
-                g.data[p] = t.data_ptr()
-            else:
-                g.data_t[p - 3] = t.data_ptr()
-        if self.kind == LP_GRID_HEXPLANE:
-            g.NT = int(self.data[3].shape[2])
-            g.t_min, g.t_max = float(self.t_range[0]), float(self.t_range[1])
-        for a in range(3):
-            g.aabb_min[a] = float(self.aabb_min[a])
-            g.aabb_max[a] = float(self.aabb_max[a])
-        g.contract_a = float(self.contract_a)
-        return g
+            ptr[p] = t.data_ptr()
+        lo, hi = self.aabb_min, self.aabb_max
+        hexplane = self.kind == LP_GRID_HEXPLANE
+        return _Grid(self.kind, shapes[0][0], shapes[0][-1], int(nx), int(ny), int(nz), tuple(ptr[:3]),
+                     (float(lo[0]), float(lo[1]), float(lo[2])), (float(hi[0]), float(hi[1]), float(hi[2])),
+                     float(self.contract_a), _GRID_DTYPES[dt], shapes[0][1] if self.kind == LP_GRID_HASH else 0, tuple(ptr[3:]),
+                     shapes[3][2] if hexplane else 0, float(self.t_range[0]) if hexplane else 0.0,
+                     float(self.t_range[1]) if hexplane else 0.0)
 
 
 @dataclasses.dataclass
@@ -224,20 +225,18 @@ class Mlp:
 
     @property
     def dims(self):
-        return [int(self.weights[0].shape[1])] + [int(w.shape[0]) for w in self.weights]
+        return [self.weights[0].shape[1], *[w.shape[0] for w in self.weights]]
 
-    def c_struct(self) -> _Mlp:
-        if len(self.weights) != len(self.biases) or not 1 <= len(self.weights) <= LP_MAX_LAYERS:
+    def c_struct(self, dims=None) -> _Mlp:
+        """`dims`: self.dims, if the caller has it."""
+        weights, biases = self.weights, self.biases
+        if len(weights) != len(biases) or not 1 <= len(weights) <= LP_MAX_LAYERS:
             raise ValueError("MLP needs 1..8 layers with one bias per weight matrix")
-        m = _Mlp()
-        m.n_layers = len(self.weights)
-        dims = self.dims
-        for i, d in enumerate(dims):
-            m.dims[i] = d
-        for l, (w, b) in enumerate(zip(self.weights, self.biases)):
-            m.W[l] = _dev_f32(w, f"weights[{l}]", (dims[l + 1], dims[l]))
-            m.b[l] = _dev_f32(b, f"biases[{l}]", (dims[l + 1],))
-        return m
+        if dims is None:
+            dims = self.dims
+        return _Mlp(len(weights), tuple(dims),
+                    tuple([_dev_f32(w, "weights", (dims[l + 1], dims[l]), l) for l, w in enumerate(weights)]),
+                    tuple([_dev_f32(b, "biases", (dims[l + 1],), l) for l, b in enumerate(biases)]))
 
 
 @dataclasses.dataclass
@@ -269,34 +268,32 @@ class Rays:
 
     @property
     def n_rays(self) -> int:
-        return int(self.origins.shape[0])
+        return self.origins.shape[0]
 
     def c_struct(self) -> _Rays:
         m = self.n_rays
-        r = _Rays()
-        r.M, r.S = m, int(self.samples)
-        r.origins = _dev_f32(self.origins, "origins", (m, 3))
-        r.dirs = _dev_f32(self.dirs, "dirs", (m, 3))
-        r.near = _dev_f32(self.near, "near", (m,))
-        r.far = _dev_f32(self.far, "far", (m,))
-        if self.scene is not None:
-            s = self.scene
-            if not (s.is_cuda and s.dtype == torch.int32 and s.is_contiguous() and tuple(s.shape) == (m,)):
+        scene = self.scene
+        if scene is not None:
+            if not (scene.is_cuda and scene.dtype is torch.int32 and scene.is_contiguous() and scene.shape == (m,)):
                 raise ValueError("scene must be a contiguous int32 GPU tensor of shape [M]")
-            r.scene = s.data_ptr()
-        if self.time is not None:
-            r.time = _dev_f32(self.time, "time", (m,))
-        return r
+            scene = scene.data_ptr()
+        return _Rays(m, int(self.samples), _dev_f32(self.origins, "origins", (m, 3)), _dev_f32(self.dirs, "dirs", (m, 3)),
+                     _dev_f32(self.near, "near", (m,)), _dev_f32(self.far, "far", (m,)), scene,
+                     _dev_f32(self.time, "time", (m,)))
 
 
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # (the current stream's handle without building a Stream object around it)
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return C.c_void_p(stream.cuda_stream)
 
 
+_Float3, _Pointers6, _PointersL = C.c_float * 3, C.c_void_p * 6, C.c_void_p * LP_MAX_LAYERS
+
+
 def _bg(bg) -> C.Array:
-    return (C.c_float * 3)(*[float(v) for v in bg])
+    return _Float3(*[float(v) for v in bg])
 
 
 def lp_version() -> int:
@@ -377,17 +374,15 @@ def lp_render_bwd(grid: Grid, mlp: Mlp, rays: Rays, bg, d_rgb: torch.Tensor,
 
 def _render_bwd(grid, mlp, rays, bg, d_rgb, d_alpha, d_depth, ray_cache, d_grid, dW, db, workspace, math_mode, stream):
     m = rays.n_rays
-    g, ml, r = grid.c_struct(), mlp.c_struct(), rays.c_struct()
-    shapes = grid.shapes()
+    shapes, dims = grid.shapes(), mlp.dims
+    g, ml, r = grid.c_struct(shapes), mlp.c_struct(dims), rays.c_struct()
     if len(d_grid) != len(shapes):
         raise ValueError("d_grid needs one tensor per grid tensor")
-    dg = (C.c_void_p * 6)(*[_dev_f32(d_grid[p], f"d_grid[{p}]", shapes[p]) if p < len(shapes) else None
-                            for p in range(6)])
-    dims = mlp.dims
+    dg = _Pointers6(*[_dev_f32(t, "d_grid", s, p) for p, (t, s) in enumerate(zip(d_grid, shapes))])
     if len(dW) != len(mlp.weights) or len(db) != len(mlp.weights):
         raise ValueError("dW / db need one tensor per layer")
-    dWp = (C.c_void_p * LP_MAX_LAYERS)(*[_dev_f32(w, f"dW[{l}]", (dims[l + 1], dims[l])) for l, w in enumerate(dW)])
-    dbp = (C.c_void_p * LP_MAX_LAYERS)(*[_dev_f32(b, f"db[{l}]", (dims[l + 1],)) for l, b in enumerate(db)])
+    dWp = _PointersL(*[_dev_f32(w, "dW", (dims[l + 1], dims[l]), l) for l, w in enumerate(dW)])
+    dbp = _PointersL(*[_dev_f32(b, "db", (dims[l + 1],), l) for l, b in enumerate(db)])
     common = (C.byref(g), C.byref(ml), C.byref(r), _bg(bg),
               _dev_f32(d_rgb, "d_rgb", (m, 3)), _dev_f32(d_alpha, "d_alpha", (m,)),
               _dev_f32(d_depth, "d_depth", (m,)), _dev_f32(ray_cache, "ray_cache", (m,)), dg, dWp, dbp)
@@ -567,8 +562,8 @@ def lp_splat_bwd(target: _Grid, rays: Rays, splat: Splat, theta_w: List[torch.Te
     dWp, dbp = (C.c_void_p * LP_MAX_LAYERS)(), (C.c_void_p * LP_MAX_LAYERS)()
     if splat.mlp is not None:
         dims = splat.mlp.dims
-        dWp = (C.c_void_p * LP_MAX_LAYERS)(*[_dev_f32(w, f"dW[{l}]", (dims[l + 1], dims[l])) for l, w in enumerate(dW)])
-        dbp = (C.c_void_p * LP_MAX_LAYERS)(*[_dev_f32(b, f"db[{l}]", (dims[l + 1],)) for l, b in enumerate(db)])
+        dWp = (C.c_void_p * LP_MAX_LAYERS)(*[_dev_f32(w, "dW", (dims[l + 1], dims[l]), l) for l, w in enumerate(dW)])
+        dbp = (C.c_void_p * LP_MAX_LAYERS)(*[_dev_f32(b, "db", (dims[l + 1],), l) for l, b in enumerate(db)])
     wp, wn = _workspace(workspace)
     _check(_lib.lp_splat_bwd(C.byref(target), C.byref(r), C.byref(s),
                              _ptr3(theta_w, _target_shapes(target, None), "theta_w"),
