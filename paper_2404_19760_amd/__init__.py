@@ -227,13 +227,11 @@ class Mlp:
     def dims(self):
         return [self.weights[0].shape[1], *[w.shape[0] for w in self.weights]]
 
-    def c_struct(self, dims=None) -> _Mlp:
-        """`dims`: self.dims, if the caller has it."""
+    def c_struct(self) -> _Mlp:
         weights, biases = self.weights, self.biases
         if len(weights) != len(biases) or not 1 <= len(weights) <= LP_MAX_LAYERS:
             raise ValueError("MLP needs 1..8 layers with one bias per weight matrix")
-        if dims is None:
-            dims = self.dims
+        dims = self.dims
         return _Mlp(len(weights), tuple(dims),
                     tuple([_dev_f32(w, "weights", (dims[l + 1], dims[l]), l) for l, w in enumerate(weights)]),
                     tuple([_dev_f32(b, "biases", (dims[l + 1],), l) for l, b in enumerate(biases)]))
@@ -374,8 +372,9 @@ def lp_render_bwd(grid: Grid, mlp: Mlp, rays: Rays, bg, d_rgb: torch.Tensor,
 
 def _render_bwd(grid, mlp, rays, bg, d_rgb, d_alpha, d_depth, ray_cache, d_grid, dW, db, workspace, math_mode, stream):
     m = rays.n_rays
-    shapes, dims = grid.shapes(), mlp.dims
-    g, ml, r = grid.c_struct(shapes), mlp.c_struct(dims), rays.c_struct()
+    shapes = grid.shapes()
+    g, ml, r = grid.c_struct(shapes), mlp.c_struct(), rays.c_struct()
+    dims = ml.dims   # (of an MLP that c_struct has found to be one)
     if len(d_grid) != len(shapes):
         raise ValueError("d_grid needs one tensor per grid tensor")
     dg = _Pointers6(*[_dev_f32(t, "d_grid", s, p) for p, (t, s) in enumerate(zip(d_grid, shapes))])

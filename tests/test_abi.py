@@ -167,6 +167,28 @@ def test_fast_path_queries_are_host_logic():
     assert splat(grid(0, 32), 30, 0, grid(0, 32), mlp(67, 64, 32)) == 0                  # inconsistent widths
 
 
+def test_an_mlp_without_layers_is_refused_by_name():
+    """By the backward as by the forward: the widths are read only once the layers are known to be there."""
+    import paper_2404_19760_amd as lp
+    import torch
+
+    class AnyGrid:
+        def shapes(self):
+            return []
+
+        def c_struct(self, shapes=None):
+            return lp._Grid()
+
+    t = torch.zeros(1)
+    rays = lp.Rays(torch.zeros(1, 3), torch.zeros(1, 3), t, t, 4)
+    for call in (lambda m: lp.lp_render_fwd(AnyGrid(), m, rays, (1, 1, 1), t, None, None, None),
+                 lambda m: lp.lp_render_bwd(AnyGrid(), m, rays, (1, 1, 1), t, None, None, t, [], [], [], t),
+                 lambda m: lp.lp_render_bwd_static(AnyGrid(), m, rays, (1, 1, 1), t, None, None, t, [], [], [])):
+        for mlp in (lp.Mlp([], []), lp.Mlp([torch.zeros(4, 4)], []), lp.Mlp([torch.zeros(4, 4)] * 9, [t] * 9)):
+            with pytest.raises(ValueError, match="1..8 layers"):
+                call(mlp)
+
+
 def test_product_path_does_not_reach_the_oracle():
     """Nothing under the package names, imports or links the oracle."""
     pkg = os.path.join(ROOT, "paper_2404_19760_amd")
