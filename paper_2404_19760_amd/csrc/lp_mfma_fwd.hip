@@ -29,12 +29,12 @@ constexpr int kWaves = 4;
 template <int KIND, int C, int CG>
 constexpr bool kWaveGather = C == 32 && CG == C && KIND != LP_GRID_HEXPLANE;
 
-// LDS: the MLP, then (16-byte units from kGatherAt) the waves' gather areas, then their rays.
-template <int KIND, int C, int H, int NH, int CG>
+// LDS: the MLP, then (16-byte units from kGatherAt) the waves' gather areas, then (PAIRS) their rays.
+template <int KIND, int C, int H, int NH, int CG, bool PAIRS>
 struct FwdLds {
     static constexpr int kGatherAt = (MlpLds<C, H, NH, false, 2>::END + 15) / 16 * 16;
     static constexpr int kWave = kWaveGather<KIND, C, CG> ? WaveGatherLds<KIND == LP_GRID_HEXPLANE ? LP_GRID_VOXEL : KIND, CG>::kBytes : 0;
-    static constexpr int kRays = 2 * 48;   // of a wave: the geometry of its two rays
+    static constexpr int kRays = PAIRS ? 2 * 48 : 0;   // of a wave: the geometry of its two rays
     static constexpr int RAYS_AT = kGatherAt * 16 + kWaves * kWave;
     static constexpr int kBytes = RAYS_AT + kWaves * kRays;
     static_assert(RAYS_AT % 16 == 0, "alignment");
@@ -44,96 +44,104 @@ struct FwdLds {
 template <int KIND, int C, int CG>
 constexpr bool kPairs = CG == C && KIND != LP_GRID_HEXPLANE;
 
-// Lane l owns sample l of a step: of 64 samples of a ray, or (`pairs`) of 32 of ray l / 32 of two.
+// Lane l owns sample l of a step: of 64 samples of a ray, or (PAIRS) of 32 of ray l / 32 of two.
 // (three waves per SIMD where the registers allow it without spilling)
-template <int KIND, int C, int H, int NH, bool CC, int CG, int GT>
-__global__ __launch_bounds__(kWaves * 64, (kPairs<KIND, C, CG> ? 3 : 1)) void fwd_mfma_kernel(GridDev g, MlpDev m, RaysDev rays, FwdOut out, bool pairs)
+template <int KIND, int C, int H, int NH, bool CC, int CG, int GT, bool PAIRS>
+__global__ __launch_bounds__(kWaves * 64, (kPairs<KIND, C, CG> ? 3 : 1)) void fwd_mfma_kernel(GridDev g, MlpDev m, RaysDev rays, FwdOut out)
 {
+    static_assert(!PAIRS || kPairs<KIND, C, CG>);
+    constexpr int kLanes = PAIRS ? 32 : 64;   // of a ray: its samples of a step
     using L = MlpLds<C, H, NH, false, 2>;
-    using F = FwdLds<KIND, C, H, NH, CG>;
+    using F = FwdLds<KIND, C, H, NH, CG, PAIRS>;
     extern __shared__ uint4 lds[];
     stage_mlp<C, H, NH, false, 2, CG>(lds, m);
     __syncthreads();
 
-    const int lane = threadIdx.x & 63, half = lane >> 5;
-    const bool two = kPairs<KIND, C, CG> && pairs;
-    const RaySchedule sched = ray_schedule(two ? (rays.M + 1) / 2 : rays.M, kWaves);
-    const int S = rays.S, step = two ? 32 : 64;
+    const int lane = threadIdx.x & 63, half = PAIRS ? lane >> 5 : 0;
+    const RaySchedule sched = ray_schedule(PAIRS ? (rays.M + 1) / 2 : rays.M, kWaves);
+    const int S = rays.S;
     const bool identity = m.feat_act != 0;   // rendered features without the sigmoid (two-MLP decoder only)
     const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)reinterpret_cast<char*>(lds) + F::kGatherAt * 16 +
                           __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * F::kWave;
     const uint32_t ray_at = (uint32_t)(uintptr_t)(LdsByte*)reinterpret_cast<char*>(lds) + F::RAYS_AT + (threadIdx.x >> 5) * (F::kRays / 2);
 
     for (long long item = sched.first; item < sched.end; item += sched.stride) {
-        const long long ray = two ? 2 * item : item;   // the first one
+        const long long ray = PAIRS ? 2 * item : item;   // the first one
         RayGeom q0 = load_ray_geom(rays, ray);
         if constexpr (CG != C) set_direction_inputs(m, q0);
-        const RayGeom q1 = kPairs<KIND, C, CG> ? load_ray_geom(rays, two ? min(ray + 1, rays.M - 1) : ray) : q0;
-        wave_lds_fence();
-        if ((lane & 31) == 0) {   // each half's ray
-            const RayGeom& q = half ? q1 : q0;
-            lds_put<f32x4>(ray_at, f32x4{q.ox, q.oy, q.oz, q.dx});
-            lds_put<f32x4>(ray_at + 16, f32x4{q.dy, q.dz, q.near, q.delta});
-            lds_put<double>(ray_at + 32, q.delta64);
+        const RayGeom q1 = PAIRS ? load_ray_geom(rays, min(ray + 1, rays.M - 1)) : q0;
+        if constexpr (PAIRS) {
+            wave_lds_fence();
+            if ((lane & 31) == 0) {   // each half's ray
+                const RayGeom& q = half ? q1 : q0;
+                lds_put<f32x4>(ray_at, f32x4{q.ox, q.oy, q.oz, q.dx});
+                lds_put<f32x4>(ray_at + 16, f32x4{q.dy, q.dz, q.near, q.delta});
+                lds_put<double>(ray_at + 32, q.delta64);
+            }
+            wave_lds_fence();
         }
-        wave_lds_fence();
         float tau = 0.0f;                                              // optical depth of earlier steps
         float acc_r = 0.0f, acc_g = 0.0f, acc_b = 0.0f, acc_d = 0.0f;  // per-lane partial sums
 
-        for (int j0 = 0; j0 < S; j0 += step) {
-            const int j = j0 + (two ? lane & 31 : lane);
+        for (int j0 = 0; j0 < S; j0 += kLanes) {
+            const int j = j0 + (lane & (kLanes - 1));
             struct { float z[4]; } a;
-            RayGeom q;   // the lane's ray (from LDS: kept in registers it would cost ten, or twenty converted to fp64 ahead of the loop)
-            {
+            // the samples' cells, column lane % 32 of both N blocks
+            Cell3 pair[2];
+            if constexpr (PAIRS) {
+                RayGeom q;   // the lane's ray (from LDS: kept in registers it would cost ten, or twenty converted to fp64 ahead of the loop)
                 uint32_t at = ray_at;
                 refresh(at);
                 const f32x4 u = lds_get<f32x4>(at), v = lds_get<f32x4>(at + 16);
                 q.ox = u[0]; q.oy = u[1]; q.oz = u[2]; q.dx = u[3]; q.dy = v[0]; q.dz = v[1]; q.near = v[2]; q.delta = v[3];
                 q.delta64 = lds_get<double>(at + 32);
+                block_cells(sample_cell_for<CC, GT>(g, q, min(j, S - 1)), pair);
             }
-            const Cell3 mine = sample_cell_for<CC, GT>(g, q, min(j, S - 1));
+            auto cell = [&](int nb) {
+                if constexpr (PAIRS) return pair[nb];
+                else return sample_cell_for<CC, GT>(g, q0, min(j0 + 32 * nb + (lane & 31), S - 1));
+            };
             if constexpr (kWaveGather<KIND, C, CG>) {
                 using G = WaveGatherLds<KIND, C>;
                 Frag fh[2][C / 16], fl[2][C / 16];
-                Cell3 c[2];
-                block_cells(mine, c);
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb)
-                    wave_features<KIND, C, GT>(g, nb ? q1.scene : q0.scene, c[nb], area, area + G::IMG, lane, fh[nb], fl[nb]);
+                    wave_features<KIND, C, GT>(g, nb ? q1.scene : q0.scene, cell(nb), area, area + G::IMG, lane, fh[nb], fl[nb]);
                 mlp_outputs<C, H, NH>(lds, reinterpret_cast<const float*>(lds + L::BIAS), lane, fh, fl, a.z);
             } else {
-                forward_outputs<KIND, C, H, NH, CG, GT>(g, lds, q0, q1, mine, lane, a.z);
+                forward_outputs<KIND, C, H, NH, CG, GT>(g, lds, q0, q1, cell, lane, a.z);
             }
 
             // heads and emission-absorption update
-            uint32_t at = ray_at;
-            refresh(at);
-            const float near = lds_get<float>(at + 24), delta = lds_get<float>(at + 28);
+            float near = q0.near, delta = q0.delta;
+            if constexpr (PAIRS) {
+                uint32_t at = ray_at;
+                refresh(at);
+                near = lds_get<float>(at + 24);
+                delta = lds_get<float>(at + 28);
+            }
             const float t = near + ((float)j + 0.5f) * delta;
             const float sd = j < S ? fast_softplus(a.z[0]) * delta : 0.0f;
-            float incl = group_scan_incl<32>(sd, lane);
-            incl += two ? 0.0f : dpp_or_zero<0x143, 0xc>(incl);   // (one ray: the lower half's sum into the upper half)
+            const float incl = group_scan_incl<kLanes>(sd, lane);
             const float Tprev = __expf(-(tau + (incl - sd)));
             const float w = Tprev * one_minus_exp_neg(sd);
             acc_r += w * feature_head(a.z[1], identity);
             acc_g += w * feature_head(a.z[2], identity);
             acc_b += w * feature_head(a.z[3], identity);
             acc_d += w * t;
-            const float sum31 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(incl), 31));
-            const float sum63 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(incl), 63));
-            tau += two && half == 0 ? sum31 : sum63;
+            tau += __shfl(incl, kLanes - 1, kLanes);
         }
 
         auto ray_sum = [&](float v) {
 #pragma unroll
-            for (int k = 16; k > 0; k >>= 1) v += __shfl_xor(v, k, 64);
-            return two ? v : v + __shfl_xor(v, 32, 64);
+            for (int k = kLanes / 2; k > 0; k >>= 1) v += __shfl_xor(v, k, 64);
+            return v;
         };
         acc_r = ray_sum(acc_r);
         acc_g = ray_sum(acc_g);
         acc_b = ray_sum(acc_b);
         acc_d = ray_sum(acc_d);
-        if (lane == 0 || (two && lane == 32 && ray + 1 < rays.M)) {
+        if (lane == 0 || (PAIRS && lane == 32 && ray + 1 < rays.M)) {
             const long long r = ray + half;
             const float T = __expf(-tau);
             out.rgb[3 * r + 0] = acc_r + T * out.bg[0];
@@ -146,25 +154,37 @@ __global__ __launch_bounds__(kWaves * 64, (kPairs<KIND, C, CG> ? 3 : 1)) void fw
     }
 }
 
+template <int KIND, int C, int H, int NH, bool CC, int CG, int GT, bool PAIRS>
+hipError_t launch_items(const GridDev& g, const MlpDev& m, const RaysDev& rays, const FwdOut& out, long long blocks, hipStream_t stream)
+{
+    constexpr int kLdsBytes = FwdLds<KIND, C, H, NH, CG, PAIRS>::kBytes;
+    auto kernel = fwd_mfma_kernel<KIND, C, H, NH, CC, CG, GT, PAIRS>;
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (e != hipSuccess) return e;
+    const long long items = PAIRS ? (rays.M + 1) / 2 : rays.M, need = (items + kWaves - 1) / kWaves;
+    if (blocks > need) blocks = (need + 7) / 8 * 8;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, g, m, rays, out);
+    return hipGetLastError();
+}
+
 template <int KIND, int C, int H, int NH, bool CC, int CG, int GT = LP_F32>
 hipError_t launch_fwd(const GridDev& g, const MlpDev& m, const RaysDev& rays, const FwdOut& out, int n_cu,
                       hipStream_t stream)
 {
-    constexpr int kLdsBytes = FwdLds<KIND, C, H, NH, CG>::kBytes;
-    auto kernel = fwd_mfma_kernel<KIND, C, H, NH, CC, CG, GT>;
-    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (e != hipSuccess) return e;
     // persistent grid: as many workgroups as fit a compute unit's registers, a multiple of the 8 XCDs, no more than the rays need
-    long long blocks = (3LL * n_cu + 7) / 8 * 8;
-    // pairs where the wave with the most items has no more steps that way
-    const long long waves = blocks * kWaves;
-    auto rounds = [&](long long items) { return (items + waves - 1) / waves; };
-    const long long pair_items = (rays.M + 1) / 2;
-    const bool pairs = kPairs<KIND, C, CG> && rounds(pair_items) * ((rays.S + 31) / 32) <= rounds(rays.M) * ((rays.S + 63) / 64);
-    const long long need = ((pairs ? pair_items : rays.M) + kWaves - 1) / kWaves;
-    if (blocks > need) blocks = (need + 7) / 8 * 8;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, g, m, rays, out, pairs);
-    return hipGetLastError();
+    const long long blocks = (3LL * n_cu + 7) / 8 * 8;
+    if constexpr (kPairs<KIND, C, CG>) {
+        // Pairs where a SIMD has no more steps that way, and two waves for each SIMD remain unless a ray is one step either way.
+        // 256 .. 44 000 rays x 24 .. 330 samples, eight structures and decoders, time in single rays over that in pairs: where
+        // pairs are taken 0.97 .. 1.84 (330 samples: 0.96 .. 1.18; 24: up to 1.8), elsewhere 0.60 .. 1.24 (up to 2000 rays of more
+        // than 64 samples 0.60 .. 1.08: fewer waves, each with more steps in a row).
+        const long long simds = 4LL * n_cu, pair_items = (rays.M + 1) / 2;
+        auto share = [&](long long items) { return (items + simds - 1) / simds; };
+        const bool no_more = share(pair_items) * ((rays.S + 31) / 32) <= share(rays.M) * ((rays.S + 63) / 64);
+        if (no_more && (rays.S <= 32 || pair_items >= 2 * simds))
+            return launch_items<KIND, C, H, NH, CC, CG, GT, true>(g, m, rays, out, blocks, stream);
+    }
+    return launch_items<KIND, C, H, NH, CC, CG, GT, false>(g, m, rays, out, blocks, stream);
 }
 
 template <int KIND>

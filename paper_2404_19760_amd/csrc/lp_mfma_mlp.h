@@ -461,19 +461,17 @@ __device__ __forceinline__ void block_cells(const Cell3& mine, Cell3 (&c)[2])
     }
 }
 
-// Sampling + MLP of one step of the forward kernel, 32 samples of ray q0 and 32 of ray q1 (or of the same ray); `mine`: the
-// lane's own cell.  z = outputs of the lane's sample: N block lane / 32, column lane % 32.
-template <int KIND, int C, int H, int NH, int CG = C, int GT = LP_F32>
-__device__ __forceinline__ void forward_outputs(const GridDev& g, const uint4* lds, const RayGeom& q0, const RayGeom& q1, const Cell3& mine,
+// Sampling + MLP of one step of the forward kernel, 32 samples of ray q0 and 32 of ray q1 (or of the same ray); cell(nb): the cell
+// of column lane % 32 of N block nb.  z = outputs of the lane's sample: N block lane / 32, column lane % 32.
+template <int KIND, int C, int H, int NH, int CG = C, int GT = LP_F32, class CellOf>
+__device__ __forceinline__ void forward_outputs(const GridDev& g, const uint4* lds, const RayGeom& q0, const RayGeom& q1, CellOf cell,
                                                 int lane, float (&z)[4])
 {
     using L = MlpLds<C, H, NH, false, 2>;
     constexpr int KS1 = L::KS1;
     Frag fh[2][KS1], fl[2][KS1];
-    Cell3 c[2];
-    block_cells(mine, c);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) sample_features<KIND, C, CG, GT>(g, nb ? q1 : q0, c[nb], lane >> 5, fh[nb], fl[nb]);
+    for (int nb = 0; nb < 2; ++nb) sample_features<KIND, C, CG, GT>(g, nb ? q1 : q0, cell(nb), lane >> 5, fh[nb], fl[nb]);
     mlp_outputs<C, H, NH>(lds, reinterpret_cast<const float*>(lds + L::BIAS), lane, fh, fl, z);
 }
 

@@ -7,25 +7,19 @@ import lp_inputs
 from lp_inputs import HASH, TRIPLANE, VOXEL
 
 from parity import FWD_RTOL, close
+from tile_rules import forward_in_pairs
 
 pytestmark = pytest.mark.gpu
-
-
-def _pairs(n_rays, samples, n_cu=256):
-    """The launch rule of lp_mfma_fwd.hip."""
-    waves = (3 * n_cu + 7) // 8 * 8 * 4
-    rounds = lambda items: -(-items // waves)
-    return rounds((n_rays + 1) // 2) * -(-samples // 32) <= rounds(n_rays) * -(-samples // 64)
 
 
 @pytest.mark.parametrize("kind,channels,dims,dtype", [(VOXEL, 16, (16, 64, 64, 4), torch.float32), (VOXEL, 32, (32, 32, 4), torch.bfloat16),
                                                       (TRIPLANE, 32, (32, 64, 64, 4), torch.float32), (TRIPLANE, 16, (16, 32, 32, 4), torch.float16),
                                                       (HASH, 16, (16, 64, 4), torch.float32)])
-@pytest.mark.parametrize("n_rays,samples,pairs", [(1, 1, True), (6143, 31, True), (6143, 33, True), (6143, 95, True), (77, 65, False), (9001, 161, False)])
+@pytest.mark.parametrize("n_rays,samples,pairs", [(1, 1, True), (6143, 31, True), (6143, 33, True), (6143, 95, True), (77, 65, False), (9001, 161, False), (4093, 49, False), (4095, 49, True),
+                                                  (4690, 252, False)])
 def test_equals_the_generic_kernels(lp, kind, channels, dims, dtype, n_rays, samples, pairs):
-    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    if n_cu == 256:
-        assert _pairs(n_rays, samples) == pairs
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert forward_in_pairs(n_rays, samples) == pairs
     kw = dict(hash_size=4096) if kind == HASH else {}
     inp = lp_inputs.make_small(kind, channels=channels, res=(24, 21, 26), mlp_dims=dims, n_rays=n_rays, samples=samples, seed=71 + samples,
                                n_scenes=3, grid_std=0.3, **kw)

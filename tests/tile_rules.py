@@ -1,4 +1,4 @@
-"""The launch and scatter rules of the tile kernels (lp_mfma_bwd_tile.h, lp_tile_scatter.h) on the CPU: which way the steps
+"""The launch and scatter rules of the kernels (lp_mfma_bwd_tile.h, lp_tile_scatter.h, lp_mfma_fwd.hip) on the CPU: which way the steps
 of a problem take, so that a test can tell whether it reaches the branch it is meant for."""
 from collections import Counter
 
@@ -16,6 +16,13 @@ def backward_in_tiles(n_rays, samples, n_cu=256):
     rounds = lambda items: -(-items // waves)
     tile_steps = rounds(-(-n_rays // TILE_RAYS)) * -(-samples // TILE_SAMPLES)
     return 20 * tile_steps <= 21 * (rounds(n_rays) * -(-samples // 32))
+
+
+def forward_in_pairs(n_rays, samples, n_cu=256):
+    """Whether the Renderer's forward takes rays in pairs (lp_mfma_fwd.hip launch_fwd)."""
+    simds, items = 4 * n_cu, (n_rays + 1) // 2
+    share = lambda n: -(-n // simds)
+    return share(items) * -(-samples // 32) <= share(n_rays) * -(-samples // 64) and (samples <= 32 or items >= 2 * simds)
 
 
 def image_row(inp, pixel, step):
