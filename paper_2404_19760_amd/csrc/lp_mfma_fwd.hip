@@ -16,6 +16,8 @@
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
 
+#include <type_traits>
+
 namespace lp {
 
 namespace {
@@ -80,7 +82,8 @@ __global__ __launch_bounds__(kWaves * 64, (kPairs<KIND, C, CG> ? 3 : 1)) void fw
             }
             wave_lds_fence();
         }
-        float tau = 0.0f;                                              // optical depth of earlier steps
+        // optical depth of earlier steps; in pairs, which have twice as many of them, summed in fp64
+        typename std::conditional<PAIRS, double, float>::type tau = 0;
         float acc_r = 0.0f, acc_g = 0.0f, acc_b = 0.0f, acc_d = 0.0f;  // per-lane partial sums
 
         for (int j0 = 0; j0 < S; j0 += kLanes) {
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(kWaves * 64, (kPairs<KIND, C, CG> ? 3 : 1)) void fw
             const float t = near + ((float)j + 0.5f) * delta;
             const float sd = j < S ? fast_softplus(a.z[0]) * delta : 0.0f;
             const float incl = group_scan_incl<kLanes>(sd, lane);
-            const float Tprev = __expf(-(tau + (incl - sd)));
+            const float Tprev = __expf(-(float)(tau + (incl - sd)));
             const float w = Tprev * one_minus_exp_neg(sd);
             acc_r += w * feature_head(a.z[1], identity);
             acc_g += w * feature_head(a.z[2], identity);
@@ -143,13 +146,13 @@ __global__ __launch_bounds__(kWaves * 64, (kPairs<KIND, C, CG> ? 3 : 1)) void fw
         acc_d = ray_sum(acc_d);
         if (lane == 0 || (PAIRS && lane == 32 && ray + 1 < rays.M)) {
             const long long r = ray + half;
-            const float T = __expf(-tau);
+            const float depth = (float)tau, T = __expf(-depth);
             out.rgb[3 * r + 0] = acc_r + T * out.bg[0];
             out.rgb[3 * r + 1] = acc_g + T * out.bg[1];
             out.rgb[3 * r + 2] = acc_b + T * out.bg[2];
-            if (out.alpha) out.alpha[r] = one_minus_exp_neg(tau);
+            if (out.alpha) out.alpha[r] = one_minus_exp_neg(depth);
             if (out.depth) out.depth[r] = acc_d;
-            if (out.cache) out.cache[r] = tau;
+            if (out.cache) out.cache[r] = depth;
         }
     }
 }

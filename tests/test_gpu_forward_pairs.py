@@ -30,3 +30,24 @@ def test_equals_the_generic_kernels(lp, kind, channels, dims, dtype, n_rays, sam
     want = lp.render_fwd(grid, mlp, rays, bg, lp.LP_MATH_GENERIC)
     for name, a, b in zip(("rgb", "alpha", "depth", "cache"), got, want):
         close(a.cpu().numpy(), b.double().cpu().numpy(), FWD_RTOL, f"{name} M={n_rays} S={samples}")
+
+
+@pytest.mark.parametrize("channels,dims", [(16, (16, 32, 4)), (32, (32, 64, 64, 4))])
+def test_optical_depth_of_a_long_ray(lp, channels, dims):
+    """Pairs add up the optical depth over twice as many steps as single rays; it comes out within one rounding of the sum
+    over all samples and one of the last, partial step.  The density is 20 everywhere (softplus(20) = 20 in fp32), so that the
+    sums of whole steps are exact: 32 times one value."""
+    n_rays, samples = 8192, 999
+    assert forward_in_pairs(n_rays, samples)
+    inp = lp_inputs.make_small(VOXEL, channels=channels, res=(8, 9, 7), mlp_dims=dims, n_rays=n_rays, samples=samples, seed=5)
+    grid, mlp, rays, bg = lp.to_device(inp, "cuda:0")
+    for w in mlp.weights:
+        w.zero_()
+    for b in mlp.biases:
+        b.zero_()
+    mlp.biases[-1][0] = 20.0
+    rays.far = rays.near + torch.rand(n_rays, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(6)) + 0.5
+    cache = lp.render_fwd(grid, mlp, rays, bg, lp.LP_MATH_BF16X3)[3].double()
+    one = (20.0 * ((rays.far.double() - rays.near.double()) / samples).float()).double()   # density x length, rounded once
+    want = samples * one
+    assert ((cache - want).abs() <= 2.0 ** -24 * (want + samples % 32 * one) * (1 + 2.0 ** -10)).all(), float(((cache - want).abs() / want).max() * 2 ** 24)
