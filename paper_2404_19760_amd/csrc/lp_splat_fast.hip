@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kWaves * 64) void splat_patch_kernel(GridDev tgt, R
             val[r] = there ? sp.feats[(size_t)at * C + (lane & (C - 1))] : 0.0f;
             probe = fmaf(val[r], 0.0f, probe);   // (an infinite feature would spread over the window)
         }
-        if (__ballot(probe != 0.0f) != 0ull || !patch_holds<KIND, CC>(tgt, q, ok, S)) {
+        if (__ballot(probe != 0.0f) != 0ull || !patch_holds<KIND, kPatchRays, CC>(tgt, q, ok, S, lane)) {
             one_by_one(j_from, j_to);
             continue;
         }

@@ -269,7 +269,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev
     for (long long patch = sched.first; patch < sched.end; patch += sched.stride) {
         bool ok;
         const RayGeom q = load_ray_geom(rays, grid.ray(patch, lane & (kPatchRays - 1), ok));
-        bool whole = patch_holds<KIND, CC>(tgt, q, ok, S);
+        bool whole = patch_holds<KIND, kPatchRays, CC>(tgt, q, ok, S, lane);
         f32x4 acc[C / 16];
 #pragma unroll
         for (int h = 0; h < C / 16; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};

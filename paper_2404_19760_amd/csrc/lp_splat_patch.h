@@ -337,26 +337,38 @@ __device__ __forceinline__ size_t scene_texel(const GridDev& g, int pl, int scen
     else return (size_t)scene * g.N[0] * g.N[1] * g.N[2];
 }
 
-// Whether the rays of a patch can be marched together: in one scene, finite, and not far apart at both ends (a step's
-// window is checked again at every step).
-template <int KIND, bool CC>
-__device__ __forceinline__ bool patch_holds(const GridDev& g, const RayGeom& q, bool ok, int S)
+// Whether the rays of a patch can be marched together: in one scene, finite, and at both ends near their neighbours in the patch
+// and not far apart as a whole (a step's window is checked again at every step).  The neighbours: a patch across the border of two
+// views of a small structure lies within any bound on the whole that an image's patches need, and its steps would go ray by ray
+// (2 x 157 x 139 rays x 237 points, 42 x 31 x 34 x 16 voxels: 20 such patches of 1400 took 2.0 of 2.2 ms).
+template <int KIND, int RAYS, bool CC>
+__device__ __forceinline__ bool patch_holds(const GridDev& g, const RayGeom& q, bool ok, int S, int lane)
 {
     const float geometry[8] = {q.ox, q.oy, q.oz, q.dx, q.dy, q.dz, q.near, q.delta};
     float probe = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) probe = fmaf(geometry[i], 0.0f, probe);
     const Cell3 c0 = sample_cell<CC>(g, q, 0), c1 = sample_cell<CC>(g, q, S - 1);
-    constexpr int kApart = 24;   // texels
+    constexpr int kApart = 24, kNext = 5;   // texels: of the whole, of neighbours
     bool bad = probe != 0.0f;
     const unsigned long long oks = __ballot(ok);
     if (oks == 0ull) return false;
     const int lead = __builtin_ctzll(oks);
     auto of_lead = [&](int v) { return __builtin_amdgcn_readlane(v, lead); };
     bad = bad || q.scene != of_lead(q.scene);
+    // (lanes of the wave's upper part compare with what the lower part holds as well)
+    const int ray = lane & (RAYS - 1), left = ray % PatchGrid<RAYS>::kW ? ray - 1 : ray, above = ray >= PatchGrid<RAYS>::kW ? ray - PatchGrid<RAYS>::kW : ray;
+    const bool has_left = (oks >> left) & 1ull, has_above = (oks >> above) & 1ull;
+    auto far_from_next = [&](int v) {
+        const int l = abs(v - __shfl(v, left, 64)), u = abs(v - __shfl(v, above, 64));   // (all lanes take part)
+        return (has_left && l > kNext) || (has_above && u > kNext);
+    };
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 3; ++a) {
         bad = bad || abs(c0.i[a] - of_lead(c0.i[a])) > kApart || abs(c1.i[a] - of_lead(c1.i[a])) > kApart;
+        const bool far0 = far_from_next(c0.i[a]), far1 = far_from_next(c1.i[a]);
+        bad = bad || far0 || far1;
+    }
     return __ballot(ok && bad) == 0ull;
 }
 

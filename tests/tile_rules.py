@@ -59,6 +59,72 @@ def image_row(inp, pixel, step):
     return row if close else 0
 
 
+SLOTS = {32: 224, 16: 160}   # texels of a step of a patch, by its rays
+PATCH_TEXELS, PATCH_POINTS = 1024, 8
+
+
+def patches(inp, row, n_rays=32):
+    """The patches of an image whose rows are `row` long, as lists of rays (-1: none there)."""
+    w = n_rays // 4
+    lines = -(-inp.n_rays // row)
+    for y0 in range(0, lines, 4):
+        for x0 in range(0, row, w):
+            at = (y0 + np.arange(4))[:, None] * row + x0 + np.arange(w)
+            yield np.where((x0 + np.arange(w) < row) & (at < inp.n_rays), at, -1)
+
+
+def push_segment(n_rays, samples, n_cu=256):
+    """Points of an item of the Splatter's patch push."""
+    waves = (n_cu + 7) // 8 * 8 * 4
+    points = (n_rays // 32 + 1) * samples // (8 * waves)
+    return min(max(points // PATCH_POINTS * PATCH_POINTS, PATCH_POINTS), samples)
+
+
+def patch_routes(inp, row, n_rays=32, seg=None):
+    """Counter of how the points of an image's patches are taken (lp_splat_patch.h): "lines": a patch whose rays go one line after
+    the other (or, its gradient, one by one), 8 | 4 | 1: points of a step of all its rays, "ray": one point of one ray."""
+    c = cells(inp)
+    scene = inp.scene if inp.scene is not None else np.zeros(inp.n_rays, int)
+    planes = [(0, 1), (1, 2), (2, 0)] if inp.kind == TRIPLANE else [(0, 1, 2)]
+    corners = {n: np.stack(np.meshgrid(*[(0, 1)] * n, indexing="ij"), -1).reshape(-1, n) for n in (2, 3)}
+    routes = Counter()
+
+    def fits(at):   # [points][axes]
+        if np.prod(at.max(0) - at.min(0) + 2) > PATCH_TEXELS:
+            return False
+        return len(np.unique((at[:, None] + corners[at.shape[1]]).reshape(-1, at.shape[1]), axis=0)) <= SLOTS[n_rays]
+
+    for patch in patches(inp, row, n_rays):
+        there = patch >= 0
+        ends = c[patch][:, :, [0, -1]]
+        lead = ends[there][0]
+        apart = np.abs(ends - lead).max((2, 3)) > 24
+        apart[:, 1:] |= there[:, :-1] & (np.abs(np.diff(ends, axis=1)).max((2, 3)) > 5)
+        apart[1:] |= there[:-1] & (np.abs(np.diff(ends, axis=0)).max((2, 3)) > 5)
+        if (there & (apart | (scene[patch] != scene[patch[there][0]]))).any():
+            routes["lines"] += 1
+            continue
+        rays = patch[there]
+        for first in range(0, inp.samples, seg or inp.samples):
+            for j0 in range(first, min(first + (seg or inp.samples), inp.samples), PATCH_POINTS):
+                end = min(first + (seg or inp.samples), inp.samples)
+                for axes in planes:
+                    at, n = 0, PATCH_POINTS
+                    while at < PATCH_POINTS:
+                        points = c[rays][:, j0 + at:min(j0 + at + n, end)][..., axes].reshape(-1, len(axes))
+                        if len(points) == 0 or fits(points):
+                            routes[n] += len(points) > 0
+                        elif n > 1:
+                            n = 4 if n > 4 else 1
+                            continue
+                        else:
+                            routes["ray"] += 1
+                        at += n
+                        if at % 4 == 0:
+                            n = 4
+    return routes
+
+
 def cells(inp):
     """[rays][samples][3] cell indices."""
     delta = (inp.far.astype(np.float64) - inp.near) / inp.samples
