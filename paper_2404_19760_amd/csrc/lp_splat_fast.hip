@@ -60,7 +60,9 @@ __device__ __forceinline__ void push_rays(const GridDev& tgt, const RaysDev& ray
         for (int j0 = j_from; j0 < j_to; j0 += step) {
             const int j = j0 + k;
             const Cell3 c = sample_cell<CC>(tgt, q, min(j, rays.S - 1));
-            scatter_step<KIND, C, Scatter::kPushRay>(tgt, sp.theta, scene, area, area_ptr, c, val, lane, tile,
+            uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
+            refresh(lane_here);
+            scatter_step<KIND, C, Scatter::kPushRay>(tgt, sp.theta, scene, area, area_ptr, c, val, lane_here, tile,
                                                      sp.theta_w, ray_ok && j < j_to);
         }
     }
@@ -77,12 +79,15 @@ __device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& 
     return find_row(g, rays, KIND == LP_GRID_TRIPLANE ? 1.5 : 0.9, 1e30);
 }
 
-// Rays in their order.  `patches`: the patch kernel has been launched before and takes what it finds to be an image.
-template <int KIND, int C, bool CC>
-__global__ __launch_bounds__(kWaves * 64, 3) void splat_naive_kernel(GridDev tgt, RaysDev rays, SplatDev sp, PushOrder order, bool patches)
+// Rays in their order.  PATCHES: the patch kernel has been launched before and takes what it finds to be an image (an
+// instantiation of its own: launches of few rays, which never look for one, took 1 us of 40 longer with the search in their code).
+template <int KIND, int C, bool CC, bool PATCHES>
+__global__ __launch_bounds__(kWaves * 64, 3) void splat_naive_kernel(GridDev tgt, RaysDev rays, SplatDev sp, PushOrder order)
 {
     __shared__ __align__(16) char areas[kWaves][kArea];
-    if (patches && image_row<KIND>(tgt, rays) != 0) return;
+    if constexpr (PATCHES) {
+        if (image_row<KIND>(tgt, rays) != 0) return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rays_per_item = order.tiles ? kTileRays : 1;
@@ -228,8 +233,8 @@ hipError_t launch(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, i
     blocks = (blocks + 7) / 8 * 8;
     const PushOrder order = push_order(rays, blocks * kWaves, kWaves);
     if (blocks > order.n_groups) blocks = (order.n_groups + 7) / 8 * 8;
-    hipLaunchKernelGGL((splat_naive_kernel<KIND, C, CC>), dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt,
-                       rays, sp, order, patches);
+    auto kernel = patches ? splat_naive_kernel<KIND, C, CC, true> : splat_naive_kernel<KIND, C, CC, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt, rays, sp, order);
     return hipGetLastError();
 }
 

@@ -157,12 +157,14 @@ __device__ __forceinline__ void ray_gradient(const GridDev& tgt, const RaysDev& 
 constexpr long long kMinRays = 65536, kMinPoints = 4000000;
 __device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& rays) { return find_row(g, rays, 0.9, 2.0); }
 
-// Rays in their order.  `patches`: the patch kernel has been launched before and takes what it finds to be an image.
-template <int KIND, int C, bool CC>
-__global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tgt, RaysDev rays, SplatDev sp, bool patches)
+// Rays in their order.  PATCHES: the patch kernel has been launched before and takes what it finds to be an image.
+template <int KIND, int C, bool CC, bool PATCHES>
+__global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tgt, RaysDev rays, SplatDev sp)
 {
     __shared__ __align__(16) char records[kWaves][PushRecords<KIND>::kBytes];
-    if (patches && image_row(tgt, rays) != 0) return;
+    if constexpr (PATCHES) {
+        if (image_row(tgt, rays) != 0) return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)records[wave];
@@ -308,8 +310,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev
 template <int KIND, int C, bool CC>
 hipError_t launch_t(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu, hipStream_t stream)
 {
-    const bool patches = KIND != LP_GRID_TRIPLANE && rays.M >= kMinRays && rays.M * rays.S >= kMinPoints;
-    if constexpr (KIND != LP_GRID_TRIPLANE) if (patches) {
+    constexpr bool kMayPatch = KIND != LP_GRID_TRIPLANE;
+    const bool patches = kMayPatch && rays.M >= kMinRays && rays.M * rays.S >= kMinPoints;
+    if constexpr (kMayPatch) if (patches) {
         auto kernel = splat_patch_bwd_kernel<KIND, C, CC>;
         const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWaves * kPatchBytes);
         if (e != hipSuccess) return e;
@@ -320,7 +323,8 @@ hipError_t launch_t(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp,
     const long long need = (rays.M + kWaves - 1) / kWaves;
     if (blocks > need) blocks = need;
     blocks = (blocks + 7) / 8 * 8;
-    hipLaunchKernelGGL((splat_naive_bwd_kernel<KIND, C, CC>), dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt, rays, sp, patches);
+    auto kernel = patches ? splat_naive_bwd_kernel<KIND, C, CC, kMayPatch> : splat_naive_bwd_kernel<KIND, C, CC, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), 0, stream, tgt, rays, sp);
     return hipGetLastError();
 }
 
