@@ -72,6 +72,9 @@ __device__ __forceinline__ void push_rays(const GridDev& tgt, const RaysDev& ray
 // points a ray), push time in tiles of a row over that in patches: 1.3 .. 1.5 at 0.66 texels from pixel to pixel, 2.1 .. 3.2 at
 // 0.2 and 0.33, 0.25 .. 0.9 at 1.3 (a step then takes one point at a time). 160^2 triplanes 1.2 .. 5.6 at 1.3, 0.45 .. 1.75 at
 // 2.1.  Over structures of 24 and 64 texels an axis: 384 rays 0.04 .. 1.5, 1600 rays 0.75 .. 3.6, 3072 rays 1.7 .. 6.4.
+// What is no image pays for the question, from 2048 rays on: lists 2 to 4 us for the second launch (3072 rays x 24 points, 80 to
+// 210 us: 0.97 .. 0.98 of the speed without it), images whose pixels are too far apart 4 to 8 us (2112 rays, 80 to 640 us:
+// 0.92 .. 0.99, the slowest at 1.0 to 1.2 texels a pixel, where a row is looked for and found).
 constexpr long long kMinRays = 2048;
 template <int KIND>
 __device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& rays)
@@ -154,8 +157,8 @@ __device__ __forceinline__ bool push_points(const GridDev& g, const SplatDev& sp
     return true;
 }
 
-// Images, patch after patch (lp_splat_patch.h).  An item is a patch and `seg` points of its rays.  Where a patch's rays are not
-// neighbours or not finite, and at steps that reach too many texels, its rays are pushed line by line like a list's.
+// Images, patch after patch (lp_splat_patch.h).  An item is a patch and `seg` points of its rays.  Where rays of a line are not
+// neighbours or not finite, they are pushed line by line like a list's.
 template <int KIND, int C, bool CC>
 __global__ __launch_bounds__(kWaves * 64) void splat_patch_kernel(GridDev tgt, RaysDev rays, SplatDev sp, int seg)
 {
@@ -178,40 +181,44 @@ __global__ __launch_bounds__(kWaves * 64) void splat_patch_kernel(GridDev tgt, R
         if (item >= n_items) continue;
         const long long patch = item % grid.count;
         const int j_from = (int)(item / grid.count) * seg, j_to = min(j_from + seg, S);
-        auto one_by_one = [&](int from, int to) {
-            for (int t = 0; t < kPatchRays / kTileRays; ++t) {
-                long long first, end;
-                grid.line(patch, t / 2, first, end);
-                first += (t & 1) * kTileRays;
-                end = min(end, first + kTileRays);
-                if (first < end) push_rays<KIND, C, CC>(tgt, rays, sp, first, end, from, to, true, area_ptr, lane);
-            }
-        };
-        bool ok;
-        const RayGeom q = load_ray_geom(rays, grid.ray(patch, lane & (kPatchRays - 1), ok));
+        bool there;
+        const RayGeom q = load_ray_geom(rays, grid.ray(patch, lane & (kPatchRays - 1), there));
         // features: matrix operand, lane = channel, register r = ray kRays (lane / C) + r
         constexpr int kRays = C / 2;
         float val[kRays], probe = 0.0f;
 #pragma unroll
         for (int r = 0; r < kRays; ++r) {
-            bool there;
-            const long long at = grid.ray(patch, kRays * (lane / C) + r, there);
-            val[r] = there ? sp.feats[(size_t)at * C + (lane & (C - 1))] : 0.0f;
+            bool has;
+            const long long at = grid.ray(patch, kRays * (lane / C) + r, has);
+            val[r] = has ? sp.feats[(size_t)at * C + (lane & (C - 1))] : 0.0f;
             probe = fmaf(val[r], 0.0f, probe);   // (an infinite feature would spread over the window)
         }
-        if (__ballot(probe != 0.0f) != 0ull || !patch_holds<KIND, kPatchRays, CC>(tgt, q, ok, S, lane)) {
-            one_by_one(j_from, j_to);
-            continue;
-        }
-        const int scene = __builtin_amdgcn_readfirstlane(__shfl(q.scene, __builtin_ctzll(__ballot(ok)), 64));
-        for (int j0 = j_from; j0 < j_to; j0 += kPatchPoints) {
-            const PatchCells cells = patch_cells<CC>(tgt, q, ok, j0, j_to, S);
+        const bool finite = __ballot(probe != 0.0f) == 0ull;
+        patch_parts(patch_lines<kPatchRays, CC>(tgt, q, there, S, lane), [&](int y0, int y1, bool by_lines) {
+            const int y = (lane & (kPatchRays - 1)) / PatchGrid<kPatchRays>::kW;
+            const bool ok = there && y >= y0 && y < y1;
+            const unsigned long long oks = __ballot(ok);
+            if (oks == 0ull) return;
+            if (by_lines || !finite) {
+                for (int t = 2 * y0; t < 2 * y1; ++t) {
+                    long long first, end;
+                    grid.line(patch, t / 2, first, end);
+                    first += (t & 1) * kTileRays;
+                    end = min(end, first + kTileRays);
+                    if (first < end) push_rays<KIND, C, CC>(tgt, rays, sp, first, end, j_from, j_to, true, area_ptr, lane);
+                }
+                return;
+            }
+            const int scene = __builtin_amdgcn_readfirstlane(__shfl(q.scene, __builtin_ctzll(oks), 64));
+            for (int j0 = j_from; j0 < j_to; j0 += kPatchPoints) {
+                const PatchCells cells = patch_cells<CC>(tgt, q, ok, j0, j_to, S);
 #pragma unroll 1
-            for (int pl = 0; pl < kPlanes; ++pl)
-                patch_steps<kPatchRays>([&](int from, int len, int only) {
-                    return push_points<KIND, C>(tgt, sp, scene, area, cells, from, len, only, pl, val, lane);
-                });
-        }
+                for (int pl = 0; pl < kPlanes; ++pl)
+                    patch_steps<kPatchRays>([&](int from, int len, int only) {
+                        return push_points<KIND, C>(tgt, sp, scene, area, cells, from, len, only, pl, val, lane);
+                    });
+            }
+        });
     }
 }
 

@@ -252,8 +252,8 @@ __device__ __forceinline__ bool pull_points(const GridDev& g, const SplatDev& sp
     return true;
 }
 
-// Images, patch after patch (lp_splat_patch.h).  A patch whose rays are not neighbours or not finite, or that reads a gradient
-// that is not (a product would spread it over all of its rays), is taken ray by ray.
+// Images, patch after patch (lp_splat_patch.h).  A part of a patch whose rays are not neighbours or not finite, or that reads a
+// gradient that is not (a product would spread it over all of its rays), is taken ray by ray.
 template <int KIND, int C, bool CC>
 __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev tgt, RaysDev rays, SplatDev sp)
 {
@@ -269,41 +269,59 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev
     const int S = rays.S;
     const RaySchedule sched = ray_schedule(grid.count, kWaves);
     for (long long patch = sched.first; patch < sched.end; patch += sched.stride) {
-        bool ok;
-        const RayGeom q = load_ray_geom(rays, grid.ray(patch, lane & (kPatchRays - 1), ok));
-        bool whole = patch_holds<KIND, kPatchRays, CC>(tgt, q, ok, S, lane);
-        f32x4 acc[C / 16];
+        constexpr int kW = PatchGrid<kPatchRays>::kW;
+        auto my_ray = [&](bool& there) {
+            uint32_t lane_here = lane;   // (loaded for every part anew: kept beside the texels of a step it would cost spills)
+            refresh(lane_here);
+            return load_ray_geom(rays, grid.ray(patch, lane_here & (kPatchRays - 1), there));
+        };
+        unsigned lines;
+        {
+            bool there;
+            const RayGeom q = my_ray(there);
+            lines = patch_lines<kPatchRays, CC>(tgt, q, there, S, lane);
+        }
+        patch_parts(lines, [&](int y0, int y1, bool by_rays) {
+            bool there;
+            const RayGeom q = my_ray(there);
+            const int y = (lane & (kPatchRays - 1)) / kW;
+            const bool ok = there && y >= y0 && y < y1;
+            const unsigned long long oks = __ballot(ok);
+            if (oks == 0ull) return;
+            bool whole = !by_rays;
+            f32x4 acc[C / 16];
 #pragma unroll
-        for (int h = 0; h < C / 16; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (whole) {
-            const int scene = __builtin_amdgcn_readfirstlane(__shfl(q.scene, __builtin_ctzll(__ballot(ok)), 64));
-            float probe = 0.0f;
-            for (int j0 = 0; j0 < S; j0 += kPatchPoints) {
-                const PatchCells cells = patch_cells<CC>(tgt, q, ok, j0, S, S);
+            for (int h = 0; h < C / 16; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (whole) {
+                const int scene = __builtin_amdgcn_readfirstlane(__shfl(q.scene, __builtin_ctzll(oks), 64));
+                float probe = 0.0f;
+                for (int j0 = 0; j0 < S; j0 += kPatchPoints) {
+                    const PatchCells cells = patch_cells<CC>(tgt, q, ok, j0, S, S);
 #pragma unroll 1
-                for (int pl = 0; pl < kPlanes; ++pl)
-                    patch_steps<kPatchRays>([&](int from, int len, int only) {
-                        return pull_points<KIND, C>(tgt, sp, scene, area, cells, from, len, only, pl, acc, probe, lane);
-                    });
+                    for (int pl = 0; pl < kPlanes; ++pl)
+                        patch_steps<kPatchRays>([&](int from, int len, int only) {
+                            return pull_points<KIND, C>(tgt, sp, scene, area, cells, from, len, only, pl, acc, probe, lane);
+                        });
+                }
+                whole = __ballot(probe != 0.0f) == 0ull;
             }
-            whole = __ballot(probe != 0.0f) == 0ull;
-        }
-        for (int i = 0; i < kPatchRays; ++i) {
-            if (whole) break;
-            bool there;
-            const long long at = grid.ray(patch, i, there);
-            if (there) ray_gradient<KIND, C, CC>(tgt, rays, sp, at, area, lane);
-        }
+            for (int i = kW * y0; i < kW * y1; ++i) {
+                if (whole) break;
+                bool has;
+                const long long at = grid.ray(patch, i, has);
+                if (has) ray_gradient<KIND, C, CC>(tgt, rays, sp, at, area, lane);
+            }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {   // register r: ray 4 (lane / 16) + r, the lane's channels
-            bool there;
-            const long long at = grid.ray(patch, 4 * (lane >> 4) + r, there);
-            if (!whole || !there) continue;
-            float* out = sp.d_feats + (size_t)at * C + C / 16 * (lane & 15);
-            if constexpr (C == 32) *reinterpret_cast<f32x2*>(out) = f32x2{acc[0][r], acc[C / 16 - 1][r]};
-            else *out = acc[0][r];
-        }
-        wave_lds_fence();
+            for (int r = 0; r < 4; ++r) {   // register r: ray 4 (lane / 16) + r, the lane's channels
+                bool has;
+                const long long at = grid.ray(patch, 4 * (lane >> 4) + r, has);
+                if (!whole || !has || (lane >> 4) < y0 || (lane >> 4) >= y1) continue;
+                float* out = sp.d_feats + (size_t)at * C + C / 16 * (lane & 15);
+                if constexpr (C == 32) *reinterpret_cast<f32x2*>(out) = f32x2{acc[0][r], acc[C / 16 - 1][r]};
+                else *out = acc[0][r];
+            }
+            wave_lds_fence();
+        });
     }
 }
 

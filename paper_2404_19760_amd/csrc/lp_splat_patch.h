@@ -47,7 +47,7 @@ __device__ __forceinline__ double texels_between(const GridDev& g, const RaysDev
 
 // Length of a row if the list of rays looks like the pixels of images, row after row: the first ray whose end point is
 // back near the first ray's, with the ray behind it and the one a row further on where they then have to be; and if neighbouring pixels are at most
-// `pixel` texels apart in the middle of their rays, and consecutive points of a ray `step` texels.  0 otherwise.  All
+// `pixel` texels apart in the middle of their rays (tested where the list is half over, then well inside an image), and consecutive points of a ray `step` texels.  0 otherwise.  All
 // threads of the workgroup call it and receive the same value, and so does every workgroup and the other kernel of a pair, of
 // which exactly one must find that the work is its own: no contraction of products and sums, which the compiler may choose
 // differently in each.
@@ -76,6 +76,11 @@ __device__ __forceinline__ long long find_row(const GridDev& g, const RaysDev& r
     // the second pixel's step is the first's
     const float two[3] = {p1[0] + ahead[0], p1[1] + ahead[1], p1[2] + ahead[2]};
     if (!(distance2(two, p2) < 0.25f * along)) return 0;
+    // Pixels far apart: no row to look for.  (Two pairs of neighbours, one of which may lie across two rows; in contract
+    // coordinates pixels may be nearer each other in the middle of an image than here.  Looking for a row takes 4 us: 2112 rays x 64 points into 86^3 x 16 voxels, 1.4 texels a pixel, are pushed in 111.)
+    const long long mid = last / 2;
+    const double t_mid = 0.5 * ((double)rays.near[mid] + (double)rays.far[mid]);
+    if (!(g.contract > 0.0) && texels_between(g, rays, mid, t_mid, mid + 1, t_mid) > pixel && texels_between(g, rays, mid + 1, t_mid, min(mid + 2, last), t_mid) > pixel) return 0;
     if (threadIdx.x == 0) found = 0x7fffffff;
     __syncthreads();
     const long long limit = min((long long)kMaxRow, last / 2);   // (rays k + 1 and 2 k exist)
@@ -337,39 +342,51 @@ __device__ __forceinline__ size_t scene_texel(const GridDev& g, int pl, int scen
     else return (size_t)scene * g.N[0] * g.N[1] * g.N[2];
 }
 
-// Whether the rays of a patch can be marched together: in one scene, finite, and at both ends near their neighbours in the patch
-// and not far apart as a whole (a step's window is checked again at every step).  The neighbours: a patch across the border of two
-// views of a small structure lies within any bound on the whole that an image's patches need, and its steps would go ray by ray
-// (2 x 157 x 139 rays x 237 points, 42 x 31 x 34 x 16 voxels: 20 such patches of 1400 took 2.0 of 2.2 ms).
-template <int KIND, int RAYS, bool CC>
-__device__ __forceinline__ bool patch_holds(const GridDev& g, const RayGeom& q, bool ok, int S, int lane)
+// How the lines of a patch are taken: in parts of consecutive lines, each marched as one.  Bit y: line y begins a part, as its
+// rays do not lie near those of line y - 1 at both ends: the border of two views, mostly.  (However small the structure is: no
+// bound on the whole of a patch that an image's need tells the two apart, and steps across a border go one point of one ray
+// at a time: 20 such patches of 1400 took 2.0 of 2.2 ms, 2 x 157 x 139 rays x 237 points, 42 x 31 x 34 x 16 voxels.)
+// Bit 4 + y: not all rays of line y near each other, in one scene and finite; its part goes ray by ray.
+template <int RAYS, bool CC>
+__device__ __forceinline__ unsigned patch_lines(const GridDev& g, const RayGeom& q, bool ok, int S, int lane)
 {
+    constexpr int kW = PatchGrid<RAYS>::kW, kNext = 5;   // kNext: texels between neighbours
     const float geometry[8] = {q.ox, q.oy, q.oz, q.dx, q.dy, q.dz, q.near, q.delta};
     float probe = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) probe = fmaf(geometry[i], 0.0f, probe);
     const Cell3 c0 = sample_cell<CC>(g, q, 0), c1 = sample_cell<CC>(g, q, S - 1);
-    constexpr int kApart = 24, kNext = 5;   // texels: of the whole, of neighbours
-    bool bad = probe != 0.0f;
     const unsigned long long oks = __ballot(ok);
-    if (oks == 0ull) return false;
-    const int lead = __builtin_ctzll(oks);
-    auto of_lead = [&](int v) { return __builtin_amdgcn_readlane(v, lead); };
-    bad = bad || q.scene != of_lead(q.scene);
-    // (lanes of the wave's upper part compare with what the lower part holds as well)
-    const int ray = lane & (RAYS - 1), left = ray % PatchGrid<RAYS>::kW ? ray - 1 : ray, above = ray >= PatchGrid<RAYS>::kW ? ray - PatchGrid<RAYS>::kW : ray;
-    const bool has_left = (oks >> left) & 1ull, has_above = (oks >> above) & 1ull;
-    auto far_from_next = [&](int v) {
-        const int l = abs(v - __shfl(v, left, 64)), u = abs(v - __shfl(v, above, 64));   // (all lanes take part)
-        return (has_left && l > kNext) || (has_above && u > kNext);
-    };
+    const int ray = lane & (RAYS - 1), left = ray % kW ? ray - 1 : ray, above = ray >= kW ? ray - kW : ray;
+    auto apart_from = [&](int other) {   // (all lanes take part)
+        int most = 0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        bad = bad || abs(c0.i[a] - of_lead(c0.i[a])) > kApart || abs(c1.i[a] - of_lead(c1.i[a])) > kApart;
-        const bool far0 = far_from_next(c0.i[a]), far1 = far_from_next(c1.i[a]);
-        bad = bad || far0 || far1;
+        for (int a = 0; a < 3; ++a)
+            most = max(most, max(abs(c0.i[a] - __shfl(c0.i[a], other, 64)), abs(c1.i[a] - __shfl(c1.i[a], other, 64))));
+        const int scene = __shfl(q.scene, other, 64);
+        return ((oks >> other) & 1ull) != 0ull && (most > kNext || scene != q.scene);
+    };
+    const bool from_above = apart_from(above), from_left = apart_from(left);
+    const unsigned long long breaks = __ballot(ok && from_above), bad = __ballot(ok && (from_left || probe != 0.0f));
+    unsigned lines = 1u;
+#pragma unroll
+    for (int y = 0; y < kPatchH; ++y) {
+        const unsigned long long line = ((1ull << kW) - 1ull) << (y * kW);
+        lines |= ((breaks & line) ? 1u << y : 0u) | ((bad & line) ? 16u << y : 0u);
     }
-    return __ballot(ok && bad) == 0ull;
+    return lines;
+}
+
+// Calls part(first line, line behind the last, whether its rays go one by one) for every part.
+template <class Part>
+__device__ __forceinline__ void patch_parts(unsigned lines, Part part)
+{
+    for (int y0 = 0; y0 < kPatchH;) {
+        int y1 = y0 + 1;
+        while (y1 < kPatchH && !((lines >> y1) & 1u)) ++y1;
+        part(y0, y1, ((lines >> (4 + y0)) & ((1u << (y1 - y0)) - 1u)) != 0u);
+        y0 = y1;
+    }
 }
 
 }  // namespace

@@ -32,6 +32,19 @@ def image_row(inp, pixel, step):
     along, ahead = d2(end[0], end[1]), end[1] - end[0]
     if not d2(end[1] + ahead, end[2]) < 0.25 * along:
         return 0
+    def texel(r, t):
+        x = inp.origins[r].astype(np.float64) + t * inp.dirs[r]
+        if inp.contract_a:
+            a, m = inp.contract_a, np.maximum(np.abs(x), 1.0)
+            x = np.where(np.abs(x) <= 1.0, 0.5 * a * x, 0.5 * np.sign(x) * ((2.0 - a) * (1.0 - 1.0 / m) + a))
+        lo, hi, n = (np.asarray(v, dtype=np.float64) for v in (inp.aabb_min, inp.aabb_max, inp.res))
+        return np.clip((x - lo) * (n - 1) / (hi - lo), 0, n - 1)
+
+    apart = lambda a, b: np.sqrt(((a - b) ** 2).sum())
+    at = (inp.n_rays - 1) // 2
+    t = 0.5 * (float(inp.near[at]) + float(inp.far[at]))
+    if not inp.contract_a and min(apart(texel(at + i, t), texel(min(at + i + 1, inp.n_rays - 1), t)) for i in (0, 1)) > pixel:
+        return 0
     k = np.arange(8, min(4096, (inp.n_rays - 1) // 2) + 1)
     back = d2(end[k], end[0])
     k = k[(back < 16 * along) & (back < 0.25 * d2(end[k - 1], end[0])) & (d2(end[k + 1], end[k] + ahead) < 0.25 * along) &
@@ -44,17 +57,8 @@ def image_row(inp, pixel, step):
         return 0
     at = min(inp.n_rays // row - 1, row // 2) * row + row // 2
 
-    def texel(r, t):
-        x = inp.origins[r].astype(np.float64) + t * inp.dirs[r]
-        if inp.contract_a:
-            a, m = inp.contract_a, np.maximum(np.abs(x), 1.0)
-            x = np.where(np.abs(x) <= 1.0, 0.5 * a * x, 0.5 * np.sign(x) * ((2.0 - a) * (1.0 - 1.0 / m) + a))
-        lo, hi, n = (np.asarray(v, dtype=np.float64) for v in (inp.aabb_min, inp.aabb_max, inp.res))
-        return np.clip((x - lo) * (n - 1) / (hi - lo), 0, n - 1)
-
     near, far = float(inp.near[at]), float(inp.far[at])
     t = 0.5 * (near + far)
-    apart = lambda a, b: np.sqrt(((a - b) ** 2).sum())
     close = apart(texel(at, t), texel(at + 1, t)) <= pixel and apart(texel(at, t), texel(at, t + (far - near) / inp.samples)) <= step
     return row if close else 0
 
@@ -81,8 +85,8 @@ def push_segment(n_rays, samples, n_cu=256):
 
 
 def patch_routes(inp, row, n_rays=32, seg=None):
-    """Counter of how the points of an image's patches are taken (lp_splat_patch.h): "lines": a patch whose rays go one line after
-    the other (or, its gradient, one by one), 8 | 4 | 1: points of a step of all its rays, "ray": one point of one ray."""
+    """Counter of how the points of an image's patches are taken (lp_splat_patch.h): "part": a patch that falls into parts, "lines": a
+    part whose rays go line by line (its gradient: ray by ray), 8 | 4 | 1: points of a step of all rays, "ray": one point of one ray."""
     c = cells(inp)
     scene = inp.scene if inp.scene is not None else np.zeros(inp.n_rays, int)
     planes = [(0, 1), (1, 2), (2, 0)] if inp.kind == TRIPLANE else [(0, 1, 2)]
@@ -94,20 +98,10 @@ def patch_routes(inp, row, n_rays=32, seg=None):
             return False
         return len(np.unique((at[:, None] + corners[at.shape[1]]).reshape(-1, at.shape[1]), axis=0)) <= SLOTS[n_rays]
 
-    for patch in patches(inp, row, n_rays):
-        there = patch >= 0
-        ends = c[patch][:, :, [0, -1]]
-        lead = ends[there][0]
-        apart = np.abs(ends - lead).max((2, 3)) > 24
-        apart[:, 1:] |= there[:, :-1] & (np.abs(np.diff(ends, axis=1)).max((2, 3)) > 5)
-        apart[1:] |= there[:-1] & (np.abs(np.diff(ends, axis=0)).max((2, 3)) > 5)
-        if (there & (apart | (scene[patch] != scene[patch[there][0]]))).any():
-            routes["lines"] += 1
-            continue
-        rays = patch[there]
+    def march(rays):
         for first in range(0, inp.samples, seg or inp.samples):
-            for j0 in range(first, min(first + (seg or inp.samples), inp.samples), PATCH_POINTS):
-                end = min(first + (seg or inp.samples), inp.samples)
+            end = min(first + (seg or inp.samples), inp.samples)
+            for j0 in range(first, end, PATCH_POINTS):
                 for axes in planes:
                     at, n = 0, PATCH_POINTS
                     while at < PATCH_POINTS:
@@ -122,6 +116,20 @@ def patch_routes(inp, row, n_rays=32, seg=None):
                         at += n
                         if at % 4 == 0:
                             n = 4
+
+    for patch in patches(inp, row, n_rays):
+        there = patch >= 0
+        ends = c[patch][:, :, [0, -1]]
+        other = lambda axis: (np.abs(np.diff(ends, axis=axis)).max((2, 3)) > 5) | (np.diff(scene[patch], axis=axis) != 0)
+        bad = (there[:, 1:] & there[:, :-1] & other(1)).any(1)
+        starts = [0] + [y for y in range(1, 4) if (there[y] & there[y - 1] & other(0)[y - 1]).any()] + [4]
+        routes["part"] += sum(there[y0:y1].any() for y0, y1 in zip(starts, starts[1:])) > 1
+        for y0, y1 in zip(starts, starts[1:]):
+            rays = patch[y0:y1][there[y0:y1]]
+            if len(rays) and bad[y0:y1].any():
+                routes["lines"] += 1
+            elif len(rays):
+                march(rays)
     return routes
 
 
