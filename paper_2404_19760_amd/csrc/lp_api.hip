@@ -853,7 +853,7 @@ lp_status lp_splat_bwd_workspace_bytes(const lp_grid* target, const lp_rays* ray
     if (compute_units(&n_cu, &err)) return fail(LP_ERR_HIP, err);
     const bool fast = m.n_layers > 0 && lp::splat_mfma_supported(g, m, sd);
     const int records = fast ? lp::mfma_bwd_records(n_cu) : generic_bwd_blocks(n_cu);
-    *bytes = align256(sizeof(float) * (size_t)records * (size_t)ws_stride(m)) + 256;
+    *bytes = align256(sizeof(float) * (size_t)records * (size_t)ws_stride(m)) + 256;   // (behind the records: the matrix-core kernels' choice)
     return LP_OK;
 }
 

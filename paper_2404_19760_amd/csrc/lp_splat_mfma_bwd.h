@@ -18,9 +18,13 @@
 //
 // What bounds it: one wave per SIMD (the accumulators fill its registers) that waits for its own loads and LDS reads half of
 // the time; the matrix cores are busy 21 %.  160^3 x 32 voxels, prior alike, MLP 67-64-64-32, 4 x 64^2 rays x 160 points: ray by
-// ray 6.8 lines of atomic adds per point, 1.48 ms; in tiles 4.6 lines, 1.38; with all texel loads of a gather under way at once
-// 1.36.  160^2 triplanes forward and backward 4.57 -> 2.29.  Tiles only where a wave has no more steps that way: at twice as
-// many (1600 rays x 160 points) 0.53 to 0.97 times as fast as ray by ray.
+// ray 6.8 lines of atomic adds per point, 1.48 ms; in tiles 4.6 lines, 1.36.
+// Tiles only where a wave has no more steps that way (single rays over tiles at fewer rays: 0.33 .. 1.0), and where the rays run in
+// tiles.  The tiles have a kernel of their own: one for both held the geometry, the inputs and the sums of four rays for a
+// single one too (16-channel voxels 0.79 .. 0.96 times as fast as the kernel before tiles).  Against that kernel, 384 to 65 536
+// rays, 24 to 160 texels an axis: images 0.94 .. 1.8 (16-channel voxels), 0.99 .. 2.0 (32), 0.98 .. 2.3 and 1.17 .. 2.8 (triplanes
+// of 16 and 32); lists of rays 0.93 .. 1.02, 0.94 .. 1.13, 0.93 .. 1.19, 1.17 .. 1.8: the second launch and the look at the rays cost
+// 5 to 10 us.
 //
 // This header holds the kernel and its launcher templates; two translation units instantiate
 // them (the instantiations for 32-channel triplanes are built without the build flag that keeps
@@ -184,13 +188,67 @@ __device__ __forceinline__ void gather_normalised(const GridDev& tgt, const Spla
     }
 }
 
-template <int KIND, int KSP, int KSE, int NH>
+// Whether the rays run in tiles: in three of four among 256 tiles they lie side by side, and a step is at most `step` texels long in the
+// middle.  All threads of a workgroup call it, and every workgroup finds the same.  (In fp32 and with all loads under way at once, as
+// every launch waits for it.)
+__device__ __forceinline__ bool rays_run_in_tiles(const GridDev& g, const RaysDev& rays, float step)
+{
+    __shared__ int together;
+    const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays;
+    const long long first = (long long)threadIdx.x * n_tiles / blockDim.x * kTileRays;
+    float near[kTileRays], far[kTileRays], o[kTileRays][3], d[kTileRays][3];
+#pragma unroll
+    for (int i = 0; i < kTileRays; ++i) {
+        const long long r = min(first + i, rays.M - 1);
+        near[i] = rays.near[r];
+        far[i] = rays.far[r];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) { o[i][a] = rays.origins[3 * r + a]; d[i][a] = rays.dirs[3 * r + a]; }
+    }
+    if (threadIdx.x == 0) together = 0;
+    const float contract = (float)g.contract;
+    auto texel = [&](int i, int a, float t) {
+        float x = o[i][a] + t * d[i][a];
+        if (contract > 0.0f) {
+            const float m = fabsf(x), far = 0.5f * ((2.0f - contract) * (1.0f - 1.0f / fmaxf(m, 1.0f)) + contract);
+            x = m <= 1.0f ? 0.5f * contract * x : x < 0.0f ? -far : far;
+        }
+        return fminf(fmaxf((x - (float)g.amin[a]) * (float)g.scale[a], 0.0f), (float)(g.N[a] - 1));
+    };
+    const float middle = 0.5f * (near[0] + far[0]), ahead = middle + (float)kTileSamples * (far[0] - near[0]) / (float)rays.S;
+    bool apart = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float n0 = texel(0, a, near[0]), f0 = texel(0, a, far[0]);
+#pragma unroll
+        for (int i = 1; i < kTileRays; ++i)
+            apart = apart || !(fabsf(texel(i, a, near[i]) - n0) <= (float)kPushApart) || !(fabsf(texel(i, a, far[i]) - f0) <= (float)kPushApart);
+        apart = apart || !(fabsf(texel(0, a, ahead) - texel(0, a, middle)) <= step);
+    }
+    __syncthreads();
+    const int n = __popcll(__ballot(!apart));
+    if ((threadIdx.x & 63) == 0) atomicAdd(&together, n);
+    __syncthreads();
+    return 4 * together >= 3 * (int)blockDim.x;
+}
+
+// TILE: items are tiles, else single rays.  `choice`: both kernels are launched, and the one that the rays suit works; that of the
+// tiles, the first, decides and leaves its answer there (looking costs both together 7 to 10 us of a backward of 100 or more).
+template <int KIND, int KSP, int KSE, int NH, bool TILE>
 __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt, MlpDev m, RaysDev rays,
-                                                                     SplatDev sp, BwdIo io, PushOrder order)
+                                                                     SplatDev sp, BwdIo io, PushOrder order, int* choice)
 {
     using L = SplatBwdLds<KSP, KSE, NH>;
     constexpr int MB = L::MB, KSH = L::KSH, NBE = L::NBE;
     constexpr int CP = 16 * KSP;          // channels of the prior and of the target
+    if constexpr (TILE) {
+        // (16-channel voxels: where a step of a tile does not fit a window, single rays are the faster ones)
+        const bool tiles = rays_run_in_tiles(sp.prior, rays, KIND == LP_GRID_VOXEL && CP == 16 ? (float)kWinExtent : 1e30f);
+        if (blockIdx.x == 0 && threadIdx.x == 0) *choice = tiles;
+        if (!tiles) return;
+    } else {
+        if (choice && *choice) return;
+    }
     extern __shared__ uint4 lds[];
     stage_splat_bwd<KSP, KSE, NH>(lds, m, sp.n_in);
     __syncthreads();
@@ -207,6 +265,7 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
     auto block = [&](int unit) { return unit < 4096 ? lds + unit : lds_upper + (unit - 4096); };
     uint4* wave_area = const_cast<uint4*>(block(L::WAVE)) + wave * L::W_UNITS;
     char* const area_ptr = reinterpret_cast<char*>(wave_area);
+    float* info = reinterpret_cast<float*>(wave_area);
     const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)area_ptr;
     float* ray_bias = reinterpret_cast<float*>(wave_area + L::W_BIAS);   // [4][64]
     float* ray_sum = reinterpret_cast<float*>(wave_area + L::W_SUM);     // [4][64]
@@ -264,32 +323,31 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) db1[mb] = db2[mb] = 0.0f;
 
-    const int rays_per_item = order.tiles ? kTileRays : 1;
-    const RaySchedule sched = ray_schedule(order.n_groups * kWaves, kWaves);
     const int S = rays.S;
-    for (long long seq = sched.first; seq < sched.end; seq += sched.stride) {
-        const long long first = (((seq / kWaves) * order.group_mul % order.n_groups) * kWaves + seq % kWaves) * rays_per_item;
-        if (first >= rays.M) continue;
-        const long long end = min(first + rays_per_item, rays.M);
-        const bool tile = order.tiles && side_by_side<kPushApart>(rays, first, end, col, [&](const RayGeom& r, int j) { return sample_cell_any(sp.prior, r, j); });
-        const int n_sub = tile ? 1 : (int)(end - first);
-        for (int sub = 0; sub < n_sub; ++sub) {
-        const long long ray = first + (tile ? col / kTileSamples : sub);
-        const bool ray_ok = ray < end;
-        const int my_ray = tile ? col / kTileSamples : 0;   // of the item, that the lane's column belongs to
-        int scene;
-        {   // the rays' geometry is kept in LDS between its uses
-            const RayGeom q = load_ray_geom(rays, min(ray, end - 1));
-            scene = __builtin_amdgcn_readfirstlane(q.scene);
+    constexpr int kRays = TILE ? kTileRays : 1;
+    // Single rays, measured against the kernel before tiles (24 .. 160 texels an axis, 384 .. 65 536 rays, 24 .. 160 points): 16-channel
+    // voxels with the geometry in registers and the walk of run-merged records, 0.99 .. 1.05 times as fast (windows of whole steps
+    // 0.84 .. 1.28); 32-channel voxels with the walk in the order of the ray 0.97 .. 1.15 (records 0.91 .. 1.04: spills);
+    // triplanes with windows 0.97 .. 1.31 (16 channels, where a step can fit one) and 1.07 .. 1.68 (32).
+    constexpr bool kRecords = !TILE && KIND == LP_GRID_VOXEL && CP == 16;
+    constexpr bool kKept = TILE || CP == 32;   // the rays' geometry is kept in LDS between its uses
+    // the rays [first, end) of a tile, or the ray `first`
+    auto march = [&](long long first, long long end) __attribute__((always_inline)) {
+        const int my_ray = TILE ? col / kTileSamples : 0;   // of the item, that the lane's column belongs to
+        const bool ray_ok = first + my_ray < end;
+        const RayGeom one = load_ray_geom(rays, TILE ? min(first + my_ray, end - 1) : first);
+        const int scene = TILE ? __builtin_amdgcn_readfirstlane(one.scene) : one.scene;
+        if constexpr (kKept) {
             wave_lds_fence();
-            if (grp == 0 && (tile ? col % kTileSamples : col) == 0) {
-                lds_put<f32x4>(geo_at + 48 * my_ray, f32x4{q.ox, q.oy, q.oz, q.dx});
-                lds_put<f32x4>(geo_at + 48 * my_ray + 16, f32x4{q.dy, q.dz, q.near, q.delta});
-                lds_put<double>(geo_at + 48 * my_ray + 32, q.delta64);
+            if (grp == 0 && col % (32 / kRays) == 0) {
+                lds_put<f32x4>(geo_at + 48 * my_ray, f32x4{one.ox, one.oy, one.oz, one.dx});
+                lds_put<f32x4>(geo_at + 48 * my_ray + 16, f32x4{one.dy, one.dz, one.near, one.delta});
+                lds_put<double>(geo_at + 48 * my_ray + 32, one.delta64);
             }
             wave_lds_fence();
         }
         auto geometry = [&]() {
+            if constexpr (!kKept) return one;
             uint32_t at = geo_at + 48 * my_ray;
             refresh(at);   // (or what is derived from it is kept through the step)
             const f32x4 a = lds_get<f32x4>(at), b = lds_get<f32x4>(at + 16);
@@ -305,13 +363,12 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
         {
             wave_lds_fence();
 #pragma unroll
-            for (int i = 0; i < kTileRays; ++i) {
-                const long long at = min(first + (tile ? i : sub), end - 1);
+            for (int i = 0; i < kRays; ++i) {
+                const long long at = TILE ? min(first + i, end - 1) : first;
                 const float d[3] = {rays.dirs[3 * at], rays.dirs[3 * at + 1], rays.dirs[3 * at + 2]};
                 const float x_lane = lane < n_in ? sp.feats[(size_t)at * n_in + lane]
                                                  : lane < n_extra ? dir_encoding(d, lane - n_in) : 0.0f;
                 if (lane < 48) ray_x[48 * i + lane] = x_lane;
-                if (!tile) break;
             }
             wave_lds_fence();
             f32x16 acc[MB][1];
@@ -327,30 +384,36 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
             }
             layer_mfma<MB, KSE, 1>(acc, block(L::A1E), lane, eh, el);
             wave_lds_fence();
-            if (col % kTileSamples == 0) {  // the columns of a ray hold the same values
+            if (col % (32 / kRays) == 0) {  // the columns of a ray hold the same values
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) ray_bias[kHidden * (col / kTileSamples) + 32 * mb + d_row(r, grp)] = acc[mb][0][r];
+                    for (int r = 0; r < 16; ++r) ray_bias[kHidden * my_ray + 32 * mb + d_row(r, grp)] = acc[mb][0][r];
             }
             wave_lds_fence();
         }
-        // dZ1 summed over this lane group's points of the columns 8 i .. 8 i + 7 (ray i of a tile), hidden unit 32 mb + col
-        float dbr[MB][kTileRays];
+        // dZ1 summed over this lane group's points of ray i (in a tile: of the columns 8 i .. 8 i + 7), hidden unit 32 mb + col
+        float dbr[MB][kRays];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int i = 0; i < kTileRays; ++i) dbr[mb][i] = 0.0f;
+            for (int i = 0; i < kRays; ++i) dbr[mb][i] = 0.0f;
         __builtin_amdgcn_sched_barrier(0);
 
-        const int step = tile ? kTileSamples : kBwdStep, k = tile ? col % kTileSamples : col;
-        for (int j0 = 0; j0 < S; j0 += step) {
-            const int j = j0 + k;
+        constexpr int kStep = TILE ? kTileSamples : kBwdStep;
+        bool windows = true;   // whether a step may fit a window (asked per step it costs 3 % where none does)
+        if constexpr (!TILE && KIND == LP_GRID_TRIPLANE && CP == 16) {
+            const Cell3 c0 = sample_cell_any(sp.prior, geometry(), 0), c1 = sample_cell_any(sp.prior, geometry(), S - 1);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) windows = windows && (long long)abs(c1.i[a] - c0.i[a]) * kStep <= (long long)kWinExtent * S;
+        }
+        for (int j0 = 0; j0 < S; j0 += kStep) {
+            const int j = j0 + (TILE ? col % kTileSamples : kRecords ? slot_to_sample(col) : col);
             const bool valid = ray_ok && j < S;
             const int jj = min(j, S - 1);
             Frag fh[1][KSP], fl[1][KSP];
+            const Cell3 cp = sample_cell_any(sp.prior, geometry(), jj);
             {
-                const Cell3 cp = sample_cell_any(sp.prior, geometry(), jj);
                 GatherRaw<KIND, 8, LP_F32> raw[KSP];
 #pragma unroll
                 for (int s = 0; s < KSP; ++s) gather_issue<KIND, CP, 8, LP_F32>(sp.prior, scene, cp, 16 * s + 8 * grp, raw[s]);
@@ -365,6 +428,10 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
             }
             Frag gv_h[1][KSP], gv_l[1][KSP];
             gather_normalised<KIND, CP>(tgt, sp, scene, sample_cell_any(tgt, geometry(), jj), grp, valid, gv_h, gv_l);
+            if constexpr (kRecords) {   // scatter record of this lane's point in the prior, read at the end of the step
+                wave_lds_fence();
+                if (grp == 0) write_scatter_record<KIND, CP>(info + col * 16, sp.prior, cp);
+            }
 
             // ---- forward of the hidden layers ----
             Frag h1h[1][KSH], h1l[1][KSH], h2h[1][KSH], h2l[1][KSH];
@@ -435,13 +502,18 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
                     Frag ah[kBwdKS], al[kBwdKS];
                     transpose_hidden(gz_h, gz_l, mb, ah, al);
 #pragma unroll
-                    for (int ks = 0; ks < kBwdKS; ++ks)
+                    for (int ks = 0; ks < kBwdKS; ++ks) {
+                        if constexpr (TILE) {
 #pragma unroll
-                        for (int h = 0; h < 2; ++h) {   // half a fragment: four points of column group 2 ks + h
-                            float& sum = dbr[mb][2 * ks + h];
-                            sum = pair_sum(al[ks].d[2 * h], pair_sum(al[ks].d[2 * h + 1], sum));
-                            sum = pair_sum(ah[ks].d[2 * h], pair_sum(ah[ks].d[2 * h + 1], sum));
+                            for (int h = 0; h < 2; ++h) {   // half a fragment: four points of column group 2 ks + h
+                                float& sum = dbr[mb][2 * ks + h];
+                                sum = pair_sum(al[ks].d[2 * h], pair_sum(al[ks].d[2 * h + 1], sum));
+                                sum = pair_sum(ah[ks].d[2 * h], pair_sum(ah[ks].d[2 * h + 1], sum));
+                            }
+                        } else {
+                            dbr[mb][0] = frag_sum(al[ks], frag_sum(ah[ks], dbr[mb][0]));
                         }
+                    }
                     mfma6_parked(dW1p[mb], ah, al, bh, bl);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -456,54 +528,56 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
             }
             __builtin_amdgcn_sched_barrier(0);
             wave_lds_fence();
-            uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
-            refresh(lane_here);
-            scatter_step<KIND, CP, Scatter::kGradient, RayWindows::kWhole>(sp.prior, io.d_grid, scene, area, area_ptr, sample_cell_any(sp.prior, geometry(), jj), dXp, lane_here, tile);
+            if constexpr (kRecords) {
+                scatter_channels<KIND, CP>(sp.prior, io.d_grid, scene, info, dXp, col, grp);
+            } else {
+                constexpr RayWindows kWindows = KIND == LP_GRID_TRIPLANE ? RayWindows::kWhole : RayWindows::kNone;
+                uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
+                refresh(lane_here);
+                scatter_step<KIND, CP, Scatter::kGradient, kWindows>(sp.prior, io.d_grid, scene, area, area_ptr, sample_cell_any(sp.prior, geometry(), jj),
+                                                                     dXp, lane_here, TILE, nullptr, true, windows);
+            }
         }
 
         // ---- per-ray inputs: with s = sum of dZ1 over a ray, dW1 += s x^T and dx = W1^T s ----
-        float sz[MB][kTileRays];
+        float sz[MB][kRays];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            const float all = (dbr[mb][0] + dbr[mb][1]) + (dbr[mb][2] + dbr[mb][3]);
-            db1[mb] += all;
+            if constexpr (TILE) db1[mb] += (dbr[mb][0] + dbr[mb][kRays / 4]) + (dbr[mb][kRays / 2] + dbr[mb][kRays - 1]);
+            else db1[mb] += dbr[mb][0];
 #pragma unroll
-            for (int i = 0; i < kTileRays; ++i) {   // a single ray: all columns are its
-                const float mine = tile ? dbr[mb][i] : i == 0 ? all : 0.0f;
-                sz[mb][i] = mine + __shfl_xor(mine, 32, 64);
-            }
+            for (int i = 0; i < kRays; ++i) sz[mb][i] = dbr[mb][i] + __shfl_xor(dbr[mb][i], 32, 64);
         }
         wave_lds_fence();
         if (grp == 0) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int i = 0; i < kTileRays; ++i) ray_sum[kHidden * i + 32 * mb + col] = sz[mb][i];
+                for (int i = 0; i < kRays; ++i) ray_sum[kHidden * i + 32 * mb + col] = sz[mb][i];
         }
-        // a product over the rays: K indices 0 .. 3 (elements 0 .. 3 of lane group 0)
+        // a product over the rays: K indices 0 .. kRays - 1 (elements of lane group 0)
 #pragma unroll
         for (int be = 0; be < NBE; ++be) {
             Frag bh, bl;
             {
 #pragma unroll
-                for (int w = 0; w < 2; ++w) {
-                    const bool there = 32 * be + col < 48, both = there && tile;   // (a single ray: only x of ray 0 stands there)
-                    uint32_t h, l;
-                    split2((w == 0 ? there : both) ? ray_x[48 * 2 * w + 32 * be + col] : 0.0f,
-                           both ? ray_x[48 * (2 * w + 1) + 32 * be + col] : 0.0f, h, l);
+                for (int w = 0; w < 4; ++w) {   // dword w: rays 2 w and 2 w + 1
+                    uint32_t h = 0u, l = 0u;
+                    if (2 * w < kRays) {
+                        auto x = [&](int i) { return i < kRays && 32 * be + col < 48 ? ray_x[48 * i + 32 * be + col] : 0.0f; };
+                        split2(x(2 * w), x(2 * w + 1), h, l);
+                    }
                     bh.d[w] = grp == 0 ? h : 0u; bl.d[w] = grp == 0 ? l : 0u;
-                    bh.d[2 + w] = bl.d[2 + w] = 0u;
                 }
             }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 Frag ah, al;
 #pragma unroll
-                for (int w = 0; w < 2; ++w) {
-                    uint32_t h, l;
-                    split2(sz[mb][2 * w], sz[mb][2 * w + 1], h, l);
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t h = 0u, l = 0u;
+                    if (2 * w < kRays) split2(sz[mb][2 * w < kRays ? 2 * w : 0], 2 * w + 1 < kRays ? sz[mb][2 * w + 1 < kRays ? 2 * w + 1 : 0] : 0.0f, h, l);
                     ah.d[w] = grp == 0 ? h : 0u; al.d[w] = grp == 0 ? l : 0u;
-                    ah.d[2 + w] = al.d[2 + w] = 0u;
                 }
                 dW1e[mb][be] = mfma3(ah, al, bh, bl, dW1e[mb][be]);
                 park(dW1e[mb][be]);
@@ -512,13 +586,13 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
         }
         wave_lds_fence();
         {
-            // s as an operand over the hidden units, row i = ray i / 8
+            // s as an operand over the hidden units; in a tile row i = ray i / 8, else the same in every row
             Frag zh[KSH], zl[KSH];
 #pragma unroll
             for (int s = 0; s < KSH; ++s) {
                 float v[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = ray_sum[kHidden * (col / kTileSamples) + k_hidden(s, grp, e)];
+                for (int e = 0; e < 8; ++e) v[e] = ray_sum[kHidden * my_ray + k_hidden(s, grp, e)];
                 split8(v, zh[s], zl[s]);
             }
 #pragma unroll
@@ -533,15 +607,25 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
                 const int k = 32 * be + col;
                 if (grp == 0 && k < n_in) {   // register 4 i of lane group 0: row 8 i
 #pragma unroll
-                    for (int i = 0; i < kTileRays; ++i) {
-                        const long long at = first + (tile ? i : sub);
-                        if ((tile || i == 0) && at < end) sp.d_feats[(size_t)at * n_in + k] = dx[4 * i];
-                    }
+                    for (int i = 0; i < kRays; ++i)
+                        if (first + i < end) sp.d_feats[(size_t)(first + i) * n_in + k] = dx[4 * i];
                 }
             }
         }
         __builtin_amdgcn_sched_barrier(0);
+    };
+
+    const RaySchedule sched = ray_schedule(order.n_groups * kWaves, kWaves);
+    for (long long seq = sched.first; seq < sched.end; seq += sched.stride) {
+        const long long first = (((seq / kWaves) * order.group_mul % order.n_groups) * kWaves + seq % kWaves) * kRays;
+        if (first >= rays.M) continue;
+        const long long end = min(first + kRays, rays.M);
+        long long each = kRays;
+        if constexpr (TILE) {   // (rays of two scenes: one after the other; those far apart take the scatter's walk)
+            const int scene = rays.scene ? rays.scene[min(first + col / kTileSamples, end - 1)] : 0;
+            if (__ballot(scene != __builtin_amdgcn_readfirstlane(scene)) != 0ull) each = 1;
         }
+        for (long long at = first; at < end; at += each) march(at, min(at + each, end));
     }
 
     // ---- this wave's record of partial sums ----
@@ -590,13 +674,21 @@ hipError_t launch(const GridDev& tgt, const MlpDev& m, const RaysDev& rays, cons
                   int n_cu, hipStream_t stream)
 {
     constexpr int kLdsBytes = SplatBwdLds<KSP, KSE, NH>::UNITS * 16;
-    static_assert(kLdsBytes <= 160 * 1024, "LDS budget of a gfx950 compute unit");
-    auto kernel = splat_mfma_bwd_kernel<KIND, KSP, KSE, NH>;
+    static_assert(kLdsBytes + 16 <= 160 * 1024, "LDS budget of a gfx950 compute unit, with the counter of rays_run_in_tiles");
+    const int blocks = mfma_bwd_records(n_cu) / kWaves;  // every wave writes a record, busy or not
+    const long long waves = (long long)blocks * kWaves;
+    int* const choice = reinterpret_cast<int*>(io.ws + (size_t)waves * io.ws_stride);   // (the workspace goes on behind the records)
+    const PushOrder tiles = push_order(rays, waves, kWaves, 1.05), single = push_order(rays, waves, kWaves, 0.0);
+    if (tiles.tiles) {
+        auto kernel = splat_mfma_bwd_kernel<KIND, KSP, KSE, NH, true>;
+        const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, io, tiles, choice);
+    }
+    auto kernel = splat_mfma_bwd_kernel<KIND, KSP, KSE, NH, false>;
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
-    const int blocks = mfma_bwd_records(n_cu) / kWaves;  // every wave writes a record, busy or not
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, io,
-                       push_order(rays, (long long)blocks * kWaves, kWaves, 1.05));
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, io, single, tiles.tiles ? choice : nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_params_kernel, dim3((m.param_total + 63) / 64), dim3(kReduceThreads), 0, stream,

@@ -303,11 +303,11 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
 // runs of consecutive samples (of every ray of the tile) with a window each: rays that leave the unit cube of contract
 // coordinates between two samples, mostly.  The products would spread an infinite or
 // undefined gradient over its window, so a step that holds one takes the walk, which keeps it to the sample's own corners.
-// Steps of a single ray: see RayWindows.
+// Steps of a single ray: see RayWindows; `windows` false: the walk.
 template <int KIND, int C, Scatter WHAT = Scatter::kGradient, RayWindows RAYS = WHAT == Scatter::kGradient ? RayWindows::kSplit : RayWindows::kNone>
 __device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
                                              char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, bool tile,
-                                             float* const* sums = nullptr, bool valid = true)
+                                             float* const* sums = nullptr, bool valid = true, bool windows = true)
 {
     constexpr bool kPushes = WHAT != Scatter::kGradient, kOfRay = WHAT == Scatter::kPushRay;
     const int col = lane & 31, k = tile ? (col & (kTileSamples - 1)) : col, full = tile ? kTileSamples : 32;
@@ -319,10 +319,14 @@ __device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_gr
 #pragma unroll
         for (int a = 0; a < 3; ++a) probe = fmaf(cell.f[a], 0.0f, probe);
     }
-    const bool finite = __ballot(probe != 0.0f) == 0ull && (RAYS != RayWindows::kNone || tile);
+    const bool finite = __ballot(probe != 0.0f) == 0ull && (RAYS != RayWindows::kNone || tile) && windows;
     int len = full;
-    Window win = find_window(cell, true);
-    bool fits = finite && window_fits<KIND>(win);
+    Window win;
+    bool fits = false;
+    if (finite) {
+        win = find_window(cell, true);
+        fits = window_fits<KIND>(win);
+    }
     while (!fits && finite && len > full / 4 && (RAYS == RayWindows::kSplit || tile)) {
         len >>= 1;
         fits = true;
