@@ -71,7 +71,45 @@ __device__ __forceinline__ void stage_splat_mlp(uint4* lds, const MlpDev& m, int
     if (threadIdx.x < 32) sbias[2 * kHidden + threadIdx.x] = m.b[NH][threadIdx.x & (CO - 1)];
 }
 
-template <int KIND, int KSP, int KSE, int NH>
+// Scatter of 32 points of one ray, column c = point slot_to_sample(c): a window where the whole step fits one (`windows`: it may), else
+// the walk of run-merged records.
+template <int KIND, int C>
+__device__ __forceinline__ void push_ray_step(const GridDev& g, const SplatDev& sp, int scene, uint32_t area, char* area_ptr, const Cell3& cell,
+                                              f32x16& v, int lane, bool valid, bool windows)
+{
+    const int col = lane & 31, grp = lane >> 5;
+    if (windows) {
+        float probe = 0.0f;   // (a product would spread an infinite vector over its window)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) probe = fmaf(v[r], 0.0f, probe);
+        const Window win = find_window(cell, true);
+        if (window_fits<KIND>(win) && __ballot(probe != 0.0f) == 0ull) {
+            scatter_window<KIND, C, Scatter::kPushPoints>(g, sp.theta, sp.theta_w, scene, area, win, cell, valid, v, lane);
+            return;
+        }
+    }
+    float* info = reinterpret_cast<float*>(area_ptr);
+    wave_lds_fence();
+    if (grp == 0) {
+        float* rec = info + col * 16;
+        write_scatter_record<KIND, C, true>(rec, g, cell);
+        if (!valid) {   // a point past the end of the ray pushes nothing
+#pragma unroll
+            for (int k = 0; k < (KIND == LP_GRID_VOXEL ? 8 : 12); ++k) rec[k] = 0.0f;
+        }
+    }
+    const unsigned there = (unsigned)__ballot(valid);
+    if (there != 0xffffffffu) {   // (weight zero alone would turn an infinite vector into an undefined one)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = ((there >> d_row(r, grp)) & 1u) ? v[r] : 0.0f;
+    }
+    wave_lds_fence();
+    scatter_channels<KIND, C>(g, sp.theta, scene, info, v, col, grp);
+    scatter_weights<KIND, C>(g, sp.theta_w, scene, info, col, grp);
+}
+
+// TILES: items are tiles of four rays (those that do not lie side by side go one after the other), else single rays.
+template <int KIND, int KSP, int KSE, int NH, bool TILES>
 __global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt, MlpDev m, RaysDev rays, SplatDev sp, PushOrder order)
 {
     constexpr int CO = 16 * KSP;  // the target has the prior's channel count
@@ -92,14 +130,14 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt,
     const float bias_out = sbias[2 * kHidden + col];
     const int n_in = sp.n_in, n_extra = sp.n_in + m.n_enc;
 
-    const int rays_per_item = order.tiles ? kTileRays : 1;
+    constexpr int rays_per_item = TILES ? kTileRays : 1;
     const RaySchedule sched = ray_schedule(order.n_groups * kWaves, kWaves);
     const int S = rays.S;
     for (long long seq = sched.first; seq < sched.end; seq += sched.stride) {
         const long long first = (((seq / kWaves) * order.group_mul % order.n_groups) * kWaves + seq % kWaves) * rays_per_item;
         if (first >= rays.M) continue;
         const long long end = min(first + rays_per_item, rays.M);
-        const bool tile = order.tiles && side_by_side<kPushApart>(rays, first, end, col, [&](const RayGeom& r, int j) { return sample_cell_any(tgt, r, j); });
+        const bool tile = TILES && side_by_side<kPushApart>(rays, first, end, col, [&](const RayGeom& r, int j) { return sample_cell_any(tgt, r, j); });
         const int n_sub = tile ? 1 : (int)(end - first);
         for (int sub = 0; sub < n_sub; ++sub) {
             const long long ray = first + (tile ? col / kTileSamples : sub);
@@ -133,7 +171,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt,
                 }
                 layer_mfma<MB, KSE, 1>(start, lds + L::A1E, lane, eh, el);
             }
-            const int step = tile ? kTileSamples : 32, k = tile ? col % kTileSamples : col;
+            const int step = tile ? kTileSamples : 32, k = tile ? col % kTileSamples : TILES ? col : slot_to_sample(col);
+            bool windows = true;   // single rays: whether a step may fit a window
+            if constexpr (!TILES) {
+                const Cell3 c0 = sample_cell_any(tgt, q, 0), c1 = sample_cell_any(tgt, q, S - 1);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) windows = windows && (long long)abs(c1.i[a] - c0.i[a]) * min(32, S) <= (long long)kWinExtent * S;
+            }
             for (int j0 = 0; j0 < S; j0 += step) {
                 const int j = j0 + k, jj = min(j, S - 1);
                 Frag fh[1][KSP], fl[1][KSP];
@@ -174,7 +218,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt,
                 __builtin_amdgcn_sched_barrier(0);
                 uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
                 refresh(lane_here);
-                scatter_step<KIND, CO, Scatter::kPushPoints, RayWindows::kWhole>(tgt, sp.theta, scene, area, area_ptr, sample_cell_any(tgt, q, jj), v, lane_here, tile, sp.theta_w, ray_ok && j < S);
+                const Cell3 cell = sample_cell_any(tgt, q, jj);
+                const bool valid = ray_ok && j < S;
+                if constexpr (TILES) scatter_step<KIND, CO, Scatter::kPushPoints, RayWindows::kWhole>(tgt, sp.theta, scene, area, area_ptr, cell, v, lane_here, tile, sp.theta_w, valid);
+                else push_ray_step<KIND, CO>(tgt, sp, scene, area, area_ptr, cell, v, lane_here, valid, windows);
             }
         }
     }
@@ -185,12 +232,12 @@ hipError_t launch(const GridDev& tgt, const MlpDev& m, const RaysDev& rays, cons
                   hipStream_t stream)
 {
     constexpr int kLdsBytes = SplatLds<KSP, KSE, NH>::UNITS * 16;
-    auto kernel = splat_mfma_kernel<KIND, KSP, KSE, NH>;
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (e != hipSuccess) return e;
     long long blocks = (2LL * n_cu + 7) / 8 * 8;
     const PushOrder order = push_order(rays, blocks * kWaves, kWaves);
     if (blocks > order.n_groups) blocks = (order.n_groups + 7) / 8 * 8;
+    auto kernel = order.tiles ? splat_mfma_kernel<KIND, KSP, KSE, NH, true> : splat_mfma_kernel<KIND, KSP, KSE, NH, false>;
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, order);
     return hipGetLastError();
 }

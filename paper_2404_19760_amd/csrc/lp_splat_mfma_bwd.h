@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
         if constexpr (!TILE && KIND == LP_GRID_TRIPLANE && CP == 16) {
             const Cell3 c0 = sample_cell_any(sp.prior, geometry(), 0), c1 = sample_cell_any(sp.prior, geometry(), S - 1);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) windows = windows && (long long)abs(c1.i[a] - c0.i[a]) * kStep <= (long long)kWinExtent * S;
+            for (int a = 0; a < 3; ++a) windows = windows && (long long)abs(c1.i[a] - c0.i[a]) * min(kStep, S) <= (long long)kWinExtent * S;
         }
         for (int j0 = 0; j0 < S; j0 += kStep) {
             const int j = j0 + (TILE ? col % kTileSamples : kRecords ? slot_to_sample(col) : col);
