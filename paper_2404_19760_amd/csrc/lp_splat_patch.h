@@ -197,7 +197,7 @@ __device__ __forceinline__ PatchCells patch_cells(const GridDev& g, const RayGeo
 // Plane `pl` of the points [from, from + len) of every ray (`only` >= 0: of this one): the texels that they reach get slots, and
 // weights[slot][ray] receives the sum of the ray's interpolation weights on the texel.  Number of slots; 0: no
 // points; -1: too many texels.  A cell's corners are shared out to the lane groups of a ray (32 rays: by the slowest axis; 16: by
-// the two slowest), so that no two lanes meet in a weight.
+// the two slowest), so that no two lanes meet in a weight of one point.
 template <int KIND, int C, int RAYS>
 __device__ __forceinline__ int patch_weights(uint32_t area, const GridDev& g, const PatchCells& cells, int from, int len, int only,
                                              int pl, int lane)
@@ -284,7 +284,8 @@ __device__ __forceinline__ int patch_weights(uint32_t area, const GridDev& g, co
     if (n_slots > L::kSlots) return -1;
     for (int i = lane; i < n_slots * (L::kRow / 16); i += 64) lds_put<u32x4>(area + 16 * i, u32x4{0u, 0u, 0u, 0u});
     wave_lds_fence();
-    // the weights: a lane adds to its own ray's column, point after point
+    // the weights: a lane adds to its own ray's column, point after point.  (The upper face of a point may be the lower one of the
+    // next, which is another lane's: a fence between points.)
     const uint32_t column = area + 4 * ray;
     uint32_t where[kPatchPoints][kFace];
 #pragma unroll
@@ -295,7 +296,7 @@ __device__ __forceinline__ int patch_weights(uint32_t area, const GridDev& g, co
                 where[k][d] = column + L::kRow * (uint32_t)lds_get<uint8_t>(area + L::MAP + dense[k] + (along1(d) - along1(0)) * e2 + along2(d));
         }
 #pragma unroll
-    for (int k = 0; k < kPatchPoints; ++k)
+    for (int k = 0; k < kPatchPoints; ++k) {
         if ((members >> k) & 1u) {
             const Cell3& c = cells.c[k];
             const float w0 = d0 ? atf(c.f, a0) : atf(c.g, a0);
@@ -309,7 +310,8 @@ __device__ __forceinline__ int patch_weights(uint32_t area, const GridDev& g, co
                 lds_put<float>(where[k][d], old[d] + w);
             }
         }
-    wave_lds_fence();
+        wave_lds_fence();
+    }
     return n_slots;
 }
 

@@ -89,3 +89,76 @@ def test_scatter_begins_with_a_fence(function):
     body = _between(_source("lp_tile_scatter.h"), r"void %s\(" % function, r"^}")
     lds = next(i for i, l in enumerate(body) if re.search(r"lds_put|lds_get|wave_lds_fence|write_scatter_record", l))
     assert "wave_lds_fence()" in body[lds]
+
+
+def test_weights_of_a_patch():
+    """The lanes of a ray add to its column of weights in turn: what one has stored another reads at the next point, so a fence
+    stands in every turn of the loop, behind the clearing stores and in front of what follows."""
+    body = _between(_source("lp_splat_patch.h"), r"^    for \(int i = lane; i < n_slots \* \(L::kRow", r"^    return n_slots;")
+    events = _events(body, [FENCE, (r"lds_put<u32x4>\(area \+ 16 \* i", [("clear", "weights")]), (r"lds_get<float>\(where", [("read", "weights")]),
+                            (r"lds_put<float>\(where", [("add", "weights")])])
+    assert [w for w, _ in events] == ["clear", "fence", "read", "add", "fence"]
+    loop = _between(body, r"^    for \(int k = 0; k < kPatchPoints; \+\+k\) \{", r"^    \}")
+    assert [w for w, _ in _events(loop, [FENCE])] == ["fence"] and loop[-1] == "        wave_lds_fence();"   # all lanes pass it
+
+
+def test_slots_of_a_patch():
+    """The window's map: cleared, marked by the lanes that reach a texel, read and numbered by the lane that holds its byte, and read
+    by the lanes that marked it."""
+    body = _between(_source("lp_splat_patch.h"), r"int patch_weights\(", r"^}")
+    step = _events(body, [FENCE, (r"lds_put<u32x4>\(area \+ L::MAP", [("store", "map")]),
+                          (r"lds_put<uint8_t>\(area \+ L::MAP \+ dense", [("store", "map")]),
+                          (r"lds_get<uint8_t>\(area \+ L::MAP \+ n\)", [("read", "map")]),   # (the number goes into the byte that the lane has read)
+                          (r"lds_get<uint8_t>\(area \+ L::MAP \+ dense", [("read", "map")])])
+    assert [w for w, _ in step].count("read") == 2 and [w for w, _ in step].count("store") == 2
+    _check(step)
+    number = [w for w, _ in _events(body, [FENCE, (r"lds_put<uint8_t>\(area \+ L::MAP \+ n, ", [("store", "map")]),
+                                           (r"lds_get<uint8_t>\(area \+ L::MAP \+ dense", [("read", "map")])])]
+    assert "fence" in number[number.index("store"):number.index("read")]
+
+
+def test_rays_of_a_forward_in_pairs():
+    body = _between(_source("lp_mfma_fwd.hip"), r"^    for \(long long item = sched.first", r"^    }")
+    step = _events(body, [FENCE, (r"lds_put<\w+>\(ray_at", [("store", "rays")]), (r"lds_get<\w+>\(at\b", [("read", "rays")])])
+    assert {w for w, _ in step} == {"fence", "store", "read"}
+    _check(step)
+
+
+def test_inputs_of_the_mlp_splatter_push():
+    body = _between(_source("lp_splat_mfma.hip"), r"^        for \(int sub = 0;", r"^        }")
+    step = _events(body, [FENCE, (r"\) ray_x\[", [("store", "inputs")]), (r"= ray_x \+", [("read", "inputs")]),
+                          (r"\bscatter_step<|\bpush_ray_step<", [("fence", None)])])   # (an area of its own)
+    assert {b for w, b in step if w == "read"} == {"inputs"} == {b for w, b in step if w == "store"}
+    _check(step)
+
+
+def test_a_ray_pushed_by_the_mlp_splatter():
+    """push_ray_step's records, in the area that the next step's table or records take."""
+    body = _between(_source("lp_splat_mfma.hip"), r"void push_ray_step\(", r"^}")
+    walk = body[next(i for i, l in enumerate(body) if "float* info" in l):]
+    step = _events(walk, [FENCE, (r"write_scatter_record<", [("store", "records")]), (r"rec\[k\] = ", [("store", "records")]),
+                          (r"scatter_(?:channels|weights)<", [("read", "records")])])
+    assert [w for w, _ in step][0] == "fence"
+    _check(step)
+
+
+def test_rays_of_the_mlp_splatter_backward():
+    """Geometry, inputs, biases and sums of an item's rays; the scatter of the step's gradient begins with a fence and has an area of its own."""
+    body = _between(_source("lp_splat_mfma_bwd.h"), r"^    auto march = ", r"^    };")
+    step = _events(body, [
+        FENCE,
+        (r"lds_put<\w+>\(geo_at", [("store", "geometry")]),
+        (r"\bgeometry\(\)", [("read", "geometry")]),
+        (r"\) ray_x\[", [("store", "inputs")]),
+        (r"= ray_x \+|\? ray_x\[", [("read", "inputs")]),
+        (r"; \+\+r\) ray_bias\[", [("store", "biases")]),
+        (r"\(acc, ray_bias", [("read", "biases")]),
+        (r"; \+\+i\) ray_sum\[", [("store", "sums")]),
+        (r"= ray_sum\[", [("read", "sums")]),
+        (r"write_scatter_record<", [("store", "records")]),
+        (r"\bscatter_channels<", [("read", "records")]),
+        (r"\bscatter_step<", [("fence", None)]),
+    ])
+    buffers = {"geometry", "inputs", "biases", "sums", "records"}
+    assert {b for w, b in step if w == "read"} == buffers == {b for w, b in step if w == "store"}
+    _check(step)
