@@ -28,6 +28,7 @@ using Patch = PatchLds<kPatchRays>;
 constexpr int kPointUnit = 32;   // they are read in multiples of this many (the rest: weight zero)
 
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(2 * sizeof(double)))) double f64x2;
 
 template <int KIND>
 struct PushRecords {
@@ -38,9 +39,11 @@ struct PushRecords {
     static constexpr int kBytes = kPlanes * kPlane;
 };
 
-// LDS of a patch's wave: two arrays of a float per slot take the map's place and a little more
-constexpr int kPatchBytes = Patch::MAP + Patch::kSlots * 8;
-static_assert(kPatchBytes >= Patch::kBytes, "the map");
+// LDS of a patch's wave: two arrays of a float per slot take the map's place and a little more, then the rays' sums, up to eight to a lane
+constexpr int kTotals = Patch::MAP + Patch::kSlots * 8;
+constexpr int kPatchBytes = kTotals + 64 * 8 * 8;
+static_assert(kTotals >= Patch::kBytes && kTotals % 16 == 0, "the map");
+static_assert(2 * kWaves * kPatchBytes <= 160 * 1024, "the LDS of two workgroups fits a compute unit");
 
 // Weights over the weight sums of the forward (0 where nothing landed, and past the ray's end) and texel
 // offsets of the lane's point.
@@ -150,12 +153,21 @@ __device__ __forceinline__ void ray_gradient(const GridDev& tgt, const RaysDev& 
     }
 }
 
-// Patches are taken from this many rays on, where points share texels. Time ray by ray over that in patches, 24^3 .. 160^3
-// voxels: 1.3 .. 2.5 at 65 536 rays, 0.7 .. 1.3 at 16 384 (fewer patches than wavefronts), 0.9 .. 1.25 where the points of a
-// ray are 3.6 texels apart.  Looking for an image takes 7 us, 8 % of 1.6e6 points ray by ray.  Triplanes stay ray by ray
-// (0.3 .. 1.4).
-constexpr long long kMinRays = 65536, kMinPoints = 4000000;
-__device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& rays) { return find_row(g, rays, 0.9, 2.0); }
+// Patches are taken from this many rays on, where points share texels: up to `longest` texels from point to point.  Time ray by ray over
+// that in patches, 62^3 .. 233^3 voxels, 64 to 130 points a ray: 1.09 .. 1.6 at 160 000 rays (ten thousand patches for two thousand
+// waves); at 65 536 and 90 000 rays with 16 channels 1.00 .. 1.28 up to 0.75 texels and 0.83 .. 1.02 beyond, with 32 channels 1.10 ..
+// 1.7 up to 1.25 and 0.88 .. 1.09 beyond; 0.7 .. 1.3 at 16 384.  Looking for an image takes 7 us, 8 % of 1.6e6 points ray by ray.
+// Triplanes stay ray by ray (0.3 .. 1.4).  And from this many points times channels on: with fewer the sums of a ray in its lanes,
+// S C / 32 terms long each, are nearer to 64 bits (2-norm of the error at 24 points: 16 channels 0.90e-7, in patches 0.97e-7; 32
+// channels 0.96e-7 and 0.94e-7).
+constexpr long long kMinRays = 65536, kMinPoints = 4000000, kManyRays = 131072;
+constexpr int kMinPointChannels = 768;
+template <int C>
+__device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& rays)
+{
+    const double longest = rays.M >= kManyRays ? 2.0 : C == 16 ? 0.75 : 1.25;
+    return find_row(g, rays, 0.9, longest);
+}
 
 // Rays in their order.  PATCHES: the patch kernel has been launched before and takes what it finds to be an image.
 template <int KIND, int C, bool CC, bool PATCHES>
@@ -163,7 +175,7 @@ __global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tg
 {
     __shared__ __align__(16) char records[kWaves][PushRecords<KIND>::kBytes];
     if constexpr (PATCHES) {
-        if (image_row(tgt, rays) != 0) return;
+        if (image_row<C>(tgt, rays) != 0) return;
     }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -172,13 +184,24 @@ __global__ __launch_bounds__(kWaves * 64) void splat_naive_bwd_kernel(GridDev tg
     for (long long ray = sched.first; ray < sched.end; ray += sched.stride) ray_gradient<KIND, C, CC>(tgt, rays, sp, ray, area, lane);
 }
 
-// The gradient of a patch's pixels, d_feat[ray][channel] += weights[texel][ray] / theta_w[texel] x d_theta[texel][channel] in
-// fp32, for points [from, from + len) of a step, plane `pl` (`only`: of one ray).  false: they reach too many texels.
+// Where a lane keeps the sums of its registers r and r + 1 of channel block h.
+__device__ __forceinline__ uint32_t total_at(uint32_t area, int h, int r, int lane)
+{
+    uint32_t lane_here = lane;   // (an address kept beside the texels of a step would cost spills)
+    refresh(lane_here);
+    return area + kTotals + 1024 * (2 * h + r / 2) + 16 * lane_here;
+}
+
+// The gradient of a patch's pixels, d_feat[ray][channel] += weights[texel][ray] / theta_w[texel] x d_theta[texel][channel],
+// for points [from, from + len) of a step, plane `pl` (`only`: of one ray).  false: they reach too many texels.
 // A product takes four texels; lane quarter q of a round of 32 texels reads texels 8 q .. 8 q + 7, two neighbouring channels of
 // each (16 channels: one).  `probe` becomes undefined where a gradient that was read is not finite.
+// Products in fp32, in two chains to a round, and the sums of the rounds in fp64: one fp32 chain through all texels of a ray, with
+// weights times reciprocals, was two to three times as far from 64 bits as the sums that the lanes keep ray by ray (2-norm at 160
+// points, 32 channels: 2.9e-7 against 1.3e-7; this way 0.8e-7, for 13 % of the time).
 template <int KIND, int C>
 __device__ __forceinline__ bool pull_points(const GridDev& g, const SplatDev& sp, int scene, uint32_t area, const PatchCells& cells,
-                                            int from, int len, int only, int pl, f32x4 (&acc)[C / 16], float& probe, int lane)
+                                            int from, int len, int only, int pl, float& probe, int lane)
 {
     constexpr int kRounds = Patch::kSlots / 32, kVec = C / 16;
     const int n_slots = patch_weights<KIND, C, kPatchRays>(area, g, cells, from, len, only, pl, lane);
@@ -218,36 +241,52 @@ __device__ __forceinline__ bool pull_points(const GridDev& g, const SplatDev& sp
             }
         }
     }
-    // 1 / theta_w (0 where nothing landed) behind a power of two that keeps the reciprocal of a tiny sum finite
-    constexpr int SCALE = Patch::MAP, INVERSE = Patch::MAP + Patch::kSlots * 4;
+    // theta_w and 1 / theta_w (0 where nothing landed).  Tiny sums are multiplied by a power of two that keeps the reciprocal
+    // finite, and stand there with a minus sign.
+    constexpr int SUM = Patch::MAP, INVERSE = Patch::MAP + Patch::kSlots * 4;
+    constexpr float kTiny = 0x1p-100f, kScale = 0x1p80f;
 #pragma unroll
     for (int n = 0; n < (Patch::kSlots + 63) / 64; ++n) {
         if (64 * n >= n_slots) break;
         if (64 * n + lane < Patch::kSlots) {
-            const float w = sums[n], scale = w < 0x1p-100f ? 0x1p80f : 1.0f;
+            const float w = sums[n], scaled = w < kTiny ? w * kScale : w;
             const bool there = 64 * n + lane < n_slots && w > 0.0f;
-            lds_put<float>(area + SCALE + 4 * (64 * n + lane), there ? scale : 0.0f);
-            lds_put<float>(area + INVERSE + 4 * (64 * n + lane), there ? 1.0f / (w * scale) : 0.0f);
+            lds_put<float>(area + SUM + 4 * (64 * n + lane), w < kTiny ? -scaled : scaled);
+            lds_put<float>(area + INVERSE + 4 * (64 * n + lane), there ? 1.0f / scaled : 0.0f);
         }
     }
     wave_lds_fence();
 #pragma unroll
     for (int n = 0; n < kRounds; ++n) {
         if (32 * n >= n_slots) break;
+        f32x4 part_sum[2][C / 16];
+#pragma unroll
+        for (int h = 0; h < C / 16; ++h) { part_sum[0][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f}; part_sum[1][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
             const int mine = 32 * n + 8 * q + 4 * v;
-            const f32x4 scale = lds_get<f32x4>(area + SCALE + 4 * mine), inverse = lds_get<f32x4>(area + INVERSE + 4 * mine);
+            const f32x4 sum = lds_get<f32x4>(area + SUM + 4 * mine), inverse = lds_get<f32x4>(area + INVERSE + 4 * mine);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float w = (lds_get<float>(area + min(mine + e, n_slots - 1) * Patch::kRow + 4 * i16) * scale[e]) * inverse[e];
+                const float part = lds_get<float>(area + min(mine + e, n_slots - 1) * Patch::kRow + 4 * i16) * (sum[e] < 0.0f ? kScale : 1.0f);
+                const float about = part * inverse[e], w = fmaf(fmaf(-about, fabsf(sum[e]), part), inverse[e], about);   // part / sum, rounded once
 #pragma unroll
                 for (int h = 0; h < kVec; ++h) {
                     probe = fmaf(x[n][4 * v + e][h], 0.0f, probe);
-                    acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x[n][4 * v + e][h], acc[h], 0, 0, 0);
+                    part_sum[e & 1][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x[n][4 * v + e][h], part_sum[e & 1][h], 0, 0, 0);
                 }
             }
         }
+#pragma unroll
+        for (int h = 0; h < C / 16; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; r += 2) {
+                const uint32_t at = total_at(area, h, r, lane);
+                f64x2 t = lds_get<f64x2>(at);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) t[i] += (double)part_sum[0][h][r + i] + (double)part_sum[1][h][r + i];
+                lds_put<f64x2>(at, t);
+            }
     }
     return true;
 }
@@ -258,12 +297,12 @@ template <int KIND, int C, bool CC>
 __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev tgt, RaysDev rays, SplatDev sp)
 {
     extern __shared__ uint4 lds_raw[];
-    const long long row = image_row(tgt, rays);
+    const long long row = image_row<C>(tgt, rays);
     if (row == 0) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)(reinterpret_cast<char*>(lds_raw) + wave * kPatchBytes);
-    static_assert(PushRecords<KIND>::kBytes <= kPatchBytes, "the records of a ray");
+    static_assert(PushRecords<KIND>::kBytes <= kPatchBytes, "the records of a ray");   // (taken ray by ray a part has no sums)
     constexpr int kPlanes = PushRecords<KIND>::kPlanes;
     const PatchGrid<kPatchRays> grid(rays.M, row);
     const int S = rays.S;
@@ -289,9 +328,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev
             const unsigned long long oks = __ballot(ok);
             if (oks == 0ull) return;
             bool whole = !by_rays;
-            f32x4 acc[C / 16];
 #pragma unroll
-            for (int h = 0; h < C / 16; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int h = 0; h < C / 16; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; r += 2) lds_put<f64x2>(total_at(area, h, r, lane), f64x2{0.0, 0.0});
             if (whole) {
                 const int scene = __builtin_amdgcn_readfirstlane(__shfl(q.scene, __builtin_ctzll(oks), 64));
                 float probe = 0.0f;
@@ -300,7 +340,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev
 #pragma unroll 1
                     for (int pl = 0; pl < kPlanes; ++pl)
                         patch_steps<kPatchRays>([&](int from, int len, int only) {
-                            return pull_points<KIND, C>(tgt, sp, scene, area, cells, from, len, only, pl, acc, probe, lane);
+                            return pull_points<KIND, C>(tgt, sp, scene, area, cells, from, len, only, pl, probe, lane);
                         });
                 }
                 whole = __ballot(probe != 0.0f) == 0ull;
@@ -317,8 +357,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_patch_bwd_kernel(GridDev
                 const long long at = grid.ray(patch, 4 * (lane >> 4) + r, has);
                 if (!whole || !has || (lane >> 4) < y0 || (lane >> 4) >= y1) continue;
                 float* out = sp.d_feats + (size_t)at * C + C / 16 * (lane & 15);
-                if constexpr (C == 32) *reinterpret_cast<f32x2*>(out) = f32x2{acc[0][r], acc[C / 16 - 1][r]};
-                else *out = acc[0][r];
+                auto sum = [&](int h) { return (float)lds_get<f64x2>(total_at(area, h, r & 2, lane))[r & 1]; };
+                if constexpr (C == 32) *reinterpret_cast<f32x2*>(out) = f32x2{sum(0), sum(1)};
+                else *out = sum(0);
             }
             wave_lds_fence();
         });
@@ -329,7 +370,7 @@ template <int KIND, int C, bool CC>
 hipError_t launch_t(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu, hipStream_t stream)
 {
     constexpr bool kMayPatch = KIND != LP_GRID_TRIPLANE;
-    const bool patches = kMayPatch && rays.M >= kMinRays && rays.M * rays.S >= kMinPoints;
+    const bool patches = kMayPatch && rays.M >= kMinRays && rays.M * rays.S >= kMinPoints && rays.S * C >= kMinPointChannels;
     if constexpr (kMayPatch) if (patches) {
         auto kernel = splat_patch_bwd_kernel<KIND, C, CC>;
         const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWaves * kPatchBytes);

@@ -10,7 +10,7 @@ import lp_inputs
 from lp_inputs import HASH, TRIPLANE, VOXEL
 
 from parity import check_case_splat
-from tile_rules import image_row
+from tile_rules import gradient_in_patches, image_row, patch_routes, push_segment
 
 pytestmark = pytest.mark.gpu
 
@@ -65,12 +65,27 @@ def test_pushed_images(lp, oracle, kind, channels, image):
     print(check_case_splat(lp, oracle, sp, label=f"patches kind={kind} C={channels} {image}"), flush=True)
 
 
+def _push_routes(sp, row):
+    return {k for k, n in patch_routes(sp, row, 32, push_segment(sp.n_rays, sp.samples)).items() if n}
+
+
 @pytest.mark.parametrize("kind,channels", [(VOXEL, 32), (TRIPLANE, 16), (HASH, 16)])
-@pytest.mark.parametrize("samples,res,contract", [(4, (64, 64, 64), 0.0), (16, (45, 48, 50), 0.0), (24, (64, 40, 90), 1.0)])
-def test_pushed_images_that_reach_many_texels(lp, oracle, kind, channels, samples, res, contract):
-    """Points far apart along their rays and contract coordinates: steps of four points and of one."""
+@pytest.mark.parametrize("samples,res,contract,routes,flat", [(4, (64, 64, 64), 0.0, {8, 1}, {8}), (16, (45, 48, 50), 0.0, {8}, {8}),
+                                                              (24, (64, 40, 90), 1.0, {8, 4, 1}, {8, 4})])
+def test_pushed_images_that_reach_many_texels(lp, oracle, kind, channels, samples, res, contract, routes, flat):
+    """Points far apart along their rays and contract coordinates: steps of eight points, of four and of one (`routes`; triplanes:
+    `flat`)."""
     sp = _finds(_image(kind, channels, 96, 32, samples, res, contract=contract, far=12.0 if contract else 4.0), 96)
+    assert _push_routes(sp, 96) == (flat if kind == TRIPLANE else routes)
     print(check_case_splat(lp, oracle, sp, label=f"patches many texels kind={kind} S={samples} {res}"), flush=True)
+
+
+@pytest.mark.parametrize("kind,channels", [(VOXEL, 16), (TRIPLANE, 32), (HASH, 32)])
+def test_pushed_images_one_point_of_one_ray_at_a_time(lp, oracle, kind, channels):
+    """Where a single point of a patch's rays reaches more texels than there are slots."""
+    sp = _finds(_image(kind, channels, 96, 32, 24, (120, 100, 90), contract=1.0, far=12.0), 96)
+    assert _push_routes(sp, 96) == {8, 4, 1} | (set() if kind == TRIPLANE else {"ray"})
+    print(check_case_splat(lp, oracle, sp, label=f"patches ray by ray kind={kind}"), flush=True)
 
 
 @pytest.mark.parametrize("kind,channels", STRUCTURES)
@@ -125,9 +140,19 @@ def _gradients(lp, sp, infinite=0.0):
 def test_gradients_of_images(lp, kind, channels, width, height, samples, views, cut, per_scene):
     """Against the generic kernel; the bound as in test_gpu_splat_naive_backward."""
     sp = _finds(_image(kind, channels, width, height, samples, (40, 33, 37), views, cut, per_scene), width, 0.9, 2.0)
-    assert sp.n_rays >= 65536 and sp.n_rays * samples >= 4000000
+    assert gradient_in_patches(sp, width)
     got, want, total = _gradients(lp, sp)
     assert ((got - want).abs() <= 2 * (8 * samples + 3) * 2.0 ** -24 * total).all()
+
+
+@pytest.mark.parametrize("kind,channels", [(VOXEL, 16), (VOXEL, 32), (HASH, 16), (HASH, 32)])
+def test_gradients_of_images_in_contract_coordinates(lp, kind, channels):
+    """Steps of eight points, of four and of one; the bound as above."""
+    sp = _finds(_image(kind, channels, 364, 364, 64, (128, 128, 128), contract=1.0, far=12.0), 364, 0.9, 2.0)
+    assert gradient_in_patches(sp, 364)
+    assert {k for k, n in patch_routes(sp, 364, 16, every=61).items() if n} == {8, 4, 1}
+    got, want, total = _gradients(lp, sp)
+    assert ((got - want).abs() <= 2 * (8 * sp.samples + 3) * 2.0 ** -24 * total).all()
 
 
 @pytest.mark.parametrize("kind,channels", [(VOXEL, 32), (HASH, 16)])
@@ -138,3 +163,38 @@ def test_infinite_gradients_of_images(lp, kind, channels):
     assert torch.isposinf(want).any() and torch.isfinite(want).any()
     assert torch.equal(torch.isposinf(got), torch.isposinf(want))
     assert torch.equal(torch.isnan(got), torch.isnan(want))
+
+
+@pytest.mark.parametrize("channels,samples,width", [(16, 64, 256), (16, 160, 256), (32, 24, 416), (32, 160, 256)])
+def test_gradients_of_images_are_no_further_from_64_bits(lp, channels, samples, width):
+    """The 2-norm of the error of a patch's gradients against that of the same rays as a list, which go ray by ray."""
+    import torch
+    res = (60, 55, 64)
+    sp = _finds(_image(VOXEL, channels, width, width, samples, res), width, 0.9, 2.0)
+    assert gradient_in_patches(sp, width)
+    target, rays, splat = lp.splat_to_device(sp)
+    theta, theta_w = lp.splat_fwd(target, rays, splat)
+    d_theta = torch.randn(theta[0].shape, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    order = np.random.default_rng(5).permutation(sp.n_rays)
+    listed = _finds(dataclasses.replace(sp, **{n: np.ascontiguousarray(getattr(sp, n)[order]) for n in ("origins", "dirs", "near", "far", "feats")}), 0, 0.9, 2.0)
+    patches = lp.splat_bwd(target, rays, splat, theta_w, [d_theta])[0]
+    alone = torch.empty_like(patches)
+    alone[torch.from_numpy(order).cuda()] = lp.splat_bwd(*lp.splat_to_device(listed), theta_w, [d_theta])[0]
+
+    o, d, near, far = (t.double() for t in (rays.origins, rays.dirs, rays.near, rays.far))
+    vec = lambda v: torch.tensor(np.asarray(v, dtype=np.float32), device="cuda").double()
+    lo, hi, n = vec(sp.aabb_min), vec(sp.aabb_max), vec(res)
+    weights, grad = theta_w[0].reshape(-1).double(), d_theta.reshape(-1, channels).double()
+    want = torch.zeros_like(patches, dtype=torch.float64)
+    for j in range(samples):
+        t = near + (j + 0.5) * ((far - near) / samples)
+        u = torch.minimum(((o + t[:, None] * d - lo) * ((n - 1) / (hi - lo))).clamp(min=0), n - 1)
+        cell = torch.minimum(u.long(), n.long() - 2)
+        for corner in np.ndindex(2, 2, 2):
+            b = torch.tensor(corner, device="cuda")
+            w = torch.where(b == 1, u - cell, 1 - (u - cell)).prod(1)
+            k = cell + b
+            k = (k[:, 0] * res[1] + k[:, 1]) * res[2] + k[:, 2]
+            want += torch.where(weights[k] > 0, w / weights[k], 0.0)[:, None] * grad[k]
+    error = lambda x: float((x.double() - want).norm() / want.norm())
+    assert error(patches) <= error(alone), (error(patches), error(alone))

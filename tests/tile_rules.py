@@ -1,5 +1,6 @@
 """The launch and scatter rules of the kernels (lp_mfma_bwd_tile.h, lp_tile_scatter.h, lp_mfma_fwd.hip) on the CPU: which way the steps
 of a problem take, so that a test can tell whether it reaches the branch it is meant for."""
+import dataclasses
 from collections import Counter
 
 import numpy as np
@@ -63,6 +64,13 @@ def image_row(inp, pixel, step):
     return row if close else 0
 
 
+def gradient_in_patches(sp, row):
+    """Whether the naive Splatter's gradient takes an image `row` wide in patches (lp_splat_naive_bwd.hip)."""
+    longest = 2.0 if sp.n_rays >= 131072 else 0.75 if sp.channels == 16 else 1.25
+    return sp.kind != TRIPLANE and sp.n_rays >= 65536 and sp.n_rays * sp.samples >= 4000000 and sp.samples * sp.channels >= 768 and \
+        image_row(sp, 0.9, longest) == row
+
+
 SLOTS = {32: 224, 16: 160}   # texels of a step of a patch, by its rays
 PATCH_TEXELS, PATCH_POINTS = 1024, 8
 
@@ -84,8 +92,8 @@ def push_segment(n_rays, samples, n_cu=256):
     return min(max(points // PATCH_POINTS * PATCH_POINTS, PATCH_POINTS), samples)
 
 
-def patch_routes(inp, row, n_rays=32, seg=None):
-    """Counter of how the points of an image's patches are taken (lp_splat_patch.h): "part": a patch that falls into parts, "lines": a
+def patch_routes(inp, row, n_rays=32, seg=None, every=1):
+    """Of every `every`-th patch: Counter of how the points of an image's patches are taken (lp_splat_patch.h): "part": a patch that falls into parts, "lines": a
     part whose rays go line by line (its gradient: ray by ray), 8 | 4 | 1: points of a step of all rays, "ray": one point of one ray."""
     c = cells(inp)
     scene = inp.scene if inp.scene is not None else np.zeros(inp.n_rays, int)
@@ -117,7 +125,9 @@ def patch_routes(inp, row, n_rays=32, seg=None):
                         if at % 4 == 0:
                             n = 4
 
-    for patch in patches(inp, row, n_rays):
+    for k, patch in enumerate(patches(inp, row, n_rays)):
+        if k % every:
+            continue
         there = patch >= 0
         ends = c[patch][:, :, [0, -1]]
         other = lambda axis: (np.abs(np.diff(ends, axis=axis)).max((2, 3)) > 5) | (np.diff(scene[patch], axis=axis) != 0)
@@ -178,3 +188,69 @@ def step_routes(inp):
             for r in rays[rays < inp.n_rays]:
                 march([r], "ray", 32)
     return routes
+
+
+def splat_in_tiles(n_rays, samples, waves, up_to):
+    """The Splatter's launch rule (lp_tile_scatter.h push_order)."""
+    rounds = lambda items: -(-items // waves)
+    return rounds(-(-n_rays // TILE_RAYS)) * -(-samples // TILE_SAMPLES) <= up_to * rounds(n_rays) * -(-samples // 32)
+
+
+def splat_mlp_routes(sp, n_cu=256):
+    """(push, gradient of the prior) of the Splatter with an MLP (lp_splat_mfma.hip, lp_splat_mfma_bwd.h): a Counter each of
+    ("tile" | "ray", 1 | 2 | 4 windows | "walk"); a single ray has one window or the walk."""
+    scene = sp.scene if sp.scene is not None else np.zeros(sp.n_rays, int)
+    near_by = 6 if sp.kind != TRIPLANE and sp.channels == 16 else 9
+    step = 1e30 if sp.channels == 32 else EXTENT if sp.kind != TRIPLANE else 4 * EXTENT
+
+    def fits(run):
+        e = run.reshape(-1, 3).max(0) - run.reshape(-1, 3).min(0) + 2
+        if e.max() > EXTENT:
+            return False
+        return max(e[0] * e[1], e[1] * e[2], e[2] * e[0]) <= PLANE_TEXELS if sp.kind == TRIPLANE else e.prod() <= TEXELS
+
+    def march(routes, c, rays, how, parts_of_a_step, width):
+        for j0 in range(0, sp.samples, width):
+            j = np.minimum(np.arange(j0, j0 + width), sp.samples - 1)
+            for parts in parts_of_a_step:
+                if all(fits(run) for run in np.split(c[rays][:, j], parts, axis=1)):
+                    routes[how, parts] += 1
+                    break
+            else:
+                routes[how, "walk"] += 1
+
+    def tiles(c):
+        for first in range(0, sp.n_rays, TILE_RAYS):
+            rays = np.arange(first, min(first + TILE_RAYS, sp.n_rays))
+            there = np.minimum(np.arange(first, first + TILE_RAYS), sp.n_rays - 1)
+            ends = c[rays][:, [0, -1]]
+            yield rays, there, (scene[rays] == scene[first]).all(), np.abs(ends - ends[0]).max()
+
+    def together(c, near_by, step):   # of 256 tiles
+        all_tiles = list(tiles(c))
+        middle = np.abs(c[:, min(sp.samples // 2 + TILE_SAMPLES, sp.samples - 1)] - c[:, sp.samples // 2]).max(1)   # (the kernel: to a fraction of a texel)
+        return 4 * sum(apart <= near_by and middle[rays[0]] <= step for rays, _, _, apart in (all_tiles[i * len(all_tiles) // 256] for i in range(256))) >= 3 * 256
+
+    push, c = Counter(), cells(sp)
+    in_tiles = splat_in_tiles(sp.n_rays, sp.samples, 8 * n_cu, 2.0) and together(c, 9, 1e30)
+    for rays, there, one_scene, apart in tiles(c):
+        if in_tiles and one_scene and apart <= 9:
+            march(push, c, there, "tile", (1, 2, 4), TILE_SAMPLES)
+        else:
+            for r in rays:
+                ends = c[r, [0, -1]]
+                windows = not in_tiles and (np.abs(ends[1] - ends[0]) * min(32, sp.samples) <= EXTENT * sp.samples).all()
+                march(push, c, [r], "ray", (1,) if windows else (), 32)
+
+    back, c = Counter(), cells(dataclasses.replace(sp, res=sp.prior_res))
+    in_tiles = splat_in_tiles(sp.n_rays, sp.samples, 4 * n_cu, 1.05) and together(c, near_by, step)
+    for rays, there, one_scene, _ in tiles(c):
+        if in_tiles and one_scene:
+            march(back, c, there, "tile", (1, 2, 4), TILE_SAMPLES)
+        elif in_tiles:
+            for r in rays:
+                march(back, c, [r] * TILE_RAYS, "tile", (1, 2, 4), TILE_SAMPLES)
+        else:
+            for r in rays:
+                march(back, c, [r], "ray", (1,) if sp.kind == TRIPLANE else (), 32)
+    return push, back
