@@ -12,12 +12,19 @@
 // run-time branch in the point placement (uniform over the launch).
 // What bounds it: the atomic adds.  160^3 x 32 voxels, prior alike, MLP 67-64-64-32, 4 x 64^2 rays x 160 points: ray by ray
 // 9.6 lines per point, 1.41 ms at 86 % of the rate of the adds; in tiles 5.25 lines, 0.76 ms at 86 %.
+// Tiles where the launch is large enough (push_order) and the rays run in tiles; both kernels are launched and find out which is meant,
+// 5 us.  Without the look rays that do not run side by side went one after the other through the tiles' kernel: 48^2 and 64^2
+// pixels three texels apart 0.66 .. 0.9 of the speed before tiles.  Time before tiles over that now, 32^2 .. 176^2 pixels, 24 to 160 points, both
+// structures, 16 and 32 channels: up to one texel from pixel to pixel 1.0 .. 3.9, at two 0.87 .. 2.0 (the slowest at 48^2 x 24 points,
+// 103 -> 118 us; at 160 points 1.15 and more from 64^2 on), at three and four 0.88 .. 1.12, rays in random order 0.97 .. 1.45.
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
 #include "lp_mfma_bwd_common.h"
 #include "lp_splat_common.h"
 #include "lp_tile_scatter.h"
+
+#include <algorithm>
 
 namespace lp {
 
@@ -41,7 +48,7 @@ struct SplatLds {
     // a wave's area: the scatter's, and its four rays' 48 inputs
     static constexpr int W_X = kWinBytes / 16, W_UNITS = W_X + kTileRays * 48 / 4;
     static constexpr int UNITS = WAVE + kWaves * W_UNITS;
-    static_assert(2 * UNITS * 16 <= 160 * 1024, "two workgroups fit the LDS of a compute unit");
+    static_assert(2 * (UNITS * 16 + 16) <= 160 * 1024, "two workgroups fit the LDS of a compute unit");
 };
 
 template <int KSP, int KSE, int NH, int CO>
@@ -108,10 +115,12 @@ __device__ __forceinline__ void push_ray_step(const GridDev& g, const SplatDev& 
     scatter_weights<KIND, C>(g, sp.theta_w, scene, info, col, grp);
 }
 
-// TILES: items are tiles of four rays (those that do not lie side by side go one after the other), else single rays.
+// TILES: items are tiles of four rays (those that do not lie side by side go one after the other), else single rays.  `choose`: both
+// kernels are launched, and the one that the rays suit works.
 template <int KIND, int KSP, int KSE, int NH, bool TILES>
-__global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt, MlpDev m, RaysDev rays, SplatDev sp, PushOrder order)
+__global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt, MlpDev m, RaysDev rays, SplatDev sp, PushOrder order, bool choose)
 {
+    if (choose && rays_run_in_tiles(tgt, rays, (float)kPushApart, 1e30f) != TILES) return;
     constexpr int CO = 16 * KSP;  // the target has the prior's channel count
     using L = SplatLds<KSP, KSE, NH>;
     constexpr int MB = L::MB, KSH = L::KSH;
@@ -227,19 +236,26 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt,
     }
 }
 
+long long waves_of(int n_cu) { return (2LL * n_cu + 7) / 8 * 8 * kWaves; }
+
 template <int KIND, int KSP, int KSE, int NH>
 hipError_t launch(const GridDev& tgt, const MlpDev& m, const RaysDev& rays, const SplatDev& sp, int n_cu,
                   hipStream_t stream)
 {
     constexpr int kLdsBytes = SplatLds<KSP, KSE, NH>::UNITS * 16;
-    long long blocks = (2LL * n_cu + 7) / 8 * 8;
-    const PushOrder order = push_order(rays, blocks * kWaves, kWaves);
-    if (blocks > order.n_groups) blocks = (order.n_groups + 7) / 8 * 8;
-    auto kernel = order.tiles ? splat_mfma_kernel<KIND, KSP, KSE, NH, true> : splat_mfma_kernel<KIND, KSP, KSE, NH, false>;
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, order);
-    return hipGetLastError();
+    const PushOrder tiles = push_order(rays, waves_of(n_cu), kWaves), single = push_order(rays, waves_of(n_cu), kWaves, 0.0);
+    auto start = [&](auto kernel, const PushOrder& order) {
+        const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (e != hipSuccess) return e;
+        const long long blocks = std::min(waves_of(n_cu) / kWaves, (order.n_groups + 7) / 8 * 8);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, tgt, m, rays, sp, order, tiles.tiles != 0);
+        return hipGetLastError();
+    };
+    if (tiles.tiles) {
+        const hipError_t e = start(splat_mfma_kernel<KIND, KSP, KSE, NH, true>, tiles);
+        if (e != hipSuccess) return e;
+    }
+    return start(splat_mfma_kernel<KIND, KSP, KSE, NH, false>, single);
 }
 
 template <int KIND, int KSP, int KSE>

@@ -21,10 +21,10 @@
 // ray 6.8 lines of atomic adds per point, 1.48 ms; in tiles 4.6 lines, 1.36.
 // Tiles only where a wave has no more steps that way (single rays over tiles at fewer rays: 0.33 .. 1.0), and where the rays run in
 // tiles.  The tiles have a kernel of their own: one for both held the geometry, the inputs and the sums of four rays for a
-// single one too (16-channel voxels 0.79 .. 0.96 times as fast as the kernel before tiles).  Against that kernel, 384 to 65 536
-// rays, 24 to 160 texels an axis: images 0.94 .. 1.8 (16-channel voxels), 0.99 .. 2.0 (32), 0.98 .. 2.3 and 1.17 .. 2.8 (triplanes
-// of 16 and 32); lists of rays 0.93 .. 1.02, 0.94 .. 1.13, 0.93 .. 1.19, 1.17 .. 1.8: the second launch and the look at the rays cost
-// 5 to 10 us.
+// single one too (16-channel voxels 0.79 .. 0.96 times as fast as the kernel before tiles).  Against that kernel, 32^2 to 176^2 pixels,
+// up to four texels from pixel to pixel, 24 to 160 points: images 0.97 .. 1.2 (16-channel voxels), 0.98 .. 1.55 (32), 0.89 .. 1.4 and
+// 1.0 .. 2.0 (triplanes of 16 and 32); rays in random order 1.01 .. 1.12, 0.99 .. 1.11, 0.95 .. 1.09, 1.09 .. 1.34: the second launch and
+// the look at the rays cost about 5 us.
 //
 // This header holds the kernel and its launcher templates; two translation units instantiate
 // them (the instantiations for 32-channel triplanes are built without the build flag that keeps
@@ -188,52 +188,8 @@ __device__ __forceinline__ void gather_normalised(const GridDev& tgt, const Spla
     }
 }
 
-// Whether the rays run in tiles: in three of four among 256 tiles they lie side by side, and a step is at most `step` texels long in the
-// middle.  All threads of a workgroup call it, and every workgroup finds the same.  (In fp32 and with all loads under way at once, as
-// every launch waits for it.)
-__device__ __forceinline__ bool rays_run_in_tiles(const GridDev& g, const RaysDev& rays, float step)
-{
-    __shared__ int together;
-    const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays;
-    const long long first = (long long)threadIdx.x * n_tiles / blockDim.x * kTileRays;
-    float near[kTileRays], far[kTileRays], o[kTileRays][3], d[kTileRays][3];
-#pragma unroll
-    for (int i = 0; i < kTileRays; ++i) {
-        const long long r = min(first + i, rays.M - 1);
-        near[i] = rays.near[r];
-        far[i] = rays.far[r];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) { o[i][a] = rays.origins[3 * r + a]; d[i][a] = rays.dirs[3 * r + a]; }
-    }
-    if (threadIdx.x == 0) together = 0;
-    const float contract = (float)g.contract;
-    auto texel = [&](int i, int a, float t) {
-        float x = o[i][a] + t * d[i][a];
-        if (contract > 0.0f) {
-            const float m = fabsf(x), far = 0.5f * ((2.0f - contract) * (1.0f - 1.0f / fmaxf(m, 1.0f)) + contract);
-            x = m <= 1.0f ? 0.5f * contract * x : x < 0.0f ? -far : far;
-        }
-        return fminf(fmaxf((x - (float)g.amin[a]) * (float)g.scale[a], 0.0f), (float)(g.N[a] - 1));
-    };
-    const float middle = 0.5f * (near[0] + far[0]), ahead = middle + (float)kTileSamples * (far[0] - near[0]) / (float)rays.S;
-    bool apart = false;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float n0 = texel(0, a, near[0]), f0 = texel(0, a, far[0]);
-#pragma unroll
-        for (int i = 1; i < kTileRays; ++i)
-            apart = apart || !(fabsf(texel(i, a, near[i]) - n0) <= (float)kPushApart) || !(fabsf(texel(i, a, far[i]) - f0) <= (float)kPushApart);
-        apart = apart || !(fabsf(texel(0, a, ahead) - texel(0, a, middle)) <= step);
-    }
-    __syncthreads();
-    const int n = __popcll(__ballot(!apart));
-    if ((threadIdx.x & 63) == 0) atomicAdd(&together, n);
-    __syncthreads();
-    return 4 * together >= 3 * (int)blockDim.x;
-}
-
 // TILE: items are tiles, else single rays.  `choice`: both kernels are launched, and the one that the rays suit works; that of the
-// tiles, the first, decides and leaves its answer there (looking costs both together 7 to 10 us of a backward of 100 or more).
+// tiles, the first, decides and leaves its answer there (looking and the second launch cost about 5 us of a backward of 100 or more).
 template <int KIND, int KSP, int KSE, int NH, bool TILE>
 __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt, MlpDev m, RaysDev rays,
                                                                      SplatDev sp, BwdIo io, PushOrder order, int* choice)
@@ -242,8 +198,13 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
     constexpr int MB = L::MB, KSH = L::KSH, NBE = L::NBE;
     constexpr int CP = 16 * KSP;          // channels of the prior and of the target
     if constexpr (TILE) {
-        // (16-channel voxels: where a step of a tile does not fit a window, single rays are the faster ones)
-        const bool tiles = rays_run_in_tiles(sp.prior, rays, KIND == LP_GRID_VOXEL && CP == 16 ? (float)kWinExtent : 1e30f);
+        // With 16 channels single rays are the faster ones where a step of a tile is long (time before tiles over that in tiles, 64^2 ..
+        // 176^2 pixels: voxels 0.95 .. 1.2 up to 18 texels, 0.87 .. 1.04 beyond, triplanes 1.01 .. 1.4 up to 36, 0.83 .. 1.03 beyond),
+        // and over voxels where pixels are two texels apart (0.87 .. 1.04).
+        constexpr bool kVoxel = KIND == LP_GRID_VOXEL;
+        const float near_by = kVoxel && CP == 16 ? 6.0f : (float)kPushApart;
+        const float step = CP == 32 ? 1e30f : kVoxel ? 18.0f : 36.0f;
+        const bool tiles = rays_run_in_tiles(sp.prior, rays, near_by, step);
         if (blockIdx.x == 0 && threadIdx.x == 0) *choice = tiles;
         if (!tiles) return;
     } else {

@@ -375,8 +375,56 @@ inline PushOrder push_order(const RaysDev& rays, long long waves, int waves_per_
 }
 
 // Splatter with an MLP: cells between the rays of a tile.  (64^2 pixels over 160^3 voxels, 1.3 voxels from pixel to pixel: push
-// 1.09 ms with 3, where most rays go one by one, 0.79 with 6, 0.76 with 9.)
+// 1.09 ms with 3, where most rays go one by one, 0.79 with 6, 0.76 with 9.  Pixels two texels apart are tiles with 9 and gain, 1.0 .. 2.0
+// from 64^2 pixels x 64 points on; those three apart are none, and gain by neither.)
 constexpr int kPushApart = 9;
+
+// Whether the rays run in tiles: in three of four among 64 tiles they lie side by side, within `near_by` texels at both ends, and a step is
+// at most `step` texels long in the middle.  All threads of a workgroup call it, and every workgroup and the other kernel of a pair
+// find the same: no contraction of products and sums.  (One wave looks, in fp32 and with all loads under way at once: every launch
+// waits for it.)
+__device__ __forceinline__ bool rays_run_in_tiles(const GridDev& g, const RaysDev& rays, float near_by, float step)
+{
+#pragma clang fp contract(off)
+    __shared__ int together;
+    if (threadIdx.x < 64) {
+        const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays;
+        const long long first = (long long)threadIdx.x * n_tiles / 64 * kTileRays;
+        float near[kTileRays], far[kTileRays], o[kTileRays][3], d[kTileRays][3];
+#pragma unroll
+        for (int i = 0; i < kTileRays; ++i) {
+            const long long r = min(first + i, rays.M - 1);
+            near[i] = rays.near[r];
+            far[i] = rays.far[r];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) { o[i][a] = rays.origins[3 * r + a]; d[i][a] = rays.dirs[3 * r + a]; }
+        }
+        const float contract = (float)g.contract;
+        auto texel = [&](int i, int a, float t) {
+#pragma clang fp contract(off)
+            float x = o[i][a] + t * d[i][a];
+            if (contract > 0.0f) {
+                const float m = fabsf(x), far = 0.5f * ((2.0f - contract) * (1.0f - 1.0f / fmaxf(m, 1.0f)) + contract);
+                x = m <= 1.0f ? 0.5f * contract * x : x < 0.0f ? -far : far;
+            }
+            return fminf(fmaxf((x - (float)g.amin[a]) * (float)g.scale[a], 0.0f), (float)(g.N[a] - 1));
+        };
+        const float middle = 0.5f * (near[0] + far[0]), ahead = middle + (float)kTileSamples * (far[0] - near[0]) / (float)rays.S;
+        bool apart = false;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float n0 = texel(0, a, near[0]), f0 = texel(0, a, far[0]);
+#pragma unroll
+            for (int i = 1; i < kTileRays; ++i)
+                apart = apart || !(fabsf(texel(i, a, near[i]) - n0) <= near_by) || !(fabsf(texel(i, a, far[i]) - f0) <= near_by);
+            apart = apart || !(fabsf(texel(0, a, ahead) - texel(0, a, middle)) <= step);
+        }
+        const int n = __popcll(__ballot(!apart));
+        if (threadIdx.x == 0) together = n;
+    }
+    __syncthreads();
+    return 4 * together >= 3 * 64;
+}
 
 // Whether the four rays from `first` on (those below `end`) run side by side: in one scene, and within APART cells of the
 // first at both ends.

@@ -240,8 +240,11 @@ def check_case_dec(lp, oracle, inp, math_mode=0, aux_grads=True, seed=0, label="
 
 # ---- Splatter ---------------------------------------------------------------------------------
 
-def check_case_splat(lp, oracle, sp, seed=0, label="", max_strict_fail=MAX_STRICT_FAIL, width_cap=WIDTH_CAP):
-    """Splatter parity: normalised structure, weight sums and every gradient against the oracle."""
+def check_case_splat(lp, oracle, sp, seed=0, label="", max_strict_fail=MAX_STRICT_FAIL, width_cap=WIDTH_CAP, sparse=False):
+    """Splatter parity: normalised structure, weight sums and every gradient against the oracle.  `sparse`: most texels are reached by
+    no point, and the structure's tolerance is relative to the root mean square of those that are: the error of a pushed vector does not get
+    smaller with the empty texels around (1e-4 of 0.175 over all 90 x 64 x 70, a twelfth of them reached, is 1.7e-5; a vector's
+    largest error is 3.3e-5, ray by ray and in tiles alike)."""
     import torch
     prob = oracle.SplatProblem(sp)
     o_theta, o_w = oracle.splat_fwd(prob)
@@ -263,9 +266,15 @@ def check_case_splat(lp, oracle, sp, seed=0, label="", max_strict_fail=MAX_STRIC
         # the sums the kernel accumulates, then the normalised result: both at the plain tolerance
         # (the corner weights keep their relative accuracy however small they are: f and 1 - f are
         # both rounded from the fp64 index)
+        def empty(ref):
+            if not sparse:
+                return None
+            reached = ref[np.broadcast_to((o_w[p] > 0)[..., None], ref.shape)]
+            return FWD_RTOL * float(np.sqrt(np.mean(reached * reached)))
+
         worst[f"sum{p}"] = close(g_t.astype(np.float64) * g_w[..., None], o_theta[p] * o_w[p][..., None], FWD_RTOL,
-                                 f"{label} theta[{p}] * theta_w[{p}]")
-        worst[f"theta{p}"] = close(g_t, o_theta[p], FWD_RTOL, f"{label} theta[{p}]")
+                                 f"{label} theta[{p}] * theta_w[{p}]", empty(o_theta[p] * o_w[p][..., None]))
+        worst[f"theta{p}"] = close(g_t, o_theta[p], FWD_RTOL, f"{label} theta[{p}]", empty(o_theta[p]))
     flat = lambda r: [("d_feats", r[0])] + [(f"d_prior{i}", a) for i, a in enumerate(r[1])] \
         + [(f"dW{i}", a) for i, a in enumerate(r[2])] + [(f"db{i}", a) for i, a in enumerate(r[3])]
     gpu = [d_feats] + list(d_prior) + list(dW) + list(db)

@@ -201,7 +201,7 @@ def splat_mlp_routes(sp, n_cu=256):
     ("tile" | "ray", 1 | 2 | 4 windows | "walk"); a single ray has one window or the walk."""
     scene = sp.scene if sp.scene is not None else np.zeros(sp.n_rays, int)
     near_by = 6 if sp.kind != TRIPLANE and sp.channels == 16 else 9
-    step = 1e30 if sp.channels == 32 else EXTENT if sp.kind != TRIPLANE else 4 * EXTENT
+    step = 1e30 if sp.channels == 32 else 18 if sp.kind != TRIPLANE else 36
 
     def fits(run):
         e = run.reshape(-1, 3).max(0) - run.reshape(-1, 3).min(0) + 2
@@ -226,10 +226,10 @@ def splat_mlp_routes(sp, n_cu=256):
             ends = c[rays][:, [0, -1]]
             yield rays, there, (scene[rays] == scene[first]).all(), np.abs(ends - ends[0]).max()
 
-    def together(c, near_by, step):   # of 256 tiles
+    def together(c, near_by, step):   # of 64 tiles
         all_tiles = list(tiles(c))
         middle = np.abs(c[:, min(sp.samples // 2 + TILE_SAMPLES, sp.samples - 1)] - c[:, sp.samples // 2]).max(1)   # (the kernel: to a fraction of a texel)
-        return 4 * sum(apart <= near_by and middle[rays[0]] <= step for rays, _, _, apart in (all_tiles[i * len(all_tiles) // 256] for i in range(256))) >= 3 * 256
+        return 4 * sum(apart <= near_by and middle[rays[0]] <= step for rays, _, _, apart in (all_tiles[i * len(all_tiles) // 64] for i in range(64))) >= 3 * 64
 
     push, c = Counter(), cells(sp)
     in_tiles = splat_in_tiles(sp.n_rays, sp.samples, 8 * n_cu, 2.0) and together(c, 9, 1e30)
