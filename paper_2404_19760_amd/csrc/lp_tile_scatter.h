@@ -309,16 +309,12 @@ __device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_gr
                                              char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, bool tile,
                                              float* const* sums = nullptr, bool valid = true, bool windows = true)
 {
-    constexpr bool kPushes = WHAT != Scatter::kGradient, kOfRay = WHAT == Scatter::kPushRay;
+    constexpr bool kOfRay = WHAT == Scatter::kPushRay;
     const int col = lane & 31, k = tile ? (col & (kTileSamples - 1)) : col, full = tile ? kTileSamples : 32;
     float probe = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r)
         if (!kOfRay || r % 4 == 0) probe = fmaf(dFt[r], 0.0f, probe);
-    if constexpr (kPushes) {   // (an undefined ray: its weights)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) probe = fmaf(cell.f[a], 0.0f, probe);
-    }
     const bool finite = __ballot(probe != 0.0f) == 0ull && (RAYS != RayWindows::kNone || tile) && windows;
     int len = full;
     Window win;
