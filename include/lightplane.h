@@ -283,7 +283,8 @@ lp_status lp_splat_fwd(const lp_grid* target, const lp_rays* rays, const lp_spla
                        float* const theta[3], float* const theta_w[3], void* stream);
 
 /* 1 if lp_splat_fwd (and, with an MLP, lp_splat_bwd) runs this target / splat on the
-   wavefront-per-ray kernels, else 0 (generic kernels, same results).  Covered: targets of 16 or
+   kernels for 16 and 32 channels (a wavefront takes a patch of an image's pixels, a tile of four
+   rays or one ray), else 0 (generic kernels, same results).  Covered: targets of 16 or
    32 channels, with or without contract coordinates (voxel grids, triplanes and, for the naive
    Splatter, hash tables whose size is a power of two); with an MLP, voxel grids and triplanes
    with a prior of the same channel count and contraction in fp32, one or two hidden layers of

@@ -786,14 +786,14 @@ lp_status lp_splat_fwd(const lp_grid* target, const lp_rays* rays, const lp_spla
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail("Splatter clear kernels", e);
     if (rays->M > 0 && m.n_layers == 0 && lp::splat_naive_supported(g)) {
-        // naive Splatter with 16 or 32 channels: wavefront per ray, run-merged whole-line atomics
+        // naive Splatter with 16 or 32 channels: patches of an image's pixels, tiles of four rays or single ones
         std::string err;
         int n_cu = 0;
         if (compute_units(&n_cu, &err)) return fail(LP_ERR_HIP, err);
         e = lp::launch_splat_naive(g, r, sd, n_cu, s);
         if (e != hipSuccess) return hip_fail("Splatter forward kernel launch", e);
     } else if (rays->M > 0 && m.n_layers > 0 && lp::splat_mfma_supported(g, m, sd)) {
-        // MLP of the covered shapes: wavefront per ray, MLP on the matrix cores, the same push
+        // MLP of the covered shapes: tiles of four rays or single ones, MLP on the matrix cores
         std::string err;
         int n_cu = 0;
         if (compute_units(&n_cu, &err)) return fail(LP_ERR_HIP, err);
@@ -900,7 +900,7 @@ lp_status lp_splat_bwd(const lp_grid* target, const lp_rays* rays, const lp_spla
     int n_cu = 0;
     if (compute_units(&n_cu, &err)) return fail(LP_ERR_HIP, err);
     if (m.n_layers > 0 && lp::splat_mfma_supported(g, m, sd)) {
-        // covered MLP shapes: wavefront per ray, MLP forward and backward on the matrix cores
+        // covered MLP shapes: tiles of four rays or single ones, MLP forward and backward on the matrix cores
         hipError_t e = lp::launch_splat_mfma_bwd(g, m, r, sd, io, n_cu, s);
         if (e != hipSuccess) return hip_fail("Splatter backward kernel launch", e);
         return LP_OK;

@@ -52,7 +52,7 @@ bool bwd_ws_supported(const GridDev& g, const MlpDev& m);
 hipError_t launch_bwd_mfma_ws(const GridDev& g, const MlpDev& m, const RaysDev& rays, const BwdIo& io,
                               int n_cu, hipStream_t stream);
 
-// ---- naive Splatter forward, wavefront per ray (lp_splat_fast.hip): 16 or 32 channels ----
+// ---- naive Splatter forward (lp_splat_fast.hip: patches of an image, tiles of four rays or single ones): 16 or 32 channels ----
 bool splat_naive_supported(const GridDev& tgt);
 hipError_t launch_splat_naive(const GridDev& tgt, const RaysDev& rays, const SplatDev& sp, int n_cu,
                               hipStream_t stream);

@@ -1,4 +1,4 @@
-// Pieces shared by the Splatter's wavefront-per-ray kernels (Section 3.3 "Splatter").
+// Pieces shared by the Splatter's kernels for 16 and 32 channels (Section 3.3 "Splatter").
 #pragma once
 #include "lp_mfma.h"
 #include "lp_mfma_bwd_common.h"

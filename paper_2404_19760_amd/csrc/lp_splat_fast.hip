@@ -4,11 +4,11 @@
 // What bounds it: the rate of atomic adds (2.1e10 64-byte lines/s on this chip). Pushed ray by ray, a point adds
 // about 10 lines after runs in a cell are merged. Neighbouring rays reach the same texels, so a step takes several of them and
 // adds once per texel what a matrix product of interpolation weights and pixel features gives:
-//   - images: patches of 8 x 4 pixels, eight points of each (lp_splat_patch.h), 1.45 lines per point, weight sums included;
+//   - images: patches of 8 x 4 pixels, eight points of each (lp_splat_patch.h), 1.55 lines per point, weight sums included;
 //   - other lists of rays: tiles of four neighbouring ones (lp_tile_scatter.h), 3.93 lines per point on the same rays; rays that
 //     do not run side by side one after the other, 32 points per step, by the run-merging walk.
-// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.41 ms ray by ray, 2.12 in tiles (3.95e7 atomic requests of the L2: 89 % of
-// the rate of the adds), 0.89 in patches (1.53e7: 82 %; one wave per SIMD, whose LDS holds the weights).
+// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.41 ms ray by ray, 2.18 in tiles (4.12e7 atomic requests of the L2: 90 % of
+// the rate of the adds), 1.00 in patches (1.62e7: 77 %; one wave per SIMD, whose LDS holds the weights).
 // Items are visited in scrambled order like the Renderer's backward
 // (atomic adds of neighbouring rays queue up at the same L2 channel).
 #include "lp_kernels.h"

@@ -13,10 +13,11 @@
 // What bounds it: the atomic adds.  160^3 x 32 voxels, prior alike, MLP 67-64-64-32, 4 x 64^2 rays x 160 points: ray by ray
 // 9.6 lines per point, 1.41 ms at 86 % of the rate of the adds; in tiles 5.25 lines, 0.76 ms at 86 %.
 // Tiles where the launch is large enough (push_order) and the rays run in tiles; both kernels are launched and find out which is meant,
-// 5 us.  Without the look rays that do not run side by side went one after the other through the tiles' kernel: 48^2 and 64^2
-// pixels three texels apart 0.66 .. 0.9 of the speed before tiles.  Time before tiles over that now, 32^2 .. 176^2 pixels, 24 to 160 points, both
-// structures, 16 and 32 channels: up to one texel from pixel to pixel 1.0 .. 3.9, at two 0.87 .. 2.0 (the slowest at 48^2 x 24 points,
-// 103 -> 118 us; at 160 points 1.15 and more from 64^2 on), at three and four 0.88 .. 1.12, rays in random order 0.97 .. 1.45.
+// 5 us.  Without the look rays that do not run side by side went one after the other through the tiles' kernel: push of 48^2 pixels
+// three and four texels apart 0.69 .. 1.05 of the speed before tiles (0.89 .. 1.06 now), of 2304 rays in random order 0.78 .. 1.14 (0.90 ..
+// 1.47).  Time of a forward before tiles over that now, 32^2 .. 176^2 pixels, 24 to 160 points, both structures, 16 and 32 channels:
+// up to one texel from pixel to pixel 1.0 .. 3.9, at two 0.87 .. 2.0 (the slowest at 48^2 x 24 points, 103 -> 118 us), at three and
+// four 0.88 .. 1.12, rays in random order 0.97 .. 1.46.
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"

@@ -8,8 +8,9 @@
 // sum of what it read over the whole ray, and the corners meet once per ray.
 // Large images are taken in patches of 4 x 4 pixels (lp_splat_patch.h): a texel is read once for the step's 128 points, 0.75
 // reads per point instead of eight, and a matrix product hands it to the rays; then instructions bound it (two waves a SIMD).
-// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.86 ms with a lane per ray (lp_generic.hip), 0.52 ms by texel pieces, 0.35 ms
-// in patches (in patches of 8 x 4 pixels, whose weights leave room for one wave a SIMD, 0.66).
+// 160^3 x 32 voxels, 4 x 128^2 rays x 160 points: 5.86 ms with a lane per ray (lp_generic.hip), 0.51 ms by texel pieces, 0.44 ms
+// in patches (0.38 with sums in fp32, further from 64 bits than ray by ray: pull_points; in patches of 8 x 4 pixels, whose weights
+// leave room for one wave a SIMD, twice as long).
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
