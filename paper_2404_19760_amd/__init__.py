@@ -280,10 +280,15 @@ class Rays:
                      _dev_f32(self.time, "time", (m,)))
 
 
+# the current stream's handle without a Stream object around it, where torch has it (a private name: else the public one)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
-        # (the current stream's handle without building a Stream object around it)
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        if _raw_stream is not None:
+            return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 

@@ -189,6 +189,19 @@ def test_an_mlp_without_layers_is_refused_by_name():
                 call(mlp)
 
 
+def test_the_current_stream_without_torchs_private_name(monkeypatch):
+    import types
+    import paper_2404_19760_amd as lp
+    import torch
+    monkeypatch.setattr(lp, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=64))
+    assert lp._stream_ptr(None).value == 64
+    monkeypatch.setattr(lp, "_raw_stream", lambda device: 128)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    assert lp._stream_ptr(None).value == 128
+    assert lp._stream_ptr(types.SimpleNamespace(cuda_stream=192)).value == 192
+
+
 def test_product_path_does_not_reach_the_oracle():
     """Nothing under the package names, imports or links the oracle."""
     pkg = os.path.join(ROOT, "paper_2404_19760_amd")
