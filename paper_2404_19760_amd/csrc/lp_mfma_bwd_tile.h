@@ -735,7 +735,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         __builtin_amdgcn_sched_barrier(0);
         refresh(lane_id);
         scatter_step<KIND, C>(g, io.d_grid, here_scene, acts + L::A, reinterpret_cast<char*>(lds_raw) + wave * 2 * L::kAct,
-                              here, dFt, lane_id, here_tile);
+                              here, dFt, lane_id, here_tile ? kTileSamples : 32);
         wave_lds_fence();
     }
 

@@ -62,7 +62,7 @@ __device__ __forceinline__ void push_rays(const GridDev& tgt, const RaysDev& ray
             const Cell3 c = sample_cell<CC>(tgt, q, min(j, rays.S - 1));
             uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
             refresh(lane_here);
-            scatter_step<KIND, C, Scatter::kPushRay>(tgt, sp.theta, scene, area, area_ptr, c, val, lane_here, tile,
+            scatter_step<KIND, C, Scatter::kPushRay>(tgt, sp.theta, scene, area, area_ptr, c, val, lane_here, step,
                                                      sp.theta_w, ray_ok && j < j_to);
         }
     }

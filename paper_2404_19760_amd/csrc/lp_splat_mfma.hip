@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt,
                 refresh(lane_here);
                 const Cell3 cell = sample_cell_any(tgt, q, jj);
                 const bool valid = ray_ok && j < S;
-                if constexpr (TILES) scatter_step<KIND, CO, Scatter::kPushPoints, RayWindows::kWhole>(tgt, sp.theta, scene, area, area_ptr, cell, v, lane_here, tile, sp.theta_w, valid);
+                if constexpr (TILES) scatter_step<KIND, CO, Scatter::kPushPoints, RayWindows::kWhole>(tgt, sp.theta, scene, area, area_ptr, cell, v, lane_here, step, sp.theta_w, valid);
                 else push_ray_step<KIND, CO>(tgt, sp, scene, area, area_ptr, cell, v, lane_here, valid, windows);
             }
         }

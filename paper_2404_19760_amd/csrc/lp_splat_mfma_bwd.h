@@ -496,7 +496,7 @@ __global__ __launch_bounds__(kWaves * 64) void splat_mfma_bwd_kernel(GridDev tgt
                 uint32_t lane_here = lane;   // (or what the scatter derives from the lane number is kept through the loop)
                 refresh(lane_here);
                 scatter_step<KIND, CP, Scatter::kGradient, kWindows>(sp.prior, io.d_grid, scene, area, area_ptr, sample_cell_any(sp.prior, geometry(), jj),
-                                                                     dXp, lane_here, TILE, nullptr, true, windows);
+                                                                     dXp, lane_here, kStep, nullptr, true, windows);
             }
         }
 

@@ -8,6 +8,8 @@
 #include "lp_splat_common.h"
 #include "lp_tile_lds.h"
 
+#include <type_traits>
+
 namespace lp {
 
 namespace {
@@ -37,12 +39,24 @@ constexpr int kWinExtent = 12;                       // texels of a window along
 constexpr int kWinTexels = 512;                      // texels of a window of a grid at most; larger ones are split
 constexpr int kWinPlaneTexels = 128;                 // the same of a plane
 constexpr int kWinRow = 144;                         // bytes of a table row: 32 samples (and 16 of padding: no bank conflicts)
-constexpr int kWinZeroRow = 3 * kWinExtent;          // a row of zeros, for lanes without a texel
-constexpr int kWinOffsets = (kWinZeroRow + 1) * kWinRow;
-constexpr int kWinMarks = kWinOffsets + 32 * 4;      // a byte per texel: touched
-constexpr int kWinList = kWinMarks + kWinTexels;     // the touched texels, 16 bits each: at most 8 per sample
-constexpr int kWinBytes = kWinList + 32 * 8 * 2;
-static_assert(kWinBytes <= 8192 && kWinBytes % 16 == 0 && kWinOffsets % 16 == 0, "the table fits a wave's area");
+constexpr int kWinRows = 3 * kWinExtent + 1;         // rows of the table at most: the axes' one after the other, then one of zeros
+
+// The wave's area: the table, a byte per texel of the window (of each plane) that says whether a sample reaches it, and the
+// list of those that one does: where the texel is added to, and its rows of the table.
+// FAR: the list holds texels of planes in different tensors (8-byte addresses, else element offsets in a scene).
+template <bool FLAT, bool FAR>
+struct WinLds {
+    static constexpr int kMarks = FLAT ? 3 * kWinPlaneTexels : kWinTexels;
+    static constexpr int kList = FAR ? 240 : 256;    // (of a grid 8 per sample at most; of planes: see scatter_window)
+    static constexpr int kWhere = FAR ? 8 : 4, kWhich = FLAT ? 2 : 4;   // bytes of an entry
+    static constexpr int MARKS = kWinRows * kWinRow;
+    static constexpr int WHERE = MARKS + kMarks;
+    static constexpr int WHICH = WHERE + kList * kWhere;
+    static constexpr int kBytes = WHICH + kList * kWhich;
+    static_assert(kList % 16 == 0 && kList >= kWinPlaneTexels && MARKS % 16 == 0 && WHERE % 16 == 0, "16-byte accesses; a plane's list fits");
+};
+constexpr int kWinBytes = 8192;
+static_assert(WinLds<false, false>::kBytes <= kWinBytes && WinLds<true, false>::kBytes <= kWinBytes && WinLds<true, true>::kBytes <= kWinBytes);
 
 struct Window {
     int lo[3], ext[3];   // uniform: first texel and number of texels along each axis
@@ -105,157 +119,211 @@ __device__ __forceinline__ int small_div(int n, float inv) { return (int)(((floa
 
 // dFt: feature gradient, lane = channel (16 channels: lanes 16 .. 31 repeat lanes 0 .. 15), register r =
 // column d_row(r, grp) of the step.  `member`: the lane's sample belongs to the window (others have weight
-// zero).  `area`: the wave's LDS area for the table.  `sums`: the Splatter's weight sums.
+// zero).  `area`: the wave's LDS area.  `sums`: the Splatter's weight sums.
+//
+// A window is mostly empty (the samples of a step lie along a line through it), and a product is the dearest thing here: the
+// matrix cores take fp32 at a sixteenth of their rate in bf16.  So the products run over a list of the texels that a sample
+// reaches, 16 texels each (32 channels: two products side by side), and over the texels of all three planes of a triplane
+// in one list.  Against products over whole windows (32 texels of 32 channels; lists only of windows larger than two
+// products; a plane at a time), backward: eight triplanes 256^2 x 32 (3.5 x 32 texels a step, now 3.8 x 16 of 55 reached) 95.5 -> 88.4 ms,
+// 160^3 x 32 voxels in contract coordinates 7.0 -> 6.3, 64^3 x 32 voxels 7.3 -> 7.0, 256^3 x 16 voxels 48.2 -> 47.8 ms.
 template <int KIND, int C, Scatter WHAT>
 __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_grid[3], float* const* sums, int scene,
                                                uint32_t area, const Window& win, const Cell3& cell, bool member,
                                                const f32x16& dFt, int lane)
 {
     constexpr bool kPushes = WHAT != Scatter::kGradient, kOfRay = WHAT == Scatter::kPushRay;
+    constexpr bool kFlat = KIND == LP_GRID_TRIPLANE, kFar = kFlat && !kPushes;   // (a push keeps the planes apart: their weight sums)
+    constexpr int kPlanes = kFlat ? 3 : 1;
+    using L = WinLds<kFlat, kFar>;
+    using Which = typename std::conditional<kFlat, uint16_t, uint32_t>::type;
     const int col = lane & 31, grp = lane >> 5;
-    // the table: zeros, then this sample's two entries per axis (lane group 0 the lower, 1 the upper)
+    const int first_row[3] = {0, win.ext[0], win.ext[0] + win.ext[1]}, zero_row = first_row[2] + win.ext[2];
+    // axes of the window (of plane pl), slowest first
+    auto axis0 = [](int pl) { return kFlat ? pl : 0; };
+    auto axis1 = [](int pl) { return kFlat ? (pl + 1) % 3 : 1; };
+
+    // the table: zeros, then this sample's two entries per axis (lane group 0 the lower, 1 the upper), and the marks: the
+    // lane group's face of the sample's cell
     wave_lds_fence();
-    for (int i = lane; i < (kWinZeroRow + 1) * kWinRow / 16; i += 64)
-        lds_put<u32x4>(area + 16 * i, u32x4{0u, 0u, 0u, 0u});
+    for (int i = lane; i < (zero_row + 1) * (kWinRow / 16); i += 64) lds_put<u32x4>(area + 16 * i, u32x4{0u, 0u, 0u, 0u});
+    if (lane < L::kMarks / 16) lds_put<u32x4>(area + L::MARKS + 16 * lane, u32x4{0u, 0u, 0u, 0u});
     wave_lds_fence();
-    const int pos = slot_to_sample(col);   // 16 grp + r for column d_row(r, grp)
     if (member) {
+        const int pos = slot_to_sample(col);   // 16 grp + r for column d_row(r, grp)
+        int at[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const int row = a * kWinExtent + cell.i[a] - win.lo[a] + grp;
-            lds_put<float>(area + row * kWinRow + pos * 4, grp ? cell.f[a] : kPushes ? cell.g[a] : 1.0f - cell.f[a]);
+            at[a] = cell.i[a] - win.lo[a];
+            lds_put<float>(area + (first_row[a] + at[a] + grp) * kWinRow + pos * 4, grp ? cell.f[a] : kPushes ? cell.g[a] : 1.0f - cell.f[a]);
+        }
+        const uint8_t one = 1;
+#pragma unroll
+        for (int pl = 0; pl < kPlanes; ++pl) {
+            const int a0 = axis0(pl), a1 = axis1(pl), e2 = kFlat ? 1 : win.ext[2];
+            const uint32_t m = area + L::MARKS + kWinPlaneTexels * pl + ((at[a0] + grp) * win.ext[a1] + at[a1]) * e2 + (kFlat ? 0 : at[2]);
+            lds_put<uint8_t>(m, one);
+            lds_put<uint8_t>(m + 1, one);
+            if constexpr (!kFlat) {
+                lds_put<uint8_t>(m + e2, one);
+                lds_put<uint8_t>(m + e2 + 1, one);
+            }
         }
     }
     wave_lds_fence();
 
-    constexpr int kLanes = C == 32 ? 32 : 16;         // texels per matrix product
-    constexpr int kVec = C == 32 ? 4 : 2;             // 16-byte vectors of samples per lane
-    const int slot = lane & (kLanes - 1);
-    const int first = C == 32 ? 64 * grp : 32 * (lane >> 4);   // byte offset of this lane's samples in a row
-    float b16[8];
-    if constexpr (C == 16) {
+    // texels that a sample of plane pl reaches, appended to the list; scene_at: the scene's first texel in the plane's tensor
+    int n_list = 0;
+    auto texels_of_scene = [&](int pl) -> size_t {
+        if constexpr (KIND == LP_GRID_TRIPLANE) return (size_t)g.N[axis0(pl)] * g.N[axis1(pl)];
+        else if constexpr (KIND == LP_GRID_HASH) return (size_t)g.hash_size;
+        else return (size_t)g.N[0] * g.N[1] * g.N[2];
+    };
+    auto append = [&](int pl) {
+        const int a0 = axis0(pl), a1 = axis1(pl);
+        const int e1 = win.ext[a1], e2 = kFlat ? 1 : win.ext[2], total = win.ext[a0] * e1 * e2;
+        const float inv12 = __builtin_amdgcn_rcpf((float)(e1 * e2)), inv2 = __builtin_amdgcn_rcpf((float)e2);
+        for (int n0 = 0; n0 < total; n0 += 64) {
+            const int n = n0 + lane;
+            const bool touched = lds_get<uint8_t>(area + L::MARKS + kWinPlaneTexels * pl + n) != 0;   // (0 behind the window)
+            const unsigned long long all = __ballot(touched);
+            if (touched) {
+                const int t0 = small_div(n, inv12), rest = n - t0 * (e1 * e2);
+                const int t1 = kFlat ? rest : small_div(rest, inv2), t2 = rest - t1 * e2;
+                unsigned off;
+                if constexpr (KIND == LP_GRID_TRIPLANE)
+                    off = ((unsigned)(win.lo[a0] + t0) * (unsigned)g.N[a1] + (unsigned)(win.lo[a1] + t1)) * C;
+                else if constexpr (KIND == LP_GRID_HASH)   // (a table whose size is a power of two; colliding texels add up)
+                    off = (((unsigned)(win.lo[0] + t0) ^ (unsigned)(win.lo[1] + t1) * 2654435761u ^
+                            (unsigned)(win.lo[2] + t2) * 805459861u) & (g.hash_size - 1u)) * C;
+                else
+                    off = (((unsigned)(win.lo[0] + t0) * (unsigned)g.N[1] + (unsigned)(win.lo[1] + t1)) * (unsigned)g.N[2] +
+                           (unsigned)(win.lo[2] + t2)) * C;
+                const int at = n_list + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(all >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)all, 0u));
+                if constexpr (kFar)
+                    lds_put<uint64_t>(area + L::WHERE + 8 * at, (uint64_t)(uintptr_t)(d_grid[pl] + scene * texels_of_scene(pl) * C) + 4ull * off);
+                else
+                    lds_put<uint32_t>(area + L::WHERE + 4 * at, off);
+                int rows = (first_row[a0] + t0) | (first_row[a1] + t1) << 8;
+                if constexpr (!kFlat) rows |= (first_row[2] + t2) << 16;
+                lds_put<Which>(area + L::WHICH + L::kWhich * at, (Which)rows);
+            }
+            n_list += __popcll(all);
+        }
+    };
+
+    // The gradient as matrix operand: lane = channel of a half (lane & 15), register k of the lanes 16 q .. 16 q + 15 =
+    // position 8 q + k of the table.
+    constexpr int kHalves = C / 16, kKeep = kOfRay ? 2 : 8;
+    float b[kHalves][kKeep];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            float a = dFt[k], b = dFt[k + 8];
-            asm("" : "+v"(a), "+v"(b));   // (or the compiler turns the choice into an indexed read of dFt)
-            b16[k] = (lane & 16) ? b : a;
+    for (int i = 0; i < kKeep; ++i) {
+        const int k = kOfRay ? 4 * i : i;
+        if constexpr (C == 32) {
+            const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(dFt[k]), __float_as_uint(dFt[k + 8]), false, false);
+            b[0][i] = __uint_as_float(r[0]);
+            b[1][i] = __uint_as_float(r[1]);
+        } else {
+            float x = dFt[k], y = dFt[k + 8];
+            asm("" : "+v"(x), "+v"(y));   // (or the compiler turns the choice into an indexed read of dFt)
+            b[0][i] = (lane & 16) ? y : x;
         }
     }
 
-    constexpr int kPlanes = KIND == LP_GRID_TRIPLANE ? 3 : 1;
-#pragma unroll
-    for (int pl = 0; pl < kPlanes; ++pl) {
-        // axes of the window, slowest first
-        const int a0 = KIND == LP_GRID_TRIPLANE ? pl : 0, a1 = KIND == LP_GRID_TRIPLANE ? (pl + 1) % 3 : 1;
-        const int e1 = win.ext[a1], e2 = KIND == LP_GRID_TRIPLANE ? 1 : win.ext[2];
-        const int total = win.ext[a0] * e1 * e2;
-        // A large window is mostly empty: the samples of a step lie along a line through it. Its products then run over
-        // the texels that a sample reaches, in the order of the window (a product over 32 texels of 32 channels occupies
-        // the matrix cores for 1024 cycles; finding the texels takes some 400).  Windows up to two products stay whole: at
-        // most one product is to be saved there.  Hash table over a 128^3 lattice, 5.6 -> 3.4 products a step: backward
-        // 0.457 -> 0.412 ms; 5003 rays in random order through 97 x 128 x 75 x 16 voxels, whose steps of one ray fit one
-        // window of 512 texels instead of several of 128: 0.319 -> 0.268 ms.
-        int n_texels = total;
-        const bool listed = KIND != LP_GRID_TRIPLANE && total > 2 * kLanes;
-        if (listed) {
-            lds_put<u32x2>(area + kWinMarks + 8 * lane, u32x2{0u, 0u});
-            wave_lds_fence();
-            if (member) {   // the lane group's face of the sample's cell
-                const uint32_t at = area + kWinMarks + ((cell.i[0] - win.lo[0] + grp) * e1 + cell.i[1] - win.lo[1]) * e2 +
-                                    cell.i[2] - win.lo[2];
-                const uint8_t one = 1;
-                lds_put<uint8_t>(at, one);
-                lds_put<uint8_t>(at + 1, one);
-                lds_put<uint8_t>(at + e2, one);
-                lds_put<uint8_t>(at + e2 + 1, one);
-            }
-            wave_lds_fence();
-            n_texels = 0;
-            for (int n = 0; n < total; n += 64) {
-                const bool touched = lds_get<uint8_t>(area + kWinMarks + n + lane) != 0;
-                const unsigned long long all = __ballot(touched);
-                const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(all >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)all, 0u));
-                if (touched) lds_put<uint16_t>(area + kWinList + 2 * (n_texels + before), (uint16_t)(n + lane));
-                n_texels += __popcll(all);
-            }
-            wave_lds_fence();
+    const int slot = lane & 15, quarter = lane >> 4;
+    auto products = [&](int pl) {
+        char* out = nullptr;   // the scene in plane pl's tensor
+        size_t scene_at = 0;
+        if constexpr (!kFar) {
+            scene_at = scene * (!kFlat || pl == 0 ? texels_of_scene(0) : pl == 1 ? texels_of_scene(1) : texels_of_scene(2));
+            out = reinterpret_cast<char*>((!kFlat || pl == 0 ? d_grid[0] : pl == 1 ? d_grid[1] : d_grid[2]) + scene_at * C);
         }
-        const float inv12 = __builtin_amdgcn_rcpf((float)(e1 * e2)), inv2 = __builtin_amdgcn_rcpf((float)e2);
-        size_t scene_at;   // first texel of the scene
-        if constexpr (KIND == LP_GRID_TRIPLANE) scene_at = (size_t)scene * g.N[a0] * g.N[a1];
-        else if constexpr (KIND == LP_GRID_HASH) scene_at = (size_t)scene * g.hash_size;
-        else scene_at = (size_t)scene * g.N[0] * g.N[1] * g.N[2];
-        char* out = reinterpret_cast<char*>(d_grid[pl] + scene_at * C);
-        for (int n0 = 0; n0 < n_texels; n0 += kLanes) {
-            const bool live = n0 + slot < n_texels;
-            const int at = live ? n0 + slot : 0, n = listed ? (int)lds_get<uint16_t>(area + kWinList + 2 * at) : at;   // (lanes without a texel: weights zero, the first one's address)
-            const int t0 = small_div(n, inv12), rest = n - t0 * (e1 * e2);
-            const int t1 = KIND == LP_GRID_TRIPLANE ? rest : small_div(rest, inv2), t2 = rest - t1 * e2;
-            unsigned off;
-            if constexpr (KIND == LP_GRID_TRIPLANE)
-                off = ((unsigned)(win.lo[a0] + t0) * (unsigned)g.N[a1] + (unsigned)(win.lo[a1] + t1)) * C;
-            else if constexpr (KIND == LP_GRID_HASH)   // (a table whose size is a power of two; colliding texels add up)
-                off = (((unsigned)(win.lo[0] + t0) ^ (unsigned)(win.lo[1] + t1) * 2654435761u ^
-                        (unsigned)(win.lo[2] + t2) * 805459861u) & (g.hash_size - 1u)) * C;
-            else
-                off = (((unsigned)(win.lo[0] + t0) * (unsigned)g.N[1] + (unsigned)(win.lo[1] + t1)) * (unsigned)g.N[2] +
-                       (unsigned)(win.lo[2] + t2)) * C;
-            const uint32_t r0 = area + (live ? a0 * kWinExtent + t0 : kWinZeroRow) * kWinRow + first;
-            const uint32_t r1 = area + (live ? a1 * kWinExtent + t1 : kWinZeroRow) * kWinRow + first;
-            const uint32_t r2 = area + (live ? 2 * kWinExtent + t2 : kWinZeroRow) * kWinRow + first;
-            float w[4 * kVec];
+        [[maybe_unused]] float weight = 0.0f;
+        auto rows_of = [&](int n) {   // the lane's texel (none: rows of zeros)
+            return n + slot < n_list ? (int)lds_get<Which>(area + L::WHICH + L::kWhich * (n + slot)) : zero_row * 0x010101;
+        };
+        int rows = rows_of(0);
+        for (int n0 = 0; n0 < n_list; n0 += 16) {
+            const uint32_t r0 = area + (rows & 0xff) * kWinRow + 32 * quarter, r1 = area + ((rows >> 8) & 0xff) * kWinRow + 32 * quarter;
+            float w[8];
 #pragma unroll
-            for (int v = 0; v < kVec; ++v) {
+            for (int v = 0; v < 2; ++v) {
                 const f32x4 x = lds_get<f32x4>(r0 + 16 * v), y = lds_get<f32x4>(r1 + 16 * v);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[4 * v + e] = x[e] * y[e];
-                if constexpr (KIND != LP_GRID_TRIPLANE) {
-                    const f32x4 z = lds_get<f32x4>(r2 + 16 * v);
+                if constexpr (!kFlat) {
+                    const f32x4 z = lds_get<f32x4>(area + (rows >> 16) * kWinRow + 32 * quarter + 16 * v);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) w[4 * v + e] *= z[e];
                 }
             }
+            rows = rows_of(n0 + 16);
             if constexpr (kPushes) {
-                float sum = 0.0f;
-#pragma unroll
-                for (int k = 0; k < 4 * kVec; ++k) sum += w[k];
-                if constexpr (C == 16) sum += __shfl_xor(sum, 16, 64);
-                sum += __shfl_xor(sum, 32, 64);
-                if (lane < kLanes && live && sum != 0.0f) atomicAdd(sums[pl] + scene_at + off / C, sum);
+                float sum = ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
+                u32x2 both = __builtin_amdgcn_permlane16_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+                sum = __uint_as_float(both[0]) + __uint_as_float(both[1]);   // quarters 0 and 1, or 2 and 3
+                both = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+                sum = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+// one add for the sums of four products, each kept by a quarter of the wave
+                weight = quarter == ((n0 >> 4) & 3) ? sum : weight;
+                const int n = (n0 & ~63) + lane;
+                if ((n0 & 48) == 48 || n0 + 16 >= n_list)
+                    if (n < n_list && weight != 0.0f) atomicAdd((!kFlat || pl == 0 ? sums[0] : pl == 1 ? sums[1] : sums[2]) + scene_at + lds_get<uint32_t>(area + L::WHERE + 4 * n) / C, weight);
             }
-            if constexpr (kOfRay) {
-#pragma unroll
-                for (int v = 0; v < kVec; ++v) w[v] = (w[4 * v] + w[4 * v + 1]) + (w[4 * v + 2] + w[4 * v + 3]);
+            if constexpr (kOfRay) {   // (a lane's eight positions are four points each of two rays)
+                w[0] = (w[0] + w[1]) + (w[2] + w[3]);
+                w[1] = (w[4] + w[5]) + (w[6] + w[7]);
             }
-            // offsets of all texels of this product, for the lanes that will hold their rows
-            wave_lds_fence();
-            if (lane < kLanes) lds_put<uint32_t>(area + kWinOffsets + 4 * slot, off);
-            wave_lds_fence();
-            auto add = [&](unsigned texel_off, float v) {
-                if (v != 0.0f) atomicAdd(reinterpret_cast<float*>(out + 4u * (texel_off + (unsigned)(lane & (C - 1)))), v);
+            f32x4 acc[kHalves];
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < kKeep; ++k)
+#pragma unroll
+                for (int h = 0; h < kHalves; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b[h][k], acc[h], 0, 0, 0);
+            // rows 4 quarter + p of the product (of places behind the list's end: zeros, nothing is added)
+            typedef __attribute__((address_space(1))) float GlobalFloat;
+            auto add = [&](GlobalFloat* at, float v) {
+                if (v != 0.0f) __hip_atomic_fetch_add(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             };
-            if constexpr (C == 32) {
-                f32x16 acc = zero16();
+            if constexpr (kFar) {
+                typedef __attribute__((__vector_size__(2 * sizeof(uint64_t)))) uint64_t u64x2;
 #pragma unroll
-                for (int r = 0; r < (kOfRay ? 4 : 16); ++r)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[r], dFt[kOfRay ? 4 * r : r], acc, 0, 0, 0);
+                for (int i = 0; i < 2; ++i) {
+                    const u64x2 o = lds_get<u64x2>(area + L::WHERE + 8 * (n0 + 4 * quarter + 2 * i));
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (n0 + 8 * q >= n_texels) break;
-                    const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 4 * (8 * q + 4 * grp));
+                    for (int p = 0; p < 2; ++p)
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) add(o[p], acc[4 * q + p]);
+                        for (int h = 0; h < kHalves; ++h) add((GlobalFloat*)(uintptr_t)(o[p] + 4 * slot) + 16 * h, acc[h][2 * i + p]);
                 }
             } else {
-                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+                const u32x4 o = lds_get<u32x4>(area + L::WHERE + 4 * (n0 + 4 * quarter));
 #pragma unroll
-                for (int k = 0; k < (kOfRay ? 2 : 8); ++k)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], b16[kOfRay ? 4 * k : k], acc, 0, 0, 0);
-                const u32x4 o = lds_get<u32x4>(area + kWinOffsets + 16 * (lane >> 4));
+                for (int p = 0; p < 4; ++p)
 #pragma unroll
-                for (int p = 0; p < 4; ++p) add(o[p], acc[p]);
+                    for (int h = 0; h < kHalves; ++h) add((GlobalFloat*)(out + 4u * (o[p] + (unsigned)slot)) + 16 * h, acc[h][p]);
             }
         }
+    };
+
+    if constexpr (kFlat) {
+        // all planes at once where the list holds all their windows' texels, else one after the other
+        const bool one_list = kFar && win.ext[0] * win.ext[1] + win.ext[1] * win.ext[2] + win.ext[2] * win.ext[0] <= L::kList;
+        for (int from = 0; from < 3;) {
+            const int to = one_list ? 3 : from + 1;
+            n_list = 0;
+            if (from > 0) wave_lds_fence();
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                if (pl >= from && pl < to) append(pl);
+            wave_lds_fence();
+            products(from);
+            from = to;
+        }
+    } else {
+        append(0);
+        wave_lds_fence();
+        products(0);
     }
 }
 
@@ -264,11 +332,11 @@ __device__ __forceinline__ void scatter_window(const GridDev& g, float* const d_
 // one backwards, so that the step from ray to ray is a short one.
 template <int KIND, int C, Scatter WHAT>
 __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_grid[3], float* const* sums, int scene, char* area,
-                                             const Cell3& cell, bool valid, const f32x16& dFt, int lane, bool tile)
+                                             const Cell3& cell, bool valid, const f32x16& dFt, int lane, int full)
 {
     constexpr bool kPushes = WHAT != Scatter::kGradient, kOfRay = WHAT == Scatter::kPushRay;
     const int col = lane & 31, grp = lane >> 5;
-    auto flip = [tile](int c) { return (tile && (c & 8)) ? c ^ 7 : c; };   // column <-> position of the walk
+    auto flip = [full](int c) { return (c & full) ? c ^ (full - 1) : c; };   // column <-> position of the walk
     float* info = reinterpret_cast<float*>(area);
     float* grad = reinterpret_cast<float*>(area + 2048);
     wave_lds_fence();
@@ -303,14 +371,15 @@ __device__ __forceinline__ void scatter_walk(const GridDev& g, float* const d_gr
 // runs of consecutive samples (of every ray of the tile) with a window each: rays that leave the unit cube of contract
 // coordinates between two samples, mostly.  The products would spread an infinite or
 // undefined gradient over its window, so a step that holds one takes the walk, which keeps it to the sample's own corners.
-// Steps of a single ray: see RayWindows; `windows` false: the walk.
+// `full`: samples of a ray in the step.  Steps of a single ray: see RayWindows; `windows` false: the walk.
 template <int KIND, int C, Scatter WHAT = Scatter::kGradient, RayWindows RAYS = WHAT == Scatter::kGradient ? RayWindows::kSplit : RayWindows::kNone>
 __device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_grid[3], int scene, uint32_t area,
-                                             char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, bool tile,
+                                             char* area_ptr, const Cell3& cell, const f32x16& dFt, int lane, int full,
                                              float* const* sums = nullptr, bool valid = true, bool windows = true)
 {
     constexpr bool kOfRay = WHAT == Scatter::kPushRay;
-    const int col = lane & 31, k = tile ? (col & (kTileSamples - 1)) : col, full = tile ? kTileSamples : 32;
+    const int k = lane & (full - 1);
+    const bool tile = full < 32;
     float probe = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r)
@@ -332,7 +401,7 @@ __device__ __forceinline__ void scatter_step(const GridDev& g, float* const d_gr
         }
     }
     if (!fits) {
-        scatter_walk<KIND, C, WHAT>(g, d_grid, sums, scene, area_ptr, cell, valid, dFt, lane, tile);
+        scatter_walk<KIND, C, WHAT>(g, d_grid, sums, scene, area_ptr, cell, valid, dFt, lane, full);
         return;
     }
     for (int p = 0;;) {   // `win` is the first run's

@@ -12,7 +12,7 @@ import lp_inputs
 from lp_inputs import HASH, TRIPLANE, VOXEL
 
 from parity import check_case, summary
-from tile_rules import backward_in_tiles, step_routes
+from tile_rules import backward_in_tiles, plane_lists, step_routes
 
 pytestmark = pytest.mark.gpu
 
@@ -108,6 +108,17 @@ def test_split_windows(lp, oracle, kind, channels, dims, res):
                                grid_std=0.3, aabb_min=(-1.5,) * 3, aabb_max=(1.5,) * 3)
     inp = _with_camera_rays(inp, 2048 * 4, 128, 64)
     print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"windows {kind} {dims} res={res}")), flush=True)
+
+
+@pytest.mark.parametrize("channels,dims", [(16, (16, 32, 4)), (32, (32, 64, 64, 4))])
+def test_lists_of_planes(lp, oracle, channels, dims):
+    """Steps whose planes' texels share one list and steps whose windows are too large for that."""
+    inp = lp_inputs.make_small(TRIPLANE, channels=channels, res=(64, 64, 64), mlp_dims=dims, n_rays=8, samples=40, seed=263,
+                               grid_std=0.3, aabb_min=(-1.5,) * 3, aabb_max=(1.5,) * 3)
+    inp = _with_camera_rays(inp, 2048 * 4, 128, 64)
+    lists = plane_lists(inp)
+    assert min(lists["together"], lists["apart"]) > 500, lists
+    print(summary(check_case(lp, oracle, inp, lp.LP_MATH_BF16X3, label=f"lists of planes {dims}")), flush=True)
 
 
 @pytest.mark.parametrize("n_rays,samples,tiles", [(2049, 64, False), (2600, 64, False), (4103, 64, False), (8197, 8, True), (9300, 8, True)])

@@ -190,6 +190,20 @@ def step_routes(inp):
     return routes
 
 
+def plane_lists(inp):
+    """Of the tiles' steps whose samples fit one window of each plane of a triplane: how many list the texels of all planes together,
+    how many one plane after the other (lp_tile_scatter.h)."""
+    c, lists = cells(inp), Counter()
+    for first in range(0, inp.n_rays - TILE_RAYS + 1, TILE_RAYS):
+        for j0 in range(0, inp.samples, TILE_SAMPLES):
+            run = c[first:first + TILE_RAYS, j0:j0 + TILE_SAMPLES].reshape(-1, 3)
+            e = run.max(0) - run.min(0) + 2
+            planes = (e[0] * e[1], e[1] * e[2], e[2] * e[0])
+            if e.max() <= EXTENT and max(planes) <= PLANE_TEXELS:
+                lists["together" if sum(planes) <= 240 else "apart"] += 1
+    return lists
+
+
 def splat_in_tiles(n_rays, samples, waves, up_to):
     """The Splatter's launch rule (lp_tile_scatter.h push_order)."""
     rounds = lambda items: -(-items // waves)
