@@ -99,6 +99,7 @@ void to_device_views(const lp_grid* grid, const lp_mlp* mlp, const lp_rays* rays
     for (int p = 0; p < 3; ++p) g->data[p] = grid->data[p];
     for (int a = 0; a < 3; ++a) {
         g->amin[a] = (double)grid->aabb_min[a];
+        g->top[a] = (double)(g->N[a] - 1);
         g->scale[a] = (double)(g->N[a] - 1) / ((double)grid->aabb_max[a] - (double)grid->aabb_min[a]);
     }
     g->contract = (double)grid->contract_a;
@@ -108,6 +109,7 @@ void to_device_views(const lp_grid* grid, const lp_mlp* mlp, const lp_rays* rays
         for (int p = 0; p < 3; ++p) g->data_t[p] = grid->data_t[p];
         g->NT = grid->NT;
         g->tmin = (double)grid->t_min;
+        g->ttop = (double)(grid->NT - 1);
         g->tscale = (double)(grid->NT - 1) / ((double)grid->t_max - (double)grid->t_min);
     }
     std::memset(m, 0, sizeof(*m));
@@ -128,7 +130,7 @@ void to_device_views(const lp_grid* grid, const lp_mlp* mlp, const lp_rays* rays
     m->max_width = maxw;
     m->act_total = act;
     m->n_freq = 0; m->n_enc = 0; m->n_feat = 3; m->feat_act = 0;
-    r->M = rays->M; r->S = rays->S;
+    r->M = rays->M; r->S = rays->S; r->samples = (double)rays->S;
     r->origins = rays->origins; r->dirs = rays->dirs; r->near = rays->near; r->far = rays->far;
     r->scene = rays->scene;
     r->time = rays->time;

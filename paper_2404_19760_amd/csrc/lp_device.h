@@ -17,12 +17,13 @@ struct GridDev {
     int N[3];
     double amin[3];
     double scale[3];  // (N-1)/(max-min): world -> continuous index
+    double top[3];    // N-1
     double contract;  // foreground scale a of the contract coordinates, 0 = off
     unsigned hash_size;  // LP_GRID_HASH: entries of one scene's table
     // LP_GRID_HEXPLANE: the space-time planes (pair p: plane data[p] with data_t[p] over (axis p + 2, time))
     const void* data_t[3];
     int NT;
-    double tmin, tscale;  // (NT-1)/(t_max-t_min)
+    double tmin, tscale, ttop;  // (NT-1)/(t_max-t_min), NT-1
 };
 
 struct MlpDev {
@@ -46,6 +47,7 @@ struct MlpDev {
 struct RaysDev {
     long long M;
     int S;
+    double samples;  // S
     const float* origins;
     const float* dirs;
     const float* near;
@@ -118,33 +120,28 @@ struct SplatDev {
 // g = 1 - f, rounded from the fp64 index as well: formed from the rounded f it would carry an
 // absolute error of 6e-8 however small it is, which the Splatter's division by a cell's weight
 // sum turns into an unbounded relative error for cells that only receive tiny weights.
+// top = N - 1, a uniform value like the others: it and lo and scale are scalar operands (converted here they took a register
+// pair of every lane each, which the widest kernels read back from scratch memory behind their atomic adds).
 template <bool CC = false>
-__device__ __forceinline__ void axis_cell(double x, double lo, double scale, int N, double contract, int& i,
+__device__ __forceinline__ void axis_cell(double x, double lo, double scale, int N, double top, double contract, int& i,
                                           float& f, float& g)
 {
     if constexpr (CC) {
         const double m = fmax(fabs(x), 1.0);
-        double r = (double)__frcp_rn((float)m);
+        double r = (double)__builtin_amdgcn_rcpf((float)m);   // 22 bits, then 44, then all
+        r = r * (2.0 - m * r);
         r = r * (2.0 - m * r);
         const double far = copysign(0.5 * ((2.0 - contract) * (1.0 - r) + contract), x);
         x = fabs(x) <= 1.0 ? 0.5 * contract * x : far;
     }
-    double u = (x - lo) * scale;
-    u = fmin(fmax(u, 0.0), (double)(N - 1));
+    double u = fmax((x - lo) * scale, 0.0);
+    asm("v_min_f64 %0, %1, %2" : "=v"(u) : "v"(u), "s"(top));   // fmin(u, top), without making both canonical first
     int c = (int)u;  // u >= 0: truncation is floor
     c = min(c, N - 2);
     i = c;
     const double fr = u - (double)c;
     f = (float)fr;
     g = (float)(1.0 - fr);
-}
-
-template <bool CC = false>
-__device__ __forceinline__ void axis_cell(double x, double lo, double scale, int N, double contract, int& i,
-                                          float& f)
-{
-    float g;
-    axis_cell<CC>(x, lo, scale, N, contract, i, f, g);
 }
 
 // Entry e of the view-direction encoding (Section 3.3: the feature MLP also receives the view

@@ -41,12 +41,12 @@ struct Cell {
 __device__ __forceinline__ Cell locate(const GridDev& g, double x, double y, double z)
 {
     Cell c;
-    if (g.contract > 0.0) axis_cell<true>(x, g.amin[0], g.scale[0], g.N[0], g.contract, c.i[0], c.f[0], c.g[0]);
-    else axis_cell<false>(x, g.amin[0], g.scale[0], g.N[0], g.contract, c.i[0], c.f[0], c.g[0]);
-    if (g.contract > 0.0) axis_cell<true>(y, g.amin[1], g.scale[1], g.N[1], g.contract, c.i[1], c.f[1], c.g[1]);
-    else axis_cell<false>(y, g.amin[1], g.scale[1], g.N[1], g.contract, c.i[1], c.f[1], c.g[1]);
-    if (g.contract > 0.0) axis_cell<true>(z, g.amin[2], g.scale[2], g.N[2], g.contract, c.i[2], c.f[2], c.g[2]);
-    else axis_cell<false>(z, g.amin[2], g.scale[2], g.N[2], g.contract, c.i[2], c.f[2], c.g[2]);
+    if (g.contract > 0.0) axis_cell<true>(x, g.amin[0], g.scale[0], g.N[0], g.top[0], g.contract, c.i[0], c.f[0], c.g[0]);
+    else axis_cell<false>(x, g.amin[0], g.scale[0], g.N[0], g.top[0], g.contract, c.i[0], c.f[0], c.g[0]);
+    if (g.contract > 0.0) axis_cell<true>(y, g.amin[1], g.scale[1], g.N[1], g.top[1], g.contract, c.i[1], c.f[1], c.g[1]);
+    else axis_cell<false>(y, g.amin[1], g.scale[1], g.N[1], g.top[1], g.contract, c.i[1], c.f[1], c.g[1]);
+    if (g.contract > 0.0) axis_cell<true>(z, g.amin[2], g.scale[2], g.N[2], g.top[2], g.contract, c.i[2], c.f[2], c.g[2]);
+    else axis_cell<false>(z, g.amin[2], g.scale[2], g.N[2], g.top[2], g.contract, c.i[2], c.f[2], c.g[2]);
     return c;
 }
 
@@ -366,7 +366,7 @@ __device__ __forceinline__ Cell sample_cell(const GridDev& g, const RayRegs& q, 
     Cell c = locate(g, (double)q.o[0] + t * (double)q.d[0], (double)q.o[1] + t * (double)q.d[1],
                     (double)q.o[2] + t * (double)q.d[2]);
     // the time axis is not contracted
-    if (g.kind == LP_GRID_HEXPLANE) axis_cell<false>((double)q.time, g.tmin, g.tscale, g.NT, 0.0, c.it, c.ft, c.gt);
+    if (g.kind == LP_GRID_HEXPLANE) axis_cell<false>((double)q.time, g.tmin, g.tscale, g.NT, g.ttop, 0.0, c.it, c.ft, c.gt);
     return c;
 }
 

@@ -249,9 +249,9 @@ template <bool CC>
 __device__ __forceinline__ Cell3 locate3(const GridDev& g, double x, double y, double z)
 {
     Cell3 c;
-    axis_cell<CC>(x, g.amin[0], g.scale[0], g.N[0], g.contract, c.i[0], c.f[0], c.g[0]);
-    axis_cell<CC>(y, g.amin[1], g.scale[1], g.N[1], g.contract, c.i[1], c.f[1], c.g[1]);
-    axis_cell<CC>(z, g.amin[2], g.scale[2], g.N[2], g.contract, c.i[2], c.f[2], c.g[2]);
+    axis_cell<CC>(x, g.amin[0], g.scale[0], g.N[0], g.top[0], g.contract, c.i[0], c.f[0], c.g[0]);
+    axis_cell<CC>(y, g.amin[1], g.scale[1], g.N[1], g.top[1], g.contract, c.i[1], c.f[1], c.g[1]);
+    axis_cell<CC>(z, g.amin[2], g.scale[2], g.N[2], g.top[2], g.contract, c.i[2], c.f[2], c.g[2]);
     return c;
 }
 
@@ -390,7 +390,7 @@ __device__ __forceinline__ void gather_half(const GridDev& g, int scene, const C
 __device__ __forceinline__ void time_cell(const GridDev& g, float time, int& it, float& ft)
 {
     float gt;
-    axis_cell<false>((double)time, g.tmin, g.tscale, g.NT, 0.0, it, ft, gt);
+    axis_cell<false>((double)time, g.tmin, g.tscale, g.NT, g.ttop, 0.0, it, ft, gt);
 }
 
 // feat[0..NCH) = channels [ch0, ch0 + NCH) of a HexPlane at cell c and time `time`: for each of the three

@@ -1,6 +1,7 @@
-// Matrix-core backward kernel of the Renderer (Eq. (2), Section 3.4 of the paper) over TILES of rays: a
-// wavefront marches four neighbouring rays together, eight samples of each per 32-sample step, from the
-// last samples to the first (rays that do not run side by side are marched one at a time, 32 samples per step).
+// Matrix-core backward kernel of the Renderer (Eq. (2), Section 3.4 of the paper) over neighbouring rays: a
+// wavefront marches a PATCH of an image (four pixels each of two rows, four samples of each ray per 32-sample step), a TILE
+// of a list (four consecutive rays, eight samples of each) or, where rays do not run side by side, one ray (32 samples),
+// from the last samples to the first.
 // A workgroup is eight wavefronts of 256 registers, two per SIMD, that share the MLP's weights in LDS
 // and nothing else: no wave waits for another between the staging of the weights and the final sums.
 //
@@ -18,7 +19,9 @@
 //   - The grid gradient is bound by the rate of atomic adds (2.1e10 64-byte lines/s on this chip, whatever
 //     the locality). One ray's samples touch 3.1 (voxel) and 9.9 (triplane) lines per sample after run
 //     merging; the union of the texels that four neighbouring rays touch with eight samples each is 0.70 and
-//     3.63 lines per sample (counted: 2.31e8 lines in 48.4 ms, 23 % of that rate, and 1.46e9 in 96.3 ms, 73 %).
+//     3.47 lines per sample, of a patch with four samples each 0.53 and 2.42, and the scatter's matrix products shrink
+//     alike.  (Patches against tiles, a whole training step: eight triplanes 115.7 -> 107.6 ms, one triplane 128^2 x 32, 128^2 rays,
+//     735 -> 665 us, 256^3 x 16 voxels 61.1 -> 60.7 ms, a hash table 460 -> 451 us.)
 //   - A wave does not overlap its own vector and matrix instructions; two waves per SIMD do. The
 //     accumulators of the weight gradients (94 registers for 16-64-64-4: the two thin matrices on 16 x 16
 //     and 4 x 4 tiles) leave room for two waves only if a step's activations live in LDS instead of registers.
@@ -32,6 +35,7 @@
 //     that would be empty, or in empty parts of the K range: 8 instead of 12 in the forward, 2 instead of 6 in the
 //     input-gradient chain.  The weight gradient takes 24 products of sixteen 4 x 4 blocks instead of 12 of 32 x 32.
 #pragma once
+#include "lp_image_rows.h"
 #include "lp_kernels.h"
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
@@ -45,6 +49,10 @@ namespace lp {
 namespace {
 
 constexpr int kTileWaves = 8;
+// A patch: four neighbouring pixels each of two rows of an image, four samples of each ray per step.
+constexpr int kPatchRays = 8, kPatchSamples = 4, kLogPatchSamples = 2, kLogTileSamples = 3;
+static_assert((1 << kLogPatchSamples) == kPatchSamples && (1 << kLogTileSamples) == kTileSamples && kPatchRays * kPatchSamples == 32);
+constexpr double kPixelTexels = 1.5;   // from pixel to pixel at most
 
 // LDS in bytes: the waves' step tensors first (so that a wave's base has none of the address bits that the
 // images' exclusive-ors flip), then the weights, then the waves' small areas.
@@ -61,19 +69,22 @@ struct TileLds {
     static constexpr int WO_AT = W1_AT + 2 * W1::bytes(H);       // 4 rows hi, 4 rows lo
     static constexpr int BIAS_AT = WO_AT + 8 * kWo;              // b1[H] b2[H] bo[4]
     static constexpr int SMALL_AT = BIAS_AT + (2 * H + 4) * 4;
-    // one wave: output gradients; per ray its geometry (10 floats) and upstream gradients (5 floats)
-    static constexpr int kRayBytes = 64;
-    static constexpr int RAY = 512;
-    static constexpr int DEPTH = RAY + kTileRays * kRayBytes;    // per ray, fp64: optical depth up to the end of the current step
-    static constexpr int kSmall = DEPTH + kTileRays * 8;
+    // one wave: output gradients; per ray of a step, fp64, the optical depth up to the step's end
+    static constexpr int DEPTH = 512;
+    static constexpr int kSmall = DEPTH + kPatchRays * 8;
     static constexpr int kTotal = SMALL_AT + kTileWaves * kSmall;
     static_assert(W2_AT % 4096 == 0 && W1_AT % 1024 == 0 && SMALL_AT % 16 == 0 && kSmall % 16 == 0, "alignment");
     static_assert(kTotal <= 160 * 1024, "LDS budget of a gfx950 compute unit");
 };
 
-// Inclusive prefix sum over the samples of a ray: segments of 8 lanes (`tile`) or of 32.  k = position in
+// All of the wave's loads have arrived.  For loads whose values only some lanes use: the others' way around that use leaves
+// them outstanding to the compiler, and whatever next takes their registers then waits, in every turn of a loop, for all memory
+// operations issued since.
+__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
+// Inclusive prefix sum over the samples of a ray: segments of 4 or 8 lanes, or (`alone`) of 32.  k = position in
 // the segment.
-__device__ __forceinline__ float ray_scan(float v, int k, bool tile)
+__device__ __forceinline__ float ray_scan(float v, int k, bool alone)
 {
     float t = dpp_or_zero<0x111, 0xf>(v);
     v += k >= 1 ? t : 0.0f;
@@ -82,9 +93,9 @@ __device__ __forceinline__ float ray_scan(float v, int k, bool tile)
     t = dpp_or_zero<0x114, 0xf>(v);
     v += k >= 4 ? t : 0.0f;
     t = dpp_or_zero<0x118, 0xf>(v);
-    v += tile ? 0.0f : t;
+    v += alone ? t : 0.0f;
     t = dpp_or_zero<0x142, 0xa>(v);
-    v += tile ? 0.0f : t;
+    v += alone ? t : 0.0f;
     return v;
 }
 
@@ -156,16 +167,49 @@ __device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const
     }
 }
 
-// One launch's work items: consecutive tiles of kTileRays rays (`tiles`) or single rays.  As many rounds as leave no wave of
+// One launch's work items: patches (four pixels each of two rows of an image), consecutive tiles of kTileRays rays, or single rays.  As many rounds as leave no wave of
 // any workgroup without an item hand them out in groups of kTileWaves, the groups in a scrambled order (neighbouring rays
 // add into the same lines; spread over time their adds do not queue up at one L2 channel).  What is left goes to the first
 // `busy` waves of a workgroup, to as many workgroups as that takes: up to four of them have a SIMD each, where a ray takes 0.55 to 0.7 of the time beside
 // another.  (2600 rays in random order x 480 samples, 96^3 x 16 voxels, 16-64-64-4: the last 552 rays on 69 full workgroups 303 us,
 // spread over all 243; 32-64-64-4 on triplanes 128^2 469 -> 400.)
+enum class Items { kRays, kTiles, kPatches };   // kPatches: if the rays are found to be an image's, else tiles
 struct TileSchedule {
     long long rounds, group_mul, group_step;
-    int tiles, busy, tail_per_xcd;   // (tail_per_xcd: workgroups of an XCD that the last, partial round reaches)
+    int busy, tail_per_xcd;   // (tail_per_xcd: workgroups of an XCD that the last, partial round reaches)
+    Items items;
 };
+
+// Int: long long, or unsigned on the device (items below 2^31)
+template <class Int>
+__host__ __device__ inline TileSchedule tile_schedule(Items kind, Int items, Int blocks)
+{
+    TileSchedule sc;
+    sc.items = kind;
+    const Int waves = blocks * (Int)kTileWaves, rounds = items / waves, tail = items - rounds * waves;
+    Int busy = (tail + blocks - 1) / blocks;
+    if (rounds && busy > (Int)(kTileWaves / 2)) busy = (Int)kTileWaves;   // (they share SIMDs anyhow: 5128 tiles, 679 -> 669 us)
+    sc.rounds = (long long)rounds;
+    sc.busy = (int)busy;
+    sc.tail_per_xcd = busy ? (int)(((tail + busy - 1) / busy + 7) / 8) : 0;
+    // multiplier of the scramble: a prime that does not divide the number of groups, so that
+    // group -> group * mul mod n_groups is a bijection
+    const Int n_groups = rounds * blocks;
+    Int mul = 1;
+    for (Int p : {(Int)7919, (Int)7907, (Int)7901, (Int)7883})
+        if (n_groups > p && n_groups % p != 0) { mul = p; break; }
+    sc.group_mul = (long long)mul;
+    sc.group_step = n_groups ? (long long)((blocks / 8) * mul % n_groups) : 0;
+    return sc;
+}
+
+// Steps of the longest wave.
+template <class Int>
+__host__ __device__ inline Int wave_steps(Int items, Int blocks, Int samples, Int step)
+{
+    const Int waves = blocks * (Int)kTileWaves;
+    return (items + waves - 1) / waves * ((samples + step - 1) / step);
+}
 
 template <int KIND, int C, int H, int NH, bool CC, int GT>
 __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, MlpDev m, RaysDev rays, BwdIo io,
@@ -205,7 +249,6 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t acts = lds + wave * 2 * L::kAct;               // this wave's step tensors
     const uint32_t dz_at = lds + L::SMALL_AT + wave * L::kSmall;  // its output gradients
-    const uint32_t ray_at = dz_at + L::RAY;                       // its rays
     const int S = rays.S;
 
     // gradient accumulators, alive for the whole kernel
@@ -230,13 +273,36 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     }
 
     // ---- work items ----
-    const bool tiles = sched.tiles != 0;
-    const int rays_per_item = tiles ? kTileRays : 1;
+    // (the rays' pixels must share texels for a patch to be worth it, see launch_bwd_tile)
+    int row = 0, per_row = 0;   // of the image: pixels, patches
+    if (sched.items == Items::kPatches) {
+        row = __builtin_amdgcn_readfirstlane((int)find_row(g, rays, kPixelTexels, 1e30, *reinterpret_cast<int*>(lds_raw)));
+        sched.items = Items::kTiles;
+        if (row) {
+            const unsigned lines = ((unsigned)rays.M + row - 1) / row;
+            per_row = (row + kTileRays - 1) / kTileRays;
+            const unsigned n_patches = per_row * ((lines + 1) / 2), n_tiles = ((unsigned)rays.M + kTileRays - 1) / kTileRays;
+            // (rows that are no multiple of four leave places empty)
+            if (20 * wave_steps<unsigned>(n_patches, gridDim.x, S, kPatchSamples) <= 21 * wave_steps<unsigned>(n_tiles, gridDim.x, S, kTileSamples))
+                sched = tile_schedule<unsigned>(Items::kPatches, n_patches, gridDim.x);
+        }
+    }
+    const Items items = sched.items;
     const int xcd = blockIdx.x % 8, at = blockIdx.x / 8;
     const long long n_groups = sched.rounds * gridDim.x;   // of the whole rounds
     int left = (int)sched.rounds;                          // rounds to come; -1: the partial one is over too
     long long group = left ? ((n_groups / 8 * xcd + at) * sched.group_mul) % n_groups : 0, item = 0;
-    auto item_ray = [&]() { return item * rays_per_item; };   // first ray of the item
+    // rays [first, end) of line y of the item (a patch has two lines, another item one; none: first >= end)
+    auto line = [&](int y, long long& first, long long& end) {
+        if (items == Items::kPatches) {
+            const unsigned p = (unsigned)item, l = 2 * (p / (unsigned)per_row) + y, x = p % (unsigned)per_row * kTileRays;
+            first = (long long)l * row + x;
+            end = min(min(first + kTileRays, ((long long)l + 1) * row), rays.M);
+        } else {
+            first = items == Items::kTiles ? item * kTileRays : item;
+            end = y ? first : min(first + (items == Items::kTiles ? kTileRays : 1), rays.M);
+        }
+    };
     auto next_item = [&]() {   // false: none left
         if (left > 0) {
             item = group * kTileWaves + wave;
@@ -248,15 +314,26 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         if (left < 0) return false;
         left = -1;
         item = n_groups * kTileWaves + ((long long)sched.tail_per_xcd * xcd + at) * sched.busy + wave;
-        return wave < sched.busy && at < sched.tail_per_xcd && item_ray() < rays.M;
+        if (wave >= sched.busy || at >= sched.tail_per_xcd) return false;
+        long long first, end;
+        line(0, first, end);
+        return first < rays.M;
     };
     bool live = next_item();
 
-    // the rays being marched: `tile` (four rays, eight samples each per step) or one ray, number `sub` of the item
-    bool tile = false;
-    int sub = 0, j0 = 0, scene = 0;
-    auto step_sample = [&]() { return (int)lane_id & (tile ? kTileSamples - 1 : 31); };   // this lane's sample in the step
+    // the rays being marched, from number `sub` of the item on (four to a line): 2^(5 - log_samples) of them, 2^log_samples samples of each
+    // per step.  (The lane's columns: ray col >> log_samples, sample col & (2^log_samples - 1).)
+    int log_samples = 5, sub = 0, j0 = 0, scene = 0;
+    auto step_sample = [&]() { return (int)lane_id & ((1 << log_samples) - 1); };   // this lane's sample in the step
     bool ray_ok = false;        // the lane's ray exists
+    // What a step needs of its rays, 16 floats each, in two registers of the wave: value v of ray r in lane 8 r + v % 8 of
+    // register v / 8.  (LDS has no room for eight rays beside the weights of 32-64-64-4.)
+    int ray_data[2] = {0, 0};
+    enum { kOrigin = 0, kDir = 3, kNear = 6, kDelta = 7, kDelta64 = 8, kDelta64Hi = 9, kThrough = 10, kUpstream = 11, kUpstreamDepth = 14 };
+    auto ray_value = [&](int v) {
+        return __builtin_amdgcn_ds_bpermute(((((int)lane_id & 31) >> log_samples) * 8 + v % 8) * 4, ray_data[v / 8]);
+    };
+    auto ray_float = [&](int v) { return __int_as_float(ray_value(v)); };
     // Optical depth up to the end of the current step (fp64: see Eq. (2) below).  The widest kernels have no registers left
     // for it: in scratch memory it would be read behind the last step's atomic adds (triplane 128^2 x 32, 16 384 rays x 77
     // samples: 350 us of backward with the depth in LDS, 366 in registers; 64^3 x 32 voxels under 32-64-4: 9.86 ms a step
@@ -267,28 +344,45 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     Cell3 cell;
     Frag fh[KS1], fl[KS1];
 
-    // the lane's ray, kept in LDS between the steps
     auto geometry = [&]() {
-        const int col = lane_id & 31;
-        const uint32_t p = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
-        const f32x4 a = lds_get<f32x4>(p), b = lds_get<f32x4>(p + 16);
         RayGeom q;
-        q.ox = a[0]; q.oy = a[1]; q.oz = a[2]; q.dx = a[3]; q.dy = b[0]; q.dz = b[1]; q.near = b[2]; q.delta = b[3];
-        q.delta64 = lds_get<double>(p + 32);
+        q.ox = ray_float(kOrigin); q.oy = ray_float(kOrigin + 1); q.oz = ray_float(kOrigin + 2);
+        q.dx = ray_float(kDir); q.dy = ray_float(kDir + 1); q.dz = ray_float(kDir + 2);
+        q.near = ray_float(kNear); q.delta = 0.0f;
+        q.delta64 = __hiloint2double(ray_value(kDelta64Hi), ray_value(kDelta64));
         q.scene = scene;
         q.time = 0.0f;
         return q;
     };
-    // loads the rays of the current item (`sub` = 0: and decides how they are marched)
+    // Loads the rays from `sub` on: a whole patch, a line of a patch or a tile, if they run side by side, else one.
     auto load_rays = [&]() {
         const int col = lane_id & 31, grp = lane_id >> 5;
-        const long long first = item_ray();
-        if (tiles && sub == 0) {
-            tile = side_by_side(rays, first, rays.M, col, [&](const RayGeom& q, int j) { return sample_cell_for<CC, GT>(g, q, j); });
+        long long first, end;
+        line(sub >> 2, first, end);
+        first += sub & 3;
+        const long long there = min(first, rays.M - 1);   // (behind an image's last line a patch may hold no ray)
+        auto cell_of = [&](const RayGeom& q, int j) { return sample_cell_for<CC, GT>(g, q, j); };
+        // the lane's ray of a patch
+        auto patch_ray = [&](bool& ok) {
+            long long first, end;
+            line((col >> kLogPatchSamples) >> 2, first, end);
+            const long long r = first + ((col >> kLogPatchSamples) & 3);
+            ok = r < end;
+            return r;
+        };
+        bool patch = false;
+        if (items == Items::kPatches && sub == 0) {
+            bool ok;
+            const long long r = patch_ray(ok);
+            patch = side_by_side(rays, ok ? r : there, cell_of);
         }
-        const long long r = first + (tile ? (col >> 3) : sub);
-        ray_ok = r < rays.M;
-        const long long ray = min(r, rays.M - 1);
+        bool tile = false;
+        if (items != Items::kRays && !patch && (sub & 3) == 0) tile = side_by_side(rays, min(first + col / kTileSamples, end - 1), cell_of);
+        log_samples = patch ? kLogPatchSamples : tile ? kLogTileSamples : 5;
+        long long r = first + (tile ? col / kTileSamples : 0);
+        ray_ok = r < end;
+        if (patch) r = patch_ray(ray_ok);
+        const long long ray = ray_ok ? r : there;
         const RayGeom q = load_ray_geom(rays, ray);
         scene = __builtin_amdgcn_readfirstlane(q.scene);
         const int k = step_sample();
@@ -298,22 +392,25 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         const float tau_S = io.cache[ray];
         // d(loss)/dT_S through alpha = 1 - T_S and rgb += T_S bg, times T_S
         const float kS = __expf(-tau_S) * (p_alpha - (p0 * io.bg[0] + p1 * io.bg[1] + p2 * io.bg[2]));
+        // through the wave's LDS (nothing of a step is in it here) into the registers
         wave_lds_fence();
         if (k == 0 && grp == 0) {
-            const uint32_t p = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
-            const f32x4 v[3] = {{q.ox, q.oy, q.oz, q.dx}, {q.dy, q.dz, q.near, q.delta}, {p0, p1, p2, p_depth}};
-            lds_put<f32x4>(p, v[0]);
-            lds_put<f32x4>(p + 16, v[1]);
-            lds_put<double>(p + 32, q.delta64);
-            lds_put<float>(p + 40, kS);
-            lds_put<f32x4>(p + 48, v[2]);
-            if constexpr (kDepthInLds) lds_put<double>(dz_at + L::DEPTH + (tile ? (col >> 3) : 0) * 8, (double)tau_S);
+            const uint32_t p = acts + L::B + (col >> log_samples) * 32;
+            lds_put<f32x4>(p, f32x4{q.ox, q.oy, q.oz, q.dx});
+            lds_put<f32x4>(p + 16, f32x4{q.dy, q.dz, q.near, q.delta});
+            lds_put<double>(p + 256, q.delta64);
+            lds_put<float>(p + 264, kS);
+            lds_put<float>(p + 268, p0);
+            lds_put<f32x4>(p + 272, f32x4{p1, p2, p_depth, 0.0f});
+            if constexpr (kDepthInLds) lds_put<double>(dz_at + L::DEPTH + (col >> log_samples) * 8, (double)tau_S);
         }
         wave_lds_fence();
+        ray_data[0] = lds_get<int>(acts + L::B + 4 * lane_id);
+        ray_data[1] = lds_get<int>(acts + L::B + 256 + 4 * lane_id);
+        loads_done();
         tau_end = (double)tau_S;
         carry = 0.0f;
-        const int step = tile ? kTileSamples : 32;
-        j0 = ((S - 1) / step) * step;
+        j0 = ((S - 1) >> log_samples) << log_samples;
     };
     // features of the lane's sample of the step at j0
     auto sample = [&]() {
@@ -488,21 +585,19 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         // ---- Eq. (2); column col stands for sample j0 + k of the lane's ray (both lane groups alike) ----
         uint32_t zh0, zl0, zh1, zl1;
         {
-            const uint32_t geo = ray_at + (tile ? (col >> 3) : 0) * L::kRayBytes;
-            const float near = lds_get<float>(geo + 24), delta = lds_get<float>(geo + 28), kS = lds_get<float>(geo + 40);
-            const f32x4 p = lds_get<f32x4>(geo + 48);
-            const float p0 = p[0], p1 = p[1], p2 = p[2], p_depth = p[3];
+            const float near = ray_float(kNear), delta = ray_float(kDelta), kS = ray_float(kThrough);
+            const float p0 = ray_float(kUpstream), p1 = ray_float(kUpstream + 1), p2 = ray_float(kUpstream + 2), p_depth = ray_float(kUpstreamDepth);
             const int k = step_sample(), j = j0 + k;
-            const bool valid = ray_ok && j < S;
-            const int last = lane | (tile ? kTileSamples - 1 : 31);
+            const bool valid = ray_ok && j < S, alone = log_samples == 5;
+            const int last = lane | ((1 << log_samples) - 1);
             const float t = near + ((float)j + 0.5f) * delta;
             // softplus and its derivative from one exponential
             const float ez = __expf(-fabsf(z[0])), rz = recip(1.0f + ez);
             const float sd = valid ? (fmaxf(z[0], 0.0f) + __logf(1.0f + ez)) * delta : 0.0f;
-            const float incl = ray_scan(sd, k, tile);
+            const float incl = ray_scan(sd, k, alone);
             // (in fp64: a step of eight samples takes four times the subtractions of one of 32, and in fp32 each of them
             // rounds to the spacing of the whole depth, which at the front of an opaque ray is all of its weight)
-            const uint32_t depth_at = dz_at + L::DEPTH + (tile ? (col >> 3) : 0) * 8;
+            const uint32_t depth_at = dz_at + L::DEPTH + (col >> log_samples) * 8;
             if constexpr (kDepthInLds) tau_end = lds_get<double>(depth_at);
             tau_end -= (double)__shfl(incl, last, 64);
             const float tau_start = (float)tau_end;
@@ -512,7 +607,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             const float c1 = recip(1.0f + __expf(-z[1])), c2 = recip(1.0f + __expf(-z[2])), c3 = recip(1.0f + __expf(-z[3]));
             const float aa = p0 * c1 + p1 * c2 + p2 * c3 + p_depth * t;
             const float wa = w * aa;
-            const float pre = ray_scan(wa, k, tile);
+            const float pre = ray_scan(wa, k, alone);
             const float wa_total = __shfl(pre, last, 64);
             const float suf = wa_total - pre + wa;
             const float dsigma = delta * (Tq * aa - (suf - wa + carry) + kS);
@@ -720,12 +815,18 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         // ---- features of the next step, then the scatter of this one ----
         const Cell3 here = cell;
         const int here_scene = scene;
-        const bool here_tile = tile;
-        j0 -= tile ? kTileSamples : 32;
+        const int here_samples = 1 << log_samples;
+        j0 -= here_samples;
         if (j0 < 0) {
-            if (tiles && !tile && sub + 1 < kTileRays && item_ray() + sub + 1 < rays.M) {
-                ++sub;
-            } else {
+            // the item's next ray that has not been marched: on the same line, or the first of the next one
+            long long first, end;
+            sub += 32 >> log_samples;
+            line(sub >> 2, first, end);
+            if ((sub & 3) && first + (sub & 3) >= end) {
+                sub = (sub | 3) + 1;
+                line(sub >> 2, first, end);
+            }
+            if (items == Items::kRays || sub >= (items == Items::kPatches ? kPatchRays : kTileRays) || first >= end) {
                 sub = 0;
                 live = next_item();
             }
@@ -735,7 +836,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         __builtin_amdgcn_sched_barrier(0);
         refresh(lane_id);
         scatter_step<KIND, C>(g, io.d_grid, here_scene, acts + L::A, reinterpret_cast<char*>(lds_raw) + wave * 2 * L::kAct,
-                              here, dFt, lane_id, here_tile ? kTileSamples : 32);
+                              here, dFt, lane_id, here_samples);
         wave_lds_fence();
     }
 
@@ -841,32 +942,17 @@ hipError_t launch_bwd_tile(const GridDev& g, const MlpDev& m, const RaysDev& ray
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, L::kTotal);
     if (e != hipSuccess) return e;
     const int blocks = (n_cu + 7) / 8 * 8;
-    const long long waves = (long long)blocks * kTileWaves;
     // Tiles or single rays: the longest wave's number of steps decides.  A tile's step is cheaper to scatter, but a
     // launch of few rays spreads over more waves ray by ray.  Neighbouring rays, backward time in single rays over that
     // in tiles, for 16- and 32-channel voxel grids and triplanes and a hash table at 64 and 256 samples:
     // 1.03 .. 2.6 where a wave's steps are as many, 0.81 .. 1.65 at 1.33 times as many in tiles (16-channel voxels and the
     // hash table at 256 samples lose, 32 channels at 64 samples gain most), 0.68 .. 1.4 at 1.6 times.  The line stands
-    // where no structure loses.
-    auto rounds = [&](long long items) { return (items + waves - 1) / waves; };
-    const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays;
-    const long long tile_steps = rounds(n_tiles) * ((rays.S + kTileSamples - 1) / kTileSamples);
-    const long long ray_steps = rounds(rays.M) * ((rays.S + 31) / 32);
-    TileSchedule sc;
-    sc.tiles = 20 * tile_steps <= 21 * ray_steps;
-    const long long items = sc.tiles ? n_tiles : rays.M;
-    sc.rounds = items / waves;
-    const long long tail = items - sc.rounds * waves;
-    sc.busy = (int)((tail + blocks - 1) / blocks);
-    if (sc.rounds && sc.busy > kTileWaves / 2) sc.busy = kTileWaves;   // (they share SIMDs anyhow: 5128 tiles, 679 -> 669 us)
-    sc.tail_per_xcd = sc.busy ? (int)(((tail + sc.busy - 1) / sc.busy + 7) / 8) : 0;
-    // multiplier of the scramble: a prime that does not divide the number of groups, so that
-    // group -> group * mul mod n_groups is a bijection
-    const long long n_groups = sc.rounds * blocks;
-    sc.group_mul = 1;
-    for (long long p : {7919LL, 7907LL, 7901LL, 7883LL})
-        if (n_groups > p && n_groups % p != 0) { sc.group_mul = p; break; }
-    sc.group_step = n_groups ? ((long long)(blocks / 8) * sc.group_mul) % n_groups : 0;
+    // where no structure loses.  Patches against tiles alike.
+    const long long n_tiles = (rays.M + kTileRays - 1) / kTileRays, n_patches = (rays.M + kPatchRays - 1) / kPatchRays;
+    auto steps = [&](long long items, long long step) { return wave_steps<long long>(items, blocks, rays.S, step); };
+    const bool tiles = 20 * steps(n_tiles, kTileSamples) <= 21 * steps(rays.M, 32);
+    const bool patches = tiles && 20 * steps(n_patches, kPatchSamples) <= 21 * steps(n_tiles, kTileSamples) && rays.M < (1LL << 31);
+    const TileSchedule sc = tile_schedule<long long>(patches ? Items::kPatches : tiles ? Items::kTiles : Items::kRays, tiles ? n_tiles : rays.M, blocks);
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTileWaves * 64), L::kTotal, stream, g, m, rays, io, sc);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -195,7 +195,7 @@ __device__ __forceinline__ RayGeom load_ray_geom(const RaysDev& rays, long long 
     q.ox = rays.origins[3 * ray + 0]; q.oy = rays.origins[3 * ray + 1]; q.oz = rays.origins[3 * ray + 2];
     q.dx = rays.dirs[3 * ray + 0]; q.dy = rays.dirs[3 * ray + 1]; q.dz = rays.dirs[3 * ray + 2];
     q.near = rays.near[ray];
-    q.delta64 = ((double)rays.far[ray] - (double)q.near) / (double)rays.S;
+    q.delta64 = ((double)rays.far[ray] - (double)q.near) / rays.samples;
     q.delta = (float)q.delta64;
     q.scene = rays.scene ? rays.scene[ray] : 0;
     q.time = rays.time ? rays.time[ray] : -INFINITY;

@@ -40,7 +40,7 @@ __device__ __forceinline__ void push_rays(const GridDev& tgt, const RaysDev& ray
 {
     const uint32_t area = (uint32_t)(uintptr_t)(LdsByte*)area_ptr;
     const int col = lane & 31;
-    const bool tile = tiles && side_by_side(rays, first, end, col, [&](const RayGeom& r, int j) { return sample_cell<CC>(tgt, r, j); });
+    const bool tile = tiles && side_by_side(rays, min(first + col / kTileSamples, end - 1), [&](const RayGeom& r, int j) { return sample_cell<CC>(tgt, r, j); });
     const int n_sub = tile ? 1 : (int)(end - first);
     for (int sub = 0; sub < n_sub; ++sub) {
         const long long r = first + (tile ? col / kTileSamples : sub);
@@ -79,7 +79,8 @@ constexpr long long kMinRays = 2048;
 template <int KIND>
 __device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& rays)
 {
-    return find_row(g, rays, KIND == LP_GRID_TRIPLANE ? 1.5 : 0.9, 1e30);
+    __shared__ int found;
+    return find_row(g, rays, KIND == LP_GRID_TRIPLANE ? 1.5 : 0.9, 1e30, found);
 }
 
 // Rays in their order.  PATCHES: the patch kernel has been launched before and takes what it finds to be an image (an

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void splat_mfma_kernel(GridDev tgt,
         const long long first = (((seq / kWaves) * order.group_mul % order.n_groups) * kWaves + seq % kWaves) * rays_per_item;
         if (first >= rays.M) continue;
         const long long end = min(first + rays_per_item, rays.M);
-        const bool tile = TILES && side_by_side<kPushApart>(rays, first, end, col, [&](const RayGeom& r, int j) { return sample_cell_any(tgt, r, j); });
+        const bool tile = TILES && side_by_side<kPushApart>(rays, min(first + col / kTileSamples, end - 1), [&](const RayGeom& r, int j) { return sample_cell_any(tgt, r, j); });
         const int n_sub = tile ? 1 : (int)(end - first);
         for (int sub = 0; sub < n_sub; ++sub) {
             const long long ray = first + (tile ? col / kTileSamples : sub);

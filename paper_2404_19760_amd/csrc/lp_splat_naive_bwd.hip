@@ -167,7 +167,8 @@ template <int C>
 __device__ __forceinline__ long long image_row(const GridDev& g, const RaysDev& rays)
 {
     const double longest = rays.M >= kManyRays ? 2.0 : C == 16 ? 0.75 : 1.25;
-    return find_row(g, rays, 0.9, longest);
+    __shared__ int found;
+    return find_row(g, rays, 0.9, longest, found);
 }
 
 // Rays in their order.  PATCHES: the patch kernel has been launched before and takes what it finds to be an image.

@@ -491,12 +491,11 @@ __device__ __forceinline__ bool rays_run_in_tiles(const GridDev& g, const RaysDe
     return 4 * together >= 3 * 64;
 }
 
-// Whether the four rays from `first` on (those below `end`) run side by side: in one scene, and within APART cells of the
-// first at both ends.
+// Whether the rays that the lanes name run side by side: in one scene, and within APART cells of the first lane's at both ends.
 template <int APART = 3, class CellOf>
-__device__ __forceinline__ bool side_by_side(const RaysDev& rays, long long first, long long end, int col, CellOf cell_of)
+__device__ __forceinline__ bool side_by_side(const RaysDev& rays, long long ray, CellOf cell_of)
 {
-    const RayGeom q = load_ray_geom(rays, min(first + col / kTileSamples, end - 1));
+    const RayGeom q = load_ray_geom(rays, ray);
     const Cell3 c0 = cell_of(q, 0), c1 = cell_of(q, rays.S - 1);
     bool apart = q.scene != __builtin_amdgcn_readfirstlane(q.scene);
 #pragma unroll

@@ -76,7 +76,7 @@ def test_step_of_the_tile_backward(hidden_layers):
         (r"lds_put<\w+>\(geo ", [("store", "rays")]),
         (r"lds_get<double>\(depth_at", [("read", "depths")]),
         (r"lds_put<double>\(depth_at", [("store", "depths")]),
-        (r"\bload_rays\(\)", [("fence", None), ("store", "rays"), ("store", "depths"), ("fence", None)]),
+        (r"\bload_rays\(\)", [("fence", None), ("store", "rays"), ("store", "depths"), ("fence", None), ("read", "rays")]),
         (r"\bscatter_step<", [("fence", None), ("store", "A"), ("fence", None), ("read", "A")]),
     ], names)
     assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "rays", "depths"} == {b for w, b in step if w == "store"}

@@ -19,6 +19,16 @@ def backward_in_tiles(n_rays, samples, n_cu=256):
     return 20 * tile_steps <= 21 * (rounds(n_rays) * -(-samples // 32))
 
 
+def backward_in_patches(n_rays, samples, row, n_cu=256):
+    """Whether it hands out patches of an image whose rows are `row` long: 4 x 2 pixels, four samples of each ray per step."""
+    waves = (n_cu + 7) // 8 * 8 * 8
+    steps = lambda items, step: -(-items // waves) * -(-samples // step)
+    tiles = 21 * steps(-(-n_rays // TILE_RAYS), TILE_SAMPLES)
+    lines = -(-n_rays // row) if row else 0
+    return bool(row) and backward_in_tiles(n_rays, samples, n_cu) and 20 * steps(-(-n_rays // 8), 4) <= tiles and \
+        20 * steps(-(-row // 4) * -(-lines // 2), 4) <= tiles
+
+
 def forward_in_pairs(n_rays, samples, n_cu=256):
     """Whether the Renderer's forward takes rays in pairs (lp_mfma_fwd.hip launch_fwd)."""
     simds, items = 4 * n_cu, (n_rays + 1) // 2
@@ -156,10 +166,11 @@ def cells(inp):
 
 
 def step_routes(inp):
-    """Counter of (how the rays are marched, how the step is scattered): ("tile" | "ray", 1 | 2 | 4 windows | "walk")."""
+    """Counter of (how the rays are marched, how the step is scattered): ("patch" | "tile" | "ray", 1 | 2 | 4 windows | "walk")."""
     c = cells(inp)
     ray_scene = inp.scene if inp.scene is not None else np.zeros(inp.n_rays, int)
     in_tiles = backward_in_tiles(inp.n_rays, inp.samples)
+    row = image_row(inp, 1.5, 1e30)
 
     def fits(run):   # [rays][samples][3]
         e = run.reshape(-1, 3).max(0) - run.reshape(-1, 3).min(0) + 2
@@ -177,16 +188,35 @@ def step_routes(inp):
             else:
                 routes[how, "walk"] += 1
 
-    routes = Counter()
-    for first in range(0, inp.n_rays, TILE_RAYS):
-        rays = np.arange(first, first + TILE_RAYS)
-        there = np.minimum(rays, inp.n_rays - 1)
-        ends = c[there][:, [0, -1]]
-        if in_tiles and (ray_scene[there] == ray_scene[first]).all() and np.abs(ends - ends[0]).max() <= 3:
+    def together(rays):
+        ends = c[rays][:, [0, -1]]
+        return (ray_scene[rays] == ray_scene[rays[0]]).all() and np.abs(ends - ends[0]).max() <= 3
+
+    def line(rays):   # at most four
+        there = np.concatenate([rays, np.full(TILE_RAYS - len(rays), rays[-1])])
+        if in_tiles and together(there):
             march(there, "tile", TILE_SAMPLES)
         else:
-            for r in rays[rays < inp.n_rays]:
+            for r in rays:
                 march([r], "ray", 32)
+
+    routes = Counter()
+    if backward_in_patches(inp.n_rays, inp.samples, row):
+        for y in range(0, -(-inp.n_rays // row), 2):
+            for x in range(0, row, TILE_RAYS):
+                lines = [np.arange(l * row + x, min(l * row + min(x + TILE_RAYS, row), inp.n_rays)) for l in (y, y + 1)]
+                lines = [l for l in lines if len(l)]
+                if not lines:
+                    continue
+                rays = np.concatenate(lines)
+                if together(rays):
+                    march(rays, "patch", 4)
+                else:
+                    for l in lines:
+                        line(l)
+        return routes
+    for first in range(0, inp.n_rays, TILE_RAYS):
+        line(np.arange(first, min(first + TILE_RAYS, inp.n_rays)))
     return routes
 
 
