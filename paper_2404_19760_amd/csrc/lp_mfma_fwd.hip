@@ -16,6 +16,7 @@
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace lp {
@@ -169,7 +170,9 @@ hipError_t launch_items(const GridDev& g, const MlpDev& m, const RaysDev& rays, 
     // that of three workgroups of equal work the first was done early and the last ran alone; now others follow. 32 steps to a wave: 563 563 rays x
     // 330 samples, 256^3 x 16 voxels in bf16, 8.62 -> 7.88 ms (16 steps 7.99, 64 steps 7.97), 64^3 x 32 voxels 2.43 -> 2.33,
     // eight triplanes 26.2 -> 25.5; one step or two to a wave (5003 rays x 193 samples) took 6 % longer.
-    const long long fine = items * ((rays.S + (PAIRS ? 31 : 63)) / (PAIRS ? 32 : 64)) / (kWaves * 32) / 8 * 8;
+    // At most 2^20: a launch holds fewer than 2^32 threads, and by then 341 workgroups follow each other in a place.
+    const long long steps = (rays.S + (PAIRS ? 31 : 63)) / (PAIRS ? 32 : 64);
+    const long long fine = std::min(items * steps / (kWaves * 32) / 8 * 8, 1LL << 20);
     if (blocks < fine) blocks = fine;
     if (blocks > need) blocks = (need + 7) / 8 * 8;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWaves * 64), kLdsBytes, stream, g, m, rays, out);
