@@ -7,7 +7,7 @@ import lp_inputs
 from lp_inputs import HASH, TRIPLANE, VOXEL
 
 from parity import FWD_RTOL, close
-from tile_rules import forward_in_pairs
+from tile_rules import forward_in_pairs, forward_workgroups
 
 pytestmark = pytest.mark.gpu
 
@@ -16,10 +16,11 @@ pytestmark = pytest.mark.gpu
                                                       (TRIPLANE, 32, (32, 64, 64, 4), torch.float32), (TRIPLANE, 16, (16, 32, 32, 4), torch.float16),
                                                       (HASH, 16, (16, 64, 4), torch.float32)])
 @pytest.mark.parametrize("n_rays,samples,pairs", [(1, 1, True), (6143, 31, True), (6143, 33, True), (6143, 95, True), (77, 65, False), (9001, 161, False), (4093, 49, False), (4095, 49, True),
-                                                  (4690, 252, False)])
+                                                  (4690, 252, False), (50003, 129, True), (101001, 49, False)])   # (the last two: more workgroups than fit at once)
 def test_equals_the_generic_kernels(lp, kind, channels, dims, dtype, n_rays, samples, pairs):
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert forward_in_pairs(n_rays, samples) == pairs
+        assert (forward_workgroups(n_rays, samples) > 768) == (n_rays > 50000)
     kw = dict(hash_size=4096) if kind == HASH else {}
     inp = lp_inputs.make_small(kind, channels=channels, res=(24, 21, 26), mlp_dims=dims, n_rays=n_rays, samples=samples, seed=71 + samples,
                                n_scenes=3, grid_std=0.3, **kw)

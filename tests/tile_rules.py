@@ -36,6 +36,14 @@ def forward_in_pairs(n_rays, samples, n_cu=256):
     return share(items) * -(-samples // 32) <= share(n_rays) * -(-samples // 64) and (samples <= 32 or items >= 2 * simds)
 
 
+def forward_workgroups(n_rays, samples, n_cu=256):
+    """Workgroups of the Renderer's forward (lp_mfma_fwd.hip launch_items)."""
+    pairs = forward_in_pairs(n_rays, samples, n_cu)
+    items, steps = ((n_rays + 1) // 2, -(-samples // 32)) if pairs else (n_rays, -(-samples // 64))
+    blocks = max((3 * n_cu + 7) // 8 * 8, min(items * steps // 128 // 8 * 8, 1 << 20))
+    return min(blocks, (-(-items // 4) + 7) // 8 * 8)
+
+
 def image_row(inp, pixel, step):
     """Length of an image's row that the Splatter's patch kernels find in a list of rays (lp_splat_patch.h find_row), 0: none."""
     end = (inp.origins + inp.far[:, None] * inp.dirs).astype(np.float32)
