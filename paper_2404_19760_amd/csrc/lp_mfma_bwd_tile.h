@@ -19,14 +19,14 @@
 //   - The grid gradient is bound by the rate of atomic adds (2.1e10 64-byte lines/s on this chip, whatever
 //     the locality). One ray's samples touch 3.1 (voxel) and 9.9 (triplane) lines per sample after run
 //     merging; the union of the texels that four neighbouring rays touch with eight samples each is 0.70 and
-//     3.47 lines per sample, of a patch with four samples each 0.53 and 2.42, and the scatter's matrix products shrink
+//     3.63 lines per sample, of a patch with four samples each 0.52 and 2.56 (counted), and the scatter's matrix products shrink
 //     alike.  (Patches against tiles, a whole training step: eight triplanes 115.7 -> 107.6 ms, one triplane 128^2 x 32, 128^2 rays,
 //     735 -> 665 us, 256^3 x 16 voxels 61.1 -> 60.7 ms, a hash table 460 -> 451 us.)
 //   - A wave does not overlap its own vector and matrix instructions; two waves per SIMD do. The
 //     accumulators of the weight gradients (94 registers for 16-64-64-4: the two thin matrices on 16 x 16
 //     and 4 x 4 tiles) leave room for two waves only if a step's activations live in LDS instead of registers.
-//     Per SIMD the voxel kernel issues vector instructions in 50 % of the cycles and keeps the matrix cores busy in
-//     37 %, the triplane kernel 38 % and 45 % (1357 and 1662 vector instructions a step).
+//     Per SIMD the voxel kernel issues vector instructions in 52 % of the cycles and keeps the matrix cores busy in
+//     39 %, the triplane kernel 45 % and 38 % (1312 and 1629 vector instructions a step; 45.6 and 79.7 ms a launch).
 //   - In LDS they are transposed by the reads (lp_tile_lds.h); on the matrix cores the transposition by 0/1
 //     products took 36 of the 168 products of a step and as many permutes. The transposed weights of the
 //     input-gradient chain are column reads of the same images, which halves the LDS that weights take.
@@ -492,7 +492,12 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             lds_put_chunk((own_h ^ IH::own_step(s)) + where + kLoH, l[0][s]);
         }
     };
+    // (a wave with an item of the partial round starts an item behind the others: it is to be done when they are)
     int n_steps = 0;
+    if (wave < sched.busy && at < sched.tail_per_xcd) {
+        const int step = items == Items::kPatches ? kPatchSamples : items == Items::kTiles ? kTileSamples : 32;
+        n_steps = -((S + step - 1) / step);
+    }
     while (live) {
         refresh(own_h); refresh(own_f); refresh(lane_id);
         // Waves w and w + 4 share a SIMD, which serves the older one first: left alone, waves 0 .. 3 were done after 0.91 of the

@@ -7,10 +7,11 @@
 // matrix cores for the 64 samples (two N blocks of 32, a stage apart), then lane l owns sample l of the step
 // for the density / colour heads and the emission-absorption update, where the transmittance
 // prefix is a scan of sigma * Delta over the lanes of a ray.  Nothing per sample is written to memory.
-// What bounds it: instruction issue (256^3 x 16 voxels in bf16, 563 563 rays x 330 samples: 967 wave instructions on the vector ALU
-// a step, the products among them, issue in 70 % of a SIMD's cycles and the matrix cores are busy in 44 %).  So rays come in pairs,
+// What bounds it: instruction issue (256^3 x 16 voxels in bf16, 563 563 rays x 330 samples: 984 wave instructions on the vector ALU
+// a step, the products among them, issue in 80 % of a SIMD's cycles and the matrix cores are busy in 49 %).  So rays come in pairs,
 // which leaves fewer places empty at their ends (330 samples: 6 % instead of 14 %), each lane forms the cell of one sample and the
-// halves of the wave exchange them, and a load's address is a uniform pointer and the lane's offset: 9.57 -> 8.46 ms.
+// halves of the wave exchange them, and a load's address is a uniform pointer and the lane's offset: 9.57 -> 8.46 ms.  And more
+// workgroups than fit at once (launch_items): 8.52 -> 7.54.
 #include "lp_gather.h"
 #include "lp_kernels.h"
 #include "lp_mfma.h"
