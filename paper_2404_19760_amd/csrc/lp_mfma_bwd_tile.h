@@ -421,6 +421,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         wave_lds_fence();
         ray_data[0] = lds_get<int>(acts + L::B + 4 * lane_id);
         ray_data[1] = lds_get<int>(acts + L::B + 256 + 4 * lane_id);
+        wave_lds_fence();   // (the first rays are read right in front of a step, whose activations go to the same bytes)
         loads_done();
         tau_end = (double)tau_S;
         carry = 0.0f;

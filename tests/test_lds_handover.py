@@ -1,7 +1,7 @@
 """Hand-overs between the lanes of one wave through LDS, checked on the CPU from the kernels' source.  Lanes store pieces of
 a buffer that other lanes read; no address of a single lane depends on that, so the compiler may exchange the two unless a
 `wave_lds_fence` stands between them.  Required, over two steps in a row: between a store into a buffer and a read of other
-lanes' bytes of it, and between such a read and the next store, there is a fence.  Accesses are taken in the order in which
+lanes' bytes of it, and between such a read and the next store, there is a fence (also from what stands before the loop).  Accesses are taken in the order in which
 they are written down (a lambda's stand where it is defined, right before its use)."""
 import os
 import re
@@ -33,9 +33,9 @@ def _events(lines, rules, names=None):
     return out
 
 
-def _check(step):
+def _check(step, before=()):
     open_accesses = set()
-    for what, buffer in step + step:
+    for what, buffer in [*before, *step, *step]:
         if what == "fence":
             open_accesses.clear()
             continue
@@ -54,7 +54,10 @@ def test_sampling_by_whole_texels():
 
 @pytest.mark.parametrize("hidden_layers", [1, 2])
 def test_step_of_the_tile_backward(hidden_layers):
-    body = _between(_source("lp_mfma_bwd_tile.h"), r"^    while \(live\) \{", r"^    // ---- sums|^    constexpr int kRegs")
+    """The first rays are loaded in front of the loop, the next ones inside of it, through the bytes of a step tensor."""
+    source = _source("lp_mfma_bwd_tile.h")
+    load = _between(source, r"^    auto load_rays = ", r"^    };")
+    body = _between(source, r"^    while \(live\) \{", r"^    // ---- sums|^    constexpr int kRegs")
     if hidden_layers == 1:   # without the part between the output layer and the first one
         a = next(i for i, l in enumerate(body) if l.rstrip() == "        if constexpr (NH == 2) {")
         b = next(i for i in range(a, len(body)) if body[i].rstrip() == "        }")
@@ -63,7 +66,13 @@ def test_step_of_the_tile_backward(hidden_layers):
     names = {"kHere": "B" if two else "A", "kLast": "B" if two else "A", "kZ": "A" if two else "B", "kF": "B" if two else "A",
              "L::A": "A", "L::B": "B"}
     area = r"(L::A|L::B|kHere|kLast|kZ|kF)\b"
-    step = _events(body, [
+    at_rays = re.search(r"const uint32_t p = acts \+ " + area, "\n".join(load)).group(1)
+    rays = [FENCE,
+            (r"lds_put<\w+>\(p\b", [("store", at_rays)]),
+            (r"lds_get<\w+>\(acts \+ " + area, [("read", "$1")]),
+            (r"lds_put<double>\(dz_at \+ L::DEPTH", [("store", "depths")])]
+    loading = _events(load, rays, names)
+    rules = [
         FENCE,
         (r"activate_pair\([^()]*, " + area, [("store", "$1")]),
         (r"store_hidden\(" + area, [("store", "$1")]),
@@ -72,15 +81,16 @@ def test_step_of_the_tile_backward(hidden_layers):
         (r"lds_tr\(zp ", [("read", "output gradients")]),
         (r"lds_tr\(hp [^;]*?\+ " + area, [("read", "$1")]),
         (r"I(?:H|W1)::read\((?:col_h|col16_h|col_f)\b[^;]*?" + area, [("read", "$1")]),
-        (r"lds_get<\w+>\(geo ", [("read", "rays")]),
-        (r"lds_put<\w+>\(geo ", [("store", "rays")]),
         (r"lds_get<double>\(depth_at", [("read", "depths")]),
         (r"lds_put<double>\(depth_at", [("store", "depths")]),
-        (r"\bload_rays\(\)", [("fence", None), ("store", "rays"), ("store", "depths"), ("fence", None), ("read", "rays")]),
+        (r"\bload_rays\(\)", loading),
         (r"\bscatter_step<", [("fence", None), ("store", "A"), ("fence", None), ("read", "A")]),
-    ], names)
-    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "rays", "depths"} == {b for w, b in step if w == "store"}
-    _check(step)
+    ]
+    for pattern, lines in [(r, load) for r, _ in rays] + [(r, body) for r, _ in rules]:
+        assert any(re.search(pattern, l) for l in lines), f"nothing is checked by {pattern}"
+    step = _events(body, rules, names)
+    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "depths"} == {b for w, b in step if w == "store"}
+    _check(step, loading)
 
 
 @pytest.mark.parametrize("function", ["scatter_window", "scatter_walk"])
