@@ -69,9 +69,9 @@ struct TileLds {
     static constexpr int WO_AT = W1_AT + 2 * W1::bytes(H);       // 4 rows hi, 4 rows lo
     static constexpr int BIAS_AT = WO_AT + 8 * kWo;              // b1[H] b2[H] bo[4]
     static constexpr int SMALL_AT = BIAS_AT + (2 * H + 4) * 4;
-    // one wave: output gradients; per ray of a step, fp64, the optical depth up to the step's end
-    static constexpr int DEPTH = 512;
-    static constexpr int kSmall = DEPTH + kPatchRays * 8;
+    // one wave: output gradients; per ray of a step, fp64, the optical depth up to the step's end and the sum over later steps
+    static constexpr int SUMS = 512;
+    static constexpr int kSmall = SUMS + kPatchRays * 16;
     static constexpr int STEPS_AT = SMALL_AT + kTileWaves * kSmall;   // steps that each wave has done
     static constexpr int kTotal = STEPS_AT + kTileWaves * 4;
     static_assert(W2_AT % 4096 == 0 && W1_AT % 1024 == 0 && SMALL_AT % 16 == 0 && kSmall % 16 == 0, "alignment");
@@ -348,13 +348,13 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         return __builtin_amdgcn_ds_bpermute(((((int)lane_id & 31) >> log_samples) * 8 + v % 8) * 4, ray_data[v / 8]);
     };
     auto ray_float = [&](int v) { return __int_as_float(ray_value(v)); };
-    // Optical depth up to the end of the current step (fp64: see Eq. (2) below).  The widest kernels have no registers left
-    // for it: in scratch memory it would be read behind the last step's atomic adds (triplane 128^2 x 32, 16 384 rays x 77
-    // samples: 350 us of backward with the depth in LDS, 366 in registers; 64^3 x 32 voxels under 32-64-4: 9.86 ms a step
-    // in LDS, 9.66 in registers).
-    constexpr bool kDepthInLds = C == 32 && H == 64 && NH == 2;
-    double tau_end = 0.0;
-    float carry = 0.0f;         // sum of w_j a_j over all later steps
+    // Optical depth up to the end of the current step, and the sum of w_j a_j over all later steps (fp64: see Eq. (2) below).  The
+    // widest kernels have no registers left for them: in scratch memory they would be read behind the last step's atomic adds
+    // (triplane 128^2 x 32, 16 384 rays x 77 samples: 350 us of backward with the depth in LDS, 366 in registers; 64^3 x 32 voxels under
+    // 32-64-4: 9.86 ms a step in LDS, 9.66 in registers).
+    constexpr bool kSumsInLds = C == 32 && H == 64 && NH == 2;
+    typedef __attribute__((__vector_size__(2 * sizeof(double)))) double f64x2;
+    double tau_end = 0.0, carry = 0.0;
     Cell3 cell;
     Frag fh[KS1], fl[KS1];
 
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             lds_put<float>(p + 264, kS);
             lds_put<float>(p + 268, p0);
             lds_put<f32x4>(p + 272, f32x4{p1, p2, p_depth, 0.0f});
-            if constexpr (kDepthInLds) lds_put<double>(dz_at + L::DEPTH + (col >> log_samples) * 8, (double)tau_S);
+            if constexpr (kSumsInLds) lds_put<f64x2>(dz_at + L::SUMS + (col >> log_samples) * 16, f64x2{(double)tau_S, 0.0});
         }
         wave_lds_fence();
         ray_data[0] = lds_get<int>(acts + L::B + 4 * lane_id);
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         wave_lds_fence();   // (the first rays are read right in front of a step, whose activations go to the same bytes)
         loads_done();
         tau_end = (double)tau_S;
-        carry = 0.0f;
+        carry = 0.0;
         j0 = ((S - 1) >> log_samples) << log_samples;
     };
     // features of the lane's sample of the step at j0
@@ -626,9 +626,15 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             const float sd = valid ? (fmaxf(z[0], 0.0f) + __logf(1.0f + ez)) * delta : 0.0f;
             const float incl = ray_scan(sd, k, alone);
             // (in fp64: a step of eight samples takes four times the subtractions of one of 32, and in fp32 each of them
-            // rounds to the spacing of the whole depth, which at the front of an opaque ray is all of its weight)
-            const uint32_t depth_at = dz_at + L::DEPTH + (col >> log_samples) * 8;
-            if constexpr (kDepthInLds) tau_end = lds_get<double>(depth_at);
+            // rounds to the spacing of the whole depth, which at the front of an opaque ray is all of its weight; so does the sum over
+            // later steps: summed in fp32 over 4096 samples, a patch's gradient of a ray whose terms cancel was 2.7 times as far from 64 bits as
+            // a single ray's)
+            const uint32_t sums_at = dz_at + L::SUMS + (col >> log_samples) * 16;
+            if constexpr (kSumsInLds) {
+                const f64x2 sums = lds_get<f64x2>(sums_at);
+                tau_end = sums[0];
+                carry = sums[1];
+            }
             tau_end -= (double)__shfl(incl, last, 64);
             const float tau_start = (float)tau_end;
             const float Tprev = __expf(-(tau_start + (incl - sd)));
@@ -640,8 +646,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             const float pre = ray_scan(wa, k, alone);
             const float wa_total = __shfl(pre, last, 64);
             const float suf = wa_total - pre + wa;
-            const float dsigma = delta * (Tq * aa - (suf - wa + carry) + kS);
-            carry += wa_total;
+            const float dsigma = delta * (Tq * aa - (suf - wa + (float)carry) + kS);
+            carry += (double)wa_total;
             float dz[4];
             dz[0] = valid ? dsigma * (z[0] >= 0.0f ? rz : ez * rz) : 0.0f;
             dz[1] = valid ? w * p0 * c1 * (1.0f - c1) : 0.0f;
@@ -652,8 +658,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
             split2(dz[0], dz[1], zh0, zl0);
             split2(dz[2], dz[3], zh1, zl1);
             lds_put<u32x4>(dz_at + col * 16, u32x4{zh0, zh1, zl0, zl1});   // (both lane groups the same)
-            wave_lds_fence();   // the activations, the output gradients; every lane has read its ray's depth
-            if (kDepthInLds && k == 0 && grp == 0) lds_put<double>(depth_at, tau_end);
+            wave_lds_fence();   // the activations, the output gradients; every lane has read its ray's sums
+            if (kSumsInLds && k == 0 && grp == 0) lds_put<f64x2>(sums_at, f64x2{tau_end, carry});
         }
         __builtin_amdgcn_sched_barrier(0);
 

@@ -70,7 +70,7 @@ def test_step_of_the_tile_backward(hidden_layers):
     rays = [FENCE,
             (r"lds_put<\w+>\(p\b", [("store", at_rays)]),
             (r"lds_get<\w+>\(acts \+ " + area, [("read", "$1")]),
-            (r"lds_put<double>\(dz_at \+ L::DEPTH", [("store", "depths")])]
+            (r"lds_put<f64x2>\(dz_at \+ L::SUMS", [("store", "sums")])]
     loading = _events(load, rays, names)
     rules = [
         FENCE,
@@ -81,15 +81,15 @@ def test_step_of_the_tile_backward(hidden_layers):
         (r"lds_tr\(zp ", [("read", "output gradients")]),
         (r"lds_tr\(hp [^;]*?\+ " + area, [("read", "$1")]),
         (r"I(?:H|W1)::read\((?:col_h|col16_h|col_f)\b[^;]*?" + area, [("read", "$1")]),
-        (r"lds_get<double>\(depth_at", [("read", "depths")]),
-        (r"lds_put<double>\(depth_at", [("store", "depths")]),
+        (r"lds_get<f64x2>\(sums_at", [("read", "sums")]),
+        (r"lds_put<f64x2>\(sums_at", [("store", "sums")]),
         (r"\bload_rays\(\)", loading),
         (r"\bscatter_step<", [("fence", None), ("store", "A"), ("fence", None), ("read", "A")]),
     ]
     for pattern, lines in [(r, load) for r, _ in rays] + [(r, body) for r, _ in rules]:
         assert any(re.search(pattern, l) for l in lines), f"nothing is checked by {pattern}"
     step = _events(body, rules, names)
-    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "depths"} == {b for w, b in step if w == "store"}
+    assert {b for w, b in step if w == "read"} == {"A", "B", "output gradients", "sums"} == {b for w, b in step if w == "store"}
     _check(step, loading)
 
 
