@@ -500,6 +500,10 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         const int step = items == Items::kPatches ? kPatchSamples : items == Items::kTiles ? kTileSamples : 32;
         n_steps = -((S + step - 1) / step);
     }
+    // The staging's loads too: a lane without a share of the weights passes by their use, and the kernels of one or two hidden layers of 32 waited
+    // at the top of every step, and so for the adds of the step before.  (Backward, 2559 rays in random order x 445 samples through voxels, 16-32-32-4:
+    // 169.4 -> 163.4 us, 16-32-4 139.5 -> 135.9, a hash table 171.3 -> 165.0.)
+    loads_done();
     while (live) {
         refresh(own_h); refresh(own_f); refresh(lane_id);
         // Waves w and w + 4 share a SIMD, which serves the older one first: left alone, waves 0 .. 3 were done after 0.91 of the
