@@ -512,8 +512,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         // the order of the work changes, not the work.  Single rays gain too: 4096 in random order x 256 samples 243.7 -> 238.5 us a step of
         // training, 6144 x 128 on 32 channels 257 -> 253.)
         lds_put<int>(lds + L::STEPS_AT + 4 * wave, ++n_steps);
-        if (__builtin_amdgcn_readfirstlane(lds_get<int>(lds + L::STEPS_AT + 4 * (wave ^ 4))) > n_steps) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
+        const int partner_steps = lds_get<int>(lds + L::STEPS_AT + 4 * (wave ^ 4));   // (looked at where what was read behind it has arrived anyhow)
         const uint32_t own_w = own_h + to_w2, own_w1 = own_f + to_w1;
         const int lane = lane_id, col = lane & 31, grp = lane >> 5;
         // ---- MLP forward ----
@@ -548,6 +547,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
                 auto first = [&](auto i) { layer1(i); };
                 weave<3 * KS1, 0, 0>(first, none);
             }
+            if (__builtin_amdgcn_readfirstlane(partner_steps) > n_steps) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
             // second layer: the K-steps of the first block of activations for all rows, then those of the second block
             constexpr int T2 = MB * KSH;   // (row block, K-step) pairs in this order
             auto mb_of = [](int t) { return MB == 1 ? 0 : t < 4 ? t & 1 : (t - 4) >> 1; };
