@@ -52,7 +52,18 @@ constexpr int kTileWaves = 8;
 // A patch: four neighbouring pixels each of two rows of an image, four samples of each ray per step.
 constexpr int kPatchRays = 8, kPatchSamples = 4, kLogPatchSamples = 2, kLogTileSamples = 3;
 static_assert((1 << kLogPatchSamples) == kPatchSamples && (1 << kLogTileSamples) == kTileSamples && kPatchRays * kPatchSamples == 32);
-constexpr double kPixelTexels = 1.5;   // from pixel to pixel at most
+// From pixel to pixel at most, in the middle of the rays.  Images of 96^2 to 256^2 pixels, 16 and 32 channels, 64 to 512 samples; time of the
+// backward in tiles over that in patches, mean (least, largest), by pixel distance, where from 0.7 on more and more patches fall apart
+// into tiles and from 1 on into single rays:
+//              0.6    0.7 .. 0.85         0.9 .. 1.0          1.02 .. 1.1         1.2                  1.33 .. 1.5
+//   voxels 16  1.19   0.99 (0.86, 1.23)   0.99 (0.90, 1.11)   1.02 (0.96, 1.12)   1.00 (0.98, 1.06)    0.99 (0.93, 1.06)
+//   voxels 32  1.35   1.05 (0.98, 1.32)   1.03 (1.00, 1.10)   1.02 (0.97, 1.06)   1.01 (0.98, 1.03)    1.00 (0.95, 1.01)
+//   planes     1.23   1.06 (0.90, 1.32)   1.06 (1.00, 1.17)   1.03 (0.98, 1.10)   1.01 (0.97, 1.05)    1.00 (0.94, 1.06)
+//   hash       1.21   1.00 (0.88, 1.18)   1.01 (0.95, 1.08)   1.04 (0.99, 1.07)   1.02 (1.00, 1.05)    1.00 (0.97, 1.07)
+// Behind the lines nothing is gained on average, and images of voxels took up to 1.08 times as long in patches.  (The least at 0.7 to 1.0: 128^2 pixels x 64
+// samples, one item to a wave, some of them single rays; four items to a wave, 1.00 .. 1.2.)
+template <int KIND>
+constexpr double kPixelTexels = KIND == LP_GRID_VOXEL ? 1.3 : 1.5;
 
 // LDS in bytes: the waves' step tensors first (so that a wave's base has none of the address bits that the
 // images' exclusive-ors flip), then the weights, then the waves' small areas.
@@ -283,10 +294,10 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     }
 
     // ---- work items ----
-    // (the rays' pixels must share texels for a patch to be worth it, see launch_bwd_tile)
+    // (the rays' pixels must share texels for a patch to be worth it, see kPixelTexels)
     int row = 0, per_row = 0;   // of the image: pixels, patches
     if (sched.items == Items::kPatches) {
-        row = __builtin_amdgcn_readfirstlane((int)find_row(g, rays, kPixelTexels, 1e30, *reinterpret_cast<int*>(lds_raw)));
+        row = __builtin_amdgcn_readfirstlane((int)find_row(g, rays, kPixelTexels<KIND>, 1e30, *reinterpret_cast<int*>(lds_raw)));
         sched.items = Items::kTiles;
         if (row) {
             const unsigned lines = ((unsigned)rays.M + row - 1) / row;

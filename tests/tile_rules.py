@@ -5,7 +5,7 @@ from collections import Counter
 
 import numpy as np
 
-from lp_inputs import TRIPLANE
+from lp_inputs import TRIPLANE, VOXEL
 
 TILE_RAYS, TILE_SAMPLES = 4, 8
 EXTENT, TEXELS, PLANE_TEXELS = 12, 512, 128   # of a window
@@ -45,7 +45,7 @@ def forward_workgroups(n_rays, samples, n_cu=256):
 
 
 def image_row(inp, pixel, step):
-    """Length of an image's row that the Splatter's patch kernels find in a list of rays (lp_splat_patch.h find_row), 0: none."""
+    """Length of an image's row that the Splatter's patch kernels find in a list of rays (lp_image_rows.h find_row), 0: none."""
     end = (inp.origins + inp.far[:, None] * inp.dirs).astype(np.float32)
     d2 = lambda a, b: ((a - b) ** 2).sum(-1)
     along, ahead = d2(end[0], end[1]), end[1] - end[0]
@@ -178,7 +178,7 @@ def step_routes(inp):
     c = cells(inp)
     ray_scene = inp.scene if inp.scene is not None else np.zeros(inp.n_rays, int)
     in_tiles = backward_in_tiles(inp.n_rays, inp.samples)
-    row = image_row(inp, 1.5, 1e30)
+    row = image_row(inp, 1.3 if inp.kind == VOXEL else 1.5, 1e30)
 
     def fits(run):   # [rays][samples][3]
         e = run.reshape(-1, 3).max(0) - run.reshape(-1, 3).min(0) + 2
