@@ -180,13 +180,16 @@ __device__ __forceinline__ void gather_stream(const GridDev& g, int scene, const
 }
 
 // One launch's work items: patches (four pixels each of two rows of an image), consecutive tiles of kTileRays rays, or single
-// rays.  As many rounds as leave no wave of any workgroup without an item hand them out; what is to come in a round is
-// spread over the list: wave w takes from its w-th eighth, the workgroups of a round stand at places scrambled by `group_mul`
-// (neighbouring rays add into the same lines; spread over time their adds do not queue up at one L2 channel), and from
-// round to round a workgroup moves by `shift` places, or it would meet the same columns of an image again and again.
-// Items cost unlike amounts, by where their rays lie: with eight neighbours to a workgroup and the places in their order in short
-// lists, the dearest workgroup took 1.28 times the mean of 160^3 x 32 voxels in contract coordinates (256^2 rays, four rounds), now
-// a step of training takes 6.6 instead of 8.3 ms; eight triplanes 107.8 -> 107.0, the others alike.  What is left goes to the first
+// rays.  As many rounds as leave no wave of any workgroup without an item hand them out: in groups of kTileWaves, the workgroups of a
+// round at places scrambled by `group_mul` (neighbouring rays add into the same lines; spread over time their adds do not queue up at one
+// L2 channel), and from round to round a workgroup moves by `shift` places, or it would meet the same columns of an image again and again.
+// A group is eight neighbours, or (`spread`) one item of each eighth of the list.  Items cost unlike amounts, by where their rays
+// lie: with eight neighbouring patches to a workgroup and the places in their order in short lists, the dearest workgroup took 1.28 times the
+// mean of 160^3 x 32 voxels in contract coordinates (256^2 rays, four rounds), now a step of training takes 6.6 instead of 8.3 ms; eight
+// triplanes 107.8 -> 107.0, the others alike.  Tiles are spread in contract coordinates only (150^2 to 300^2 pixels, seven shapes each, of
+// neighbours 0.95 to 1.02 times the speed): elsewhere neighbours share more than the spread evens out (150^2 pixels x 48 samples, 90^3
+// voxels and planes, 1.17 times the speed of the spread, 16-32-4 1.25; 181^2 to 300^2 pixels 1.00 to 1.03), and so do single rays (32^2 to
+// 140^2 pixels, 64 to 400 samples, 1.00 to 1.02).  What is left goes to the first
 // `busy` waves of a workgroup, to as many workgroups as that takes: up to four of them have a SIMD each, where a ray takes 0.55 to 0.7 of the time beside
 // another.  (2600 rays in random order x 480 samples, 96^3 x 16 voxels, 16-64-64-4: the last 552 rays on 69 full workgroups 303 us,
 // spread over all 243; 32-64-64-4 on triplanes 128^2 469 -> 400.)
@@ -309,6 +312,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
         }
     }
     const Items items = sched.items;
+    const bool spread = items == Items::kPatches || (items == Items::kTiles && g.contract > 0.0);   // (see TileSchedule)
     const int xcd = blockIdx.x % 8, at = blockIdx.x / 8;
     const long long n_groups = sched.rounds * gridDim.x;   // of the whole rounds
     int left = (int)sched.rounds;                          // rounds to come; -1: the partial one is over too
@@ -327,7 +331,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void bwd_tile_kernel(GridDev g, Ml
     };
     auto next_item = [&]() {   // false: none left
         if (left > 0) {
-            item = wave * n_groups + group;
+            item = spread ? wave * n_groups + group : group * kTileWaves + wave;
             place += sched.shift;
             const bool wraps = place >= (int)gridDim.x;
             if (wraps) place -= (int)gridDim.x;

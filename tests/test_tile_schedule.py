@@ -5,8 +5,8 @@ import pytest
 WAVES = 8
 
 
-def _items(items, blocks):
-    """How often each item is handed out."""
+def _items(items, blocks, spread):
+    """How often each item is handed out.  `spread`: a group is one item of each eighth of the list, else eight neighbours."""
     waves = blocks * WAVES
     rounds, tail = divmod(items, waves)
     busy = -(-tail // blocks)
@@ -22,7 +22,7 @@ def _items(items, blocks):
         place, group = block, block * mul % n_groups if rounds else 0
         for _ in range(rounds):
             for wave in range(WAVES):
-                count[wave * n_groups + group] += 1
+                count[wave * n_groups + group if spread else group * WAVES + wave] += 1
             place += shift
             wraps = place >= blocks
             place -= blocks * wraps
@@ -35,15 +35,16 @@ def _items(items, blocks):
     return count
 
 
+@pytest.mark.parametrize("spread", [False, True])
 @pytest.mark.parametrize("blocks", [8, 24, 80, 256, 304])
-def test_every_item_once(blocks):
+def test_every_item_once(blocks, spread):
     waves = blocks * WAVES
     for items in (1, 7, blocks - 1, blocks, blocks + 1, 3 * blocks + 5, waves - 1, waves, waves + 1, waves + blocks, waves + 5 * blocks, 2 * waves,
                   3 * waves + 517, 4 * waves + 1, 7 * waves - 1, 19 * waves + 4 * blocks + 3):
-        assert set(_items(items, blocks)) == {1}, items
+        assert set(_items(items, blocks, spread)) == {1}, items
 
 
 @pytest.mark.parametrize("blocks,rounds", [(8, 7919), (8, 7907), (16, 7919)])
 def test_rounds_that_the_first_prime_divides(blocks, rounds):
     for tail in (0, 3, 5 * blocks):
-        assert set(_items(rounds * blocks * WAVES + tail, blocks)) == {1}
+        assert set(_items(rounds * blocks * WAVES + tail, blocks, tail == 0)) == {1}
