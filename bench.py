@@ -38,11 +38,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 # HBM bytes per launch of the backward kernel, from counters: FETCH_SIZE (x 2.00 against a 1 GiB copy in the same run)
 # and WRITE_SIZE (x 1.00), KiB.  A workload that is not listed was not counted.
-MEASURED_BWD_HBM_BYTES = {"large": (2 * 2158500 + 14421000) * 1024, "batched": (2 * 23738000 + 91288000) * 1024}
+MEASURED_BWD_HBM_BYTES = {"large": (2 * 2727900 + 10713000) * 1024, "batched": (2 * 17914000 + 64492000) * 1024}
 # 64-byte lines of atomic adds per launch of the backward kernel: TCC_ATOMIC (each request is one line,
 # written through as 64 bytes); profiles/atomic_line_rate.md
-MEASURED_BWD_ATOMIC_LINES = {"large": 2.3065e8, "batched": 1.4605e9, "contract": 6.7183e7, "voxel": 6.882e7, "hash": 3.0464e6,
-                             "single_scene": 6.0008e6, "hexplane": 2.0268e7, "decoder": 5.2145e7}
+MEASURED_BWD_ATOMIC_LINES = {"large": 1.7132e8, "batched": 1.0318e9, "contract": 5.7045e7, "voxel": 5.6997e7, "hash": 2.3066e6,
+                             "single_scene": 4.5241e6, "hexplane": 2.0268e7, "decoder": 5.2145e7}
 
 
 def parse():

@@ -2,8 +2,9 @@
 // wavefront marches a PATCH of an image (four pixels each of two rows, four samples of each ray per 32-sample step), a TILE
 // of a list (four consecutive rays, eight samples of each) or, where rays do not run side by side, one ray (32 samples),
 // from the last samples to the first.
-// A workgroup is eight wavefronts of 256 registers, two per SIMD, that share the MLP's weights in LDS
-// and nothing else: no wave waits for another between the staging of the weights and the final sums.
+// A workgroup is eight wavefronts of 256 registers, two per SIMD, that share the MLP's weights in LDS: no wave waits for another
+// between the staging of the weights and the final sums.  Each also publishes the number of its steps there, and the other wave of its SIMD reads
+// it, as it is found: nothing but s_setprio may depend on it.
 //
 // Per step a wave
 //   1. recomputes the MLP forward from the sampled features (nothing was stored but one scalar per ray),
@@ -26,7 +27,7 @@
 //     accumulators of the weight gradients (94 registers for 16-64-64-4: the two thin matrices on 16 x 16
 //     and 4 x 4 tiles) leave room for two waves only if a step's activations live in LDS instead of registers.
 //     Per SIMD the voxel kernel issues vector instructions in 52 % of the cycles and keeps the matrix cores busy in
-//     39 %, the triplane kernel 45 % and 38 % (1312 and 1629 vector instructions a step; 45.6 and 79.7 ms a launch).
+//     39 %, the triplane kernel 45 % and 38 % (1315 and 1634 vector instructions a step; 46.4 and 82.1 ms a launch).
 //   - In LDS they are transposed by the reads (lp_tile_lds.h); on the matrix cores the transposition by 0/1
 //     products took 36 of the 168 products of a step and as many permutes. The transposed weights of the
 //     input-gradient chain are column reads of the same images, which halves the LDS that weights take.

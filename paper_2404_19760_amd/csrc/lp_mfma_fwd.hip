@@ -171,7 +171,8 @@ hipError_t launch_items(const GridDev& g, const MlpDev& m, const RaysDev& rays, 
     // that of three workgroups of equal work the first was done early and the last ran alone; now others follow. 32 steps to a wave: 563 563 rays x
     // 330 samples, 256^3 x 16 voxels in bf16, 8.62 -> 7.88 ms (16 steps 7.99, 64 steps 7.97), 64^3 x 32 voxels 2.43 -> 2.33,
     // eight triplanes 26.2 -> 25.5; one step or two to a wave (5003 rays x 193 samples) took 6 % longer.
-    // At most 2^20: a launch holds fewer than 2^32 threads, and by then 341 workgroups follow each other in a place.
+    // At most 2^20: by then 1365 workgroups follow each other in each of the 768 places of 256 compute units, and a launch of 256 threads
+    // each stays a factor of 16 below the 2^32 threads that it may hold.
     const long long steps = (rays.S + (PAIRS ? 31 : 63)) / (PAIRS ? 32 : 64);
     const long long fine = std::min(items * steps / (kWaves * 32) / 8 * 8, 1LL << 20);
     if (blocks < fine) blocks = fine;

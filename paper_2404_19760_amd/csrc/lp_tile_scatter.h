@@ -1,6 +1,7 @@
 // Scatter of a 32-sample step into a structure, one atomic add per texel and channel that the step touches: the
-// gradient of the Renderer's backward (tile kernels) and what the Splatter pushes.  A step is a tile (four
-// neighbouring rays, eight samples of each: column 8 i + k is sample k of ray i) or 32 samples of one ray.
+// gradient of the Renderer's backward (tile kernels) and what the Splatter pushes.  A step is 32
+// samples: of a patch (four neighbouring pixels each of two rows, four samples of each), of a tile (four neighbouring rays, eight samples of
+// each) or of one ray; with `full` samples of a ray in the step column full i + k is sample k of ray i.
 #pragma once
 #include "lp_mfma.h"
 #include "lp_mfma_mlp.h"
